@@ -21,7 +21,7 @@ namespace {
 
 constexpr uint32_t kInf = 1u << 30;
 constexpr int kT = 8;  // stage-block size of the fill
-constexpr int kCH = 4;  // 64-column chunks of m per gemm work-group
+constexpr int kCH = 2;  // 64-column chunks of m per gemm work-group
 constexpr int kRowWG = 256;  // threads (columns of m) per work-group of the row kernels
 std::atomic<int> g_last_hip_error{0};
 
@@ -76,6 +76,8 @@ inline bool hip_ok(hipError_t e) {
 //                          of 64 columns; tiles = nblk (nblk + 1) / 2, chunks = pitch / 64
 //   tick  [nblk][4] int32  ticket counter of the tile_rows_kernel launch of diagonal D, group g
 //   fault [1]      int32   set when a bounded wait inside tile_rows_kernel expired
+//   samp  [B][4 nblk (nblk + 1)][pitch / kG][8] int32  every kG-th column of the finished cells, eight cells of a
+//                          row side by side (see gemm_kernel); left out where the workspace is too small
 // prog, tick and fault are cleared by precompute_kernel at the start of every solve.
 struct Workspace {
     int32_t* P;
@@ -90,7 +92,11 @@ struct Workspace {
     int32_t* prog;
     int32_t* tick;
     int32_t* fault;
+    int32_t* samp;  // null: no samples are kept
 };
+
+constexpr int kG = 16;  // columns between samples
+constexpr double kKeyBase = 0x1p44;
 
 constexpr int kBand = kRowWG;  // columns of m per work-group of the row kernels
 constexpr int kTickGroups = 4;
@@ -102,13 +108,19 @@ __host__ __device__ inline int bands_of(int pitch) { return (pitch + kBand - 1) 
 // index of tile (I, J), I <= J, in the row-major packed block triangle
 __host__ __device__ inline int tile_index(int nblk, int I, int J) { return I * nblk - (I * (I - 1)) / 2 + (J - I); }
 
+// Samples of one chain: [samp_rows][pitch / kG][8], cell (i, j) in row 4 J (J + 1) + i of column block J = j / 8.
+__host__ __device__ inline int samp_rows(int L) { return 4 * blocks_of(L) * (blocks_of(L) + 1); }
+__host__ __device__ inline size_t samp_ints(int L, int pitch) {
+    return blocks_of(L) < 3 ? 0 : size_t(pitch / kG) * samp_rows(L) * kT;
+}
+
 inline size_t ws_ints(int L, int pitch, int B) {
     return align64(size_t(B) * (L + 1)) + 3 * align64(size_t(B) * L) + 3 * align64(size_t(B) * L * L) +
            align64(size_t(B)) + 2 * align64(size_t(B) * L) + align64(size_t(B) * tiles_of(L) * (pitch / 64)) +
            align64(size_t(blocks_of(L)) * kTickGroups) + 64;
 }
 
-inline Workspace carve(void* base, int L, int pitch, int B) {
+inline Workspace carve(void* base, int L, int pitch, int B, bool samples) {
     int32_t* p = static_cast<int32_t*>(base);
     Workspace w;
     w.P = p;      p += align64(size_t(B) * (L + 1));
@@ -122,7 +134,8 @@ inline Workspace carve(void* base, int L, int pitch, int B) {
     w.kq = reinterpret_cast<double*>(p);  p += 2 * align64(size_t(B) * L);
     w.prog = p;   p += align64(size_t(B) * tiles_of(L) * (pitch / 64));
     w.tick = p;   p += align64(size_t(blocks_of(L)) * kTickGroups);
-    w.fault = p;
+    w.fault = p;  p += 64;
+    w.samp = samples && samp_ints(L, pitch) ? p : nullptr;
     return w;
 }
 
@@ -154,6 +167,8 @@ __device__ __forceinline__ void count_work(unsigned long long* work, int slot, u
 __host__ __device__ inline int tri_row(int L, int i, int j) {  // 0-based i <= j
     return i * L - (i * (i - 1)) / 2 + (j - i);
 }
+
+constexpr uint32_t kNoRead = 0xfffffff0u;  // buffer offset beyond any table: the load returns 0, no access
 
 // One block per chain: input checks, prefix sums, shifts and both threshold tables (last
 // display of the Theorem).
@@ -317,6 +332,15 @@ __device__ __forceinline__ uint32_t ld32(rsrc_t tab, uint32_t elem, uint32_t off
     return uint32_t(__builtin_amdgcn_raw_buffer_load_b32(tab, int(off), int(elem << 2), 0));
 }
 
+// Keeps the samples of cells (i, 8 J .. 8 J + 7): every kG-th lane stores its eight values.
+__device__ __forceinline__ void store_samples(const Ctx& c, int b, int i, int J, uint32_t m, const uint32_t (&val)[kT]) {
+    if (!c.ws.samp || (m & (kG - 1)) != kG - 1) return;
+    int4* at = reinterpret_cast<int4*>(c.ws.samp + size_t(b) * samp_ints(c.L, c.pitch)) +
+               2 * (size_t(4 * J * (J + 1) + i) * (c.pitch / kG) + m / kG);
+    at[0] = make_int4(int(val[0]), int(val[1]), int(val[2]), int(val[3]));
+    at[1] = make_int4(int(val[4]), int(val[5]), int(val[6]), int(val[7]));
+}
+
 // Which (chunk of m, tile, chain) a work-group takes.  The hardware hands work-groups out in
 // linear order and to the 8 XCDs round-robin, and the cost of a chunk grows with m (low budgets
 // are infeasible and skipped).  The linear index is therefore re-read as (tile and chain)
@@ -360,7 +384,7 @@ __device__ __forceinline__ void load_row_tail(rsrc_t tab, const int32_t* __restr
 // cell just finished, then the m_null gate, C_all with the m_all gate (smallest candidate
 // number: wins ties), saturation, store.
 template <int T, int CF, int DC>
-__device__ __forceinline__ void finish_row(const Ctx& c, size_t chain, const int32_t* __restrict__ P,
+__device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, const int32_t* __restrict__ P,
                                            const int32_t* __restrict__ mall, const int32_t* __restrict__ mnull,
                                            int L, int pitch, int i, int jb, int cend, const int (&jc)[T],
                                            uint32_t fbi, uint32_t m, uint32_t (&best)[T], uint32_t (&pick)[T],
@@ -393,235 +417,360 @@ __device__ __forceinline__ void finish_row(const Ctx& c, size_t chain, const int
             c.arg[o] = uint8_t(fpk);
         }
     }
+    store_samples(c, b, i, jb / T, m, val);
 }
 
-// Middle splits of every tile of block diagonal D >= 2.
-// One wave owns the 8x8 tile of cells for 64 consecutive m; lane = m.  Each loaded operand
-// row is used by 8 cells (1 byte of table traffic per candidate instead of 8).  The CH waves of
-// a work-group take adjacent chunks of m of the same tile: the cache lines that a shifted
-// operand read straddles are fetched once for two waves.
-// Candidates are compared as float64 keys  cost + (q+1)/256 : one add and one min per
-// candidate give the minimum cost and, among equal costs, the smallest candidate number
-// (all values are integers below 2^34 scaled by 2^-8, exact in float64).
-// Splits whose operands are infeasible for the whole chunk (frontier test) are dropped
-// from the work list before the pipeline starts.
+// Middle splits of every tile of block diagonal D >= 2, in two stages.
+//
+// Stage 1, bounds.  A cost never grows with m, so a cell's values at the two ends of a range of
+// columns bound all values in between.  The fill keeps a sample of every cell at the last of every
+// kG columns; from the samples below and above a sub-chunk of kG columns follow, for every cell of
+// the tile and every split q, a lower bound of the candidate over the sub-chunk and an upper bound of
+// the cell (the smallest upper bound of its candidates).  A split whose lower bound exceeds the upper
+// bound in every cell and sub-chunk of the wave cannot attain any minimum and is dropped; ties stay.
+// lane = (sub-chunk, split), 16 splits a pass; bounds are 32-bit sums of costs and prefix sums.
+//
+// Stage 2, candidates.  The splits that are left are evaluated for every cell and column, lane = m,
+// as float64 keys  cost + (q+1)/256 : one add and one min per candidate give the minimum cost and,
+// among equal costs, the smallest candidate number (all values are integers below 2^34 scaled by
+// 2^-8, exact in float64; 2^44 is added so that cost and number stand in fixed bits of the mantissa).
+//
+// A wave owns 4 rows x 8 columns of cells for 64 columns of m; the two halves of a tile and CH
+// adjacent chunks of m share a work-group.
 // Output, rows 0..6 of the tile: cost[] <- partial minimum clamped to 2^31 - 1, with bit 31 set as
 // the mark "not finished", arg[] <- its number; the row kernels finish them.  Row 7 has no split
 // in its own row block, so its partial minimum stays in registers and the wave finishes the row
 // itself.
-// KS > 1 (launches with too few tiles to fill the chip): KS waves share one chunk, each takes
-// every KS-th entry of the work list, and their key tiles are merged through LDS at the end.
-template <int NB, int UNR, int CH, int KS, bool CNT>
-__global__ void __launch_bounds__(64 * CH * KS, 2) gemm_kernel(Ctx c, int D) {
-    constexpr int T = kT;
-    static_assert(T == 8, "one wave per 8x8 tile");
+// What bounds it: latency of the dependent reads (samples, then operands), 30 % of the vector issue
+// slots busy; 2.9 ms a solve for L = 192, M = 4096, B = 8 at 4.0 TB/s asked for, where evaluating every
+// feasible split took 5.7 ms and 29 GB (5.5 % of the splits are left instead of 67 %).  kG = 16: bounds
+// over 64 columns leave 11.7 %, over 32 7.5 %.  Half a tile a wave keeps it at 128 registers, four waves a SIMD.
+// KS > 1 (launches with too few tiles to fill the chip): KS waves share one half chunk, each takes
+// every KS-th pass of stage 1 and every KS-th entry of the list, and their keys are merged
+// through LDS at the end.
+template <int CH, int KS, bool CNT>
+__global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
+    constexpr int T = kT, R = T / 2;
+    constexpr int NT = 128 * CH * KS;
     const Work w = work_of_block();
     const int b = c.b0 + w.chain, I = w.tile, J = I + D;
     const int L = c.L, pitch = c.pitch;
     const int qlo = (I + 1) * T, qhi = J * T;
-    const int j0 = J * T, i0 = I * T;
+    const int j0 = J * T;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    const int bx = w.chunk;
-    const int cw = wave / KS, slice = wave % KS;  // chunk within the work-group, slice of the list
-    const int chunk = bx * CH + cw;  // this wave's 64 columns of m
+    const int slice = wave % KS, half = (wave / KS) & 1, cw = wave / (2 * KS);
+    const int grp = wave / KS;       // waves of one group share a list
+    const int i0 = I * T + half * R;  // first row of this wave
+    const int chunk = w.chunk * CH + cw;  // this wave's 64 columns of m
     const uint32_t m = chunk * 64 + lane;
     const uint32_t moff = m * 4;
+    const int cend = min(T, L - j0);
     const size_t chain = size_t(b) * c.rows * pitch;
     const rsrc_t tab = table_rsrc(c.cost + chain, uint32_t(c.rows) * uint32_t(pitch) * 4u);
+    const rsrc_t atab = __builtin_amdgcn_make_buffer_rsrc(c.arg + chain, 0, int(uint32_t(c.rows) * uint32_t(pitch)), 0x00020000);
     const int32_t* need = c.ws.need + size_t(b) * L * L;
+    const int32_t* P = c.ws.P + size_t(b) * (L + 1);
 
-    int lrow0[8], jcol[8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r) lrow0[r] = tri_row(L, i0 + r, i0 + r) - (i0 + r) - 1;  // + q = row of (i, q-1)
-#pragma unroll
-    for (int cc = 0; cc < 8; ++cc) jcol[cc] = min(j0 + cc, L - 1);
-
-    // Work list of the chunk: the splits q for which some cell of the tile can have both operands
-    // feasible somewhere in these 64 columns.  Per-split constants (shift, key offset) travel
-    // with the list through LDS, so the pipeline never waits on scalar memory.  Every chunk of
-    // the work-group has a list of its own, built by its (first) wave: the lower chunks of a
-    // work-group drop splits that only its highest chunk can use.
-    __shared__ double s_kq[CKPT_MAX_L + 2][CH];
-    __shared__ int2 s_qs[CKPT_MAX_L + 2][CH];  // .x = q, .y = its shift: one LDS read per entry
-    __shared__ int32_t s_n[CH];
+    __shared__ int2 s_split[CKPT_MAX_L + 2];              // shift and prefix sum of split qlo + k
+    __shared__ int s_list[2 * CH][CKPT_MAX_L + 2];        // the splits that are left: k = q - qlo
+    __shared__ uint32_t s_ub[2 * CH][4][R * T];           // upper bound of every cell in every sub-chunk
+    __shared__ int s_n[2 * CH];
+    const int nq = qhi - qlo + 1;
+    for (int k = threadIdx.x; k < nq; k += NT)
+        s_split[k] = make_int2(c.ws.wsh[size_t(b) * L + qlo + k], P[qlo + k]);
+    // A chunk below the frontier of every cell of the wave has no candidate.
     const bool active = chunk * 64 < pitch;
+    int out_need = need[(i0 + ((lane >> 3) & (R - 1))) * L + min(j0 + (lane & 7), L - 1)];
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) out_need = min(out_need, __shfl_xor(out_need, o));
+    const bool search = active && chunk * 64 + 63 >= out_need;  // uniform over the waves of a group
     if (slice == 0) {
-        const int m_hi = min(chunk * 64 + 63, pitch - 1);  // largest m of the chunk
-        int n = 0;
-        int out_need = need[(i0 + (lane >> 3)) * L + min(j0 + (lane & 7), L - 1)];
+        for (int k = lane; k < 4 * R * T; k += 64) s_ub[grp][k >> 5][k & 31] = kInf - 1 + uint32_t(P[i0 + ((k & 31) >> 3)]);
+        if (lane == 0) s_n[grp] = 0;
+    }
+    __syncthreads();
+
+    if (c.ws.samp) {
+        const int sub = lane >> 4, x = lane & 15;
+        const int kk = chunk * 4 + sub;  // sub-chunk: columns kG kk .. kG kk + kG - 1
+        const uint32_t line = uint32_t(pitch / kG) * 32u;  // bytes of the samples of a row of eight cells
+        const rsrc_t smp = table_rsrc(c.ws.samp + size_t(b) * samp_ints(L, pitch), uint32_t(samp_rows(L)) * line);
+        const uint32_t right0 = uint32_t(4 * J * (J + 1)) * line;
+        struct Bound { uint32_t l[R], r[T]; };
+        // Samples of cells (i0 + r, q - 1) at sampled column kl and (q, j0 + cc) at sampled column kr, plus
+        // the prefix sum of q; infinite where the column does not exist.
+        auto fetch = [&](Bound& v, int q, int kl, int kr) {
+            const int jq = (q - 1) >> 3;
+            const uint32_t lo = kl >= 0 ? uint32_t(4 * jq * (jq + 1) + i0) * line + uint32_t(kl) * 32u + uint32_t((q - 1) & 7) * 4u : kNoRead;
+            const uint32_t ro = kr >= 0 ? right0 + uint32_t(q) * line + uint32_t(kr) * 32u : kNoRead;
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) out_need = min(out_need, __shfl_xor(out_need, o));
-        if (active && m_hi >= out_need) {
-            for (int base = qlo; base <= qhi; base += 64) {
-                const int q = base + lane;
-                bool on = false;
-                int sh = 0;
-                if (q <= qhi) {
-                    sh = c.ws.wsh[size_t(b) * L + q];
-                    int tl = 1 << 30, tr = 1 << 30;
+            for (int r = 0; r < R; ++r) v.l[r] = uint32_t(__builtin_amdgcn_raw_buffer_load_b32(smp, int(lo), int(uint32_t(r) * line), 0));
+            typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+            const u4 a = __builtin_amdgcn_raw_buffer_load_b128(smp, int(ro), 0, 0), d = __builtin_amdgcn_raw_buffer_load_b128(smp, int(ro), 16, 0);
 #pragma unroll
-                    for (int r = 0; r < 8; ++r) tl = min(tl, need[(i0 + r) * L + q - 1]);
+            for (int cc = 0; cc < 4; ++cc) v.r[cc] = a[cc], v.r[cc + 4] = d[cc];
+        };
+        auto settle = [&](Bound& v, uint32_t Pq, int kl, int kr) {
+            if (kl < 0) {
 #pragma unroll
-                    for (int cc = 0; cc < 8; ++cc) tr = min(tr, need[q * L + jcol[cc]]);
-                    on = m_hi >= max(tl, tr + sh);
-                }
-                const unsigned long long mask = __ballot(on);
-                if (on) {
-                    const int pos = n + __popcll(mask & ((1ull << lane) - 1ull));
-                    s_qs[pos][cw] = make_int2(q, sh);
-                    s_kq[pos][cw] = c.ws.kq[size_t(b) * L + q];
-                }
-                n += __popcll(mask);
+                for (int r = 0; r < R; ++r) v.l[r] = kInf;
+            }
+#pragma unroll
+            for (int cc = 0; cc < T; ++cc) v.r[cc] = (kr < 0 || cc >= cend ? kInf : v.r[cc]) + Pq;
+        };
+        const int passes = search ? (nq + 15) / 16 : 0;
+        // upper bounds: left operand sampled at the column before the sub-chunk, right operand at the last
+        // sampled column that the whole shifted sub-chunk lies above
+        uint32_t ub[R][T];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int cc = 0; cc < T; ++cc) ub[r][cc] = 0xffffffffu;
+        const int stride = 16 * KS;
+        auto split_of = [&](int k0) { return min(k0 + x, nq - 1); };
+        auto below = [&](int sh) { return ((kk * kG + 1 - sh) >> 4) - 1; };
+        auto above = [&](int sh) { return (kk * kG + kG - 1 - sh) >> 4; };
+        const int kend = passes * 16;
+        Bound nx;
+        int2 sp = s_split[split_of(slice * 16)];
+        if (slice * 16 < kend) fetch(nx, qlo + split_of(slice * 16), kk - 1, below(sp.x));
+        for (int k0 = slice * 16; k0 < kend; k0 += stride) {
+            Bound v = nx;
+            const int2 cur = sp;
+            sp = s_split[split_of(k0 + stride)];
+            fetch(nx, qlo + split_of(k0 + stride), kk - 1, below(sp.x));
+            __builtin_amdgcn_sched_barrier(0);
+            settle(v, uint32_t(cur.y), kk - 1, below(cur.x));
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int cc = 0; cc < T; ++cc) ub[r][cc] = min(ub[r][cc], v.l[r] + v.r[cc]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        sp = s_split[split_of(slice * 16)];
+        if (slice * 16 < kend) fetch(nx, qlo + split_of(slice * 16), kk, above(sp.x));
+        __builtin_amdgcn_sched_barrier(0);
+        if (passes > slice) {
+            // minimum over the 16 lanes of a sub-chunk: two exchanges that halve the cells a lane holds, then
+            // two rotations of the row of 16 lanes
+            uint32_t h[R * T / 2], f[R * T / 4];
+#pragma unroll
+            for (int t = 0; t < R * T / 2; ++t) {
+                const uint32_t e0 = ub[(2 * t) >> 3][(2 * t) & 7], e1 = ub[(2 * t + 1) >> 3][(2 * t + 1) & 7];
+                const uint32_t mine = (x & 1) ? e1 : e0, other = (x & 1) ? e0 : e1;
+                h[t] = min(mine, uint32_t(__builtin_amdgcn_update_dpp(0, int(other), 0xB1, 0xf, 0xf, true)));
+            }
+#pragma unroll
+            for (int t = 0; t < R * T / 4; ++t) {
+                const uint32_t mine = (x & 2) ? h[2 * t + 1] : h[2 * t], other = (x & 2) ? h[2 * t] : h[2 * t + 1];
+                f[t] = min(mine, uint32_t(__builtin_amdgcn_update_dpp(0, int(other), 0x4E, 0xf, 0xf, true)));
+                f[t] = min(f[t], uint32_t(__builtin_amdgcn_update_dpp(0, int(f[t]), 0x124, 0xf, 0xf, true)));
+                f[t] = min(f[t], uint32_t(__builtin_amdgcn_update_dpp(0, int(f[t]), 0x128, 0xf, 0xf, true)));
+                if (x < 4) atomicMin(&s_ub[grp][sub][4 * t + (x & 3)], f[t]);  // cell 4 t + 2 (x bit 1) + (x bit 0)
             }
         }
-        if (lane == 0) s_n[cw] = n;
+        if constexpr (KS > 1) __syncthreads();
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        // lower bounds: left operand sampled at the last column of the sub-chunk, right operand at the first
+        // sampled column that the whole shifted sub-chunk lies below
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int cc = 0; cc < T; ++cc) ub[r][cc] = s_ub[grp][sub][r * T + cc];
+        for (int k0 = slice * 16; k0 < kend; k0 += stride) {
+            Bound v = nx;
+            const int2 cur = sp;
+            sp = s_split[split_of(k0 + stride)];
+            fetch(nx, qlo + split_of(k0 + stride), kk, above(sp.x));
+            __builtin_amdgcn_sched_barrier(0);
+            settle(v, uint32_t(cur.y), kk, above(cur.x));
+            bool on = false;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int cc = 0; cc < T; ++cc) on = on || v.l[r] + v.r[cc] <= ub[r][cc];
+            unsigned long long mask = __ballot(on);
+            mask |= mask >> 32;
+            mask |= mask >> 16;
+            const uint32_t bits = uint32_t(mask) & 0xffffu & ((1u << min(16, nq - k0)) - 1u);
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&s_n[grp], __popc(bits));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (lane < 16 && (bits >> x & 1u)) s_list[grp][at + __popc(bits & ((1u << x) - 1u))] = k0 + x;
+        }
+        count_work<CNT>(c.work, 0, passes > slice ? 2u * (R + 8) * unsigned((passes - slice + KS - 1) / KS) : 0u, 0);
+    } else if (slice == 0 && search) {
+        // No room for samples: the splits q for which some cell of the wave can have both operands feasible
+        // somewhere in these 64 columns.
+        const int m_hi = min(chunk * 64 + 63, pitch - 1);
+        int n = 0;
+        for (int base = 0; base < nq; base += 64) {
+            const int k = base + lane, q = qlo + k;
+            bool on = false;
+            if (k < nq) {
+                int tl = 1 << 30, tr = 1 << 30;
+#pragma unroll
+                for (int r = 0; r < R; ++r) tl = min(tl, need[(i0 + r) * L + q - 1]);
+#pragma unroll
+                for (int cc = 0; cc < T; ++cc) tr = min(tr, need[q * L + min(j0 + cc, L - 1)]);
+                on = m_hi >= max(tl, tr + s_split[k].x);
+            }
+            const unsigned long long mask = __ballot(on);
+            if (on) s_list[grp][n + __popcll(mask & ((1ull << lane) - 1ull))] = k;
+            n += __popcll(mask);
+        }
+        if (lane == 0) s_n[grp] = n;
     }
     if constexpr (KS > 1) {
-        __syncthreads();  // the other slices of the chunk read the list
+        __syncthreads();  // the other slices of the group read the list
     } else {
         if (!active) return;  // KS > 1: every wave stays for the barriers of the merge
         __builtin_amdgcn_wave_barrier();  // the wave reads what its own lanes wrote: LDS keeps a wave's order
         __builtin_amdgcn_sched_barrier(0);
     }
     // this wave's entries: slice, slice + KS, ...
-    const int n_all = __builtin_amdgcn_readfirstlane(s_n[cw]);
+    const int n_all = __builtin_amdgcn_readfirstlane(s_n[grp]);
     const int n = active && n_all > slice ? (n_all - slice + KS - 1) / KS : 0;
-    auto entry = [&](int t) { return slice + KS * t; };
 
-    double key[8][8];
+    uint32_t lrow0[R], jcol[T];
 #pragma unroll
-    for (int r = 0; r < 8; ++r)
+    for (int r = 0; r < R; ++r) lrow0[r] = uint32_t(tri_row(L, i0 + r, i0 + r) - (i0 + r) - 1);  // + q = row of (i, q-1)
 #pragma unroll
-        for (int cc = 0; cc < 8; ++cc) key[r][cc] = 0x1p60;
+    for (int cc = 0; cc < T; ++cc) jcol[cc] = uint32_t(min(j0 + cc, L - 1));
+    double key[R][T];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int cc = 0; cc < T; ++cc) key[r][cc] = kKeyBase + 4294967295.0;
 
     if (n > 0) {
-        uint32_t buf[NB][16];
-        auto load = [&](uint32_t(&v)[16], int t) {
-            const int k = entry(t);
-            const int2 qs = s_qs[k][cw];
-            const int q = __builtin_amdgcn_readfirstlane(qs.x);
-            const int sh = __builtin_amdgcn_readfirstlane(qs.y);
-            const int rq = q * L - (q * (q - 1)) / 2 - q;  // + j = row of (q, j)
+        uint32_t buf[2][R + T];
+        // Entries past the end of the list read nothing and count as infinite.
+        auto load = [&](uint32_t(&v)[R + T], int t) {
+            const int k = __builtin_amdgcn_readfirstlane(s_list[grp][slice + KS * min(t, n - 1)]);
+            const int q = qlo + k;
+            const uint32_t sh = uint32_t(__builtin_amdgcn_readfirstlane(s_split[k].x));
+            const uint32_t rq = uint32_t(q * L - (q * (q - 1)) / 2 - q);  // + j = row of (q, j)
+            const uint32_t off = t < n ? moff : kNoRead;
 #pragma unroll
-            for (int r = 0; r < 8; ++r) v[r] = ld32(tab, uint32_t(lrow0[r] + q) * uint32_t(pitch), moff);
+            for (int r = 0; r < R; ++r) v[r] = ld32(tab, (lrow0[r] + uint32_t(q)) * uint32_t(pitch), off);
 #pragma unroll
-            for (int cc = 0; cc < 8; ++cc)
-                v[8 + cc] = ld32(tab, uint32_t(rq + jcol[cc]) * uint32_t(pitch) - uint32_t(sh), moff);
+            for (int cc = 0; cc < T; ++cc) v[R + cc] = ld32(tab, (rq + jcol[cc]) * uint32_t(pitch) - sh, off);
         };
-        auto compute = [&](const uint32_t(&v)[16], int t) {
-            const double cq = s_kq[entry(t)][cw];
-            double lk[8], rk[8];
+        auto compute = [&](const uint32_t(&v)[R + T], int t) {
+            const int k = __builtin_amdgcn_readfirstlane(s_list[grp][slice + KS * min(t, n - 1)]);
+            const double cq = t < n ? double(s_split[k].y) + double(qlo + k + 1) * (1.0 / 256.0) + kKeyBase : 2.0 * kKeyBase;
+            double lk[R], rk[T];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) lk[r] = double(v[r]);
+            for (int r = 0; r < R; ++r) lk[r] = double(v[r]);
 #pragma unroll
-            for (int cc = 0; cc < 8; ++cc) rk[cc] = double(v[8 + cc]) + cq;
+            for (int cc = 0; cc < T; ++cc) rk[cc] = double(v[R + cc]) + cq;
 #pragma unroll
-            for (int r = 0; r < 8; ++r)
+            for (int r = 0; r < R; ++r)
 #pragma unroll
-                for (int cc = 0; cc < 8; ++cc) key[r][cc] = fmin(key[r][cc], lk[r] + rk[cc]);
+                for (int cc = 0; cc < T; ++cc) key[r][cc] = fmin(key[r][cc], lk[r] + rk[cc]);
         };
-
-        // Straight-line pipeline: the list is padded to a multiple of the unroll by repeating
-        // its last entry (a repeated candidate cannot change a minimum), so the loop body has
-        // no branches and the loads of entry k + NB - 1 are in flight while entry k is evaluated.
-#pragma unroll
-        for (int u = 0; u < NB - 1; ++u) load(buf[u], min(u, n - 1));
-        constexpr int STEPS = NB * UNR;
-        auto steps = [&](auto count, int& k) {  // count.value pipeline steps, straight-line
-#pragma unroll
-            for (int u = 0; u < decltype(count)::value; ++u) {
-                load(buf[(u + NB - 1) % NB], min(k + NB - 1, n - 1));
-                __builtin_amdgcn_sched_barrier(0);  // keep these loads ahead of the math of entry k
-                compute(buf[u % NB], min(k, n - 1));
-                __builtin_amdgcn_sched_barrier(0);
-                ++k;
-            }
-        };
-        // long body for the bulk (the compiler's wait at a loop header is conservative, so few
-        // headers), then the remainder in bodies of NB steps: at most NB - 1 padded entries
-        int k = 0;
-        const int bulk = n / STEPS, tail = (n - bulk * STEPS + NB - 1) / NB;
-        for (int it = 0; it < bulk; ++it) steps(std::integral_constant<int, STEPS>{}, k);
-        for (int it = 0; it < tail; ++it) steps(std::integral_constant<int, NB>{}, k);
-        count_work<CNT>(c.work, 0, 16u * unsigned(NB - 1 + bulk * STEPS + tail * NB), 0);
+        // Straight-line bodies of two entries without branches, so that the loads of the next entry
+        // are in flight while one is evaluated.
+        load(buf[0], 0);
+        for (int k = 0; k < n; k += 2) {
+            load(buf[1], k + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(buf[0], k);
+            __builtin_amdgcn_sched_barrier(0);
+            load(buf[0], k + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            compute(buf[1], k + 1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        count_work<CNT>(c.work, 0, unsigned(R + T) * unsigned(n), 0);
     }
 
     if constexpr (KS > 1) {
-        // Merge: row by row of the tile, the waves of slices 1.. hand their keys to the wave of
-        // slice 0 through LDS.  Every wave of the work-group passes all sixteen barriers.
-        __shared__ double s_red[CH][KS - 1][8][64];
+        // Merge: row by row, the waves of slices 1.. hand their keys to the wave of slice 0 through LDS.
+        // Every wave of the work-group passes all barriers.
+        __shared__ double s_red[2 * CH][KS - 1][T][64];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
+        for (int r = 0; r < R; ++r) {
             if (slice > 0) {
 #pragma unroll
-                for (int cc = 0; cc < 8; ++cc) s_red[cw][slice - 1][cc][lane] = key[r][cc];
+                for (int cc = 0; cc < T; ++cc) s_red[grp][slice - 1][cc][lane] = key[r][cc];
             }
             __syncthreads();
             if (slice == 0) {
 #pragma unroll
                 for (int o = 0; o < KS - 1; ++o)
 #pragma unroll
-                    for (int cc = 0; cc < 8; ++cc) key[r][cc] = fmin(key[r][cc], s_red[cw][o][cc][lane]);
+                    for (int cc = 0; cc < T; ++cc) key[r][cc] = fmin(key[r][cc], s_red[grp][o][cc][lane]);
             }
             __syncthreads();
         }
         if (slice != 0 || !active) return;
     }
 
-    const int32_t* P = c.ws.P + size_t(b) * (L + 1);
     // Row 7: operands of its column-block splits and of C_all are requested before the other rows
     // are converted and stored -- unless the whole chunk lies below the frontier of its cells.
-    const int i7 = i0 + 7;
-    const int cend = min(8, L - j0);
-    int need7 = 1 << 30;
+    const int i7 = I * T + T - 1;
+    int jc[T];
 #pragma unroll
-    for (int cc = 0; cc < 8; ++cc) need7 = min(need7, need[i7 * L + jcol[cc]]);
-    const bool live7 = int(m | 63u) >= need7;  // wave-uniform
-    uint32_t tj[8][8], al[8];
-    if (live7)
-        load_row_tail<8, 0>(tab, c.ws.wsh + size_t(b) * L, L, pitch, i7, j0, jcol, c.ws.wabs[size_t(b) * L + i7],
-                            moff, tj, al);
+    for (int cc = 0; cc < T; ++cc) jc[cc] = int(jcol[cc]);
+    bool live7 = false;
+    uint32_t tj[T][T], al[T];
+    if (half == 1) {
+        int need7 = 1 << 30;
+#pragma unroll
+        for (int cc = 0; cc < T; ++cc) need7 = min(need7, need[i7 * L + jc[cc]]);
+        live7 = chunk * 64 + 63 >= need7;  // wave-uniform
+        if (live7)
+            load_row_tail<T, 0>(tab, c.ws.wsh + size_t(b) * L, L, pitch, i7, j0, jc, c.ws.wabs[size_t(b) * L + i7], moff, tj, al);
+    }
+    // The mantissa of a key holds 256 cost + number: cost is the 32 bits from bit 8 on.
     auto partial = [&](int r, int cc, uint32_t Pi, uint32_t& cst, uint32_t& num) {
-        const double k = key[r][cc];
-        const double fl = floor(fmin(k, 0x1p33));
-        cst = k < 0x1p32 ? uint32_t(fl) - Pi : 0xffffffffu;
-        num = uint32_t((fmin(k, 0x1p33) - fl) * 256.0);
+        const unsigned long long bits = __builtin_bit_cast(unsigned long long, key[r][cc]);
+        cst = uint32_t(bits >> 8) - Pi;
+        num = uint32_t(bits) & 255u;
     };
     // A partial minimum is stored with bit 31 set: a finished cell never exceeds 2^30, so whoever
     // reads the table can tell a cell that still waits for its row kernel from a finished one.
     // Partial minima of 2^31 - 1 and more are infeasible whatever they were and are clamped.
-    auto tagged = [](uint32_t cst) { return min(cst, 0x7fffffffu) | 0x80000000u; };
 #pragma unroll
-    for (int r = 0; r < 7; ++r) {
-        const uint32_t Pi = P[i0 + r];
-        const size_t row = chain + size_t(tri_row(L, i0 + r, j0)) * pitch + m;
+    for (int r = 0; r < R; ++r) {
+        if (r == R - 1 && half == 1) break;  // row 7
+        const uint32_t Pi = uint32_t(P[i0 + r]);
+        const uint32_t row = uint32_t(tri_row(L, i0 + r, j0)) * uint32_t(pitch);
 #pragma unroll
-        for (int cc = 0; cc < 8; ++cc) {
+        for (int cc = 0; cc < T; ++cc) {
             if (cc < cend) {
                 uint32_t cst, num;
                 partial(r, cc, Pi, cst, num);
-                c.cost[row + size_t(cc) * pitch] = int32_t(tagged(cst));
-                c.arg[row + size_t(cc) * pitch] = uint8_t(num);
+                const uint32_t at = row + uint32_t(cc) * uint32_t(pitch);
+                __builtin_amdgcn_raw_buffer_store_b32(int(min(cst, 0x7fffffffu) | 0x80000000u), tab, int(moff), int(at << 2), 0);
+                __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(num), atab, int(m), int(at), 0);
             }
         }
     }
-    count_work<CNT>(c.work, 0, live7 ? 36u : 0u, 8u * unsigned(cend));
+    count_work<CNT>(c.work, 0, live7 ? 36u : 0u, unsigned(R) * unsigned(cend));
+    if (half == 0) return;
     if (live7) {
-        uint32_t best[8], pick[8];
+        uint32_t best[T], pick[T];
 #pragma unroll
-        for (int cc = 0; cc < 8; ++cc) partial(7, cc, uint32_t(P[i7]), best[cc], pick[cc]);
-        finish_row<8, 0, 2>(c, chain, P, c.ws.mall + (size_t(b) * L + i7) * L, c.ws.mnull + (size_t(b) * L + i7) * L, L,
-                            pitch, i7, j0, cend, jcol, c.ws.fb[size_t(b) * L + i7], m, best, pick, tj, al);
+        for (int cc = 0; cc < T; ++cc) partial(R - 1, cc, uint32_t(P[i7]), best[cc], pick[cc]);
+        finish_row<T, 0, 2>(c, b, chain, P, c.ws.mall + (size_t(b) * L + i7) * L, c.ws.mnull + (size_t(b) * L + i7) * L, L,
+                            pitch, i7, j0, cend, jc, c.ws.fb[size_t(b) * L + i7], m, best, pick, tj, al);
     } else {
         const size_t row = chain + size_t(tri_row(L, i7, j0)) * pitch + m;
+        uint32_t inf[T];
 #pragma unroll
-        for (int cc = 0; cc < 8; ++cc) {
+        for (int cc = 0; cc < T; ++cc) {
+            inf[cc] = kInf;
             if (cc < cend) {
                 c.cost[row + size_t(cc) * pitch] = int32_t(kInf);
                 c.arg[row + size_t(cc) * pitch] = 0;
             }
         }
+        store_samples(c, b, i7, J, m, inf);
     }
 }
 
@@ -684,6 +833,10 @@ __global__ void __launch_bounds__(kRowWG) row_kernel(Ctx c, int D) {
                     c.arg[o] = 0;
                 }
             }
+            uint32_t inf[T];
+#pragma unroll
+            for (int cc = 0; cc < T; ++cc) inf[cc] = kInf;
+            store_samples(c, b, i, J, m, inf);
             return;
         }
     }
@@ -729,7 +882,7 @@ __global__ void __launch_bounds__(kRowWG) row_kernel(Ctx c, int D) {
         for (int cc = 0; cc < T; ++cc)
             if (pc[cc] < best[cc]) best[cc] = pc[cc], pick[cc] = pp[cc];
     }
-    finish_row<T, CF, DC>(c, chain, P, mall, mnull, L, pitch, i, jb, cend, jc, fbi, m, best, pick, tj, al);
+    finish_row<T, CF, DC>(c, b, chain, P, mall, mnull, L, pitch, i, jb, cend, jc, fbi, m, best, pick, tj, al);
 }
 
 // ---------------------------------------------------------------------------
@@ -760,7 +913,6 @@ __global__ void __launch_bounds__(kRowWG) row_kernel(Ctx c, int D) {
 // Each loaded operand of a split is kept in registers for all rows that use it: per tile and
 // lane 7 x 8 + 28 + 64 operand loads instead of the 252 + 224 + 64 of one launch per row.
 // ---------------------------------------------------------------------------
-constexpr uint32_t kNoRead = 0xfffffff0u;  // buffer offset beyond any table: the load returns 0, no access
 constexpr int kSpinLimit = 1 << 20;        // default polls of a wait before it gives up (seconds, never reached)
 
 
@@ -1021,6 +1173,7 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
                 }
             }
         }
+        store_samples(x.c, x.b, i, x.J, m, val);
         if (R > 0) {
             // the rows above read this row from LDS (this band) or from memory (bands above)
 #pragma unroll
@@ -1143,6 +1296,10 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int3
                         __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(0), x.atab, int(own >> 2), int(col), 0);
                         ++cells;
                     }
+                    uint32_t inf[T];
+#pragma unroll
+                    for (int cc = 0; cc < T; ++cc) inf[cc] = kInf;
+                    store_samples(c, x.b, x.i0 + r, x.J, x.m, inf);
                 }
                 count_work<CNT>(c.work, 2, 0, cells);
                 if (DC < 2) {  // readers in the bands above wait for this chunk's progress
@@ -1550,7 +1707,8 @@ bool allow_frontier_lds() {
 }
 
 int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, int32_t* cost, uint8_t* arg,
-               void* workspace, Profile* prof, const ckpt_solve_opts_t* opts, bool may_create_helpers) {
+               void* workspace, size_t workspace_bytes, Profile* prof, const ckpt_solve_opts_t* opts,
+               bool may_create_helpers) {
     if (!chains || !cost || !arg || !workspace) return CKPT_E_ARG;
     if (int rc = check_dims(L, M, B)) return rc;
     if (!chains->uf || !chains->ub || !chains->wa || !chains->wabar) return CKPT_E_ARG;
@@ -1577,7 +1735,13 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int pitch = int(ckpt_row_pitch(M));
     const int rows = int(ckpt_table_rows(L));
-    const Workspace ws = carve(workspace, L, pitch, B);
+    // without room for the samples (the static workspace of the entry point that allocates nothing) the
+    // block product evaluates every feasible split.  So it does where the lists of splits are so short and so
+    // few that a launch costs more than they do: 5 chains of 53 stages and 777 slots (2.0e5 by the measure below)
+    // take 2 % longer with bounds, 16 chains of 48 stages and 1024 slots (6.3e5) 2 % less.
+    const int stage_blocks = blocks_of(L);
+    const bool bounds = size_t(B) * pitch * stage_blocks * stage_blocks >= 400000;
+    const Workspace ws = carve(workspace, L, pitch, B, bounds && workspace_bytes >= ckpt_workspace_bytes(L, M, B));
 
     const size_t frontier_lds = ckpt_table_rows(L) * sizeof(int32_t);
     if (frontier_lds > 48 * 1024 && !allow_frontier_lds()) return CKPT_E_HIP;
@@ -1685,13 +1849,13 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             // where the lists are short); with fewer waves than a quarter of the chip, 4 do.
             const long long waves = (long long)(nblk - D) * (pitch / 64) * B;
             const int ks = want_ks ? want_ks : (waves <= 600 ? 4 : (waves <= 7000 ? 2 : 1));
-            const int gx = (pitch / 64 + kCH / ks - 1) / (kCH / ks);
+            const int ch = ks == 1 ? kCH : 1, gx = (pitch / 64 + ch - 1) / ch;
             for (int g = 0; g < groups; ++g) {
                 const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work};
-                const dim3 grid(gx, nblk - D, first[g + 1] - first[g]), block(64 * kCH);
-                const auto fn = ks == 4 ? (work ? gemm_kernel<3, 3, kCH / 4, 4, true> : gemm_kernel<3, 3, kCH / 4, 4, false>)
-                              : ks == 2 ? (work ? gemm_kernel<3, 3, kCH / 2, 2, true> : gemm_kernel<3, 3, kCH / 2, 2, false>)
-                                        : (work ? gemm_kernel<3, 3, kCH, 1, true> : gemm_kernel<3, 3, kCH, 1, false>);
+                const dim3 grid(gx, nblk - D, first[g + 1] - first[g]), block(128 * ch * ks);
+                const auto fn = ks == 4 ? (work ? gemm_kernel<1, 4, true> : gemm_kernel<1, 4, false>)
+                              : ks == 2 ? (work ? gemm_kernel<1, 2, true> : gemm_kernel<1, 2, false>)
+                                        : (work ? gemm_kernel<kCH, 1, true> : gemm_kernel<kCH, 1, false>);
                 hipLaunchKernelGGL(fn, grid, block, 0, gs[g], ctx, D);
                 CKPT_AFTER_LAUNCH(CKPT_K_GEMM);
                 if (D == 2 && g == 0 && side && stagger && groups >= 3) {
@@ -1739,6 +1903,11 @@ extern "C" {
 
 size_t ckpt_workspace_bytes(int L, int M, int B) {
     if (L < 1 || M < 0 || B < 1) return 0;
+    return (ws_ints(L, int(ckpt_row_pitch(M)), B) + size_t(B) * samp_ints(L, int(ckpt_row_pitch(M)))) * sizeof(int32_t);
+}
+
+// What a solve cannot do without: everything but the samples.
+static size_t least_workspace_bytes(int L, int M, int B) {
     return ws_ints(L, int(ckpt_row_pitch(M)), B) * sizeof(int32_t);
 }
 
@@ -1757,24 +1926,24 @@ int ckpt_init(int device) {
 
 int ckpt_solve_batched(const ckpt_chains_t* chains, int L, int M, int B, void* stream, int32_t* cost,
                        uint8_t* arg, void* workspace) {
-    return solve_impl(chains, L, M, B, stream, cost, arg, workspace, nullptr, nullptr, true);
+    return solve_impl(chains, L, M, B, stream, cost, arg, workspace, ~size_t(0), nullptr, nullptr, true);
 }
 
 int ckpt_solve_batched_noalloc(const ckpt_chains_t* chains, int L, int M, int B, void* stream, int32_t* cost,
                                uint8_t* arg) {
     if (int rc = check_dims(L, M, B)) return rc;
-    if (ckpt_workspace_bytes(L, M, B) > CKPT_NOALLOC_MAX_WORKSPACE) return CKPT_E_LIMIT;
+    if (least_workspace_bytes(L, M, B) > CKPT_NOALLOC_MAX_WORKSPACE) return CKPT_E_LIMIT;
     Device* dev = current_device();
     if (!dev) return CKPT_E_HIP;
     void* scratch = ensure_scratch(*dev);
     if (!scratch) return CKPT_E_HIP;
     // creates nothing: the batch is split only if the helper streams exist already
-    return solve_impl(chains, L, M, B, stream, cost, arg, scratch, nullptr, nullptr, false);
+    return solve_impl(chains, L, M, B, stream, cost, arg, scratch, CKPT_NOALLOC_MAX_WORKSPACE, nullptr, nullptr, false);
 }
 
 int ckpt_solve_batched_opts(const ckpt_chains_t* chains, int L, int M, int B, void* stream, int32_t* cost,
                             uint8_t* arg, void* workspace, const ckpt_solve_opts_t* opts) {
-    return solve_impl(chains, L, M, B, stream, cost, arg, workspace, nullptr, opts, true);
+    return solve_impl(chains, L, M, B, stream, cost, arg, workspace, ~size_t(0), nullptr, opts, true);
 }
 
 int ckpt_solve_profiled(const ckpt_chains_t* chains, int L, int M, int B, void* stream, int32_t* cost,
@@ -1786,7 +1955,7 @@ int ckpt_solve_profiled(const ckpt_chains_t* chains, int L, int M, int B, void* 
     for (int k = 0; k < CKPT_N_KERNEL_KINDS; ++k) kind_ms[k] = 0.f, kind_launches[k] = 0;
     int rc = CKPT_OK;
     if (!prof.mark(-1)) rc = CKPT_E_HIP;
-    if (rc == CKPT_OK) rc = solve_impl(chains, L, M, B, stream, cost, arg, workspace, &prof, nullptr, false);
+    if (rc == CKPT_OK) rc = solve_impl(chains, L, M, B, stream, cost, arg, workspace, ~size_t(0), &prof, nullptr, false);
     if (!hip_ok(hipStreamSynchronize(st)) && rc == CKPT_OK) rc = CKPT_E_HIP;
     for (size_t i = 1; i < prof.events.size() && rc == CKPT_OK; ++i) {
         float ms = 0.f;
@@ -1805,7 +1974,7 @@ int ckpt_solve_profiled(const ckpt_chains_t* chains, int L, int M, int B, void* 
         const size_t bytes = host.size() * sizeof(unsigned long long);
         if (!hip_ok(hipMalloc(reinterpret_cast<void**>(&count.work), bytes))) return CKPT_E_HIP;
         if (!hip_ok(hipMemsetAsync(count.work, 0, bytes, st))) rc = CKPT_E_HIP;
-        if (rc == CKPT_OK) rc = solve_impl(chains, L, M, B, stream, cost, arg, workspace, &count, nullptr, false);
+        if (rc == CKPT_OK) rc = solve_impl(chains, L, M, B, stream, cost, arg, workspace, ~size_t(0), &count, nullptr, false);
         if (rc == CKPT_OK && !hip_ok(hipMemcpyAsync(host.data(), count.work, bytes, hipMemcpyDeviceToHost, st)))
             rc = CKPT_E_HIP;
         if (!hip_ok(hipStreamSynchronize(st)) && rc == CKPT_OK) rc = CKPT_E_HIP;
@@ -1834,12 +2003,12 @@ int ckpt_check_inputs(const void* workspace, int L, int M, int B, void* stream, 
     if (!flags_host) return CKPT_E_ARG;
     if (int rc = check_dims(L, M, B)) return rc;
     if (!workspace) {  // the static workspace of ckpt_solve_batched_noalloc on the current device
-        if (ckpt_workspace_bytes(L, M, B) > CKPT_NOALLOC_MAX_WORKSPACE) return CKPT_E_LIMIT;
+        if (least_workspace_bytes(L, M, B) > CKPT_NOALLOC_MAX_WORKSPACE) return CKPT_E_LIMIT;
         Device* dev = current_device();
         workspace = dev ? ensure_scratch(*dev) : nullptr;
         if (!workspace) return CKPT_E_HIP;
     }
-    const Workspace ws = carve(const_cast<void*>(workspace), L, int(ckpt_row_pitch(M)), B);
+    const Workspace ws = carve(const_cast<void*>(workspace), L, int(ckpt_row_pitch(M)), B, false);
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (!hip_ok(hipMemcpyAsync(flags_host, ws.flags, size_t(B) * sizeof(int32_t), hipMemcpyDeviceToHost, st)))
         return CKPT_E_HIP;

@@ -77,6 +77,40 @@ def test_wide_rows_and_many_chains(amd, oracle_mod, L, M, B, seed, size_hi):
     assert_tables_equal(oracle_mod, batch, amd.solve(batch), nthreads=8)
 
 
+@pytest.mark.parametrize("L,M,size_hi,time_hi", [
+    (17, 15, 2, 40),        # one column of the last block, fewer columns than one sample
+    (24, 16, 3, 50),        # first diagonal with splits between the blocks
+    (25, 63, 4, 50),        # the last chunk ends with the row
+    (33, 64, 20, 1),        # equal times: ties between many splits
+    (40, 130, 16, 50),      # shifts of one sample and its neighbours
+    (41, 300, 0, 50),       # no shift at all: sizes zero
+    (56, 1000, 60, 1 << 21),  # costs near the sentinel
+])
+def test_splits_dropped_by_their_bounds(amd, oracle_mod, L, M, size_hi, time_hi):
+    blocks = -(-L // 8)
+    B = 400000 // (amd.ckpt_row_pitch(M) * blocks * blocks) + 1  # large enough for the bounds to be used
+    batch = random_chain_batch(L, M, B, 900 + L, size_hi=size_hi, time_hi=time_hi, zero_sizes=size_hi in (0, 16))
+    sol = amd.solve(batch)
+    assert_tables_equal(oracle_mod, batch, sol, chains=range(0, B, max(1, B // 6)))
+    for split in (1, 2, 4):
+        again = amd.solve(batch, list_split=split)
+        assert (again.cost[..., :M + 1] == sol.cost[..., :M + 1]).all() and (again.arg[..., :M + 1] == sol.arg[..., :M + 1]).all()
+
+
+def test_no_room_for_bounds(amd):
+    """The static workspace has no room for this batch's samples: every feasible split is evaluated."""
+    import torch
+    batch = random_chain_batch(64, 2000, 24, 31, size_hi=90, time_hi=900)
+    want = amd.solve(batch)
+    cost, arg = torch.full_like(want.cost, -1), torch.full_like(want.arg, 255)
+    up = lambda a: torch.from_numpy(a).cuda()
+    amd.ckpt_solve_batched_noalloc(up(batch.uf), up(batch.ub), up(batch.wa), up(batch.wabar), batch.L, batch.M, batch.B, cost, arg)
+    assert amd.ckpt_workspace_bytes(batch.L, batch.M, batch.B) > 16 << 20
+    assert amd.ckpt_check_inputs(None, batch.L, batch.M, batch.B).tolist() == [0] * batch.B
+    M = batch.M
+    assert (cost[..., :M + 1] == want.cost[..., :M + 1]).all() and (arg[..., :M + 1] == want.arg[..., :M + 1]).all()
+
+
 def test_everything_infeasible(amd, oracle_mod):
     batch = random_chain_batch(12, 3, 2, 21, size_hi=9)
     batch.wa += 5
