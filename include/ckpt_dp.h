@@ -327,13 +327,14 @@ int ckpt_discretize_sweep(const int64_t* bytes_wa, const int64_t* bytes_wabar, c
  *   ops        DEVICE [B][ops_cap]; ops_cap >= L(L+1)/2 + L always suffices
  *   n_ops      DEVICE int32 [B]: number of operations of chain b, or CKPT_E_INFEASIBLE,
  *              CKPT_E_SMALLBUF, CKPT_E_CORRUPT, CKPT_E_ARG (negative budget) for that chain
- *   workspace  DEVICE memory of ckpt_schedule_workspace_bytes(L, B) bytes
+ *   workspace  DEVICE memory of ckpt_schedule_workspace_bytes(L, B) bytes (checked, but left untouched:
+ *              the walk keeps its state on chip)
  * Returns CKPT_OK, CKPT_E_ARG, CKPT_E_LIMIT or CKPT_E_HIP.
  */
 int ckpt_schedule_batched(const uint8_t* arg, const int32_t* wa, const int32_t* wabar, int L, int M, int B,
                           const int32_t* m_budget, void* stream, ckpt_op_t* ops, int ops_cap, int32_t* n_ops,
                           void* workspace);
-/* Bytes of DEVICE workspace (16-byte aligned) ckpt_schedule_batched needs: the walk stacks. */
+/* Bytes of DEVICE workspace (16-byte aligned) ckpt_schedule_batched asks for. */
 size_t ckpt_schedule_workspace_bytes(int L, int B);
 
 /*

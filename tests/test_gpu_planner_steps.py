@@ -152,6 +152,78 @@ def test_schedule_batched_small_capacity_and_corrupt_table(amd, solved):
     assert got[3] == -7 and all(v > 0 for k, v in enumerate(got) if k != 3)
 
 
+def _walk_in_order(arg, wa, wabar, L, m, cap, row):
+    """The walk one cell after another: (operations written, their number or the error)."""
+    ops, stack, code = [], [("walk", 1, L, m)], None
+    while stack and code is None:
+        kind, s, t, m = stack.pop()
+        if kind == "B":
+            new = [(3, s)]
+        else:
+            k = 0 if m < 0 else int(arg[row(L, s, t), m])
+            if k < s or k > t:
+                code = -3 if k == 0 and not ops and (s, t) == (1, L) else -7
+                break
+            if s == t:
+                new = [(0, s), (3, s)]
+            elif k == s:
+                new = [(0, s)]
+                stack += [("B", s, s, 0), ("walk", s + 1, t, m - int(wabar[s - 1]))]
+            else:
+                new = [(1, s)] + [(2, j) for j in range(s + 1, k)]
+                stack += [("walk", s, k - 1, m), ("walk", k, t, m - int(wa[k - 1]))]
+        if len(ops) + len(new) > cap:
+            code = -4
+        ops += new[:cap - len(ops)]
+    return ops, len(ops) if code is None else code
+
+
+@pytest.mark.parametrize("L", [1, 2, 3, 17, 64, 65, 128, 254])
+def test_schedule_batched_any_table(amd, L):
+    """Tables that no solve wrote: every mix of C_all runs and splits (C_all only, splits only at the first or
+    last stage, so that the tree is as deep as it gets), holes, numbers out of range, sizes that run
+    the budget below zero or above the cell's, lists cut by the capacity."""
+    import torch
+    rng = np.random.default_rng(L)
+    M, B = 300, 14
+    rows, pitch = amd.ckpt_table_rows(L), amd.ckpt_row_pitch(M)
+    first = np.concatenate([np.full(L - s + 1, s) for s in range(1, L + 1)])
+    last = np.concatenate([np.arange(s, L + 1) for s in range(1, L + 1)])
+    arg = np.zeros((B, rows, pitch), np.uint8)
+    for b in range(B):
+        p = (1.0, 0.0, 0.9, 0.5, 0.1)[b % 5]
+        far = {0: first + 1, 1: last}.get(b % 3, None)
+        split = rng.integers(np.minimum(first + 1, last)[:, None], last[:, None], (rows, pitch), endpoint=True)
+        split = split if far is None else np.broadcast_to(np.minimum(far, last)[:, None], split.shape)
+        arg[b] = np.where(rng.random((rows, pitch)) < p, first[:, None], split)
+        if b in (5, 6, 7):
+            arg[b][rng.random((rows, pitch)) < 0.02] = 0
+        if b == 8:
+            arg[b][rng.random((rows, pitch)) < 0.01] = 255
+    arg[9, amd.ckpt_row_index(L, 1, L)] = 0
+    wa, wabar = rng.integers(0, 3, (B, L + 1)).astype(np.int32), rng.integers(0, 3, (B, L)).astype(np.int32)
+    wa[:5], wabar[:5] = 0, 0
+    wabar[10:12] = rng.integers(-1, 2, (2, L))
+    budget = rng.integers(20, 41, B).astype(np.int32)
+    budget[12], budget[13] = 5000, 0
+    full = L * (L + 1) // 2 + L
+    up = lambda a: torch.from_numpy(a).cuda()
+    ws = torch.empty(amd.ckpt_schedule_workspace_bytes(L, B), dtype=torch.uint8, device="cuda")
+    dev = up(arg), up(wa), up(wabar), up(budget)
+    codes = set()
+    for cap in (full, L + 1):
+        ops = torch.full((B, cap, 2), 77, dtype=torch.uint8, device="cuda")
+        n_ops = torch.zeros(B, dtype=torch.int32, device="cuda")
+        amd.ckpt_schedule_batched(dev[0], dev[1], dev[2], L, M, B, dev[3], ops, cap, n_ops, ws)
+        for b in range(B):
+            want, code = _walk_in_order(arg[b], wa[b], wabar[b], L, min(int(budget[b]), M), cap, amd.ckpt_row_index)
+            assert n_ops[b].item() == code, (cap, b)
+            got = [tuple(x) for x in ops[b].cpu().tolist()]
+            assert got == want + [(77, 77)] * (cap - len(want)), (cap, b)
+            codes.add(min(code, 0))
+    assert L < 17 or codes == {0, -3, -4, -7}
+
+
 def _walk_on_device(amd, batch, sol, budgets):
     import torch
     L, M, B = batch.L, batch.M, batch.B
