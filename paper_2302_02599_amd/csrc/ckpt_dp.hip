@@ -1640,85 +1640,152 @@ __global__ void __launch_bounds__(64) block_index_kernel(const ckpt_op_t* __rest
     if (lane == 0) n_blocks[b] = bad ? CKPT_E_CORRUPT : carry;
 }
 
-// Self-check of operation lists: one wave per chain executes its list under the memory model
-// of Table 1 ("List of Operations").  The lanes stage the chain's arrays and the list through
-// LDS; lane 0 carries the state: per stage j one byte with bit 0 = a^j resident on its own,
-// bit 1 = abar^j resident, bit 2 = delta^j resident, and the running sum of resident sizes.
-constexpr int kSimChunk = 256;  // operations staged per pass, a multiple of the wave size
+// Self-check of operation lists: one work-group per chain executes its list under the memory model
+// of Table 1 ("List of Operations").  What is resident of stage x (bit 0 = a^x on its own, bit 1 =
+// abar^x, bit 2 = delta^x) depends only on the operations on stages x and x + 1, in their order, as long
+// as none of them finds an operand missing -- and then the list is corrupt whatever follows.  So a thread
+// takes a stage and steps through its own operations (found by a bit mask per stage), all stages
+// at once; the thread of an operation's input stage also notes by how much the operation changes the
+// resident sum.  Then a thread takes an operation: prefix sums give the memory before each one.
+// What bounds it: a few dependent LDS reads per operation of the busiest stage.  About 8 us, where one lane
+// stepping through the whole list took 210 us for the lists of 8 chains of 192 stages.
+constexpr int kSimThreads = 256;  // at least CKPT_MAX_L + 1 stages and the empty mask after them
+constexpr int kSimChunk = 4 * kSimThreads;  // operations staged per pass
+static_assert(CKPT_MAX_L + 2 <= kSimThreads, "a thread per stage");
 
-__global__ void __launch_bounds__(64) simulate_kernel(ckpt_chains_t ch, int L, const ckpt_op_t* __restrict__ ops,
-                                                       int cap, const int32_t* __restrict__ n_ops,
-                                                       long long* __restrict__ time_out,
-                                                       long long* __restrict__ peak_out, int32_t* __restrict__ status) {
+__global__ void __launch_bounds__(kSimThreads) simulate_kernel(ckpt_chains_t ch, int L, const ckpt_op_t* __restrict__ ops,
+                                                                int cap, const int32_t* __restrict__ n_ops,
+                                                                long long* __restrict__ time_out,
+                                                                long long* __restrict__ peak_out,
+                                                                int32_t* __restrict__ status) {
+    constexpr int kPer = kSimChunk / kSimThreads, kWaves = kSimThreads / 64;
     __shared__ int32_t s_uf[CKPT_MAX_L], s_ub[CKPT_MAX_L], s_wab[CKPT_MAX_L], s_of[CKPT_MAX_L], s_ob[CKPT_MAX_L];
     __shared__ int32_t s_wa[CKPT_MAX_L + 1], s_wd[CKPT_MAX_L + 1];
-    __shared__ uint8_t s_state[CKPT_MAX_L + 2];
-    __shared__ ckpt_op_t s_ops[kSimChunk];
-    const int b = blockIdx.x, lane = threadIdx.x;
+    __shared__ uint32_t s_mask[kSimChunk / 32][kSimThreads];  // [word][stage]: which operations of the pass are the stage's
+    __shared__ uint8_t s_kind[kSimChunk], s_stage[kSimChunk];
+    __shared__ long long s_delta[kSimChunk];
+    __shared__ long long s_total[kWaves], s_peak[kWaves], s_time[kWaves];
+    __shared__ int s_bad;
+    const int b = blockIdx.x, x = threadIdx.x, lane = x & 63, wave = x >> 6;
     const int n = n_ops[b];
-    if (n < 0 || n > cap) {  // uniform over the wave
-        if (lane == 0) {
+    if (n < 0 || n > cap) {  // uniform over the work-group
+        if (x == 0) {
             status[b] = n < 0 ? n : CKPT_E_ARG;
             time_out[b] = peak_out[b] = -1;
         }
         return;
     }
     const int32_t* wd = ch.wdelta ? ch.wdelta : ch.wa;
-    for (int k = lane; k < L; k += 64) {
-        s_uf[k] = ch.uf[size_t(b) * L + k];
-        s_ub[k] = ch.ub[size_t(b) * L + k];
-        s_wab[k] = ch.wabar[size_t(b) * L + k];
-        s_of[k] = ch.of ? ch.of[size_t(b) * L + k] : 0;
-        s_ob[k] = ch.ob ? ch.ob[size_t(b) * L + k] : 0;
+    if (x == 0) s_bad = 0;
+    if (x < L) {
+        s_uf[x] = ch.uf[size_t(b) * L + x];
+        s_ub[x] = ch.ub[size_t(b) * L + x];
+        s_wab[x] = ch.wabar[size_t(b) * L + x];
+        s_of[x] = ch.of ? ch.of[size_t(b) * L + x] : 0;
+        s_ob[x] = ch.ob ? ch.ob[size_t(b) * L + x] : 0;
     }
-    for (int k = lane; k <= L; k += 64) {
-        s_wa[k] = k ? ch.wa[size_t(b) * (L + 1) + k] : 0;  // the chain input a^0 is not counted
-        s_wd[k] = wd[size_t(b) * (L + 1) + k];
-        s_state[k] = k == 0 ? 1 : k == L ? 4 : 0;  // a^0 and delta^L are there from the start
+    if (x <= L) {
+        s_wa[x] = x ? ch.wa[size_t(b) * (L + 1) + x] : 0;  // the chain input a^0 is not counted
+        s_wd[x] = wd[size_t(b) * (L + 1) + x];
     }
-    __syncthreads();
     const ckpt_op_t* list = ops + size_t(b) * cap;
-    long long time = 0, peak = 0, resident = s_wd[L];
+    int state = x == 0 ? 1 : x == L ? 4 : 0;  // a^0 and delta^L are there from the start
     bool bad = false;
-    for (int base = 0; base < n; base += kSimChunk) {  // n is uniform over the wave
-        if (base) __syncthreads();  // lane 0 is done with the previous part of the list
-        for (int k = lane; k < kSimChunk && base + k < n; k += 64) s_ops[k] = list[base + k];
+    long long time = 0, peak = 0, carry = 0;
+    for (int base = 0; base < n; base += kSimChunk) {  // n is uniform over the work-group
+        const int count = min(kSimChunk, n - base), words = (count + 31) / 32;
+        for (int w = 0; w < words; ++w) s_mask[w][x] = 0;
         __syncthreads();
-        if (lane != 0 || bad) continue;
-        const int end = min(kSimChunk, n - base);
-        for (int k = 0; k < end; ++k) {
-            const int kind = s_ops[k].kind, j = s_ops[k].stage;
-            if (j < 1 || j > L || kind > CKPT_OP_B) { bad = true; break; }
-            const int in = s_state[j - 1], self = s_state[j];
-            if (kind == CKPT_OP_B) {  // needs delta^j, abar^j and a^{j-1}; its output is not counted while it runs
-                if (!(self & 4) || !(self & 2) || !(in & 3)) { bad = true; break; }
-                peak = max(peak, resident + s_ob[j - 1]);
-                resident -= (long long)s_wd[j] + s_wab[j - 1];
-                if (in & 1) resident -= s_wa[j - 1];
-                if (!(in & 4)) resident += s_wd[j - 1];
-                s_state[j] = uint8_t(self & 1);
-                s_state[j - 1] = uint8_t((in & 2) | 4);
-                time += s_ub[j - 1];
-            } else {  // a forward operation needs room for its output; F_null drops its input
-                const int bit = kind == CKPT_OP_F_ALL ? 2 : 1;
-                if (!(in & 3) || (kind == CKPT_OP_F_NULL && !(in & 1)) || (self & bit)) { bad = true; break; }
-                const long long size = kind == CKPT_OP_F_ALL ? s_wab[j - 1] : s_wa[j];
-                peak = max(peak, resident + size + s_of[j - 1]);
-                resident += size;
-                s_state[j] = uint8_t(self | bit);
-                if (kind == CKPT_OP_F_NULL) {
-                    resident -= s_wa[j - 1];
-                    s_state[j - 1] = uint8_t(in & ~1);
+        for (int k = x; k < count; k += kSimThreads) {
+            const int kind = list[base + k].kind, j = list[base + k].stage;
+            s_kind[k] = uint8_t(kind), s_stage[k] = uint8_t(j);
+            if (j < 1 || j > L || kind > CKPT_OP_B) bad = true;
+            else atomicOr(&s_mask[k >> 5][j], 1u << (k & 31));
+        }
+        __syncthreads();
+        if (base == 0) carry = s_wd[L];
+        if (x <= L) {
+            for (int w = 0; w < words; ++w) {
+                const uint32_t next = s_mask[w][x + 1];  // operations that read a^x: those of stage x + 1
+                for (uint32_t todo = s_mask[w][x] | next; todo; todo &= todo - 1) {
+                    const int bit = __builtin_ctz(todo), k = 32 * w + bit;
+                    const int kind = s_kind[k];
+                    if (next >> bit & 1u) {  // j = x + 1
+                        if (kind == CKPT_OP_B) {  // its output is not counted while it runs
+                            bad = bad || !(state & 3);
+                            s_delta[k] = ((state & 4) ? 0ll : (long long)s_wd[x]) - ((state & 1) ? (long long)s_wa[x] : 0ll) -
+                                         s_wd[x + 1] - s_wab[x];
+                            state = (state & 2) | 4;
+                        } else {  // a forward operation adds its output; F_null drops its input
+                            const bool drops = kind == CKPT_OP_F_NULL;
+                            bad = bad || !(state & 3) || (drops && !(state & 1));
+                            s_delta[k] = (long long)(kind == CKPT_OP_F_ALL ? s_wab[x] : s_wa[x + 1]) - (drops ? (long long)s_wa[x] : 0ll);
+                            if (drops) state &= ~1;
+                        }
+                    } else if (kind == CKPT_OP_B) {  // needs delta^x and abar^x
+                        bad = bad || (state & 6) != 6;
+                        state &= 1;
+                    } else {
+                        const int made = kind == CKPT_OP_F_ALL ? 2 : 1;
+                        bad = bad || (state & made);
+                        state |= made;
+                    }
                 }
-                time += s_uf[j - 1];
             }
         }
+        __syncthreads();
+        long long delta[kPer], before = 0;  // this thread's operations follow each other
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int k = kPer * x + u;
+            delta[u] = k < count ? s_delta[k] : 0;
+            before += delta[u];
+        }
+        const long long own = before;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const long long v = __shfl_up(before, o);
+            if (lane >= o) before += v;
+        }
+        if (lane == 63) s_total[wave] = before;
+        __syncthreads();
+        before += carry - own;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (w < wave) before += s_total[w];
+            carry += s_total[w];
+        }
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const int k = kPer * x + u;
+            if (k >= count) break;
+            const int kind = s_kind[k], j = min(max(int(s_stage[k]), 1), L);
+            if (kind == CKPT_OP_B) {
+                peak = max(peak, before + s_ob[j - 1]);
+                time += s_ub[j - 1];
+            } else {  // a forward operation needs room for its output and o_f
+                peak = max(peak, before + (kind == CKPT_OP_F_ALL ? s_wab[j - 1] : s_wa[j]) + s_of[j - 1]);
+                time += s_uf[j - 1];
+            }
+            before += delta[u];
+        }
+        __syncthreads();  // the next pass overwrites the list
     }
-    if (lane == 0) {
-        if (!bad && !(s_state[0] & 4)) bad = true;  // the list must end with delta^0
-        status[b] = bad ? CKPT_E_CORRUPT : CKPT_OK;
-        time_out[b] = bad ? -1 : time;
-        peak_out[b] = bad ? -1 : peak;
+    if (x == 0 && !(state & 4)) bad = true;  // the list must end with delta^0
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        time += __shfl_xor(time, o);
+        peak = max(peak, __shfl_xor(peak, o));
+    }
+    if (lane == 0) s_time[wave] = time, s_peak[wave] = peak;
+    if (n == 0) __syncthreads();  // s_bad is set
+    if (bad) s_bad = 1;
+    __syncthreads();
+    if (x == 0) {
+        for (int w = 1; w < kWaves; ++w) time += s_time[w], peak = max(peak, s_peak[w]);
+        status[b] = s_bad ? CKPT_E_CORRUPT : CKPT_OK;
+        time_out[b] = s_bad ? -1 : time;
+        peak_out[b] = s_bad ? -1 : peak;
     }
 }
 
@@ -2237,7 +2304,7 @@ int ckpt_simulate_batched(const ckpt_chains_t* chains, int L, int B, const ckpt_
         !peak_out || !status || ops_cap < 0 || L < 1 || B < 1)
         return CKPT_E_ARG;
     if (L > CKPT_MAX_L) return CKPT_E_LIMIT;
-    hipLaunchKernelGGL(simulate_kernel, dim3(B), dim3(64), 0, static_cast<hipStream_t>(stream), *chains, L, ops,
+    hipLaunchKernelGGL(simulate_kernel, dim3(B), dim3(kSimThreads), 0, static_cast<hipStream_t>(stream), *chains, L, ops,
                        ops_cap, n_ops, reinterpret_cast<long long*>(time_out), reinterpret_cast<long long*>(peak_out),
                        status);
     return hip_ok(hipGetLastError()) ? CKPT_OK : CKPT_E_HIP;

@@ -419,6 +419,32 @@ def test_simulate_batched_edited_lists(amd, oracle_mod):
     assert kinds == {0, -1, -3, -7}
 
 
+@pytest.mark.parametrize("L", [1, 43, 44, 63, 254])
+def test_simulate_batched_lists_around_and_far_beyond_a_pass(amd, oracle_mod, L):
+    """The longest lists there are (every backward recomputes from the input: L (L + 3) / 2 operations, 989
+    and 1034 for 43 and 44 stages), whole and with one operation taken out, doubled or moved where passes meet."""
+    import torch
+    from workloads.chains import random_chain_batch
+    full = []
+    for t in range(L, 0, -1):
+        full += ([(1, 1)] + [(2, j) for j in range(2, t)] if t > 1 else []) + [(0, t), (3, t)]
+    n = len(full)
+    assert n == L * (L + 3) // 2
+    lists = [full]
+    for at in sorted({k for k in (0, 1, 31, 32, 1022, 1023, 1024, 1025, n // 2, n - 2, n - 1) if 0 <= k < n}):
+        lists += [full[:at] + full[at + 1:], full[:at + 1] + full[at:], full[:at] + full[at + 1:] + [full[at]]]
+    B, cap = len(lists), n + 1
+    batch = random_chain_batch(L, 8, B, L, size_hi=9, time_hi=900, overheads=True, own_wdelta=True)
+    ops = np.zeros((B, cap, 2), np.uint8)
+    for b, one in enumerate(lists):
+        ops[b, :len(one)] = np.array(one, np.uint8).reshape(-1, 2)
+    n_ops = torch.tensor([len(one) for one in lists], dtype=torch.int32, device="cuda")
+    time, peak, status = _simulate_on_device(amd, batch, torch.from_numpy(ops).cuda(), cap, n_ops)
+    for b, one in enumerate(lists):
+        assert (time[b], peak[b], status[b]) == _oracle_simulation(oracle_mod, batch, b, one), b
+    assert status[0] == 0 and -7 in status
+
+
 @pytest.mark.parametrize("L,M,count,base,num,den,seed", [
     (1, 1, 1, 5, 0, 1, 0), (7, 64, 10, 1000, 1, 10, 1), (48, 1024, 10, 80 << 30, 1, 10, 2),
     (192, 4096, 16, 1 << 33, 1, 8, 3), (33, 1 << 20, 5, 12345678901, 3, 20, 4),
