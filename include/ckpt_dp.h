@@ -188,8 +188,9 @@ int ckpt_solve_batched_opts(const ckpt_chains_t* chains, int L, int M, int B, vo
  * calls that overlap in time on one GPU race -- serialise them (one stream, or events).
  * The tables are those of ckpt_solve_batched, bit for bit.  ckpt_check_inputs with
  * workspace = NULL reads the flags of the most recent such solve on the current device.
- * Returns as ckpt_solve_batched, plus CKPT_E_LIMIT when ckpt_workspace_bytes(L, M, B) exceeds
- * CKPT_NOALLOC_MAX_WORKSPACE.
+ * Returns as ckpt_solve_batched, plus CKPT_E_LIMIT when the part of ckpt_workspace_bytes(L, M, B) that a
+ * solve cannot do without (all but its samples of finished cells, which bound the candidates) exceeds
+ * CKPT_NOALLOC_MAX_WORKSPACE; where the samples do not fit beside it the solve is slower.
  */
 #define CKPT_NOALLOC_MAX_WORKSPACE (16u << 20)
 int ckpt_solve_batched_noalloc(const ckpt_chains_t* chains, int L, int M, int B, void* stream, int32_t* cost,

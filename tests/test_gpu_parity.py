@@ -450,3 +450,50 @@ print("RESULT", codes, ok)
 ''' % os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
     assert "RESULT [-8, 0] True" in out.stdout, out.stdout[-2000:] + out.stderr[-2000:]
+
+
+@pytest.mark.parametrize("L", [1, 16, 17, 63, 64, 65, 128, 254])
+def test_input_flags_wherever_the_bad_value_stands(amd, oracle_mod, L):
+    """A chain per kind of bad value and position, sums of forward times around 2^30; the tables of the
+    chains that pass equal the oracle's."""
+    import torch
+    top = 1 << 28
+    good = random_chain_batch(L, 40, 1, 900 + L, size_hi=5, time_hi=50, overheads=True, own_wdelta=True)
+    rows, want = [], []
+
+    def chain(flag, **edits):
+        one = {k: getattr(good, k)[0].astype(np.int64).copy() for k in ("uf", "ub", "wa", "wabar", "wdelta", "of", "ob")}
+        for name, (at, value) in edits.items():
+            one[name][at] = value
+        rows.append(one)
+        want.append(flag)
+
+    chain(0)
+    for at in sorted({0, L // 2, L - 1}):
+        for name in ("uf", "ub"):
+            chain(1, **{name: (at, -1)})
+            chain(2, **{name: (at, 1 << 30)})
+        chain(9, wabar=(at, -1))
+        chain(4, wabar=(at, top + 1))
+        for name in ("of", "ob"):
+            chain(1, **{name: (at, -1)})
+            chain(4, **{name: (at, top + 1)})
+        chain(8, wabar=(at, 0))
+    for at in sorted({0, L // 2, L}):
+        chain(1, wa=(at, -1))
+        chain(1, wdelta=(at, -1))
+        chain(4, wdelta=(at, top + 1))
+        chain(12 if at else 4, wa=(at, top + 1))
+    rest = int(good.uf[0].sum()) - int(good.uf[0, L - 1])
+    chain(0, uf=(L - 1, (1 << 30) - 1 - rest))
+    chain(2, uf=(L - 1, (1 << 30) - rest))
+    cols = {k: np.stack([r[k] for r in rows]).astype(np.int32) for k in rows[0]}
+    batch = ChainBatch("flags", L, 40, len(rows), **cols)
+    sol = amd.solve(batch, check=False)
+    lib, flags = amd.load_library(), np.zeros(batch.B, np.int32)
+    lib.ckpt_check_inputs(sol.workspace.data_ptr(), L, 40, batch.B, None, flags.ctypes.data)
+    assert flags.tolist() == want
+    iu = np.triu_indices(L)
+    for b in (b for b in range(batch.B) if want[b] == 0):
+        cost, pick = oracle_mod.solve_chain(L, 40, *batch.chain(b))
+        assert (sol.cost[b, :, :41].cpu().numpy() == cost[iu]).all() and (sol.arg[b, :, :41].cpu().numpy() == pick[iu]).all()
