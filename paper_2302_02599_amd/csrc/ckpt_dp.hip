@@ -911,6 +911,11 @@ __global__ void __launch_bounds__(kRowWG) row_kernel(Ctx c, int D) {
 // no line of the table is touched before its owner has written it.
 // Each loaded operand of a split is kept in registers for all rows that use it: per tile and
 // lane 7 x 8 + 28 + 64 operand loads instead of the 252 + 224 + 64 of one launch per row.
+// What bounds it: the chain of row steps.  Loads and stores complete in issue order, so a load behind
+// a row's stores waits until these are written through; what a row needs from earlier launches is
+// therefore requested before the stores of the row below it, a wave asks memory for rows of
+// this launch only where a shifted column lies below its band, and a number that the gemm already stored
+// is not read and written again.  A step takes 2 to 2.5 us instead of 3 to 4 (timestamps, 5 chains of 53 stages).
 // ---------------------------------------------------------------------------
 constexpr int kSpinLimit = 1 << 20;        // default polls of a wait before it gives up (seconds, never reached)
 
@@ -921,10 +926,13 @@ constexpr int kSpinLimit = 1 << 20;        // default polls of a wait before it 
 // costs one memory round trip, and an address is one add: every access is
 // descriptor base + per-lane offset (row offset from here + 4 m - 4 shift) + cc * row pitch.
 struct TilePar {
-    int32_t mall[kT][kT], mnull[kT][kT], need[kT][kT];  // [r][cc]: cell (i0 + r, j_cc)
+    int32_t mall[kT][kT], mnull[kT][kT];  // [r][cc]: cell (i0 + r, j_cc)
+    int32_t need[kT];         // feasibility frontier of row r: the smallest of its cells
     int32_t Pi[kT + 1];       // P[i0 + u], u = 0..8
     int32_t Pj[kT];           // P[min(jb + c2 + 1, L - 1)]
     int32_t wsh[kT + 1];      // shift of split q = i0 + u
+    int32_t wshj[kT];         // shift of split q = min(jb + c2 + 1, L - 1)
+    uint32_t joff[kT];        // byte offset of cell (q, jb), the same q
     int32_t wabs[kT], fb[kT];
     uint32_t rowoff[kT + 1];  // byte offset of cell (i0 + u, jb) in the chain's cost table, u = 0..8
     uint32_t diagoff[kT];     // byte offset of cell (i0 + r, i0 + r)
@@ -949,6 +957,8 @@ struct TileCtx {
     // rj[c2][cc] = cell (jb + c2 + 1, j_cc) at its shift, c2 < cc (column block, D >= 1)
     uint32_t ri[kT + 1][kT];
     uint32_t rj[kT][kT];
+    // requested a row ahead: left operands (i, q-1) of the splits in the row block, gemm partials
+    uint32_t nl[kT], pc[kT];
 };
 
 // Table accesses of the row kernel: voff = per-lane byte offset (kNoRead: nothing is read, the
@@ -1004,6 +1014,10 @@ __device__ __forceinline__ void read_row_below(TileCtx<DC>& x, const uint32_t (*
     const bool in_band = t >= 0;
     const uint32_t voff = (!in_band && x.m >= sh) ? x.moff + rowoff - 4 * sh : kNoRead;
     if (CNT && __any(voff != kNoRead)) count_work<CNT>(x.c.work, 2, unsigned(max(0, cend - first_cc)), 0);
+#pragma unroll
+    for (int cc = 0; cc < kT; ++cc)
+        if (cc >= first_cc && cc < cend) out[cc] = below[cc][in_band ? t : 0];
+    if (!__any(voff != kNoRead)) return;  // a wave whose shifted columns all lie in its band asks memory for nothing
     uint32_t mem[kT];
     auto fetch = [&]() {
         uint32_t marks = 0;
@@ -1033,9 +1047,28 @@ __device__ __forceinline__ void read_row_below(TileCtx<DC>& x, const uint32_t (*
     }
 #pragma unroll
     for (int cc = 0; cc < kT; ++cc) {
-        if (cc >= first_cc && cc < cend) {
-            const uint32_t lds = below[cc][in_band ? t : 0];
-            out[cc] = in_band ? lds : mem[cc];
+        if (cc >= first_cc && cc < cend) out[cc] = in_band ? out[cc] : mem[cc];
+    }
+}
+
+// The number of a cell whose minimum is the gemm's partial: it stands in the table already.
+constexpr uint32_t kKeepPick = 256;
+
+// Requests what row R needs from earlier launches: left operands and the gemm's partial minima.
+template <int DC, int R, bool FULL>
+__device__ __forceinline__ void request_row(TileCtx<DC>& x) {
+    constexpr int NQ = (DC == 0) ? 0 : (DC == 1 ? kT - R : kT - 1 - R);
+    const TilePar& par = *x.par;
+    if (int(__builtin_amdgcn_readfirstlane(int(x.m)) | 63) < par.need[R]) return;  // the row is infeasible in this chunk
+    const uint32_t left = x.moff + par.diagoff[R];  // cell (i, i); (i, i + u) is u rows further
+#pragma unroll
+    for (int u = 0; u < NQ; ++u) x.nl[u] = tld(x.tab, left, x.col4[u]);
+    if (DC == 2) {  // gemm partial; bit 31 marks it
+        const int cend = FULL ? kT : x.cend;
+        const uint32_t own = x.moff + par.rowoff[R];
+#pragma unroll
+        for (int cc = 0; cc < kT; ++cc) {
+            if (cc < cend) x.pc[cc] = tld(x.tab, own, x.col4[cc]);
         }
     }
 }
@@ -1048,7 +1081,6 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
     constexpr int RF = (DC == 2) ? T - 2 : T - 1;                      // first row this kernel finishes
     constexpr int CF = (DC == 0) ? R : 0;                              // first column with j >= i
     constexpr int NQ = (DC == 0) ? 0 : (DC == 1 ? T - R : T - 1 - R);  // splits in the row block (D = 1: and q = jb)
-    constexpr int NQA = NQ > 0 ? NQ : 1;
     constexpr int U = R + 1;                                           // the row below
     const int L = x.L;
     const int cend = FULL ? T : x.cend;
@@ -1078,38 +1110,22 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
                     if (cc < cend) x.ri[U][cc] = tld(x.tab, voff, x.col4[cc]);
             }
         }
-        int row_need = 1 << 30;
-#pragma unroll
-        for (int cc = CF; cc < T; ++cc)
-            row_need = min(row_need, par.need[R][cc]);
         const int m_hi = __builtin_amdgcn_readfirstlane(int(m)) | 63;
-        const bool live = m_hi >= row_need;  // else the whole chunk lies below the feasibility frontier of the row
+        const bool live = m_hi >= par.need[R];  // else the whole chunk lies below the feasibility frontier of the row
         const unsigned cols = unsigned(max(0, cend - CF));  // cells of the row that exist
         // loads from earlier launches: the row below (first row of the kernel only), left operands, the
-        // gemm's partial minima (cost + number), C_all operands (first row only); reads of rows of this
+        // gemm's partial minima, C_all operands (first row only); reads of rows of this
         // launch are counted where they are issued, and only for waves that reach below their band
-        count_work<CNT>(x.c.work, 2, (below_here ? 0u : cols) + (live ? unsigned(NQ) + (DC == 2 ? 10u : 0u) +
+        count_work<CNT>(x.c.work, 2, (below_here ? 0u : cols) + (live ? unsigned(NQ) + (DC == 2 ? 8u : 0u) +
                                                                           (below_here ? 0u : cols) : 0u), cols);
         const uint32_t Pi = par.Pi[R];
         const uint32_t fbi = par.fb[R];
         const uint32_t wabi = par.wabs[R];
         const uint32_t own = moff + par.rowoff[R];  // this lane's cell of the row, column block start
-        uint32_t nl[NQA], pc[T], pp[T], al[T];
+        uint32_t al[T];
 #pragma unroll
-        for (int cc = 0; cc < T; ++cc) al[cc] = 0, pc[cc] = 0xffffffffu, pp[cc] = 0;
+        for (int cc = 0; cc < T; ++cc) al[cc] = 0;
         if (live) {
-            const uint32_t left = moff + par.diagoff[R];  // cell (i, i); (i, i + u) is u rows further
-#pragma unroll
-            for (int u = 0; u < NQ; ++u) nl[u] = tld(x.tab, left, x.col4[u]);
-            if (DC == 2) {  // gemm partial; bit 31 marks it
-#pragma unroll
-                for (int cc = 0; cc < T; ++cc) {
-                    if (cc < cend) {
-                        pc[cc] = tld(x.tab, own, x.col4[cc]) & 0x7fffffffu;
-                        pp[cc] = uint32_t(__builtin_amdgcn_raw_buffer_load_b8(x.atab, int(own >> 2), int(x.col4[cc] >> 2), 0));
-                    }
-                }
-            }
             // C_all: cell (i + 1, j) at m - omega_abar^{i+1}, for j > i
             if (below_here) {
                 read_row_below<DC, FULL, CNT>(x, below, par.rowoff[U], wabi, DC == 0 ? CF + 1 : CF, al);
@@ -1126,7 +1142,7 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
 #pragma unroll
             for (int u = 0; u < NQ; ++u) {
                 const int q = i + 1 + u;
-                const uint32_t lb = nl[u] + (uint32_t(par.Pi[R + 1 + u]) - Pi);
+                const uint32_t lb = x.nl[u] + (uint32_t(par.Pi[R + 1 + u]) - Pi);
 #pragma unroll
                 for (int cc = 0; cc < T; ++cc) {
                     const uint32_t v = lb + x.ri[R + 1 + u][cc];
@@ -1135,9 +1151,14 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
             }
             if (DC == 2) {
 #pragma unroll
-                for (int cc = 0; cc < T; ++cc)
-                    if (pc[cc] < best[cc]) best[cc] = pc[cc], pick[cc] = pp[cc];
+                for (int cc = 0; cc < T; ++cc) {
+                    const uint32_t v = x.pc[cc] & 0x7fffffffu;
+                    if (cc < cend && v < best[cc]) best[cc] = v, pick[cc] = kKeepPick;
+                }
             }
+            // Before this row's stores are issued: a load that follows a store would wait until the store is written through.
+            if constexpr (R > 0) request_row<DC, R - 1, FULL>(x);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int cc = CF; cc < T; ++cc) {
 #pragma unroll
@@ -1159,11 +1180,13 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
             for (int cc = CF; cc < T; ++cc) {
                 if (cc < cend) {  // cost with a device-scope store: other bands read it in this launch
                     __builtin_amdgcn_raw_buffer_store_b32(int(val[cc]), x.tab, int(own), int(x.col4[cc]), 16);
-                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(pick[cc]), x.atab, int(own >> 2),
-                                                         int(x.col4[cc] >> 2), 0);
+                    const uint32_t at = DC == 2 && pick[cc] == kKeepPick ? kNoRead : own >> 2;
+                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(pick[cc]), x.atab, int(at), int(x.col4[cc] >> 2), 0);
                 }
             }
         } else {
+            if constexpr (R > 0) request_row<DC, R - 1, FULL>(x);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int cc = CF; cc < T; ++cc) {
                 if (cc < cend) {
@@ -1254,7 +1277,11 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int3
             const size_t at = (bL + i) * L + min(x.jb + (t & 7), L - 1);  // no dynamic index into x: it stays in registers
             s_par.mall[r][t & 7] = c.ws.mall[at];
             s_par.mnull[r][t & 7] = c.ws.mnull[at];
-            s_par.need[r][t & 7] = c.ws.need[at];  // weak or exact, whichever is there: both are lower bounds
+            // weak or exact frontier, whichever is there: both are lower bounds
+            int need = (t & 7) >= (DC == 0 ? r : 0) && (t & 7) < x.cend && x.i0 + r < L ? c.ws.need[at] : 1 << 30;
+#pragma unroll
+            for (int o = 4; o > 0; o >>= 1) need = min(need, __shfl_xor(need, o));
+            if ((t & 7) == 0) s_par.need[r] = need;
         } else if (t < 64 + T + 1) {
             const int u = t - 64, q = min(x.i0 + u, L - 1);
             s_par.Pi[u] = P[min(x.i0 + u, L)];
@@ -1264,6 +1291,8 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int3
         } else if (t >= 96 && t < 96 + T) {
             const int r = t - 96, q = min(x.jb + r + 1, L - 1), i = min(x.i0 + r, L - 1);
             s_par.Pj[r] = P[q];
+            s_par.wshj[r] = wsh[q];
+            s_par.joff[r] = uint32_t(row_base(L, q) + x.jb) * uint32_t(c.pitch) * 4u;
             s_par.wabs[r] = c.ws.wabs[bL + i];
             s_par.fb[r] = c.ws.fb[bL + i];
             s_par.diagoff[r] = uint32_t(row_base(L, i) + i) * uint32_t(c.pitch) * 4u;
@@ -1277,12 +1306,8 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int3
     {   // A band below the feasibility frontier of every cell this kernel finishes in the tile: all of
         // them are infeasible there.  Store that and leave (the whole work-group decides alike).
         int tile_need = 1 << 30;
-        {   // every wave for itself: lane = cell, then a minimum over the wave
-            const int lane = threadIdx.x & 63, r = lane >> 3, cc = lane & 7;
-            if (r <= RF && cc >= (DC == 0 ? r : 0) && x.i0 + r < c.L && cc < x.cend) tile_need = s_par.need[r][cc];
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) tile_need = min(tile_need, __shfl_xor(tile_need, o));
-        }
+        for (int r = 0; r <= RF; ++r) tile_need = min(tile_need, s_par.need[r]);
         if (int(min(uint32_t(x.band) * kBand + kBand - 1, uint32_t(c.pitch) - 1)) < tile_need) {
             unsigned cells = 0;
             if (!x.idle && !x.dead) {
@@ -1322,14 +1347,16 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int3
         const int m0 = __builtin_amdgcn_readfirstlane(int(x.m));  // first column of the wave
         x.nwait = max(0, x.chunk0 - (max(0, m0 - reach) >> 6));
     }
+#pragma unroll
+    for (int cc = 0; cc < T; ++cc) x.nl[cc] = 0, x.pc[cc] = 0;
     if (DC >= 1 && !x.dead && !x.idle) {
+        if (x.cend == T) request_row<DC, RF, true>(x);
+        else request_row<DC, RF, false>(x);
         // operands of the splits in the column block, finished by earlier launches
 #pragma unroll
         for (int c2 = 0; c2 < T - 1; ++c2) {
-            const int q = min(x.jb + c2 + 1, c.L - 1);
-            const uint32_t sh = uint32_t(wsh[q]);
-            const uint32_t voff =
-                x.m >= sh ? x.moff + uint32_t(row_base(c.L, q) + x.jb) * uint32_t(c.pitch) * 4u - 4 * sh : kNoRead;
+            const uint32_t sh = uint32_t(s_par.wshj[c2]);
+            const uint32_t voff = x.m >= sh ? x.moff + s_par.joff[c2] - 4 * sh : kNoRead;
 #pragma unroll
             for (int cc = c2 + 1; cc < T; ++cc)
                 if (cc < x.cend) x.rj[c2][cc] = tld(x.tab, voff, x.col4[cc]);
