@@ -331,6 +331,12 @@ __device__ __forceinline__ uint32_t ld32(rsrc_t tab, uint32_t elem, uint32_t off
     return uint32_t(__builtin_amdgcn_raw_buffer_load_b32(tab, int(off), int(elem << 2), 0));
 }
 
+// Table accesses of the tile kernels: voff = per-lane byte offset (kNoRead: nothing is read, the
+// result is 0), soff = wave-uniform byte offset.  dev = device scope.
+__device__ __forceinline__ uint32_t tld(rsrc_t tab, uint32_t voff, uint32_t soff) {
+    return uint32_t(__builtin_amdgcn_raw_buffer_load_b32(tab, int(voff), int(soff), 0));
+}
+
 // Keeps the samples of cells (i, 8 J .. 8 J + 7): every kG-th lane stores its eight values.
 __device__ __forceinline__ void store_samples(const Ctx& c, int b, int i, int J, uint32_t m, const uint32_t (&val)[kT]) {
     if (!c.ws.samp || (m & (kG - 1)) != kG - 1) return;
@@ -444,6 +450,10 @@ __device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, co
 // slots busy; 2.9 ms a solve for L = 192, M = 4096, B = 8 at 4.0 TB/s asked for, where evaluating every
 // feasible split took 5.7 ms and 29 GB (5.5 % of the splits are left instead of 67 %).  kG = 16: bounds
 // over 64 columns leave 11.7 %, over 32 7.5 %.  Half a tile a wave keeps it at 128 registers, four waves a SIMD.
+// The epilogue reads nothing behind its stores (a load behind a store waits until it is through, and the
+// compiler moves no load across a store to the tables): gates, shifts and prefix sums of row 7 are fetched
+// with the splits at the start.  With scalar loads per column between the stores a launch took 2 to 4 us
+// more (64 x 96 stages: 3.91 ms a solve, now 3.50).
 // KS > 1 (launches with too few tiles to fill the chip): KS waves share one half chunk, each takes
 // every KS-th pass of stage 1 and every KS-th entry of the list, and their keys are merged
 // through LDS at the end.
@@ -475,14 +485,27 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
     __shared__ int s_list[2 * CH][CKPT_MAX_L + 2];        // the splits that are left: k = q - qlo
     __shared__ uint32_t s_ub[2 * CH][4][R * T];           // upper bound of every cell in every sub-chunk
     __shared__ int s_n[2 * CH];
+    // row 7: gates of its cells, and shift, prefix sum and table row of the splits in the column block
+    __shared__ int32_t s_mall[T], s_mnull[T], s_jsh[T], s_jP[T];
     const int nq = qhi - qlo + 1;
+    const int i7 = I * T + T - 1;
+    if (threadIdx.x < T) {
+        const int j = min(j0 + int(threadIdx.x), L - 1), q = min(j0 + int(threadIdx.x) + 1, L - 1);
+        s_mall[threadIdx.x] = c.ws.mall[(size_t(b) * L + i7) * L + j];
+        s_mnull[threadIdx.x] = c.ws.mnull[(size_t(b) * L + i7) * L + j];
+        s_jsh[threadIdx.x] = c.ws.wsh[size_t(b) * L + q];
+        s_jP[threadIdx.x] = P[q];
+    }
     for (int k = threadIdx.x; k < nq; k += NT)
         s_split[k] = make_int2(c.ws.wsh[size_t(b) * L + qlo + k], P[qlo + k]);
     // A chunk below the frontier of every cell of the wave has no candidate.
     const bool active = chunk * 64 < pitch;
     int out_need = need[(i0 + ((lane >> 3) & (R - 1))) * L + min(j0 + (lane & 7), L - 1)];
 #pragma unroll
-    for (int o = 16; o > 0; o >>= 1) out_need = min(out_need, __shfl_xor(out_need, o));
+    for (int o = 4; o > 0; o >>= 1) out_need = min(out_need, __shfl_xor(out_need, o));
+    const bool live7 = half == 1 && active && chunk * 64 + 63 >= __builtin_amdgcn_readlane(out_need, 8 * (R - 1));
+#pragma unroll
+    for (int o = 16; o > 4; o >>= 1) out_need = min(out_need, __shfl_xor(out_need, o));
     const bool search = active && chunk * 64 + 63 >= out_need;  // uniform over the waves of a group
     if (slice == 0) {
         for (int k = lane; k < 4 * R * T; k += 64) s_ub[grp][k >> 5][k & 31] = kInf - 1 + uint32_t(P[i0 + ((k & 31) >> 3)]);
@@ -633,11 +656,14 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
     const int n_all = __builtin_amdgcn_readfirstlane(s_n[grp]);
     const int n = active && n_all > slice ? (n_all - slice + KS - 1) / KS : 0;
 
-    uint32_t lrow0[R], jcol[T];
+    // Addresses are descriptor + per-lane offset (the split's row, one add) + a scalar offset that stays for
+    // the whole kernel: byte offsets of the wave's rows from row i0 and of the tile's columns from column j0.
+    uint32_t rowstep[R], colstep[T];
 #pragma unroll
-    for (int r = 0; r < R; ++r) lrow0[r] = uint32_t(tri_row(L, i0 + r, i0 + r) - (i0 + r) - 1);  // + q = row of (i, q-1)
+    for (int r = 0; r < R; ++r) rowstep[r] = uint32_t(row_base(L, i0 + r) - row_base(L, i0)) * uint32_t(pitch) * 4u;
 #pragma unroll
-    for (int cc = 0; cc < T; ++cc) jcol[cc] = uint32_t(min(j0 + cc, L - 1));
+    for (int cc = 0; cc < T; ++cc) colstep[cc] = uint32_t(min(cc, L - 1 - j0)) * uint32_t(pitch) * 4u;
+    const uint32_t left0 = uint32_t(row_base(L, i0) - 1);  // + q = row of (i0, q - 1)
     double key[R][T];
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -651,12 +677,12 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
             const int k = __builtin_amdgcn_readfirstlane(s_list[grp][slice + KS * min(t, n - 1)]);
             const int q = qlo + k;
             const uint32_t sh = uint32_t(__builtin_amdgcn_readfirstlane(s_split[k].x));
-            const uint32_t rq = uint32_t(q * L - (q * (q - 1)) / 2 - q);  // + j = row of (q, j)
-            const uint32_t off = t < n ? moff : kNoRead;
+            const uint32_t left = t < n ? moff + (left0 + uint32_t(q)) * uint32_t(pitch) * 4u : kNoRead;
+            const uint32_t right = t < n ? moff + (uint32_t(row_base(L, q) + j0) * uint32_t(pitch) - sh) * 4u : kNoRead;
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[r] = ld32(tab, (lrow0[r] + uint32_t(q)) * uint32_t(pitch), off);
+            for (int r = 0; r < R; ++r) v[r] = tld(tab, left, rowstep[r]);
 #pragma unroll
-            for (int cc = 0; cc < T; ++cc) v[R + cc] = ld32(tab, (rq + jcol[cc]) * uint32_t(pitch) - sh, off);
+            for (int cc = 0; cc < T; ++cc) v[R + cc] = tld(tab, right, colstep[cc]);
         };
         auto compute = [&](const uint32_t(&v)[R + T], int t) {
             const int k = __builtin_amdgcn_readfirstlane(s_list[grp][slice + KS * min(t, n - 1)]);
@@ -711,19 +737,20 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
 
     // Row 7: operands of its column-block splits and of C_all are requested before the other rows
     // are converted and stored -- unless the whole chunk lies below the frontier of its cells.
-    const int i7 = I * T + T - 1;
-    int jc[T];
-#pragma unroll
-    for (int cc = 0; cc < T; ++cc) jc[cc] = int(jcol[cc]);
-    bool live7 = false;
     uint32_t tj[T][T], al[T];
-    if (half == 1) {
-        int need7 = 1 << 30;
+    uint32_t fb7 = 0;
+    if (live7) {  // wave-uniform
 #pragma unroll
-        for (int cc = 0; cc < T; ++cc) need7 = min(need7, need[i7 * L + jc[cc]]);
-        live7 = chunk * 64 + 63 >= need7;  // wave-uniform
-        if (live7)
-            load_row_tail<T, 0>(tab, c.ws.wsh + size_t(b) * L, L, pitch, i7, j0, jc, c.ws.wabs[size_t(b) * L + i7], moff, tj, al);
+        for (int c2 = 0; c2 < T - 1; ++c2) {
+            const int q = min(j0 + c2 + 1, L - 1);
+            const uint32_t right = moff + (uint32_t(row_base(L, q) + j0) * uint32_t(pitch) - uint32_t(s_jsh[c2])) * 4u;
+#pragma unroll
+            for (int cc = c2 + 1; cc < T; ++cc) tj[c2][cc] = tld(tab, right, colstep[cc]);
+        }
+        fb7 = uint32_t(c.ws.fb[size_t(b) * L + i7]);
+        const uint32_t below = moff + (uint32_t(row_base(L, i7 + 1) + j0) * uint32_t(pitch) - uint32_t(c.ws.wabs[size_t(b) * L + i7])) * 4u;
+#pragma unroll
+        for (int cc = 0; cc < T; ++cc) al[cc] = tld(tab, below, colstep[cc]);
     }
     // The mantissa of a key holds 256 cost + number: cost is the 32 bits from bit 8 on.
     auto partial = [&](int r, int cc, uint32_t Pi, uint32_t& cst, uint32_t& num) {
@@ -731,46 +758,63 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
         cst = uint32_t(bits >> 8) - Pi;
         num = uint32_t(bits) & 255u;
     };
+    const uint32_t at7 = m + uint32_t(tri_row(L, i7, j0)) * uint32_t(pitch);
+    uint32_t best[T], pick[T];
+    if (half == 1) {
+#pragma unroll
+        for (int cc = 0; cc < T; ++cc) partial(R - 1, cc, uint32_t(P[i7]), best[cc], pick[cc]);
+    }
     // A partial minimum is stored with bit 31 set: a finished cell never exceeds 2^30, so whoever
     // reads the table can tell a cell that still waits for its row kernel from a finished one.
     // Partial minima of 2^31 - 1 and more are infeasible whatever they were and are clamped.
+    // full: the tile has all eight columns.
+    auto store = [&](auto full) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        if (r == R - 1 && half == 1) break;  // row 7
-        const uint32_t Pi = uint32_t(P[i0 + r]);
-        const uint32_t row = uint32_t(tri_row(L, i0 + r, j0)) * uint32_t(pitch);
+        for (int r = 0; r < R; ++r) {
+            if (r == R - 1 && half == 1) break;  // row 7
+            const uint32_t Pi = uint32_t(P[i0 + r]);
+            const uint32_t at = m + uint32_t(tri_row(L, i0 + r, j0)) * uint32_t(pitch);
 #pragma unroll
-        for (int cc = 0; cc < T; ++cc) {
-            if (cc < cend) {
-                uint32_t cst, num;
-                partial(r, cc, Pi, cst, num);
-                const uint32_t at = row + uint32_t(cc) * uint32_t(pitch);
-                __builtin_amdgcn_raw_buffer_store_b32(int(min(cst, 0x7fffffffu) | 0x80000000u), tab, int(moff), int(at << 2), 0);
-                __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(num), atab, int(m), int(at), 0);
+            for (int cc = 0; cc < T; ++cc) {
+                if (full || cc < cend) {
+                    uint32_t cst, num;
+                    partial(r, cc, Pi, cst, num);
+                    __builtin_amdgcn_raw_buffer_store_b32(int(min(cst, 0x7fffffffu) | 0x80000000u), tab, int(at << 2), int(colstep[cc]), 0);
+                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(num), atab, int(at), int(colstep[cc] >> 2), 0);
+                }
             }
         }
-    }
-    count_work<CNT>(c.work, 0, live7 ? 36u : 0u, unsigned(R) * unsigned(cend));
-    if (half == 0) return;
-    if (live7) {
-        uint32_t best[T], pick[T];
-#pragma unroll
-        for (int cc = 0; cc < T; ++cc) partial(R - 1, cc, uint32_t(P[i7]), best[cc], pick[cc]);
-        finish_row<T, 0, 2>(c, b, chain, P, c.ws.mall + (size_t(b) * L + i7) * L, c.ws.mnull + (size_t(b) * L + i7) * L, L,
-                            pitch, i7, j0, cend, jc, c.ws.fb[size_t(b) * L + i7], m, best, pick, tj, al);
-    } else {
-        const size_t row = chain + size_t(tri_row(L, i7, j0)) * pitch + m;
-        uint32_t inf[T];
+        count_work<CNT>(c.work, 0, live7 ? 36u : 0u, unsigned(R) * unsigned(cend));
+        if (half == 0) return;
+        // splits in the column block with the left operand (i, q-1) = the cell just finished, then the m_null gate,
+        // C_all with the m_all gate (smallest candidate number: wins ties), saturation
+        uint32_t val[T];
+        const uint32_t Pi = uint32_t(P[i7]);
 #pragma unroll
         for (int cc = 0; cc < T; ++cc) {
-            inf[cc] = kInf;
-            if (cc < cend) {
-                c.cost[row + size_t(cc) * pitch] = int32_t(kInf);
-                c.arg[row + size_t(cc) * pitch] = 0;
+            val[cc] = kInf;
+            uint32_t num = 0;
+            if (live7) {
+#pragma unroll
+                for (int c2 = 0; c2 < cc; ++c2) {
+                    const uint32_t v = val[c2] + (uint32_t(s_jP[c2]) - Pi) + tj[c2][cc];
+                    if (v < best[cc]) best[cc] = v, pick[cc] = min(j0 + c2 + 1, L - 1) + 1;
+                }
+                const uint32_t ck = (m >= uint32_t(s_mnull[cc])) ? min(best[cc], kInf) : kInf;
+                const uint32_t all = (m >= uint32_t(s_mall[cc])) ? min(fb7 + al[cc], kInf) : kInf;
+                const bool take_all = all < kInf && all <= ck;
+                val[cc] = take_all ? all : ck;
+                num = take_all ? uint32_t(i7 + 1) : (ck < kInf ? pick[cc] : 0u);
+            }
+            if (full || cc < cend) {
+                __builtin_amdgcn_raw_buffer_store_b32(int(val[cc]), tab, int(at7 << 2), int(colstep[cc]), 0);
+                __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(num), atab, int(at7), int(colstep[cc] >> 2), 0);
             }
         }
-        store_samples(c, b, i7, J, m, inf);
-    }
+        store_samples(c, b, i7, J, m, val);
+    };
+    if (cend == T) store(std::true_type{});
+    else store(std::false_type{});
 }
 
 // Finishes row R of every tile of block diagonal D: cells (i, j), i = I*T + R, j in block
@@ -961,11 +1005,6 @@ struct TileCtx {
     uint32_t nl[kT], pc[kT];
 };
 
-// Table accesses of the row kernel: voff = per-lane byte offset (kNoRead: nothing is read, the
-// result is 0), soff = wave-uniform byte offset.  dev = device scope.
-__device__ __forceinline__ uint32_t tld(rsrc_t tab, uint32_t voff, uint32_t soff) {
-    return uint32_t(__builtin_amdgcn_raw_buffer_load_b32(tab, int(voff), int(soff), 0));
-}
 __device__ __forceinline__ uint32_t tld_dev(rsrc_t tab, uint32_t voff, uint32_t soff) {
     return uint32_t(__builtin_amdgcn_raw_buffer_load_b32(tab, int(voff), int(soff), 16));
 }
