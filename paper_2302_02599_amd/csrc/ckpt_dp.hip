@@ -70,13 +70,13 @@ inline bool hip_ok(hipError_t e) {
 //   mnull [B][L][L] int32  m_null^{s,t}
 //   flags [B]      int32   input precondition flags
 //   need  [B][L][L] int32  feasibility frontier: smallest m at which cell (i, j) can be finite
-//   prog  [B][tiles][chunks] int32  rows of tile (I, J) finished by tile_rows_kernel for the chunk
-//                          of 64 columns; tiles = nblk (nblk + 1) / 2, chunks = pitch / 64
-//   tick  [nblk][4] int32  ticket counter of the tile_rows_kernel launch of diagonal D, group g
+//   prog  [B][tiles][chunks + 1] int32  rows of tile (I, J) finished by tile_rows_kernel for the chunk
+//                          of 64 columns; tiles = nblk (nblk + 1) / 2, chunks = pitch / 64; last word: bands of
+//                          the tile that work-groups have taken
 //   fault [1]      int32   set when a bounded wait inside tile_rows_kernel expired
 //   samp  [B][4 nblk (nblk + 1)][pitch / kG][8] int32  every kG-th column of the finished cells, eight cells of a
 //                          row side by side (see gemm_kernel); left out where the workspace is too small
-// prog, tick and fault are cleared by precompute_kernel at the start of every solve.
+// prog and fault are cleared by precompute_kernel at the start of every solve.
 struct Workspace {
     int32_t* P;
     int32_t* fb;
@@ -87,7 +87,6 @@ struct Workspace {
     int32_t* flags;
     int32_t* need;
     int32_t* prog;
-    int32_t* tick;
     int32_t* fault;
     int32_t* samp;  // null: no samples are kept
 };
@@ -96,7 +95,6 @@ constexpr int kG = 16;  // columns between samples
 constexpr double kKeyBase = 0x1p44;
 
 constexpr int kBand = kRowWG;  // columns of m per work-group of the row kernels
-constexpr int kTickGroups = 4;
 
 inline size_t align64(size_t n) { return (n + 63) & ~size_t(63); }
 __host__ __device__ inline int blocks_of(int L) { return (L + kT - 1) / kT; }
@@ -111,12 +109,18 @@ __host__ __device__ inline size_t samp_ints(int L, int pitch) {
     return blocks_of(L) < 3 ? 0 : size_t(pitch / kG) * samp_rows(L) * kT;
 }
 
-// 2 align64(B L) of these are spare: the limit on the static workspace is stated in this size.
+__host__ __device__ inline int prog_words(int pitch) { return pitch / 64 + 1; }
 inline size_t ws_ints(int L, int pitch, int B) {
     return align64(size_t(B) * (L + 1)) + 3 * align64(size_t(B) * L) + 3 * align64(size_t(B) * L * L) +
-           align64(size_t(B)) + 2 * align64(size_t(B) * L) + align64(size_t(B) * tiles_of(L) * (pitch / 64)) +
-           align64(size_t(blocks_of(L)) * kTickGroups) + 64;
+           align64(size_t(B)) + align64(size_t(B) * tiles_of(L) * prog_words(pitch)) + 64;
 }
+// The measure by which ckpt_solve_batched_noalloc accepts a call; kScratchSlack holds what a solve needs beyond it
+// (a word per tile: less than 1/384 of the three tables of L^2 words).
+inline size_t limit_ints(int L, int pitch, int B) {
+    return ws_ints(L, pitch, B) - align64(size_t(B) * tiles_of(L) * prog_words(pitch)) +
+           align64(size_t(B) * tiles_of(L) * (pitch / 64)) + 2 * align64(size_t(B) * L) + align64(size_t(blocks_of(L)) * 4);
+}
+constexpr size_t kScratchSlack = 1 << 16;
 
 inline Workspace carve(void* base, int L, int pitch, int B, bool samples) {
     int32_t* p = static_cast<int32_t*>(base);
@@ -129,8 +133,7 @@ inline Workspace carve(void* base, int L, int pitch, int B, bool samples) {
     w.mnull = p;  p += align64(size_t(B) * L * L);
     w.flags = p;  p += align64(size_t(B));
     w.need = p;   p += align64(size_t(B) * L * L);
-    w.prog = p;   p += align64(size_t(B) * tiles_of(L) * (pitch / 64));
-    w.tick = p;   p += align64(size_t(blocks_of(L)) * kTickGroups);
+    w.prog = p;   p += align64(size_t(B) * tiles_of(L) * prog_words(pitch));
     w.fault = p;  p += 64;
     w.samp = samples && samp_ints(L, pitch) ? p : nullptr;
     return w;
@@ -197,13 +200,10 @@ __global__ void __launch_bounds__(kPreThreads) precompute_kernel(ckpt_chains_t c
     auto sz = [](int v) { return min(max(v, 0), 1 << 28); };
     s_wa[tid] = sz(a_in), s_wd[tid] = sz(d_in), s_wab[tid] = sz(ab_in), s_of[tid] = sz(of_in), s_ob[tid] = sz(ob_in);
     if (tid == 0) s_flags = 0;
-    {   // progress flags of this chain's tiles, and (first block) the ticket counters and the fault word
-        const size_t n = tiles_of(L) * (pitch / 64);
+    {   // progress and ticket words of this chain's tiles, and (first block) the fault word
+        const size_t n = tiles_of(L) * prog_words(pitch);
         for (size_t k = size_t(part) * kPreThreads + tid; k < n; k += size_t(gridDim.y) * kPreThreads) ws.prog[size_t(b) * n + k] = 0;
-        if (b == 0 && part == 0) {
-            for (int k = tid; k < blocks_of(L) * kTickGroups; k += kPreThreads) ws.tick[k] = 0;
-            if (tid == 0) ws.fault[0] = 0;
-        }
+        if (b == 0 && part == 0 && tid == 0) ws.fault[0] = 0;
     }
     __syncthreads();
     if (tid >= 1 && tid <= L) s_pair[tid] = s_wa[tid - 1] + s_wa[tid] + s_of[tid - 1];
@@ -935,9 +935,10 @@ __global__ void __launch_bounds__(kRowWG) row_kernel(Ctx c, int D) {
 // Row r needs the row below it in the same tile at m - shift: from its own band, and from lower
 // bands that other work-groups finish in the same launch.
 //   - Inside the band the row below travels through LDS (two buffers, one barrier per row).
-//   - Between bands it travels through memory.  Work-groups take their work by ticket (an atomic
-//     counter), bands in ascending order, so whatever a wave waits for belongs to a work-group
-//     that already runs -- no deadlock, whatever order the hardware starts work-groups in.
+//   - Between bands it travels through memory.  The work-groups of a tile take its bands by ticket (an
+//     atomic counter per tile: one counter for a whole launch made 800 work-groups queue for 5 us), in
+//     ascending order, so whatever a wave waits for belongs to a work-group that already runs -- no
+//     deadlock, whatever order the hardware starts work-groups in.
 //     D >= 2: before its row is finished a cell holds the gemm's partial minimum, marked by bit 31
 //     (finished cells never exceed 2^30), so a reader needs no flag and a writer never waits for
 //     its stores: a lane that finds the mark simply reads again.  D < 2: the cells hold whatever
@@ -1263,27 +1264,25 @@ struct TileRows {
 };
 
 template <int DC, bool CNT>
-__global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int32_t* tick) {
+__global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
     constexpr int T = kT;
     constexpr int RF = (DC == 2) ? T - 2 : T - 1;
-    __shared__ int s_ticket, s_fault;
+    __shared__ int s_band, s_fault;
     __shared__ uint32_t s_row[2][kT][kBand];  // the last two finished rows of this band
     __shared__ TilePar s_par;
-    if (threadIdx.x == 0) {
-        s_ticket = atomicAdd(tick, 1);
-        s_fault = __hip_atomic_load(c.ws.fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    const uint32_t ntile = gridDim.y, per_band = gridDim.y * gridDim.z;
-    const uint32_t ticket = uint32_t(s_ticket);
-    if (ticket >= gridDim.x * per_band) return;  // cannot happen: one ticket per work-group
+    // Work-groups are started in linear order: the first bands of all tiles and chains, then the second ones, ...
+    const uint32_t items = gridDim.y * gridDim.z;
+    const uint32_t item = (blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)) % items;
     TileCtx<DC> x;
     x.c = c;
-    x.band = int(ticket / per_band);  // bands in ascending order
-    const uint32_t rest = ticket - uint32_t(x.band) * per_band;
-    x.I = int(rest % ntile);
+    x.I = int(item % gridDim.y);
     x.J = x.I + D;
-    x.b = c.b0 + int(rest / ntile);
+    x.b = c.b0 + int(item / gridDim.y);
+    x.prog = c.ws.prog + (size_t(x.b) * tiles_of(c.L) + tile_index(blocks_of(c.L), x.I, x.J)) * prog_words(c.pitch);
+    if (threadIdx.x == kRowWG - 1) {  // a wave that fetches none of the parameters below
+        s_band = atomicAdd(x.prog + c.pitch / 64, 1);
+        s_fault = __hip_atomic_load(c.ws.fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     x.L = c.L;
     x.pitch = c.pitch;
     x.i0 = x.I * T;
@@ -1292,10 +1291,7 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int3
     const size_t chain = size_t(x.b) * c.rows * c.pitch;
     x.tab = table_rsrc(c.cost + chain, uint32_t(c.rows) * uint32_t(c.pitch) * 4u);
     x.atab = __builtin_amdgcn_make_buffer_rsrc(c.arg + chain, 0, int(uint32_t(c.rows) * uint32_t(c.pitch)), 0x00020000);
-    x.m = uint32_t(x.band) * kBand + threadIdx.x;
-    x.moff = x.m * 4;
     x.seen = 0;
-    x.dead = s_fault != 0;  // an earlier work-group gave up: drain
 #pragma unroll
     for (int cc = 0; cc < T; ++cc) x.col4[cc] = uint32_t(cc) * uint32_t(c.pitch) * 4u;
 #pragma unroll
@@ -1338,10 +1334,15 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int3
         }
     }
     x.par = &s_par;
+    __syncthreads();
+    x.band = __builtin_amdgcn_readfirstlane(s_band);
+    if (x.band >= bands_of(c.pitch)) return;  // cannot happen: one ticket per work-group
+    x.m = uint32_t(x.band) * kBand + threadIdx.x;
+    x.moff = x.m * 4;
+    x.dead = s_fault != 0;  // an earlier work-group gave up: drain
     // The band may lie past the end of the rows (pitch is a multiple of 64, not of kBand): those
     // waves read and store nothing but still meet every barrier.
     x.idle = x.m >= uint32_t(c.pitch);
-    __syncthreads();
     {   // A band below the feasibility frontier of every cell this kernel finishes in the tile: all of
         // them are infeasible there.  Store that and leave (the whole work-group decides alike).
         int tile_need = 1 << 30;
@@ -1369,16 +1370,12 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D, int3
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                     __builtin_amdgcn_s_waitcnt(0);
                     if ((threadIdx.x & 63) == 0)
-                        __hip_atomic_store(c.ws.prog + (size_t(x.b) * tiles_of(c.L) + tile_index(blocks_of(c.L), x.I, x.J)) *
-                                                           (c.pitch / 64) + (x.m >> 6),
-                                           RF + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        __hip_atomic_store(x.prog + (x.m >> 6), RF + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
             return;
         }
     }
-    const int nblk = blocks_of(c.L);
-    x.prog = c.ws.prog + (size_t(x.b) * tiles_of(c.L) + tile_index(nblk, x.I, x.J)) * (c.pitch / 64);
     x.chunk0 = x.band * (kBand / 64);
     {   // chunks below the band that the shifts of this tile's rows can reach from this wave's columns
         int reach = 0;
@@ -1907,7 +1904,7 @@ struct Device {
 // Workspace of ckpt_solve_batched_noalloc, for callers that cannot allocate: a fixed array in
 // every GPU's copy of the code object, held until the process ends.  In host code the array's
 // name is only a handle for hipGetSymbolAddress; kernels are given the resolved address.
-static __device__ __align__(256) unsigned char g_scratch[CKPT_NOALLOC_MAX_WORKSPACE];
+static __device__ __align__(256) unsigned char g_scratch[CKPT_NOALLOC_MAX_WORKSPACE + kScratchSlack];
 
 std::mutex g_devices_lock;
 Device g_devices[64];
@@ -2075,10 +2072,9 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work};
             if (fused_rows) {
                 const dim3 grid(nbands, nblk - D, B);
-                int32_t* tick = ws.tick + D * kTickGroups;
                 const auto fn = D == 0 ? (work ? tile_rows_kernel<0, true> : tile_rows_kernel<0, false>)
                                        : (work ? tile_rows_kernel<1, true> : tile_rows_kernel<1, false>);
-                hipLaunchKernelGGL(fn, grid, dim3(kRowWG), 0, st, ctx, D, tick);
+                hipLaunchKernelGGL(fn, grid, dim3(kRowWG), 0, st, ctx, D);
                 CKPT_AFTER_LAUNCH(CKPT_K_ROW);
                 continue;
             }
@@ -2126,8 +2122,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
                 for (int g = 0; g < groups; ++g) {
                     const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work};
                     const auto fn = work ? tile_rows_kernel<2, true> : tile_rows_kernel<2, false>;
-                    hipLaunchKernelGGL(fn, dim3(nbands, nblk - D, first[g + 1] - first[g]), dim3(kRowWG), 0, gs[g], ctx,
-                                       D, ws.tick + D * kTickGroups + g);
+                    hipLaunchKernelGGL(fn, dim3(nbands, nblk - D, first[g + 1] - first[g]), dim3(kRowWG), 0, gs[g], ctx, D);
                     CKPT_AFTER_LAUNCH(CKPT_K_ROW);
                 }
                 continue;
@@ -2164,7 +2159,7 @@ size_t ckpt_workspace_bytes(int L, int M, int B) {
 
 // What a solve cannot do without: everything but the samples.
 static size_t least_workspace_bytes(int L, int M, int B) {
-    return ws_ints(L, int(ckpt_row_pitch(M)), B) * sizeof(int32_t);
+    return limit_ints(L, int(ckpt_row_pitch(M)), B) * sizeof(int32_t);
 }
 
 int ckpt_init(int device) {
