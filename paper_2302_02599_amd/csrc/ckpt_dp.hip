@@ -960,7 +960,10 @@ __global__ void __launch_bounds__(kRowWG) row_kernel(Ctx c, int D) {
 // a row's stores waits until these are written through; what a row needs from earlier launches is
 // therefore requested before the stores of the row below it, a wave asks memory for rows of
 // this launch only where a shifted column lies below its band, and a number that the gemm already stored
-// is not read and written again.  A step takes 2 to 2.5 us instead of 3 to 4 (timestamps, 5 chains of 53 stages).
+// is not read and written again.  Both reads of the row below (operands of the splits, of C_all) are one round
+// trip.  The rest of a step is issue: 900 instructions, so gates are selects on the operands, and what is
+// the same for the whole wave is decided once.  5 chains of 53 stages: 26 us a launch, 34 us before; 334 -> 241 us
+// a solve.
 // ---------------------------------------------------------------------------
 constexpr int kSpinLimit = 1 << 20;        // default polls of a wait before it gives up (seconds, never reached)
 
@@ -996,7 +999,6 @@ struct TileCtx {
     int nwait;        // chunks below the band that this wave's shifted reads can reach
     int seen;         // lane k < nwait: progress of chunk chunk0 - 1 - k as last looked at
     bool dead;        // a wait expired: stop working, keep meeting the barriers (per wave)
-    bool idle;        // this wave's columns lie past the end of the rows (wave-uniform)
     // right operands kept for all rows: ri[u][cc] = cell (i0 + u, j_cc) at m - omega_a^{i0+u}, u = 1..8
     // (rows of this tile; u = 8 is the first stage of the column block, D = 1 only);
     // rj[c2][cc] = cell (jb + c2 + 1, j_cc) at its shift, c2 < cc (column block, D >= 1)
@@ -1040,39 +1042,49 @@ __device__ __forceinline__ void wait_rows_below(TileCtx<DC>& x, int rows) {
     }
 }
 
-// Cells (i0 + u, jb + cc), cc = first_cc .. cend - 1, of a row finished in THIS launch, at column
-// m - sh: from LDS if that column lies in this band (`below` = the row's buffer), else from the
-// table with a device-scope load.
+// Cells (i0 + u, jb + cc), cc = first_cc .. cend - 1, of a row finished in THIS launch, at column m - sh (operands
+// of the splits, out) and, if `both`, at column m - sh2 (operands of C_all, out2): from LDS if that column lies in
+// this band (`below` = the row's buffer), else from the table with device-scope loads, in one round trip.
 // D >= 2: the cells of the tile hold the gemm's partial minima, marked by bit 31, until their
 // row is finished, so the read needs no flag: a lane that finds the mark reads again (bounded).
 // D < 2: the caller has waited for the progress flags of the chunks that are read.
 template <int DC, bool FULL, bool CNT>
-__device__ __forceinline__ void read_row_below(TileCtx<DC>& x, const uint32_t (*below)[kBand], uint32_t rowoff,
-                                               uint32_t sh, int first_cc, uint32_t (&out)[kT]) {
+__device__ __forceinline__ void read_row_below(TileCtx<DC>& x, const uint32_t (*below)[kBand], uint32_t rowoff, int first_cc,
+                                               uint32_t sh, uint32_t (&out)[kT], bool both, uint32_t sh2, uint32_t (&out2)[kT]) {
     const int cend = FULL ? kT : x.cend;
-    const int t = int(threadIdx.x) - int(sh);  // column inside the band
-    const bool in_band = t >= 0;
-    const uint32_t voff = (!in_band && x.m >= sh) ? x.moff + rowoff - 4 * sh : kNoRead;
-    if (CNT && __any(voff != kNoRead)) count_work<CNT>(x.c.work, 2, unsigned(max(0, cend - first_cc)), 0);
+    const int t = int(threadIdx.x) - int(sh), t2 = int(threadIdx.x) - int(sh2);  // columns inside the band
+    const bool in_band = t >= 0, in_band2 = t2 >= 0;
+    const bool far = !in_band && x.m >= sh, far2 = both && !in_band2 && x.m >= sh2;
 #pragma unroll
-    for (int cc = 0; cc < kT; ++cc)
-        if (cc >= first_cc && cc < cend) out[cc] = below[cc][in_band ? t : 0];
-    if (!__any(voff != kNoRead)) return;  // a wave whose shifted columns all lie in its band asks memory for nothing
-    uint32_t mem[kT];
+    for (int cc = 0; cc < kT; ++cc) {
+        if (cc >= first_cc && cc < cend) {
+            out[cc] = below[cc][in_band ? t : 0];
+            out2[cc] = below[cc][in_band2 ? t2 : 0];
+        }
+    }
+    if (!__any(far || far2)) return;  // a wave whose shifted columns all lie in its band asks memory for nothing
+    const uint32_t voff = far ? x.moff + rowoff - 4 * sh : kNoRead, voff2 = far2 ? x.moff + rowoff - 4 * sh2 : kNoRead;
+    if (CNT && __any(far)) count_work<CNT>(x.c.work, 2, unsigned(max(0, cend - first_cc)), 0);
+    if (CNT && __any(far2)) count_work<CNT>(x.c.work, 2, unsigned(max(0, cend - first_cc)), 0);
+    uint32_t mem[kT], mem2[kT];
     auto fetch = [&]() {
         uint32_t marks = 0;
 #pragma unroll
         for (int cc = 0; cc < kT; ++cc) {
-            mem[cc] = 0;
+            mem[cc] = mem2[cc] = 0;
             if (cc >= first_cc && cc < cend) mem[cc] = tld_dev(x.tab, voff, x.col4[cc]);  // only cells that exist
-            marks |= mem[cc];
         }
+#pragma unroll
+        for (int cc = 0; cc < kT; ++cc)
+            if (cc >= first_cc && cc < cend) mem2[cc] = tld_dev(x.tab, voff2, x.col4[cc]);
+#pragma unroll
+        for (int cc = 0; cc < kT; ++cc) marks |= mem[cc] | mem2[cc];
         return (marks >> 31) != 0;
     };
     bool again = fetch();
     if (DC == 2) {
         int spin = 0;
-        if (x.c.spin_limit < 0) again = !in_band && x.m >= sh;  // forced: every read from another band gives up
+        if (x.c.spin_limit < 0) again = far || far2;  // forced: every read from another band gives up
         while (__any(again)) {  // some lane met a cell that its owner has not finished yet
             if (++spin > x.c.spin_limit ||
                 ((spin & 63) == 0 && __hip_atomic_load(x.c.ws.fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
@@ -1087,7 +1099,10 @@ __device__ __forceinline__ void read_row_below(TileCtx<DC>& x, const uint32_t (*
     }
 #pragma unroll
     for (int cc = 0; cc < kT; ++cc) {
-        if (cc >= first_cc && cc < cend) out[cc] = in_band ? out[cc] : mem[cc];
+        if (cc >= first_cc && cc < cend) {
+            out[cc] = in_band ? out[cc] : mem[cc];
+            out2[cc] = in_band2 ? out2[cc] : mem2[cc];
+        }
     }
 }
 
@@ -1099,13 +1114,13 @@ template <int DC, int R, bool FULL>
 __device__ __forceinline__ void request_row(TileCtx<DC>& x) {
     constexpr int NQ = (DC == 0) ? 0 : (DC == 1 ? kT - R : kT - 1 - R);
     const TilePar& par = *x.par;
-    if (int(__builtin_amdgcn_readfirstlane(int(x.m)) | 63) < par.need[R]) return;  // the row is infeasible in this chunk
-    const uint32_t left = x.moff + par.diagoff[R];  // cell (i, i); (i, i + u) is u rows further
+    const bool live = int(__builtin_amdgcn_readfirstlane(int(x.m)) | 63) >= par.need[R];  // else the row is infeasible in this chunk
+    const uint32_t left = live ? x.moff + par.diagoff[R] : kNoRead;  // cell (i, i); (i, i + u) is u rows further
 #pragma unroll
     for (int u = 0; u < NQ; ++u) x.nl[u] = tld(x.tab, left, x.col4[u]);
     if (DC == 2) {  // gemm partial; bit 31 marks it
         const int cend = FULL ? kT : x.cend;
-        const uint32_t own = x.moff + par.rowoff[R];
+        const uint32_t own = live ? x.moff + par.rowoff[R] : kNoRead;
 #pragma unroll
         for (int cc = 0; cc < kT; ++cc) {
             if (cc < cend) x.pc[cc] = tld(x.tab, own, x.col4[cc]);
@@ -1132,17 +1147,19 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
     const uint32_t (*below)[kBand] = s_row[U & 1];
     uint32_t (*mine)[kBand] = s_row[R & 1];
     uint32_t val[T];
-#pragma unroll
-    for (int cc = 0; cc < T; ++cc) val[cc] = kInf;
 
     if (DC < 2 && below_here) wait_rows_below(x, RF - R);
-    if (!x.dead && !x.idle) {
+    if (!x.dead) {
+        const int m_hi = __builtin_amdgcn_readfirstlane(int(m)) | 63;
+        const bool live = m_hi >= par.need[R];  // else the whole chunk lies below the feasibility frontier of the row
+        const uint32_t wabi = par.wabs[R];
+        uint32_t al[T];  // operands of C_all: cell (i + 1, j) at m - omega_abar^{i+1}, for j > i
         // ---- loads of this row, all issued together ----
         // the operands that the row below contributes to all rows above it, kept
         if ((U < T || DC == 1) && x.i0 + U < L) {
             const uint32_t sh = uint32_t(par.wsh[U]);
             if (below_here) {
-                read_row_below<DC, FULL, CNT>(x, below, par.rowoff[U], sh, DC == 0 ? U : 0, x.ri[U]);
+                read_row_below<DC, FULL, CNT>(x, below, par.rowoff[U], DC == 0 ? U : 0, sh, x.ri[U], live, wabi, al);
             } else {  // finished by an earlier launch
                 const uint32_t voff = m >= sh ? moff + par.rowoff[U] - 4 * sh : kNoRead;
 #pragma unroll
@@ -1150,26 +1167,17 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
                     if (cc < cend) x.ri[U][cc] = tld(x.tab, voff, x.col4[cc]);
             }
         }
-        const int m_hi = __builtin_amdgcn_readfirstlane(int(m)) | 63;
-        const bool live = m_hi >= par.need[R];  // else the whole chunk lies below the feasibility frontier of the row
         const unsigned cols = unsigned(max(0, cend - CF));  // cells of the row that exist
         // loads from earlier launches: the row below (first row of the kernel only), left operands, the
         // gemm's partial minima, C_all operands (first row only); reads of rows of this
         // launch are counted where they are issued, and only for waves that reach below their band
         count_work<CNT>(x.c.work, 2, (below_here ? 0u : cols) + (live ? unsigned(NQ) + (DC == 2 ? 8u : 0u) +
                                                                           (below_here ? 0u : cols) : 0u), cols);
-        const uint32_t Pi = par.Pi[R];
-        const uint32_t fbi = par.fb[R];
-        const uint32_t wabi = par.wabs[R];
         const uint32_t own = moff + par.rowoff[R];  // this lane's cell of the row, column block start
-        uint32_t al[T];
-#pragma unroll
-        for (int cc = 0; cc < T; ++cc) al[cc] = 0;
         if (live) {
-            // C_all: cell (i + 1, j) at m - omega_abar^{i+1}, for j > i
-            if (below_here) {
-                read_row_below<DC, FULL, CNT>(x, below, par.rowoff[U], wabi, DC == 0 ? CF + 1 : CF, al);
-            } else if (i + 1 < L) {  // row 0 of the tile below, or row 7 finished by the gemm: earlier launches
+            const uint32_t Pi = par.Pi[R];
+            const uint32_t fbi = par.fb[R];
+            if (!below_here && i + 1 < L) {  // row 0 of the tile below, or row 7 finished by the gemm: earlier launches
                 const uint32_t voff = m >= wabi ? moff + par.rowoff[U] - 4 * wabi : kNoRead;
 #pragma unroll
                 for (int cc = (DC == 0 ? CF + 1 : CF); cc < T; ++cc)
@@ -1178,15 +1186,14 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
             // ---- evaluation, in candidate-number order with strict '<' ----
             uint32_t best[T], pick[T];
 #pragma unroll
-            for (int cc = 0; cc < T; ++cc) best[cc] = 0xffffffffu, pick[cc] = 0;
-#pragma unroll
             for (int u = 0; u < NQ; ++u) {
                 const int q = i + 1 + u;
                 const uint32_t lb = x.nl[u] + (uint32_t(par.Pi[R + 1 + u]) - Pi);
 #pragma unroll
                 for (int cc = 0; cc < T; ++cc) {
                     const uint32_t v = lb + x.ri[R + 1 + u][cc];
-                    if (v < best[cc]) best[cc] = v, pick[cc] = q + 1;
+                    if (u == 0) best[cc] = v, pick[cc] = q + 1;
+                    else if (v < best[cc]) best[cc] = v, pick[cc] = q + 1;
                 }
             }
             if (DC == 2) {
@@ -1201,6 +1208,7 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int cc = CF; cc < T; ++cc) {
+                if (NQ == 0) best[cc] = kInf, pick[cc] = 0;
 #pragma unroll
                 for (int c2 = CF; c2 < cc; ++c2) {  // splits in the column block: left operand (i, q-1) = val[c2]
                     const int q = min(x.jb + c2 + 1, L - 1);
@@ -1208,13 +1216,14 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
                     const uint32_t v = val[c2] + (uint32_t(par.Pj[c2]) - Pi) + r;
                     if (v < best[cc]) best[cc] = v, pick[cc] = q + 1;
                 }
-                const uint32_t ck = (m >= uint32_t(par.mnull[R][cc])) ? min(best[cc], kInf) : kInf;
-                uint32_t all = fbi;
+                // Gates; C_all has the smallest candidate number and wins ties.  Sums of 2^30 and more are infeasible
+                // whatever they are.
+                const uint32_t ck = m >= uint32_t(par.mnull[R][cc]) ? best[cc] : kInf;
+                uint32_t all = m >= uint32_t(par.mall[R][cc]) ? fbi : kInf;
                 if (DC != 0 || cc > CF) all += al[cc];  // j > i
-                all = (m >= uint32_t(par.mall[R][cc])) ? min(all, kInf) : kInf;
-                const bool take_all = all < kInf && all <= ck;
-                val[cc] = take_all ? all : ck;
-                pick[cc] = take_all ? uint32_t(i + 1) : (ck < kInf ? pick[cc] : 0u);
+                pick[cc] = all <= ck ? uint32_t(i + 1) : pick[cc];
+                val[cc] = min(min(all, ck), kInf);
+                pick[cc] = val[cc] < kInf ? pick[cc] : 0u;
             }
 #pragma unroll
             for (int cc = CF; cc < T; ++cc) {
@@ -1224,9 +1233,13 @@ __device__ __forceinline__ void tile_row(TileCtx<DC>& x, uint32_t (*s_row)[kT][k
                     __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(pick[cc]), x.atab, int(at), int(x.col4[cc] >> 2), 0);
                 }
             }
+#pragma unroll
+            for (int cc = 0; cc < CF; ++cc) val[cc] = kInf;  // no cells
         } else {
             if constexpr (R > 0) request_row<DC, R - 1, FULL>(x);
             __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int cc = 0; cc < T; ++cc) val[cc] = kInf;
 #pragma unroll
             for (int cc = CF; cc < T; ++cc) {
                 if (cc < cend) {
@@ -1340,9 +1353,6 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
     x.m = uint32_t(x.band) * kBand + threadIdx.x;
     x.moff = x.m * 4;
     x.dead = s_fault != 0;  // an earlier work-group gave up: drain
-    // The band may lie past the end of the rows (pitch is a multiple of 64, not of kBand): those
-    // waves read and store nothing but still meet every barrier.
-    x.idle = x.m >= uint32_t(c.pitch);
     {   // A band below the feasibility frontier of every cell this kernel finishes in the tile: all of
         // them are infeasible there.  Store that and leave (the whole work-group decides alike).
         int tile_need = 1 << 30;
@@ -1350,7 +1360,7 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
         for (int r = 0; r <= RF; ++r) tile_need = min(tile_need, s_par.need[r]);
         if (int(min(uint32_t(x.band) * kBand + kBand - 1, uint32_t(c.pitch) - 1)) < tile_need) {
             unsigned cells = 0;
-            if (!x.idle && !x.dead) {
+            if (x.m < uint32_t(c.pitch) && !x.dead) {
                 for (int r = 0; r <= RF; ++r) {
                     if (x.i0 + r >= c.L) continue;
                     const uint32_t own = x.moff + s_par.rowoff[r];
@@ -1383,9 +1393,16 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
         const int m0 = __builtin_amdgcn_readfirstlane(int(x.m));  // first column of the wave
         x.nwait = max(0, x.chunk0 - (max(0, m0 - reach) >> 6));
     }
+    // The band may lie past the end of the rows (pitch is a multiple of 64, not of kBand): those
+    // waves read and store nothing but still meet every barrier.
+    if (__builtin_amdgcn_readfirstlane(int(x.m)) >= c.pitch) {
+        for (int r = RF; r > 0; --r)
+            if (x.i0 + r < c.L) __syncthreads();
+        return;
+    }
 #pragma unroll
     for (int cc = 0; cc < T; ++cc) x.nl[cc] = 0, x.pc[cc] = 0;
-    if (DC >= 1 && !x.dead && !x.idle) {
+    if (DC >= 1 && !x.dead) {
         if (x.cend == T) request_row<DC, RF, true>(x);
         else request_row<DC, RF, false>(x);
         // operands of the splits in the column block, finished by earlier launches
