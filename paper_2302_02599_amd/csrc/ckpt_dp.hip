@@ -45,8 +45,8 @@ inline bool hip_ok(hipError_t e) {
 // j in block J.  Tiles are processed by block diagonal D = J - I; within one D every
 // tile is independent.  The splits of a cell of tile (I, J), D >= 2, fall in three groups:
 //   middle   q in [(I+1)T, JT]: both operands lie in tiles of a smaller D.  This is a
-//            min-plus product of an 8x8 register tile per lane (gemm_kernel), where each
-//            loaded operand row is reused by 8 cells.
+//            min-plus product of a register tile of cells per lane (gemm_kernel), where each
+//            loaded operand row is reused by all cells of a row or column of the tile.
 //   near-i   q in block I: the right operand (q, j) is a lower row of the SAME tile, read
 //            at a shifted m, so rows must be finished bottom-up across launches.
 //   near-j   q in block J: the left operand (i, q-1) is an earlier cell of the same row at
@@ -2053,8 +2053,10 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     }
     Device* side = groups > 1 ? dev : nullptr;
     // The exact frontier costs one long single-block launch per chain (about 2 us per stage).  On
-    // a side stream it runs beside the fill for free; on the caller's stream it pays only when
-    // the pruning it adds (about a third of the block products) saves more than it costs.
+    // a side stream it runs beside the fill (64 x 96 stages 3.31 ms, 3.45 without it; 8 x 192 stages 3.99 and
+    // 4.23); on the caller's stream it pays only when the pruning it adds saves more than it costs: one
+    // stream, 40 x 60 stages (5.4e6 by the measure below) 942 us with it, 944 without, 64 x 96 (19e6) 3.56 and
+    // 3.62 ms, but 3 x 254 (4.7e6) 3.09 and 2.43 ms.
     const bool want_frontier =
         frontier_mode == 1 || (frontier_mode == 0 && (groups > 1 || size_t(B) * pitch * nblk * nblk >= 6000000));
     std::unique_lock<std::mutex> lock;
@@ -2111,13 +2113,14 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             }
         }
         for (int D = 2; D < nblk; ++D) {
-            // Later diagonals have fewer tiles and longer work lists.  The chip holds 2048 of these
-            // waves; once a launch brings fewer than about three and a half times that, whole-list
-            // waves leave the machine half empty while the last ones finish, so 2 waves share each
-            // chunk and split its list (measured: a gain from there on, a loss with more tiles,
-            // where the lists are short); with fewer waves than a quarter of the chip, 4 do.
-            const long long waves = (long long)(nblk - D) * (pitch / 64) * B;
-            const int ks = want_ks ? want_ks : (waves <= 600 ? 4 : (waves <= 7000 ? 2 : 1));
+            // Later diagonals have fewer tiles and longer work lists.  The chip holds 2048 chunks (of two
+            // waves each); a launch with few of them leaves it half empty while the last ones finish, so 2 or 4
+            // slices of waves share a chunk.  That pays only with splits to share, 8 (D - 1) + 1 of them in
+            // passes of 16: 8 x 192 stages gain 2 % up to 7000 chunks (D = 11), while with 5000 chunks at D = 4
+            // (40 x 60 stages) or 2000 at D = 3 (30 x 32) a list for one slice is 3.5 % faster a solve; at D = 4, with
+            // two passes, 4 slices cost 16 x 48 stages 3 % against 2.
+            const long long chunks = (long long)(nblk - D) * (pitch / 64) * B;
+            const int ks = want_ks ? want_ks : (chunks <= 600 && D >= 5 ? 4 : (chunks <= 600 * D ? 2 : 1));
             const int ch = ks == 1 ? kCH : 1, gx = (pitch / 64 + ch - 1) / ch;
             for (int g = 0; g < groups; ++g) {
                 const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work};
