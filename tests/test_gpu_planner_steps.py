@@ -152,15 +152,16 @@ def test_schedule_batched_small_capacity_and_corrupt_table(amd, solved):
     assert got[3] == -7 and all(v > 0 for k, v in enumerate(got) if k != 3)
 
 
-def _walk_in_order(arg, wa, wabar, L, m, cap, row):
-    """The walk one cell after another: (operations written, their number or the error)."""
+def _walk_in_order(arg, wa, wabar, L, m, cap, row, top=1 << 40):
+    """The walk one cell after another: (operations written, their number or the error).  There are no cells above
+    column `top`."""
     ops, stack, code = [], [("walk", 1, L, m)], None
     while stack and code is None:
         kind, s, t, m = stack.pop()
         if kind == "B":
             new = [(3, s)]
         else:
-            k = 0 if m < 0 else int(arg[row(L, s, t), m])
+            k = 0 if m < 0 or m > top else int(arg[row(L, s, t), m])
             if k < s or k > t:
                 code = -3 if k == 0 and not ops and (s, t) == (1, L) else -7
                 break
@@ -222,6 +223,44 @@ def test_schedule_batched_any_table(amd, L):
             assert got == want + [(77, 77)] * (cap - len(want)), (cap, b)
             codes.add(min(code, 0))
     assert L < 17 or codes == {0, -3, -4, -7}
+
+
+@pytest.mark.parametrize("L", [2, 3, 17, 64, 65, 254])
+def test_schedule_batched_sizes_that_carry_m_above_the_table(amd, L):
+    """Negative sizes (chains that ckpt_check_inputs flags): a cell above column M is not there, and the walk ends as
+    the host's does, whether a run of C_all or a split leads to it and however far it lies."""
+    import torch
+    rng = np.random.default_rng(300 + L)
+    M, B = 63, 24  # the row ends with column M, so the next column is another cell's
+    rows = amd.ckpt_table_rows(L)
+    first = np.concatenate([np.full(L - s + 1, s) for s in range(1, L + 1)])
+    last = np.concatenate([np.arange(s, L + 1) for s in range(1, L + 1)])
+    arg = np.zeros((B, rows, amd.ckpt_row_pitch(M)), np.uint8)
+    wa, wabar = np.zeros((B, L + 1), np.int32), np.zeros((B, L), np.int32)
+    for b in range(B):
+        split = rng.integers(np.minimum(first + 1, last)[:, None], last[:, None], arg[b].shape, endpoint=True)
+        arg[b] = np.where(rng.random(arg[b].shape) < (1.0, 0.0, 0.9, 0.5)[b % 4], first[:, None], split)
+        size = (-1, -2, -M, -(1 << 31))[b // 4 % 4]
+        for sizes in (wa, wabar):
+            sizes[b, rng.random(sizes.shape[1]) < (1.0 if b >= 16 else 3 / L)] = size
+    wabar[20], wa[21] = [-M if k % 2 else M for k in range(L)], [M if k % 2 else -M for k in range(L + 1)]
+    budget = rng.integers(0, M + 1, B).astype(np.int32)
+    budget[::3] = M
+    cap = L * (L + 1) // 2 + L
+    up = lambda a: torch.from_numpy(a).cuda()
+    ops = torch.full((B, cap, 2), 77, dtype=torch.uint8, device="cuda")
+    n_ops = torch.zeros(B, dtype=torch.int32, device="cuda")
+    ws = torch.empty(amd.ckpt_schedule_workspace_bytes(L, B), dtype=torch.uint8, device="cuda")
+    amd.ckpt_schedule_batched(up(arg), up(wa), up(wabar), L, M, B, up(budget), ops, cap, n_ops, ws)
+    for b in range(B):
+        want, code = _walk_in_order(arg[b], wa[b], wabar[b], L, int(budget[b]), cap, amd.ckpt_row_index, top=M)
+        try:
+            assert amd.ckpt_schedule(arg[b], wa[b], wabar[b], L, M, 1, L, int(budget[b])) == want
+        except amd.CkptError as e:
+            assert e.code == code, b
+        assert n_ops[b].item() == code, b
+        assert [tuple(x) for x in ops[b].cpu().tolist()] == want + [(77, 77)] * (cap - len(want)), b
+    assert -7 in n_ops.tolist()
 
 
 def _walk_on_device(amd, batch, sol, budgets):
