@@ -2056,13 +2056,18 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
         }
     }
     Device* side = groups > 1 ? dev : nullptr;
-    // The exact frontier costs one long single-block launch per chain (about 2 us per stage).  On
-    // a side stream it runs beside the fill (64 x 96 stages 3.31 ms, 3.45 without it; 8 x 192 stages 3.99 and
-    // 4.23); on the caller's stream it pays only when the pruning it adds saves more than it costs: one
-    // stream, 40 x 60 stages (5.4e6 by the measure below) 942 us with it, 944 without, 64 x 96 (19e6) 3.56 and
-    // 3.62 ms, but 3 x 254 (4.7e6) 3.09 and 2.43 ms.
-    const bool want_frontier =
-        frontier_mode == 1 || (frontier_mode == 0 && (groups > 1 || size_t(B) * pitch * nblk * nblk >= 6000000));
+    // The exact frontier costs one long single-block launch per chain, 0.05 to 0.65 ms from 96 to 254 stages whatever
+    // the batch.  On a side stream it runs beside the fill (64 x 96 stages 3.29 ms, 3.43 without it; 8 x 192 stages
+    // 4.04 and 4.26; of 19 shapes only 2 x 254 stages at 8192 slots are slower with it, 4.60 and 4.48).  On the caller's
+    // stream it pays only when the pruning it adds saves more than it costs.  Both grow with the length of the
+    // chains, so the line is one of width, columns x blocks of stages: one stream, 4 x 254 stages and 1500 slots
+    // (2.0e5 by that measure) 3.32 ms with it, 2.68 without; 3 x 192, 4096 slots (3.0e5) 2.50 and 2.20; 8 x 254, 1000
+    // slots (2.6e5) 3.82 and 3.23; 6 x 192, 4096 slots (6.0e5) 3.81 and 3.65; 7 x 254, 4096 slots (9.3e5) 7.60 and 7.57;
+    // 1 x 192, 40000 slots (9.6e5) 5.36 and 5.58; 10 x 192, 4096 slots (10.0e5) 5.36 and 5.42; 60 x 64, 2048 slots
+    // (10.1e5) 1.36 and 1.38; 64 x 96, 2048 slots (16e5) 3.57 and 3.63; 12 x 254, 4096 slots (16e5) 11.3 and 11.9.
+    // Chains of few blocks have little to prune: 40 x 60 stages (5.4e6 by columns x blocks^2) 942 us and 944.
+    const bool wide = size_t(B) * pitch * nblk >= 950000 && size_t(B) * pitch * nblk * nblk >= 6000000;
+    const bool want_frontier = frontier_mode == 1 || (frontier_mode == 0 && (groups > 1 || wide));
     std::unique_lock<std::mutex> lock;
     if (side) lock = std::unique_lock<std::mutex>(side->busy);  // one fork/join at a time per device
     hipStream_t gs[kSideStreams + 1] = {st, st, st, st};  // stream of group g

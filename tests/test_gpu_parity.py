@@ -111,6 +111,25 @@ def test_no_room_for_bounds(amd):
     assert (cost[..., :M + 1] == want.cost[..., :M + 1]).all() and (arg[..., :M + 1] == want.arg[..., :M + 1]).all()
 
 
+@pytest.mark.parametrize("L,M,B,launches", [
+    (254, 1500, 4, 0),  # long chains, narrow: the frontier kernel would take a fifth of the solve
+    (254, 4096, 2, 0), (192, 4096, 3, 0),
+    (96, 1023, 77, 0), (96, 1023, 78, 1),  # 12 blocks of 1024 columns: the line lies between 77 and 78 chains
+    (32, 4095, 60, 0),  # wide enough, but chains of four blocks have little to prune
+])
+def test_exact_frontier_on_one_stream(amd, L, M, B, launches):
+    """One stream: the frontier kernel runs where the batch is wide enough to pay for its length, and the tables are
+    those of the automatic schedule."""
+    import torch
+    batch = random_chain_batch(L, M, B, 40 + L, size_hi=M // 20, time_hi=900)
+    sol = amd.solve(batch)
+    cost, arg = torch.full_like(sol.cost, -5), torch.full_like(sol.arg, 77)
+    up = lambda a: torch.from_numpy(a).cuda()
+    kinds = amd.ckpt_solve_profiled(up(batch.uf), up(batch.ub), up(batch.wa), up(batch.wabar), L, M, B, cost, arg, sol.workspace)
+    assert kinds["frontier_kernel"][1] == launches
+    assert (cost[..., :M + 1] == sol.cost[..., :M + 1]).all() and (arg[..., :M + 1] == sol.arg[..., :M + 1]).all()
+
+
 def test_everything_infeasible(amd, oracle_mod):
     batch = random_chain_batch(12, 3, 2, 21, size_hi=9)
     batch.wa += 5
