@@ -108,7 +108,9 @@ size_t ckpt_table_rows(int L);
 long ckpt_row_index(int L, int s, int t);
 /* Elements of the whole cost (or arg) table: B * rows * pitch.  0 on bad arguments. */
 size_t ckpt_table_elems(int L, int M, int B);
-/* Bytes of device workspace ckpt_solve_batched needs.  0 on bad arguments. */
+/* Bytes of device workspace ckpt_solve_batched needs: tables of L x L words per chain and, for all but small batches,
+ * samples of the finished cells, 1/16 of the cost table.  A workspace for one batch serves every batch that is
+ * no larger in L, M and B.  0 on bad arguments. */
 size_t ckpt_workspace_bytes(int L, int M, int B);
 
 /*
@@ -132,7 +134,8 @@ int ckpt_init(int device);
  *             memory; it may be captured into a HIP graph
  *   cost, arg DEVICE tables laid out as above, 256-byte aligned
  *   workspace DEVICE memory of ckpt_workspace_bytes(L, M, B) bytes, 256-byte
- *             aligned; holds per-chain prefix sums, thresholds and input flags
+ *             aligned; holds per-chain prefix sums, thresholds, the feasibility frontier,
+ *             input flags, progress words and samples of finished cells
  * Returns CKPT_OK, CKPT_E_ARG, CKPT_E_LIMIT or CKPT_E_HIP.
  */
 int ckpt_solve_batched(const ckpt_chains_t* chains, int L, int M, int B, void* stream,

@@ -75,7 +75,7 @@ inline bool hip_ok(hipError_t e) {
 //                          the tile that work-groups have taken
 //   fault [1]      int32   set when a bounded wait inside tile_rows_kernel expired
 //   samp  [B][4 nblk (nblk + 1)][pitch / kG][8] int32  every kG-th column of the finished cells, eight cells of a
-//                          row side by side (see gemm_kernel); left out where the workspace is too small
+//                          row side by side (see gemm_kernel); left out where they are not used or do not fit
 // prog and fault are cleared by precompute_kernel at the start of every solve.
 struct Workspace {
     int32_t* P;
@@ -109,6 +109,14 @@ __host__ __device__ inline size_t samp_ints(int L, int pitch) {
     return blocks_of(L) < 3 ? 0 : size_t(pitch / kG) * samp_rows(L) * kT;
 }
 
+// Whether the block product bounds its splits by samples.  Not where the lists of splits are so short and so
+// few that a launch costs more than they do: 5 chains of 53 stages and 777 slots (2.0e5 by the measure below)
+// take 2 % longer with bounds, 16 chains of 48 stages and 1024 slots (6.3e5) 2 % less.  A batch with bounds has them
+// with more chains, stages or columns too, so a workspace serves every smaller batch.
+inline bool uses_bounds(int L, int pitch, int B) {
+    return size_t(B) * pitch * blocks_of(L) * blocks_of(L) >= 400000;
+}
+
 __host__ __device__ inline int prog_words(int pitch) { return pitch / 64 + 1; }
 inline size_t ws_ints(int L, int pitch, int B) {
     return align64(size_t(B) * (L + 1)) + 3 * align64(size_t(B) * L) + 3 * align64(size_t(B) * L * L) +
@@ -135,7 +143,7 @@ inline Workspace carve(void* base, int L, int pitch, int B, bool samples) {
     w.need = p;   p += align64(size_t(B) * L * L);
     w.prog = p;   p += align64(size_t(B) * tiles_of(L) * prog_words(pitch));
     w.fault = p;  p += 64;
-    w.samp = samples && samp_ints(L, pitch) ? p : nullptr;
+    w.samp = samples && uses_bounds(L, pitch, B) && samp_ints(L, pitch) ? p : nullptr;
     return w;
 }
 
@@ -2010,12 +2018,8 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     const int pitch = int(ckpt_row_pitch(M));
     const int rows = int(ckpt_table_rows(L));
     // without room for the samples (the static workspace of the entry point that allocates nothing) the
-    // block product evaluates every feasible split.  So it does where the lists of splits are so short and so
-    // few that a launch costs more than they do: 5 chains of 53 stages and 777 slots (2.0e5 by the measure below)
-    // take 2 % longer with bounds, 16 chains of 48 stages and 1024 slots (6.3e5) 2 % less.
-    const int stage_blocks = blocks_of(L);
-    const bool bounds = size_t(B) * pitch * stage_blocks * stage_blocks >= 400000;
-    const Workspace ws = carve(workspace, L, pitch, B, bounds && workspace_bytes >= ckpt_workspace_bytes(L, M, B));
+    // block product evaluates every feasible split
+    const Workspace ws = carve(workspace, L, pitch, B, workspace_bytes >= ckpt_workspace_bytes(L, M, B));
 
     const size_t frontier_lds = ckpt_table_rows(L) * sizeof(int32_t);
     if (frontier_lds > 48 * 1024 && !allow_frontier_lds()) return CKPT_E_HIP;
@@ -2183,7 +2187,9 @@ extern "C" {
 
 size_t ckpt_workspace_bytes(int L, int M, int B) {
     if (L < 1 || M < 0 || B < 1) return 0;
-    return (ws_ints(L, int(ckpt_row_pitch(M)), B) + size_t(B) * samp_ints(L, int(ckpt_row_pitch(M)))) * sizeof(int32_t);
+    const int pitch = int(ckpt_row_pitch(M));
+    const size_t samples = uses_bounds(L, pitch, B) ? size_t(B) * samp_ints(L, pitch) : 0;
+    return (ws_ints(L, pitch, B) + samples) * sizeof(int32_t);
 }
 
 // What a solve cannot do without: everything but the samples.

@@ -48,6 +48,26 @@ def test_layout_helpers(amd):
     assert amd.ckpt_workspace_bytes(0, 4, 1) == 0 and amd.ckpt_workspace_bytes(8, 64, 1) > 0
 
 
+def test_workspace_holds_samples_only_where_they_bound_splits(amd):
+    def parts(L, M, B):
+        """Words of a workspace without samples (the exact sum, rounded up per part) and of the samples."""
+        pitch, n = amd.ckpt_row_pitch(M), -(-L // 8)
+        tiles = n * (n + 1) // 2
+        least = B * (3 * L * L + 4 * L + 2 + tiles * (pitch // 64 + 1))
+        return least, least + 64 * 10, B * (pitch // 16) * 4 * n * (n + 1) * 8
+    for L, M, B, samples in ((8, 64, 1, False), (24, 512, 1, False), (53, 777, 5, False), (254, 100, 1, False),
+                             (16, 4096, 8, False), (96, 2048, 64, True), (192, 4096, 1, True), (48, 2000, 64, True)):
+        least, most, samp = parts(L, M, B)
+        extra = samp if samples else 0
+        assert least + extra <= amd.ckpt_workspace_bytes(L, M, B) // 4 <= most + extra, (L, M, B)
+    # a workspace for one batch serves every smaller one
+    rng = np.random.default_rng(5)
+    for _ in range(2000):
+        big = [int(np.exp(rng.uniform(0, np.log(hi + 1)))) for hi in (254, 5000, 300)]
+        small = [int(np.exp(rng.uniform(0, np.log(v + 1)))) if rng.random() < 0.5 else v for v in big]
+        assert amd.ckpt_workspace_bytes(*small) <= amd.ckpt_workspace_bytes(*big), (small, big)
+
+
 def test_solve_rejects_bad_arguments_before_touching_the_gpu(amd):
     lib = amd.load_library()
     from paper_2302_02599_amd.binding import _Chains
