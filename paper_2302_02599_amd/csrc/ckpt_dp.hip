@@ -109,12 +109,26 @@ __host__ __device__ inline size_t samp_ints(int L, int pitch) {
     return blocks_of(L) < 3 ? 0 : size_t(pitch / kG) * samp_rows(L) * kT;
 }
 
-// Whether the block product bounds its splits by samples.  Not where the lists of splits are so short and so
-// few that a launch costs more than they do: 5 chains of 53 stages and 777 slots (2.0e5 by the measure below)
-// take 2 % longer with bounds, 16 chains of 48 stages and 1024 slots (6.3e5) 2 % less.  A batch with bounds has them
-// with more chains, stages or columns too, so a workspace serves every smaller batch.
+// Whether the block product bounds its splits by samples (else it evaluates every feasible one).  The bounds are two
+// more chains of dependent reads a launch, which pay where the launches have enough splits, about
+// B pitch nblk^2 / 8 on average, and where kG columns are a small part of the budget: the narrower the table,
+// the more a cost varies over a sub-chunk and the less the bounds drop.  The line was drawn through 295 shapes, each
+// timed with and without.  It is within 0.3 % of the better one on average (2e5 .. 6.4e6 by that measure, five mixes of
+// stages), and at worst 11 % (43 x 192 stages of nearly one size in 124 slots: the bounds drop little).  Both sides, without and with:
+//   one chunk of columns: 49 x 254 stages, 60 slots (3.2e6) 2857 us and 3232; 300 x 254 (2e7) 15.0 ms and 16.4
+//   three blocks: 289 x 24 stages, 565 slots (1.5e6) 196 us and 205; 1068 x 24, 4096 slots (4e7) 4477 and 4404
+//   four blocks: 137 x 32 stages, 318 slots (7.0e5) 157 and 160; 23 x 32, 4088 slots (1.5e6) 256 and 250
+//   narrow: 6 x 254 stages, 124 slots (7.9e5) 1633 and 1738; 14 x 192, 188 slots (1.5e6) 1318 and 1253; 10 x 96, 303
+//   slots (4.6e5) 424 and 443; 20 x 128, 316 slots (1.6e6) 900 and 798
+//   else: 5 x 53 stages, 777 slots (2.0e5) 239 and 249; 1 x 254, 500 slots (5.2e5) 1611 and 1739; 4 x 77, 999 slots (4.1e5)
+//   382 and 391; 1 x 128, 2048 slots (5.4e5) 633 and 618; 3 x 80, 2273 slots (6.9e5) 402 and 388; 1 x 128, 1719 slots
+//   (4.4e5) 610 and 582; 6 x 96, 1147 slots (10e5) 529 and 500
+// A batch with bounds has them with more chains, stages or columns too, so a workspace serves every smaller batch.
 inline bool uses_bounds(int L, int pitch, int B) {
-    return size_t(B) * pitch * blocks_of(L) * blocks_of(L) >= 400000;
+    const int nblk = blocks_of(L);
+    if (nblk < 3 || pitch <= 64) return false;
+    const double line = nblk == 3 ? 2e7 : nblk == 4 ? 1.4e6 : std::max(4e5, std::min(1.4e6, 4.5e8 / pitch));
+    return double(B) * pitch * nblk * nblk >= line;
 }
 
 __host__ __device__ inline int prog_words(int pitch) { return pitch / 64 + 1; }

@@ -56,7 +56,10 @@ def test_workspace_holds_samples_only_where_they_bound_splits(amd):
         least = B * (3 * L * L + 4 * L + 2 + tiles * (pitch // 64 + 1))
         return least, least + 64 * 10, B * (pitch // 16) * 4 * n * (n + 1) * 8
     for L, M, B, samples in ((8, 64, 1, False), (24, 512, 1, False), (53, 777, 5, False), (254, 100, 1, False),
-                             (16, 4096, 8, False), (96, 2048, 64, True), (192, 4096, 1, True), (48, 2000, 64, True)):
+                             (16, 4096, 8, False), (96, 2048, 64, True), (192, 4096, 1, True), (48, 2000, 64, True),
+                             (254, 500, 1, False), (128, 2048, 1, True), (80, 2273, 3, True),  # the table's width counts
+                             (254, 63, 300, False), (254, 64, 300, True),  # one chunk of columns: never
+                             (24, 1000, 60, False), (24, 4096, 1068, True), (32, 318, 137, False), (32, 4088, 23, True)):
         least, most, samp = parts(L, M, B)
         extra = samp if samples else 0
         assert least + extra <= amd.ckpt_workspace_bytes(L, M, B) // 4 <= most + extra, (L, M, B)

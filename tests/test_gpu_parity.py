@@ -85,10 +85,16 @@ def test_wide_rows_and_many_chains(amd, oracle_mod, L, M, B, seed, size_hi):
     (40, 130, 16, 50),      # shifts of one sample and its neighbours
     (41, 300, 0, 50),       # no shift at all: sizes zero
     (56, 1000, 60, 1 << 21),  # costs near the sentinel
+    (17, 64, 5, 40),        # one column of the last block, one of the last chunk
+    (24, 127, 9, 50),       # first diagonal with splits between the blocks, the last chunk ends with the row
+    (25, 65, 4, 50), (64, 100, 9, 1), (33, 1100, 80, 50),
 ])
 def test_splits_dropped_by_their_bounds(amd, oracle_mod, L, M, size_hi, time_hi):
-    blocks = -(-L // 8)
-    B = 400000 // (amd.ckpt_row_pitch(M) * blocks * blocks) + 1  # large enough for the bounds to be used
+    blocks, pitch = -(-L // 8), amd.ckpt_row_pitch(M)
+    line = {3: 2e7, 4: 1.4e6}.get(blocks, min(1.4e6, max(4e5, 4.5e8 / pitch))) if M >= 64 else 4e5
+    B = int(line) // (pitch * blocks * blocks) + 1  # large enough for the bounds to be used, but for a single chunk of columns
+    samples = B * (pitch // 16) * 4 * blocks * (blocks + 1) * 32
+    assert (amd.ckpt_workspace_bytes(L, M, B) > samples + 12 * B * L * L) == (M >= 64)
     batch = random_chain_batch(L, M, B, 900 + L, size_hi=size_hi, time_hi=time_hi, zero_sizes=size_hi in (0, 16))
     sol = amd.solve(batch)
     assert_tables_equal(oracle_mod, batch, sol, chains=range(0, B, max(1, B // 6)))
