@@ -136,13 +136,16 @@ inline size_t ws_ints(int L, int pitch, int B) {
     return align64(size_t(B) * (L + 1)) + 3 * align64(size_t(B) * L) + 3 * align64(size_t(B) * L * L) +
            align64(size_t(B)) + align64(size_t(B) * tiles_of(L) * prog_words(pitch)) + 64;
 }
-// The measure by which ckpt_solve_batched_noalloc accepts a call; kScratchSlack holds what a solve needs beyond it
-// (a word per tile: less than 1/384 of the three tables of L^2 words).
+// The measure by which ckpt_solve_batched_noalloc accepts a call.  It is the size of a layout with two more words a
+// stage, four a block and none for the tickets of the tiles, kept so that the calls which are accepted stay
+// the same.  ws_ints exceeds it by less than tiles - 2 L words a chain, which is positive for 32 blocks only, at
+// most 30, and no more than 22 such chains are accepted: kScratchSlack holds that.
 inline size_t limit_ints(int L, int pitch, int B) {
     return ws_ints(L, pitch, B) - align64(size_t(B) * tiles_of(L) * prog_words(pitch)) +
            align64(size_t(B) * tiles_of(L) * (pitch / 64)) + 2 * align64(size_t(B) * L) + align64(size_t(blocks_of(L)) * 4);
 }
-constexpr size_t kScratchSlack = 1 << 16;
+constexpr size_t kScratchSlack = 4096;
+static_assert(CKPT_MAX_L <= 256 && kScratchSlack >= 22 * 30 * sizeof(int32_t), "see limit_ints");
 
 inline Workspace carve(void* base, int L, int pitch, int B, bool samples) {
     int32_t* p = static_cast<int32_t*>(base);
@@ -2206,9 +2209,11 @@ size_t ckpt_workspace_bytes(int L, int M, int B) {
     return (ws_ints(L, pitch, B) + samples) * sizeof(int32_t);
 }
 
-// What a solve cannot do without: everything but the samples.
-static size_t least_workspace_bytes(int L, int M, int B) {
-    return limit_ints(L, int(ckpt_row_pitch(M)), B) * sizeof(int32_t);
+// Whether the static workspace has room for what a solve cannot do without (everything but the samples).
+static bool fits_static_workspace(int L, int M, int B) {
+    const int pitch = int(ckpt_row_pitch(M));
+    return limit_ints(L, pitch, B) * sizeof(int32_t) <= CKPT_NOALLOC_MAX_WORKSPACE &&
+           ws_ints(L, pitch, B) * sizeof(int32_t) <= sizeof(g_scratch);
 }
 
 int ckpt_init(int device) {
@@ -2232,7 +2237,7 @@ int ckpt_solve_batched(const ckpt_chains_t* chains, int L, int M, int B, void* s
 int ckpt_solve_batched_noalloc(const ckpt_chains_t* chains, int L, int M, int B, void* stream, int32_t* cost,
                                uint8_t* arg) {
     if (int rc = check_dims(L, M, B)) return rc;
-    if (least_workspace_bytes(L, M, B) > CKPT_NOALLOC_MAX_WORKSPACE) return CKPT_E_LIMIT;
+    if (!fits_static_workspace(L, M, B)) return CKPT_E_LIMIT;
     Device* dev = current_device();
     if (!dev) return CKPT_E_HIP;
     void* scratch = ensure_scratch(*dev);
@@ -2303,7 +2308,7 @@ int ckpt_check_inputs(const void* workspace, int L, int M, int B, void* stream, 
     if (!flags_host) return CKPT_E_ARG;
     if (int rc = check_dims(L, M, B)) return rc;
     if (!workspace) {  // the static workspace of ckpt_solve_batched_noalloc on the current device
-        if (least_workspace_bytes(L, M, B) > CKPT_NOALLOC_MAX_WORKSPACE) return CKPT_E_LIMIT;
+        if (!fits_static_workspace(L, M, B)) return CKPT_E_LIMIT;
         Device* dev = current_device();
         workspace = dev ? ensure_scratch(*dev) : nullptr;
         if (!workspace) return CKPT_E_HIP;

@@ -55,3 +55,29 @@ def test_noalloc_rejects_sizes_beyond_its_workspace():
     assert amd.ckpt_workspace_bytes(L, M, B) > 16 << 20
     assert lib.ckpt_solve_batched_noalloc(ctypes.byref(ch), L, M, B, None, 256, 256) == -2
     assert lib.ckpt_solve_batched_noalloc(ctypes.byref(ch), 0, M, B, None, 256, 256) == -1
+
+
+def test_noalloc_accepts_what_fits_its_workspace():
+    """The largest accepted batch of every length: accepted where it always was, and all that a solve writes fits.  Without
+    tables a call that passes the test for room ends with another error before anything is enqueued."""
+    import paper_2302_02599_amd as amd
+    lib = amd.load_library()
+    from paper_2302_02599_amd.binding import _Chains
+    ch = _Chains(256, 256, 256, 256, None, None, None)
+    up = lambda n: -(-n // 64) * 64
+    room = 16 << 18  # words
+    for L in range(1, 255):
+        blocks = -(-L // 8)
+        tiles = blocks * (blocks + 1) // 2
+        for M in (0, 63, 64, 500, 1500, 4096, 30000):
+            chunks = amd.ckpt_row_pitch(M) // 64
+            common = lambda B: up(B * (L + 1)) + 3 * up(B * L) + 3 * up(B * L * L) + up(B) + 64
+            measure = lambda B: common(B) + up(B * tiles * chunks) + 2 * up(B * L) + up(4 * blocks)
+            lo, hi = 0, 65535
+            while lo < hi:
+                mid = (lo + hi + 1) // 2
+                lo, hi = (mid, hi) if measure(mid) <= room else (lo, mid - 1)
+            assert common(lo) + up(lo * tiles * (chunks + 1)) <= room + 1024, (L, M, lo)
+            if lo:
+                assert lib.ckpt_solve_batched_noalloc(ctypes.byref(ch), L, M, lo, None, None, None) in (-1, -5), (L, M, lo)
+            assert lib.ckpt_solve_batched_noalloc(ctypes.byref(ch), L, M, lo + 1, None, None, None) == -2, (L, M, lo)
