@@ -201,7 +201,7 @@ int ckpt_solve_batched_noalloc(const ckpt_chains_t* chains, int L, int M, int B,
                                uint8_t* arg);
 
 /*
- * Measurement aid: the same fill as ckpt_solve_batched on one stream, with a HIP event recorded
+ * Measurement aid: the kernels that ckpt_solve_batched would run, on one stream, with a HIP event recorded
  * after every kernel launch.  The call waits for the stream, then adds the elapsed time between
  * consecutive events to the kernel kind launched in between (so a kind's time includes the
  * idle gap before each of its launches).

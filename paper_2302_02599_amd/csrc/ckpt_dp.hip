@@ -2058,7 +2058,9 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
 
     int groups = want_groups ? want_groups : (large ? kSideStreams + 1 : 1);
     groups = std::min(groups, B);
-    if (prof || nblk < 3) groups = 1;  // the event trail times one stream; no diagonal to split
+    if (nblk < 3) groups = 1;  // no diagonal to split
+    const bool would_split = groups > 1;
+    if (prof) groups = 1;  // the event trail times one stream
     Device* dev = nullptr;
     if (groups > 1) {
         dev = current_device();
@@ -2088,7 +2090,9 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     // (10.1e5) 1.36 and 1.38; 64 x 96, 2048 slots (16e5) 3.57 and 3.63; 12 x 254, 4096 slots (16e5) 11.3 and 11.9.
     // Chains of few blocks have little to prune: 40 x 60 stages (5.4e6 by columns x blocks^2) 942 us and 944.
     const bool wide = size_t(B) * pitch * nblk >= 950000 && size_t(B) * pitch * nblk * nblk >= 6000000;
-    const bool want_frontier = frontier_mode == 1 || (frontier_mode == 0 && (groups > 1 || wide));
+    // A profiled solve runs the kernels that the automatic schedule would run, on one stream.
+    const bool beside = groups > 1 || (prof && would_split);
+    const bool want_frontier = frontier_mode == 1 || (frontier_mode == 0 && (beside || wide));
     std::unique_lock<std::mutex> lock;
     if (side) lock = std::unique_lock<std::mutex>(side->busy);  // one fork/join at a time per device
     hipStream_t gs[kSideStreams + 1] = {st, st, st, st};  // stream of group g

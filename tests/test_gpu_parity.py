@@ -120,11 +120,12 @@ def test_no_room_for_bounds(amd):
 @pytest.mark.parametrize("L,M,B,launches", [
     (254, 1500, 4, 0),  # long chains, narrow: the frontier kernel would take a fifth of the solve
     (254, 4096, 2, 0), (192, 4096, 3, 0),
-    (96, 1023, 77, 0), (96, 1023, 78, 1),  # 12 blocks of 1024 columns: the line lies between 77 and 78 chains
-    (32, 4095, 60, 0),  # wide enough, but chains of four blocks have little to prune
+    (96, 79103, 1, 0), (96, 79104, 1, 1),  # 12 blocks: the line lies between these two widths
+    (32, 250000, 1, 0),  # wide enough, but chains of four blocks have little to prune
+    (96, 1023, 64, 1),  # split over streams, where it runs beside the fill: a profiled solve runs it too
 ])
-def test_exact_frontier_on_one_stream(amd, L, M, B, launches):
-    """One stream: the frontier kernel runs where the batch is wide enough to pay for its length, and the tables are
+def test_exact_frontier(amd, L, M, B, launches):
+    """On one stream the frontier kernel runs where the batch is wide enough to pay for its length; the tables are
     those of the automatic schedule."""
     import torch
     batch = random_chain_batch(L, M, B, 40 + L, size_hi=M // 20, time_hi=900)
