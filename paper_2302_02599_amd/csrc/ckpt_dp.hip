@@ -48,12 +48,12 @@ inline bool hip_ok(hipError_t e) {
 //            min-plus product of a register tile of cells per lane (gemm_kernel), where each
 //            loaded operand row is reused by all cells of a row or column of the tile.
 //   near-i   q in block I: the right operand (q, j) is a lower row of the SAME tile, read
-//            at a shifted m, so rows must be finished bottom-up across launches.
+//            at a shifted m, so the rows of a tile are finished bottom-up.
 //   near-j   q in block J: the left operand (i, q-1) is an earlier cell of the same row at
 //            the same m, kept in registers.
-// row_kernel finishes one row r of every tile of the diagonal: near-i splits, then the
-// partial minimum of gemm_kernel, then near-j splits, then C_all and the two gates.
-// Launch order per D: gemm (D >= 2), then rows r = T-1 .. 0.
+// A row is finished by its near-i splits, the partial minimum of gemm_kernel, its near-j splits, then C_all and the
+// two gates.  Launch order per D: gemm (D >= 2), which also finishes row T-1, then tile_rows_kernel, one launch for
+// rows T-2 .. 0 (T-1 .. 0 for D < 2) of every tile.  row_kernel, one launch per row, is the alternative schedule.
 //
 // Reads at m - shift are not bounds-checked against m < shift: a lane whose m is below
 // a shift of one of its splits is below m_null (m_all for C_all) of that cell, because
@@ -471,14 +471,14 @@ __device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, co
 // the mark "not finished", arg[] <- its number; the row kernels finish them.  Row 7 has no split
 // in its own row block, so its partial minimum stays in registers and the wave finishes the row
 // itself.
-// What bounds it: latency of the dependent reads (samples, then operands), 30 % of the vector issue
-// slots busy; 2.9 ms a solve for L = 192, M = 4096, B = 8 at 4.0 TB/s asked for, where evaluating every
+// What bounds it: latency of the dependent reads (samples, then operands), 23 % of the vector issue
+// slots busy; 2.5 ms a solve for L = 192, M = 4096, B = 8 at 4.6 TB/s asked for, where evaluating every
 // feasible split took 5.7 ms and 29 GB (5.5 % of the splits are left instead of 67 %).  kG = 16: bounds
 // over 64 columns leave 11.7 %, over 32 7.5 %.  Half a tile a wave keeps it at 128 registers, four waves a SIMD.
 // The epilogue reads nothing behind its stores (a load behind a store waits until it is through, and the
 // compiler moves no load across a store to the tables): gates, shifts and prefix sums of row 7 are fetched
 // with the splits at the start.  With scalar loads per column between the stores a launch took 2 to 4 us
-// more (64 x 96 stages: 3.91 ms a solve, now 3.50).
+// more (64 x 96 stages: 3.91 ms a solve with them, 3.51 without).
 // KS > 1 (launches with too few tiles to fill the chip): KS waves share one half chunk, each takes
 // every KS-th pass of stage 1 and every KS-th entry of the list, and their keys are merged
 // through LDS at the end.
@@ -987,7 +987,7 @@ __global__ void __launch_bounds__(kRowWG) row_kernel(Ctx c, int D) {
 // this launch only where a shifted column lies below its band, and a number that the gemm already stored
 // is not read and written again.  Both reads of the row below (operands of the splits, of C_all) are one round
 // trip.  The rest of a step is issue: 900 instructions, so gates are selects on the operands, and what is
-// the same for the whole wave is decided once.  5 chains of 53 stages: 26 us a launch, 34 us before; 334 -> 241 us
+// the same for the whole wave is decided once.  5 chains of 53 stages: 26 us a launch, 34 us before; 334 -> 238 us
 // a solve.
 // ---------------------------------------------------------------------------
 constexpr int kSpinLimit = 1 << 20;        // default polls of a wait before it gives up (seconds, never reached)
