@@ -1548,7 +1548,7 @@ __global__ void __launch_bounds__(kWalkThreads) schedule_kernel(const uint8_t* _
                                                                  int32_t* __restrict__ n_ops) {
     enum { kLeaf = 0, kSplit = 1, kMore = 2, kBad = 3 };  // how a node ends after its run of C_all
     struct Node {
-        int m;        // before expansion: slots of the cell, held in -1 .. M + 1 (outside 0 .. M there is no
+        int m;        // before expansion: slots of the cell, held in 32 bits (outside 0 .. M there is no
                       // cell: the node is bad); afterwards: first position of its operations
         int size;     // operations of the subtree
         short child;  // first child (the second of a split follows it)
@@ -1562,7 +1562,7 @@ __global__ void __launch_bounds__(kWalkThreads) schedule_kernel(const uint8_t* _
     const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
     const uint8_t* tab = arg + size_t(b) * rows * pitch;
     // Sizes of a chain that ckpt_check_inputs would flag are taken as they come: a negative one raises m.
-    auto slots = [&](long long m) { return int(min(max(m, -1ll), (long long)M + 1)); };
+    auto left = [](long long m, int size) { return __builtin_elementwise_sub_sat(int(m), size); };  // m in 0 .. M
     const int m0 = m_budget[b];
     if (m0 < 0) {  // uniform
         if (tid == 0) n_ops[b] = CKPT_E_ARG;
@@ -1632,11 +1632,11 @@ __global__ void __launch_bounds__(kWalkThreads) schedule_kernel(const uint8_t* _
                 nd.k = uint8_t(end == kBad && head + group == 0 && u == 0 && k == 0 ? 1 : k);
                 nd.child = short(at);
                 if (end == kSplit) {  // (k, t, m - a^{k-1}) is walked first, then (s, k - 1, m)
-                    s_node[at].s = uint8_t(k), s_node[at].t = uint8_t(t), s_node[at].m = slots(m - s_wa[k - 1]);
+                    s_node[at].s = uint8_t(k), s_node[at].t = uint8_t(t), s_node[at].m = left(m, s_wa[k - 1]);
                     s_node[at + 1].s = uint8_t(s), s_node[at + 1].t = uint8_t(k - 1), s_node[at + 1].m = int(m);
                 } else if (end == kMore) {
-                    const long long rest = goes_on ? m - s_wab[s - 1] : m;
-                    s_node[at].s = uint8_t(goes_on ? s + 1 : s), s_node[at].t = uint8_t(t), s_node[at].m = slots(rest);
+                    s_node[at].s = uint8_t(goes_on ? s + 1 : s), s_node[at].t = uint8_t(t);
+                    s_node[at].m = goes_on ? left(m, s_wab[s - 1]) : int(m);
                 }
             }
             tail += 2 * __popcll(splits) + __popcll(more);
