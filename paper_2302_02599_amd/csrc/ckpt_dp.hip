@@ -92,6 +92,7 @@ struct Workspace {
 };
 
 constexpr int kG = 16;  // columns between samples
+constexpr int kAsk = 33;  // splits from which the block product asks finished neighbours for upper bounds
 constexpr double kKeyBase = 0x1p44;
 
 constexpr int kBand = kRowWG;  // columns of m per work-group of the row kernels
@@ -570,35 +571,40 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
         // upper bounds: left operand sampled at the column before the sub-chunk, right operand at the last
         // sampled column that the whole shifted sub-chunk lies above
         uint32_t ub[R][T];
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int cc = 0; cc < T; ++cc) ub[r][cc] = 0xffffffffu;
         const int stride = 16 * KS;
         auto split_of = [&](int k0) { return min(k0 + x, nq - 1); };
         auto below = [&](int sh) { return ((kk * kG + 1 - sh) >> 4) - 1; };
         auto above = [&](int sh) { return (kk * kG + kG - 1 - sh) >> 4; };
         const int kend = passes * 16;
+        // Any splits give an upper bound; the best ones are mostly those that finished neighbours took at the end of
+        // the sub-chunk: the first row of the next tile down (8 cells), the last column of the tile to the left (4), and four
+        // (the other slices: sixteen) spread over the range.  One pass instead of one for every 16 splits, and as many
+        // splits are dropped: a pass is a gather of about 30 lines and costs the compute unit's one path to memory 200 clocks a wave.
+        // With kAsk splits and fewer sixteen spread ones do without the trip to the neighbours' numbers.
+        // 8 x 192 stages, 4096 slots: 4.00 -> 3.89 ms a solve; 3 x 254, 1500 slots: 2.39 -> 2.33.
         Bound nx;
-        int2 sp = s_split[split_of(slice * 16)];
-        if (slice * 16 < kend) fetch(nx, qlo + split_of(slice * 16), kk - 1, below(sp.x));
-        for (int k0 = slice * 16; k0 < kend; k0 += stride) {
-            Bound v = nx;
-            const int2 cur = sp;
-            sp = s_split[split_of(k0 + stride)];
-            fetch(nx, qlo + split_of(k0 + stride), kk - 1, below(sp.x));
-            __builtin_amdgcn_sched_barrier(0);
-            settle(v, uint32_t(cur.y), kk - 1, below(cur.x));
+        int2 sp;
+        if (search) {
+            const bool ask = slice == 0 && nq > kAsk;  // uniform
+            const int spread = slice > 0 ? 16 * (slice - 1) + x : ask ? x - 12 : x, of = slice > 0 ? 16 * (KS - 1) : ask ? 4 : 16;
+            int pick = ((2 * spread + 1) * nq) / (2 * of);
+            if (ask && x < 12) {
+                const int i8 = (I + 1) * T, row = x < 8 ? row_base(L, i8) + min(j0 + x, L - 1) : row_base(L, i0 + x - 8) + j0 - 1;
+                pick = int(__builtin_amdgcn_raw_buffer_load_b8(atab, row * pitch + kk * kG + kG - 1, 0, 0)) - 1 - qlo;
+                if (uint32_t(pick) >= uint32_t(nq)) pick = (x * nq) / 12;  // none, C_all, or a split in a block of the tile
+            }
+            sp = s_split[pick];
+            fetch(nx, qlo + pick, kk - 1, below(sp.x));
+            settle(nx, uint32_t(sp.y), kk - 1, below(sp.x));
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
-                for (int cc = 0; cc < T; ++cc) ub[r][cc] = min(ub[r][cc], v.l[r] + v.r[cc]);
-            __builtin_amdgcn_sched_barrier(0);
+                for (int cc = 0; cc < T; ++cc) ub[r][cc] = nx.l[r] + nx.r[cc];
         }
         sp = s_split[split_of(slice * 16)];
         if (slice * 16 < kend) fetch(nx, qlo + split_of(slice * 16), kk, above(sp.x));
         __builtin_amdgcn_sched_barrier(0);
-        if (passes > slice) {
+        if (search) {
             // minimum over the 16 lanes of a sub-chunk: two exchanges that halve the cells a lane holds, then
             // two rotations of the row of 16 lanes
             uint32_t h[R * T / 2], f[R * T / 4];
@@ -647,7 +653,7 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
             at = __builtin_amdgcn_readfirstlane(at);
             if (lane < 16 && (bits >> x & 1u)) s_list[grp][at + __popc(bits & ((1u << x) - 1u))] = k0 + x;
         }
-        count_work<CNT>(c.work, 0, passes > slice ? 2u * (R + 8) * unsigned((passes - slice + KS - 1) / KS) : 0u, 0);
+        if (search) count_work<CNT>(c.work, 0, (R + 8) * (1u + unsigned(max(0, passes - slice + KS - 1) / KS)), 0);
     } else if (slice == 0 && search) {
         // No room for samples: the splits q for which some cell of the wave can have both operands feasible
         // somewhere in these 64 columns.
