@@ -363,6 +363,27 @@ __device__ __forceinline__ uint32_t tld(rsrc_t tab, uint32_t voff, uint32_t soff
     return uint32_t(__builtin_amdgcn_raw_buffer_load_b32(tab, int(voff), int(soff), 0));
 }
 
+// Orders a wave's LDS accesses before and after: its lanes read what other lanes of the wave wrote.
+__device__ __forceinline__ void wave_settle() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Wide accesses of a wave: eight rows of the table (the cells (i, jb) .. (i, jb + 7) of a row of a tile lie in consecutive
+// ones), 64 columns each, as two instructions of 16 bytes a lane instead of eight of 4.  Lane l holds columns
+// 4 (l & 15) .. + 3 of rows l >> 4 and 4 + (l >> 4); a turn through LDS brings values to lane = column, or from there.
+// The work-groups of a compute unit share one path to memory that takes an instruction every 16 to 20 clocks.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ u32x4 tld4(rsrc_t tab, uint32_t voff) {
+    return __builtin_amdgcn_raw_buffer_load_b128(tab, int(voff), 0, 0);
+}
+
+constexpr int kPairs = kT * (kT - 1) / 2;  // splits in the column block of a row: (c2, cc), c2 < cc
+__host__ __device__ constexpr int pair_index(int c2, int cc) { return c2 * (2 * kT - 1 - c2) / 2 + cc - c2 - 1; }
+
 // Keeps the samples of cells (i, 8 J .. 8 J + 7): every kG-th lane stores its eight values.
 __device__ __forceinline__ void store_samples(const Ctx& c, int b, int i, int J, uint32_t m, const uint32_t (&val)[kT]) {
     if (!c.ws.samp || (m & (kG - 1)) != kG - 1) return;
@@ -479,7 +500,8 @@ __device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, co
 // The epilogue reads nothing behind its stores (a load behind a store waits until it is through, and the
 // compiler moves no load across a store to the tables): gates, shifts and prefix sums of row 7 are fetched
 // with the splits at the start.  With scalar loads per column between the stores a launch took 2 to 4 us
-// more (64 x 96 stages: 3.91 ms a solve with them, 3.51 without).
+// more (64 x 96 stages: 3.91 ms a solve with them, 3.51 without).  Rows go to the tables, and operands of row 7 come
+// from them, as wide accesses through LDS: 3 stores a row instead of 16 and 9 loads instead of 36.
 // KS > 1 (launches with too few tiles to fill the chip): KS waves share one half chunk, each takes
 // every KS-th pass of stage 1 and every KS-th entry of the list, and their keys are merged
 // through LDS at the end.
@@ -511,16 +533,23 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
     __shared__ int s_list[2 * CH][CKPT_MAX_L + 2];        // the splits that are left: k = q - qlo
     __shared__ uint32_t s_ub[2 * CH][4][R * T];           // upper bound of every cell in every sub-chunk
     __shared__ int s_n[2 * CH];
-    // row 7: gates of its cells, and shift, prefix sum and table row of the splits in the column block
-    __shared__ int32_t s_mall[T], s_mnull[T], s_jsh[T], s_jP[T];
+    // row 7: gates of its cells, and prefix sums and (shifted) byte offsets of the right operands of the splits in the column block
+    __shared__ int32_t s_mall[T], s_mnull[T], s_jP[T];
+    __shared__ uint32_t s_pair[kPairs];
+    __shared__ __align__(16) uint32_t s_turn[2 * CH][T][64];  // a row of the tile on its way to lane = column or back
+    __shared__ __align__(16) uint8_t s_num[2 * CH][T][64];
     const int nq = qhi - qlo + 1;
     const int i7 = I * T + T - 1;
     if (threadIdx.x < T) {
         const int j = min(j0 + int(threadIdx.x), L - 1), q = min(j0 + int(threadIdx.x) + 1, L - 1);
         s_mall[threadIdx.x] = c.ws.mall[(size_t(b) * L + i7) * L + j];
         s_mnull[threadIdx.x] = c.ws.mnull[(size_t(b) * L + i7) * L + j];
-        s_jsh[threadIdx.x] = c.ws.wsh[size_t(b) * L + q];
         s_jP[threadIdx.x] = P[q];
+    } else if (threadIdx.x >= 64 && threadIdx.x < 64 + T * T) {
+        const int c2 = int(threadIdx.x - 64) >> 3, cc = threadIdx.x & 7, q = min(j0 + c2 + 1, L - 1);
+        if (c2 < cc)
+            s_pair[pair_index(c2, cc)] =
+                cc < cend ? (uint32_t(row_base(L, q) + j0 + cc) * uint32_t(pitch) - uint32_t(c.ws.wsh[size_t(b) * L + q])) * 4u : kNoRead;
     }
     for (int k = threadIdx.x; k < nq; k += NT)
         s_split[k] = make_int2(c.ws.wsh[size_t(b) * L + qlo + k], P[qlo + k]);
@@ -768,20 +797,20 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
 
     // Row 7: operands of its column-block splits and of C_all are requested before the other rows
     // are converted and stored -- unless the whole chunk lies below the frontier of its cells.
-    uint32_t tj[T][T], al[T];
+    const int cell = lane >> 4, col = 4 * (lane & 15);
+    const uint32_t wide = uint32_t(cell * pitch + chunk * 64 + col) * 4u;  // this lane's part of a wide access: row `cell` of eight
+    u32x4 tjw[kPairs / 4], alw[2];
     uint32_t fb7 = 0;
     if (live7) {  // wave-uniform
 #pragma unroll
-        for (int c2 = 0; c2 < T - 1; ++c2) {
-            const int q = min(j0 + c2 + 1, L - 1);
-            const uint32_t right = moff + (uint32_t(row_base(L, q) + j0) * uint32_t(pitch) - uint32_t(s_jsh[c2])) * 4u;
-#pragma unroll
-            for (int cc = c2 + 1; cc < T; ++cc) tj[c2][cc] = tld(tab, right, colstep[cc]);
+        for (int k = 0; k < kPairs / 4; ++k) {
+            const uint32_t at = s_pair[4 * k + cell];
+            tjw[k] = tld4(tab, at == kNoRead ? kNoRead : at + uint32_t(chunk * 64 + col) * 4u);
         }
         fb7 = uint32_t(c.ws.fb[size_t(b) * L + i7]);
-        const uint32_t below = moff + (uint32_t(row_base(L, i7 + 1) + j0) * uint32_t(pitch) - uint32_t(c.ws.wabs[size_t(b) * L + i7])) * 4u;
-#pragma unroll
-        for (int cc = 0; cc < T; ++cc) al[cc] = tld(tab, below, colstep[cc]);
+        const uint32_t below = wide + (uint32_t(row_base(L, i7 + 1) + j0) * uint32_t(pitch) - uint32_t(c.ws.wabs[size_t(b) * L + i7])) * 4u;
+        alw[0] = tld4(tab, cell < cend ? below : kNoRead);
+        alw[1] = tld4(tab, cell + 4 < cend ? below + 16u * uint32_t(pitch) : kNoRead);
     }
     // The mantissa of a key holds 256 cost + number: cost is the 32 bits from bit 8 on.
     auto partial = [&](int r, int cc, uint32_t Pi, uint32_t& cst, uint32_t& num) {
@@ -789,7 +818,20 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
         cst = uint32_t(bits >> 8) - Pi;
         num = uint32_t(bits) & 255u;
     };
-    const uint32_t at7 = m + uint32_t(tri_row(L, i7, j0)) * uint32_t(pitch);
+    // A row of the tile from s_turn and s_num to the tables.
+    auto store_row = [&](int i) {
+        wave_settle();
+        const uint32_t at = wide + uint32_t(tri_row(L, i, j0)) * uint32_t(pitch) * 4u;
+        const u32x4 lo = *reinterpret_cast<const u32x4*>(&s_turn[grp][cell][col]), hi = *reinterpret_cast<const u32x4*>(&s_turn[grp][cell + 4][col]);
+        const u32x2 num = *reinterpret_cast<const u32x2*>(&s_num[grp][lane >> 3][8 * (lane & 7)]);
+        // No scalar offset register: behind a 16-byte store with one the compiler may write the first data register
+        // in the very next instruction, and the new value was seen in memory.
+        __builtin_amdgcn_raw_buffer_store_b128(lo, tab, int(cell < cend ? at : kNoRead), 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(hi, tab, int(cell + 4 < cend ? at + 16u * uint32_t(pitch) : kNoRead), 0, 0);
+        const uint32_t at8 = uint32_t(tri_row(L, i, j0) + (lane >> 3)) * uint32_t(pitch) + uint32_t(chunk * 64 + 8 * (lane & 7));
+        __builtin_amdgcn_raw_buffer_store_b64(num, atab, int((lane >> 3) < cend ? at8 : kNoRead), 0, 0);
+        wave_settle();
+    };
     uint32_t best[T], pick[T];
     if (half == 1) {
 #pragma unroll
@@ -798,54 +840,70 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
     // A partial minimum is stored with bit 31 set: a finished cell never exceeds 2^30, so whoever
     // reads the table can tell a cell that still waits for its row kernel from a finished one.
     // Partial minima of 2^31 - 1 and more are infeasible whatever they were and are clamped.
-    // full: the tile has all eight columns.
-    auto store = [&](auto full) {
+    uint32_t Pr[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (r == R - 1 && half == 1) break;  // row 7
-            const uint32_t Pi = uint32_t(P[i0 + r]);
-            const uint32_t at = m + uint32_t(tri_row(L, i0 + r, j0)) * uint32_t(pitch);
+    for (int r = 0; r < R; ++r) Pr[r] = uint32_t(P[i0 + r]);
 #pragma unroll
-            for (int cc = 0; cc < T; ++cc) {
-                if (full || cc < cend) {
-                    uint32_t cst, num;
-                    partial(r, cc, Pi, cst, num);
-                    __builtin_amdgcn_raw_buffer_store_b32(int(min(cst, 0x7fffffffu) | 0x80000000u), tab, int(at << 2), int(colstep[cc]), 0);
-                    __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(num), atab, int(at), int(colstep[cc] >> 2), 0);
-                }
-            }
-        }
-        count_work<CNT>(c.work, 0, live7 ? 36u : 0u, unsigned(R) * unsigned(cend));
-        if (half == 0) return;
-        // splits in the column block with the left operand (i, q-1) = the cell just finished, then the m_null gate,
-        // C_all with the m_all gate (smallest candidate number: wins ties), saturation
-        uint32_t val[T];
-        const uint32_t Pi = uint32_t(P[i7]);
+    for (int r = 0; r < R; ++r) {
+        if (r == R - 1 && half == 1) break;  // row 7
 #pragma unroll
         for (int cc = 0; cc < T; ++cc) {
-            val[cc] = kInf;
-            uint32_t num = 0;
-            if (live7) {
-#pragma unroll
-                for (int c2 = 0; c2 < cc; ++c2) {
-                    const uint32_t v = val[c2] + (uint32_t(s_jP[c2]) - Pi) + tj[c2][cc];
-                    if (v < best[cc]) best[cc] = v, pick[cc] = min(j0 + c2 + 1, L - 1) + 1;
-                }
-                const uint32_t ck = (m >= uint32_t(s_mnull[cc])) ? min(best[cc], kInf) : kInf;
-                const uint32_t all = (m >= uint32_t(s_mall[cc])) ? min(fb7 + al[cc], kInf) : kInf;
-                const bool take_all = all < kInf && all <= ck;
-                val[cc] = take_all ? all : ck;
-                num = take_all ? uint32_t(i7 + 1) : (ck < kInf ? pick[cc] : 0u);
-            }
-            if (full || cc < cend) {
-                __builtin_amdgcn_raw_buffer_store_b32(int(val[cc]), tab, int(at7 << 2), int(colstep[cc]), 0);
-                __builtin_amdgcn_raw_buffer_store_b8((unsigned char)(num), atab, int(at7), int(colstep[cc] >> 2), 0);
-            }
+            uint32_t cst, num;
+            partial(r, cc, Pr[r], cst, num);
+            s_turn[grp][cc][lane] = min(cst, 0x7fffffffu) | 0x80000000u;
+            s_num[grp][cc][lane] = uint8_t(num);
         }
-        store_samples(c, b, i7, J, m, val);
-    };
-    if (cend == T) store(std::true_type{});
-    else store(std::false_type{});
+        store_row(i0 + r);
+    }
+    count_work<CNT>(c.work, 0, live7 ? 36u : 0u, unsigned(R) * unsigned(cend));
+    if (half == 0) return;
+    // splits in the column block with the left operand (i, q-1) = the cell just finished, then the m_null gate,
+    // C_all with the m_all gate (smallest candidate number: wins ties), saturation
+    uint32_t tj[kPairs], al[T], val[T];
+    if (live7) {
+        auto turn = [&](const u32x4& a, const u32x4& d) {
+            *reinterpret_cast<u32x4*>(&s_turn[grp][cell][col]) = a;
+            *reinterpret_cast<u32x4*>(&s_turn[grp][cell + 4][col]) = d;
+            wave_settle();
+        };
+#pragma unroll
+        for (int k = 0; k < kPairs; k += T) {
+            turn(tjw[k / 4], k + 4 < kPairs ? tjw[min(k / 4 + 1, kPairs / 4 - 1)] : alw[0]);
+#pragma unroll
+            for (int u = 0; u < T; ++u) {
+                if (k + u < kPairs) tj[k + u] = s_turn[grp][u][lane];
+                else al[k + u - kPairs] = s_turn[grp][u][lane];
+            }
+            wave_settle();
+        }
+        static_assert(kPairs % T == 4, "the last turn holds four pairs and the first four operands of C_all");
+        turn(alw[1], alw[1]);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) al[4 + u] = s_turn[grp][u][lane];
+        wave_settle();
+    }
+    const uint32_t Pi = Pr[R - 1];
+#pragma unroll
+    for (int cc = 0; cc < T; ++cc) {
+        val[cc] = kInf;
+        uint32_t num = 0;
+        if (live7) {
+#pragma unroll
+            for (int c2 = 0; c2 < cc; ++c2) {
+                const uint32_t v = val[c2] + (uint32_t(s_jP[c2]) - Pi) + tj[pair_index(c2, cc)];
+                if (v < best[cc]) best[cc] = v, pick[cc] = min(j0 + c2 + 1, L - 1) + 1;
+            }
+            const uint32_t ck = (m >= uint32_t(s_mnull[cc])) ? min(best[cc], kInf) : kInf;
+            const uint32_t all = (m >= uint32_t(s_mall[cc])) ? min(fb7 + al[cc], kInf) : kInf;
+            const bool take_all = all < kInf && all <= ck;
+            val[cc] = take_all ? all : ck;
+            num = take_all ? uint32_t(i7 + 1) : (ck < kInf ? pick[cc] : 0u);
+        }
+        s_turn[grp][cc][lane] = val[cc];
+        s_num[grp][cc][lane] = uint8_t(num);
+    }
+    store_row(i7);
+    store_samples(c, b, i7, J, m, val);
 }
 
 // Finishes row R of every tile of block diagonal D: cells (i, j), i = I*T + R, j in block
@@ -1538,13 +1596,6 @@ __global__ void __launch_bounds__(64) store_budgets_kernel(SweepBudgets budget, 
 // that only continue a run.
 constexpr int kWalkNodes = 3 * CKPT_MAX_L;
 constexpr int kWalkThreads = 256;
-
-// Orders a wave's LDS accesses before and after: its lanes read what other lanes of the wave wrote.
-__device__ __forceinline__ void wave_settle() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 __global__ void __launch_bounds__(kWalkThreads) schedule_kernel(const uint8_t* __restrict__ arg,
                                                                  const int32_t* __restrict__ wa,
