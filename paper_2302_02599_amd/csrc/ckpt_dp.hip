@@ -394,17 +394,20 @@ __device__ __forceinline__ void store_samples(const Ctx& c, int b, int i, int J,
 }
 
 // Which (chunk of m, tile, chain) a work-group takes.  The hardware hands work-groups out in
-// linear order and to the 8 XCDs round-robin, and the cost of a chunk grows with m (low budgets
-// are infeasible and skipped).  The linear index is therefore re-read as (tile and chain)
-// fastest, chunk slowest and descending: the expensive chunks of all tiles start first and
-// the cheap ones fill the tail of the launch, and at every chunk level the tiles and chains
-// spread evenly over the XCDs.
+// linear order and to the 8 XCDs round-robin.  The linear index is re-read as (tile and chain)
+// fastest, chunk slowest, so at every chunk level the tiles and chains spread evenly over the XCDs.
+// rising: from the smallest budgets up.  Where the cells of a tile become feasible their upper bounds are infinite, and
+// the chunks there keep 50 to 150 splits, others 4 to 16: in a launch of few work-groups they decide when it ends,
+// so they start early, behind the ones below them that have nothing to do.  Launches of many work-groups (one slice)
+// fill their tail with the cheap chunks at the low end: from the largest budget down.  Rising and falling: 3 x 254 stages,
+// 1500 slots 2263 us and 2363, 20 x 80, 600 slots 434 and 450, 16 x 48, 1024 slots 218 and 224; with rising for one
+// slice as well 64 x 96 stages 3277 us and 3212, 128 x 96, 1024 slots 3500 and 3430, 8 x 192, 4096 slots 3727 and 3739.
 struct Work { int chunk, tile, chain; };
-__device__ __forceinline__ Work work_of_block() {
+__device__ __forceinline__ Work work_of_block(bool rising) {
     const uint32_t nt = gridDim.y * gridDim.z;
     const uint32_t lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
     const uint32_t level = lin / nt, t = lin - level * nt;
-    return {int(gridDim.x - 1 - level), int(t % gridDim.y), int(t / gridDim.y)};
+    return {int(rising ? level : gridDim.x - 1 - level), int(t % gridDim.y), int(t / gridDim.y)};
 }
 
 // + j = table row of cell (q, j)
@@ -509,7 +512,7 @@ template <int CH, int KS, bool CNT>
 __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
     constexpr int T = kT, R = T / 2;
     constexpr int NT = 128 * CH * KS;
-    const Work w = work_of_block();
+    const Work w = work_of_block(KS > 1);
     const int b = c.b0 + w.chain, I = w.tile, J = I + D;
     const int L = c.L, pitch = c.pitch;
     const int qlo = (I + 1) * T, qhi = J * T;
@@ -918,7 +921,7 @@ __global__ void __launch_bounds__(kRowWG) row_kernel(Ctx c, int D) {
     constexpr int CF = (DC == 0) ? R : 0;                              // first column with j >= i
     constexpr int NQ = (DC == 0) ? 0 : (DC == 1 ? T - R : T - 1 - R);  // near-i splits (D = 1: and q = jb)
     constexpr int NQA = NQ > 0 ? NQ : 1;
-    const Work w = work_of_block();
+    const Work w = work_of_block(false);
     const int b = c.b0 + w.chain, I = w.tile, J = I + D;
     const int L = c.L, pitch = c.pitch;
     const int i = I * T + R;
