@@ -491,7 +491,7 @@ __device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, co
 // 2^-8, exact in float64; 2^44 is added so that cost and number stand in fixed bits of the mantissa).
 //
 // A wave owns 4 rows x 8 columns of cells for 64 columns of m; the two halves of a tile and CH
-// adjacent chunks of m share a work-group.
+// adjacent chunks of m share a work-group (one half with four slices, see halves_of).
 // Output, rows 0..6 of the tile: cost[] <- partial minimum clamped to 2^31 - 1, with bit 31 set as
 // the mark "not finished", arg[] <- its number; the row kernels finish them.  Row 7 has no split
 // in its own row block, so its partial minimum stays in registers and the wave finishes the row
@@ -508,10 +508,16 @@ __device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, co
 // KS > 1 (launches with too few tiles to fill the chip): KS waves share one half chunk, each takes
 // every KS-th pass of stage 1 and every KS-th entry of the list, and their keys are merged
 // through LDS at the end.
+// Halves of a tile in one work-group.  The longest lists decide when a small launch ends, and evaluating them is float64
+// issue: four slices of both halves would be two waves on every SIMD of one compute unit while others idle, so with four slices
+// a half is a work-group of its own (1 x 254 stages, 1500 slots 1741 us with both, 1604 so; 1 x 128, 2048 slots 612 and 578;
+// 1 x 192, 4096 slots 1151 and 1119).  Two slices fill the SIMDs once and keep both halves (3 x 254 2209 us so, 2296 apart).
+constexpr int halves_of(int KS) { return KS >= 4 ? 1 : 2; }
+
 template <int CH, int KS, bool CNT>
-__global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
-    constexpr int T = kT, R = T / 2;
-    constexpr int NT = 128 * CH * KS;
+__global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(Ctx c, int D) {
+    constexpr int T = kT, R = T / 2, H = halves_of(KS);
+    constexpr int NT = 64 * H * CH * KS;
     const Work w = work_of_block(KS > 1);
     const int b = c.b0 + w.chain, I = w.tile, J = I + D;
     const int L = c.L, pitch = c.pitch;
@@ -519,10 +525,11 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
     const int j0 = J * T;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
-    const int slice = wave % KS, half = (wave / KS) & 1, cw = wave / (2 * KS);
+    const int slice = wave % KS, half = H == 1 ? w.chunk & 1 : (wave / KS) & 1;
     const int grp = wave / KS;       // waves of one group share a list
     const int i0 = I * T + half * R;  // first row of this wave
-    const int chunk = w.chunk * CH + cw;  // this wave's 64 columns of m
+    const int chunk = H == 1 ? w.chunk >> 1 : w.chunk * CH + wave / (2 * KS);  // this wave's 64 columns of m
+    static_assert(H == 2 || CH == 1, "one chunk, one half");
     const uint32_t m = chunk * 64 + lane;
     const uint32_t moff = m * 4;
     const int cend = min(T, L - j0);
@@ -533,14 +540,14 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
     const int32_t* P = c.ws.P + size_t(b) * (L + 1);
 
     __shared__ int2 s_split[CKPT_MAX_L + 2];              // shift and prefix sum of split qlo + k
-    __shared__ int s_list[2 * CH][CKPT_MAX_L + 2];        // the splits that are left: k = q - qlo
-    __shared__ uint32_t s_ub[2 * CH][4][R * T];           // upper bound of every cell in every sub-chunk
-    __shared__ int s_n[2 * CH];
+    __shared__ int s_list[H * CH][CKPT_MAX_L + 2];        // the splits that are left: k = q - qlo
+    __shared__ uint32_t s_ub[H * CH][4][R * T];           // upper bound of every cell in every sub-chunk
+    __shared__ int s_n[H * CH];
     // row 7: gates of its cells, and prefix sums and (shifted) byte offsets of the right operands of the splits in the column block
     __shared__ int32_t s_mall[T], s_mnull[T], s_jP[T];
     __shared__ uint32_t s_pair[kPairs];
-    __shared__ __align__(16) uint32_t s_turn[2 * CH][T][64];  // a row of the tile on its way to lane = column or back
-    __shared__ __align__(16) uint8_t s_num[2 * CH][T][64];
+    __shared__ __align__(16) uint32_t s_turn[H * CH][T][64];  // a row of the tile on its way to lane = column or back
+    __shared__ __align__(16) uint8_t s_num[H * CH][T][64];
     const int nq = qhi - qlo + 1;
     const int i7 = I * T + T - 1;
     if (threadIdx.x < T) {
@@ -779,7 +786,7 @@ __global__ void __launch_bounds__(128 * CH * KS, 4) gemm_kernel(Ctx c, int D) {
     if constexpr (KS > 1) {
         // Merge: row by row, the waves of slices 1.. hand their keys to the wave of slice 0 through LDS.
         // Every wave of the work-group passes all barriers.
-        __shared__ double s_red[2 * CH][KS - 1][T][64];
+        __shared__ double s_red[H * CH][KS - 1][T][64];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (slice > 0) {
@@ -2212,13 +2219,14 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             // slices of waves share a chunk.  That pays only with splits to share, 8 (D - 1) + 1 of them in
             // passes of 16: 8 x 192 stages gain 2 % up to 7000 chunks (D = 11), while with 5000 chunks at D = 4
             // (40 x 60 stages) or 2000 at D = 3 (30 x 32) a list for one slice is 3.5 % faster a solve; at D = 4, with
-            // two passes, 4 slices cost 16 x 48 stages 3 % against 2.
+            // two passes, 4 slices cost 16 x 48 stages 3 % against 2.  4 slices up to 600, 800 and 1100 chunks: 3 x 254 stages
+            // 2211, 2180 and 2163 us, 1 x 192 1124, 1105 and 1118, 20 x 80 427, 432 and 439, 8 x 128 792, 793 and 805.
             const long long chunks = (long long)(nblk - D) * (pitch / 64) * B;
-            const int ks = want_ks ? want_ks : (chunks <= 600 && D >= 5 ? 4 : (chunks <= 600 * D ? 2 : 1));
-            const int ch = ks == 1 ? kCH : 1, gx = (pitch / 64 + ch - 1) / ch;
+            const int ks = want_ks ? want_ks : (chunks <= 800 && D >= 5 ? 4 : (chunks <= 600 * D ? 2 : 1));
+            const int ch = ks == 1 ? kCH : 1, halves = halves_of(ks), gx = (pitch / 64 + ch - 1) / ch * (2 / halves);
             for (int g = 0; g < groups; ++g) {
                 const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work};
-                const dim3 grid(gx, nblk - D, first[g + 1] - first[g]), block(128 * ch * ks);
+                const dim3 grid(gx, nblk - D, first[g + 1] - first[g]), block(64 * halves * ch * ks);
                 const auto fn = ks == 4 ? (work ? gemm_kernel<1, 4, true> : gemm_kernel<1, 4, false>)
                               : ks == 2 ? (work ? gemm_kernel<1, 2, true> : gemm_kernel<1, 2, false>)
                                         : (work ? gemm_kernel<kCH, 1, true> : gemm_kernel<kCH, 1, false>);
