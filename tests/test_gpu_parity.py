@@ -523,3 +523,16 @@ def test_input_flags_wherever_the_bad_value_stands(amd, oracle_mod, L):
     for b in (b for b in range(batch.B) if want[b] == 0):
         cost, pick = oracle_mod.solve_chain(L, 40, *batch.chain(b))
         assert (sol.cost[b, :, :41].cpu().numpy() == cost[iu]).all() and (sol.arg[b, :, :41].cpu().numpy() == pick[iu]).all()
+
+
+@pytest.mark.parametrize("L,M", [(57, 191), (58, 192), (62, 193), (63, 255), (64, 256), (65, 130)])
+def test_edges_of_the_block_product(amd, oracle_mod, L, M):
+    """Block diagonals on both sides of the number of splits from which finished neighbours are asked for upper bounds
+    (33 splits: D = 5), one to eight columns in the last block, and one chunk of columns more or less than a work-group
+    takes; with four slices a half tile is a work-group of its own and the chunks are taken in rising order."""
+    blocks, pitch = -(-L // 8), amd.ckpt_row_pitch(M)
+    B = int(1.4e6) // (pitch * blocks * blocks) + 1  # the bounds are in use
+    batch = random_chain_batch(L, M, B, 1700 + L, size_hi=max(2, M // 12), time_hi=900, overheads=True, own_wdelta=True)
+    print(f"case {batch.name}", flush=True)
+    for split in (1, 2, 4):
+        assert_tables_equal(oracle_mod, batch, amd.solve(batch, list_split=split), chains=(0, B // 2, B - 1))
