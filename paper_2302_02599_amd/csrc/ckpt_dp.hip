@@ -496,8 +496,8 @@ __device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, co
 // the mark "not finished", arg[] <- its number; the row kernels finish them.  Row 7 has no split
 // in its own row block, so its partial minimum stays in registers and the wave finishes the row
 // itself.
-// What bounds it: latency of the dependent reads (samples, then operands), 23 % of the vector issue
-// slots busy; 2.5 ms a solve for L = 192, M = 4096, B = 8 at 4.6 TB/s asked for, where evaluating every
+// What bounds it: the gathers of the samples and the chunks with the longest lists, 19 % of the vector issue
+// slots busy; 2.3 ms a solve for L = 192, M = 4096, B = 8 at 4.3 TB/s asked for (2.5 and 4.6 with upper bounds from all splits), where evaluating every
 // feasible split took 5.7 ms and 29 GB (5.5 % of the splits are left instead of 67 %).  kG = 16: bounds
 // over 64 columns leave 11.7 %, over 32 7.5 %.  Half a tile a wave keeps it at 128 registers, four waves a SIMD.
 // The epilogue reads nothing behind its stores (a load behind a store waits until it is through, and the
