@@ -176,6 +176,11 @@ struct Ctx {
     // of table loads the gemm's waves asked for, [1] bytes they stored, [2], [3] the same for the
     // row kernel; a wave adds to the set its position selects, the host sums the sets
     unsigned long long* work;
+    // Rows of the block product are stored as passing through the caches: a split batch has 4 launches in flight with 50 to 90 MB of
+    // them, more than the L2 caches hold until the row kernel reads them, and they push out operands.  64 x 96 stages,
+    // 2048 slots 3211 -> 3157 us, 128 x 96, 1024 slots 3433 -> 3335, 8 x 192, 4096 slots 3731 -> 3721; on one stream, 8 x 96, 2048
+    // slots, 667 -> 678.
+    bool passing;
 };
 constexpr int kWorkSets = 256;
 
@@ -836,10 +841,16 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
         const u32x2 num = *reinterpret_cast<const u32x2*>(&s_num[grp][lane >> 3][8 * (lane & 7)]);
         // No scalar offset register: behind a 16-byte store with one the compiler may write the first data register
         // in the very next instruction, and the new value was seen in memory.
-        __builtin_amdgcn_raw_buffer_store_b128(lo, tab, int(cell < cend ? at : kNoRead), 0, 0);
-        __builtin_amdgcn_raw_buffer_store_b128(hi, tab, int(cell + 4 < cend ? at + 16u * uint32_t(pitch) : kNoRead), 0, 0);
         const uint32_t at8 = uint32_t(tri_row(L, i, j0) + (lane >> 3)) * uint32_t(pitch) + uint32_t(chunk * 64 + 8 * (lane & 7));
-        __builtin_amdgcn_raw_buffer_store_b64(num, atab, int((lane >> 3) < cend ? at8 : kNoRead), 0, 0);
+        const int to_lo = int(cell < cend ? at : kNoRead), to_hi = int(cell + 4 < cend ? at + 16u * uint32_t(pitch) : kNoRead);
+        const int to_num = int((lane >> 3) < cend ? at8 : kNoRead);
+        auto put = [&](auto policy) {
+            __builtin_amdgcn_raw_buffer_store_b128(lo, tab, to_lo, 0, policy.value);
+            __builtin_amdgcn_raw_buffer_store_b128(hi, tab, to_hi, 0, policy.value);
+            __builtin_amdgcn_raw_buffer_store_b64(num, atab, to_num, 0, policy.value);
+        };
+        if (KS == 1 && c.passing) put(std::integral_constant<int, 2>{});  // nontemporal
+        else put(std::integral_constant<int, 0>{});
         wave_settle();
     };
     uint32_t best[T], pick[T];
@@ -2189,7 +2200,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
 
         const int nbands = bands_of(pitch);
         for (int D = 0; D < 2 && D < nblk; ++D) {
-            const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work};
+            const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work, beside};
             if (fused_rows) {
                 const dim3 grid(nbands, nblk - D, B);
                 const auto fn = D == 0 ? (work ? tile_rows_kernel<0, true> : tile_rows_kernel<0, false>)
@@ -2225,7 +2236,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             const int ks = want_ks ? want_ks : (chunks <= 800 && D >= 5 ? 4 : (chunks <= 600 * D ? 2 : 1));
             const int ch = ks == 1 ? kCH : 1, halves = halves_of(ks), gx = (pitch / 64 + ch - 1) / ch * (2 / halves);
             for (int g = 0; g < groups; ++g) {
-                const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work};
+                const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, beside};
                 const dim3 grid(gx, nblk - D, first[g + 1] - first[g]), block(64 * halves * ch * ks);
                 const auto fn = ks == 4 ? (work ? gemm_kernel<1, 4, true> : gemm_kernel<1, 4, false>)
                               : ks == 2 ? (work ? gemm_kernel<1, 2, true> : gemm_kernel<1, 2, false>)
@@ -2242,7 +2253,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             }
             if (fused_rows) {  // rows 6..0 of every tile of the diagonal in one launch per group
                 for (int g = 0; g < groups; ++g) {
-                    const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work};
+                    const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, beside};
                     const auto fn = work ? tile_rows_kernel<2, true> : tile_rows_kernel<2, false>;
                     hipLaunchKernelGGL(fn, dim3(nbands, nblk - D, first[g + 1] - first[g]), dim3(kRowWG), 0, gs[g], ctx, D);
                     CKPT_AFTER_LAUNCH(CKPT_K_ROW);
@@ -2253,7 +2264,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             // finished by the gemm
             for (int r = T - 2; r >= 0; --r) {
                 for (int g = 0; g < groups; ++g) {
-                    const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work};
+                    const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, beside};
                     hipLaunchKernelGGL(kRow2[r], dim3(gx_row, nblk - D, first[g + 1] - first[g]), dim3(kRowWG), 0,
                                        gs[g], ctx, D);
                     CKPT_AFTER_LAUNCH(CKPT_K_ROW);
