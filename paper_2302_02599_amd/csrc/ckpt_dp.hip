@@ -15,6 +15,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "ckpt_rules.h"
 #include "ckpt_dp.h"
 
 namespace {
@@ -92,7 +93,6 @@ struct Workspace {
 };
 
 constexpr int kG = 16;  // columns between samples
-constexpr int kAsk = 33;  // splits from which the block product asks finished neighbours for upper bounds
 constexpr double kKeyBase = 0x1p44;
 
 constexpr int kBand = kRowWG;  // columns of m per work-group of the row kernels
@@ -624,15 +624,13 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
         // the sub-chunk: the first row of the next tile down (8 cells), the last column of the tile to the left (4), and four
         // (the other slices: sixteen) spread over the range.  One pass instead of one for every 16 splits, and as many
         // splits are dropped: a pass is a gather of about 30 lines and costs the compute unit's one path to memory 200 clocks a wave.
-        // With kAsk splits and fewer sixteen spread ones do without the trip to the neighbours' numbers.
+        // With kAsk splits and fewer all are spread, which does without the trip to the neighbours' numbers (ckpt_rules.h).
         // 8 x 192 stages, 4096 slots: 4.00 -> 3.89 ms a solve; 3 x 254, 1500 slots: 2.39 -> 2.33.
         Bound nx;
         int2 sp;
         if (search) {
-            const bool ask = slice == 0 && nq > kAsk;  // uniform
-            const int spread = slice > 0 ? 16 * (slice - 1) + x : ask ? x - 12 : x, of = slice > 0 ? 16 * (KS - 1) : ask ? 4 : 16;
-            int pick = ((2 * spread + 1) * nq) / (2 * of);
-            if (ask && x < 12) {
+            int pick = ckpt_rules::spread_split(x, slice, KS, nq);
+            if (slice == 0 && nq > ckpt_rules::kAsk && x < 12) {
                 const int i8 = (I + 1) * T, row = x < 8 ? row_base(L, i8) + min(j0 + x, L - 1) : row_base(L, i0 + x - 8) + j0 - 1;
                 pick = int(__builtin_amdgcn_raw_buffer_load_b8(atab, row * pitch + kk * kG + kG - 1, 0, 0)) - 1 - qlo;
                 if (uint32_t(pick) >= uint32_t(nq)) pick = (x * nq) / 12;  // none, C_all, or a split in a block of the tile
