@@ -808,6 +808,36 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
         if (slice != 0 || !active) return;
     }
 
+    // The mantissa of a key holds 256 cost + number: cost is the 32 bits from bit 8 on.
+    auto partial = [&](int r, int cc, uint32_t Pi, uint32_t& cst, uint32_t& num) {
+        const unsigned long long bits = __builtin_bit_cast(unsigned long long, key[r][cc]);
+        cst = uint32_t(bits >> 8) - Pi;
+        num = uint32_t(bits) & 255u;
+    };
+    // A partial minimum is stored with bit 31 set: a finished cell never exceeds 2^30, so whoever
+    // reads the table can tell a cell that still waits for its row kernel from a finished one.
+    // Partial minima of 2^31 - 1 and more are infeasible whatever they were and are clamped.
+    uint32_t Pr[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) Pr[r] = uint32_t(P[i0 + r]);
+    auto convert = [&](int r) {
+#pragma unroll
+        for (int cc = 0; cc < T; ++cc) {
+            uint32_t cst, num;
+            partial(r, cc, Pr[r], cst, num);
+            s_turn[grp][cc][lane] = min(cst, 0x7fffffffu) | 0x80000000u;
+            s_num[grp][cc][lane] = uint8_t(num);
+        }
+    };
+    // The sliced variants have no room for the 36 registers of row 7's operands beside the keys of four rows: 16 were
+    // spilled, a spill waited for the operands that had just been requested, and its reload stood behind the stores of the
+    // rows.  With one row converted first nothing is spilled (123 registers): 1 x 192 stages, 4096 slots 1096 -> 1079 us, 3 x 254,
+    // 1500 slots 2176 -> 2150, 8 x 96, 2048 slots 663 -> 653, 16 x 48, 1024 slots 213.1 -> 209.8.
+    if constexpr (KS > 1) {
+        convert(0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
     // Row 7: operands of its column-block splits and of C_all are requested before the other rows
     // are converted and stored -- unless the whole chunk lies below the frontier of its cells.
     const int cell = lane >> 4, col = 4 * (lane & 15);
@@ -825,12 +855,6 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
         alw[0] = tld4(tab, cell < cend ? below : kNoRead);
         alw[1] = tld4(tab, cell + 4 < cend ? below + 16u * uint32_t(pitch) : kNoRead);
     }
-    // The mantissa of a key holds 256 cost + number: cost is the 32 bits from bit 8 on.
-    auto partial = [&](int r, int cc, uint32_t Pi, uint32_t& cst, uint32_t& num) {
-        const unsigned long long bits = __builtin_bit_cast(unsigned long long, key[r][cc]);
-        cst = uint32_t(bits >> 8) - Pi;
-        num = uint32_t(bits) & 255u;
-    };
     // A row of the tile from s_turn and s_num to the tables.
     auto store_row = [&](int i) {
         wave_settle();
@@ -856,22 +880,10 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
 #pragma unroll
         for (int cc = 0; cc < T; ++cc) partial(R - 1, cc, uint32_t(P[i7]), best[cc], pick[cc]);
     }
-    // A partial minimum is stored with bit 31 set: a finished cell never exceeds 2^30, so whoever
-    // reads the table can tell a cell that still waits for its row kernel from a finished one.
-    // Partial minima of 2^31 - 1 and more are infeasible whatever they were and are clamped.
-    uint32_t Pr[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) Pr[r] = uint32_t(P[i0 + r]);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         if (r == R - 1 && half == 1) break;  // row 7
-#pragma unroll
-        for (int cc = 0; cc < T; ++cc) {
-            uint32_t cst, num;
-            partial(r, cc, Pr[r], cst, num);
-            s_turn[grp][cc][lane] = min(cst, 0x7fffffffu) | 0x80000000u;
-            s_num[grp][cc][lane] = uint8_t(num);
-        }
+        if (r > 0 || KS == 1) convert(r);
         store_row(i0 + r);
     }
     count_work<CNT>(c.work, 0, live7 ? 36u : 0u, unsigned(R) * unsigned(cend));
