@@ -176,11 +176,7 @@ struct Ctx {
     // of table loads the gemm's waves asked for, [1] bytes they stored, [2], [3] the same for the
     // row kernel; a wave adds to the set its position selects, the host sums the sets
     unsigned long long* work;
-    // Rows of the block product are stored as passing through the caches: a split batch has 4 launches in flight with 50 to 90 MB of
-    // them, more than the L2 caches hold until the row kernel reads them, and they push out operands.  64 x 96 stages,
-    // 2048 slots 3211 -> 3157 us, 128 x 96, 1024 slots 3433 -> 3335, 8 x 192, 4096 slots 3731 -> 3721; on one stream, 8 x 96, 2048
-    // slots, 667 -> 678.
-    bool passing;
+    bool passing;  // rows of the block product are stored as passing through the caches (see rows_pass)
 };
 constexpr int kWorkSets = 256;
 
@@ -2210,7 +2206,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
 
         const int nbands = bands_of(pitch);
         for (int D = 0; D < 2 && D < nblk; ++D) {
-            const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work, beside};
+            const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work, false};
             if (fused_rows) {
                 const dim3 grid(nbands, nblk - D, B);
                 const auto fn = D == 0 ? (work ? tile_rows_kernel<0, true> : tile_rows_kernel<0, false>)
@@ -2245,8 +2241,9 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             const long long chunks = (long long)(nblk - D) * (pitch / 64) * B;
             const int ks = want_ks ? want_ks : (chunks <= 800 && D >= 5 ? 4 : (chunks <= 600 * D ? 2 : 1));
             const int ch = ks == 1 ? kCH : 1, halves = halves_of(ks), gx = (pitch / 64 + ch - 1) / ch * (2 / halves);
+            const bool passing = beside && ckpt_rules::rows_pass(nblk - D, pitch, B);
             for (int g = 0; g < groups; ++g) {
-                const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, beside};
+                const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, passing};
                 const dim3 grid(gx, nblk - D, first[g + 1] - first[g]), block(64 * halves * ch * ks);
                 const auto fn = ks == 4 ? (work ? gemm_kernel<1, 4, true> : gemm_kernel<1, 4, false>)
                               : ks == 2 ? (work ? gemm_kernel<1, 2, true> : gemm_kernel<1, 2, false>)
@@ -2263,7 +2260,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             }
             if (fused_rows) {  // rows 6..0 of every tile of the diagonal in one launch per group
                 for (int g = 0; g < groups; ++g) {
-                    const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, beside};
+                    const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, false};
                     const auto fn = work ? tile_rows_kernel<2, true> : tile_rows_kernel<2, false>;
                     hipLaunchKernelGGL(fn, dim3(nbands, nblk - D, first[g + 1] - first[g]), dim3(kRowWG), 0, gs[g], ctx, D);
                     CKPT_AFTER_LAUNCH(CKPT_K_ROW);
@@ -2274,7 +2271,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             // finished by the gemm
             for (int r = T - 2; r >= 0; --r) {
                 for (int g = 0; g < groups; ++g) {
-                    const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, beside};
+                    const Ctx ctx{L, M, pitch, rows, first[g], spin_limit, ws, cost, arg, work, false};
                     hipLaunchKernelGGL(kRow2[r], dim3(gx_row, nblk - D, first[g + 1] - first[g]), dim3(kRowWG), 0,
                                        gs[g], ctx, D);
                     CKPT_AFTER_LAUNCH(CKPT_K_ROW);

@@ -21,4 +21,19 @@ constexpr int spread_split(int x, int slice, int KS, int nq) {
     return (2 * (x - 12) + 1) * nq / 8;
 }
 
+// Whether the rows that the block product of one diagonal stores, five bytes a cell of tiles x 64 rows of `pitch` columns for B
+// chains, are stored as passing through the caches (nontemporal).  That is for batches split over streams: the launches of
+// all groups are in flight together, and what they store pushes operands out of the caches long before the row
+// kernels read it back.  The line is half of the 256 MB memory-side cache.  us a solve with all rows of the batch passing, those of
+// diagonals from 128 MB on, from 192 MB on, and none:
+//   first diagonal 446 MB: 128 x 96 stages, 1024 slots 3603, 3604, 3617, 3720
+//   432 MB: 64 x 96, 2048 slots 3080, 3080, 3083, 3140
+//   351 MB: 12 x 192, 4096 slots 5074, 5081, 5096, 5131
+//   209 MB: 200 x 40, 1024 slots 785, 786, 788, 791
+//   160 MB: 60 x 30, 4096 slots 554.6, 552.8, 553.7, 554.1
+//   157 MB, little over the size from which batches are split: 16 x 254, 1000 slots 5386, 5386, 5393, 5401
+// Batches that only the caller splits, four groups, all passing and none from 128 MB on:
+//   117 MB: 4 x 192, 4096 slots 2229, 2218;  84 MB: 40 x 60, 1024 slots 515, 509;  54 MB: 8 x 96, 2048 slots 675, 668
+constexpr bool rows_pass(int tiles, int pitch, int B) { return 320LL * tiles * pitch * B >= 128LL * 1000 * 1000; }
+
 }  // namespace ckpt_rules

@@ -536,3 +536,12 @@ def test_edges_of_the_block_product(amd, oracle_mod, L, M):
     print(f"case {batch.name}", flush=True)
     for split in (1, 2, 4):
         assert_tables_equal(oracle_mod, batch, amd.solve(batch, list_split=split), chains=(0, B // 2, B - 1))
+
+
+@pytest.mark.parametrize("L,M,B", [(41, 1000, 97), (41, 1000, 98), (46, 1023, 98)])
+def test_rows_on_both_sides_of_what_the_caches_hold(amd, oracle_mod, L, M, B):
+    """Split batches whose first product diagonal stores a little less and a little more than 128 MB of rows, from where they
+    are stored as passing through the caches, with one and six columns in the last block."""
+    batch = random_chain_batch(L, M, B, 1900 + L + B, size_hi=M // 12, time_hi=900, overheads=True, own_wdelta=True)
+    print(f"case {batch.name}", flush=True)
+    assert_tables_equal(oracle_mod, batch, amd.solve(batch, groups=4), chains=(0, B // 2, B - 1))

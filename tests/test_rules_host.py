@@ -11,6 +11,7 @@ SHIM = """
 #include "ckpt_rules.h"
 extern "C" int ask() { return ckpt_rules::kAsk; }
 extern "C" int spread_split(int x, int slice, int KS, int nq) { return ckpt_rules::spread_split(x, slice, KS, nq); }
+extern "C" int rows_pass(int tiles, int pitch, int B) { return ckpt_rules::rows_pass(tiles, pitch, B); }
 """
 
 
@@ -40,3 +41,12 @@ def test_slices_fetch_the_bounds_of_different_splits(rules, KS):
             assert len({k for g in sharing for k in g}) == min(nq, lanes), (KS, nq)
         if asking:
             assert len(set(got[0])) == 4
+
+
+@pytest.mark.parametrize("tiles,pitch,B,passing", [
+    (10, 2112, 64, 1), (22, 4160, 8, 1), (30, 1024, 16, 1), (4, 1024, 98, 1), (29, 1 << 16, 1 << 20, 1),
+    (4, 1024, 97, 0), (22, 4160, 4, 0), (6, 1088, 40, 0), (10, 2112, 8, 0), (1, 64, 2, 0)])
+def test_rows_pass_through_the_caches_by_their_size(rules, tiles, pitch, B, passing):
+    """128 MB of rows in one diagonal: 64 x 96 stages, 8 x 192 and the smallest batch that is split unasked are above it,
+    batches of the sizes that only a caller splits below."""
+    assert rules.rows_pass(tiles, pitch, B) == passing
