@@ -382,6 +382,14 @@ __device__ __forceinline__ u32x4 tld4(rsrc_t tab, uint32_t voff) {
     return __builtin_amdgcn_raw_buffer_load_b128(tab, int(voff), 0, 0);
 }
 
+// The only way to store 16 bytes a lane to a table: there is no scalar offset to give.  Behind a store of more than 8 bytes with a
+// scalar offset register the compiler may write the first data register in the very next instruction, and the
+// new value was seen in memory; without one it keeps them apart.
+template <int policy>
+__device__ __forceinline__ void tst4(rsrc_t tab, int voff, u32x4 v) {
+    __builtin_amdgcn_raw_buffer_store_b128(v, tab, voff, 0, policy);
+}
+
 constexpr int kPairs = kT * (kT - 1) / 2;  // splits in the column block of a row: (c2, cc), c2 < cc
 __host__ __device__ constexpr int pair_index(int c2, int cc) { return c2 * (2 * kT - 1 - c2) / 2 + cc - c2 - 1; }
 
@@ -857,14 +865,12 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
         const uint32_t at = wide + uint32_t(tri_row(L, i, j0)) * uint32_t(pitch) * 4u;
         const u32x4 lo = *reinterpret_cast<const u32x4*>(&s_turn[grp][cell][col]), hi = *reinterpret_cast<const u32x4*>(&s_turn[grp][cell + 4][col]);
         const u32x2 num = *reinterpret_cast<const u32x2*>(&s_num[grp][lane >> 3][8 * (lane & 7)]);
-        // No scalar offset register: behind a 16-byte store with one the compiler may write the first data register
-        // in the very next instruction, and the new value was seen in memory.
         const uint32_t at8 = uint32_t(tri_row(L, i, j0) + (lane >> 3)) * uint32_t(pitch) + uint32_t(chunk * 64 + 8 * (lane & 7));
         const int to_lo = int(cell < cend ? at : kNoRead), to_hi = int(cell + 4 < cend ? at + 16u * uint32_t(pitch) : kNoRead);
         const int to_num = int((lane >> 3) < cend ? at8 : kNoRead);
         auto put = [&](auto policy) {
-            __builtin_amdgcn_raw_buffer_store_b128(lo, tab, to_lo, 0, policy.value);
-            __builtin_amdgcn_raw_buffer_store_b128(hi, tab, to_hi, 0, policy.value);
+            tst4<policy.value>(tab, to_lo, lo);
+            tst4<policy.value>(tab, to_hi, hi);
             __builtin_amdgcn_raw_buffer_store_b64(num, atab, to_num, 0, policy.value);
         };
         if (KS == 1 && c.passing) put(std::integral_constant<int, 2>{});  // nontemporal
