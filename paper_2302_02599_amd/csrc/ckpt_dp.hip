@@ -636,8 +636,7 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
             int pick = ckpt_rules::spread_split(x, slice, KS, nq);
             if (slice == 0 && nq > ckpt_rules::kAsk && x < 12) {
                 const int i8 = (I + 1) * T, row = x < 8 ? row_base(L, i8) + min(j0 + x, L - 1) : row_base(L, i0 + x - 8) + j0 - 1;
-                pick = int(__builtin_amdgcn_raw_buffer_load_b8(atab, row * pitch + kk * kG + kG - 1, 0, 0)) - 1 - qlo;
-                if (uint32_t(pick) >= uint32_t(nq)) pick = (x * nq) / 12;  // none, C_all, or a split in a block of the tile
+                pick = ckpt_rules::asked_split(x, int(__builtin_amdgcn_raw_buffer_load_b8(atab, row * pitch + kk * kG + kG - 1, 0, 0)), qlo, nq);
             }
             sp = s_split[pick];
             fetch(nx, qlo + pick, kk - 1, below(sp.x));

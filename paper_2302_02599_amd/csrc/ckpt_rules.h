@@ -7,7 +7,10 @@ namespace ckpt_rules {
 // of waves share them, and sixteen lanes of a slice, x = 0 .. 15, fetch the bounds of one split each.  Any splits give a
 // valid upper bound; more of them, and better ones, give a tighter one.
 
-// With more splits than this slice 0 asks finished neighbours which splits they took.
+// With more splits than this slice 0 asks finished neighbours which splits they took.  The answer is a trip to memory
+// before the gather, which tiles of few splits do not pay back.  us a solve with 17, 25, 33, 49 and 65:
+//   64 x 96 stages, 2048 slots 3501, 3501, 3508, 3519, 3533;  128 x 96, 1024 slots 3822, 3827, 3815, 3842, 3852
+//   8 x 128, 1024 slots 774.4, 773.2, 771.5, 769.8, 768.4;  16 x 48, 1024 slots 211.3, 210.8, 210.1, 210.3, 210.3
 constexpr int kAsk = 33;
 
 // The split of a lane that asks nobody, evenly spread over the tile.  Where slice 0 asks, its lanes 12 .. 15 take four places
@@ -19,6 +22,16 @@ constexpr int spread_split(int x, int slice, int KS, int nq) {
     if (nq <= kAsk) return (2 * (16 * slice + x) + 1) * nq / (32 * KS);
     if (slice > 0) return (2 * (16 * (slice - 1) + x) + 1) * nq / (32 * others);
     return (2 * (x - 12) + 1) * nq / 8;
+}
+
+// The split that an asked neighbour took, from the number of its candidate: q + 1 for split q, i + 1 for C_all of row i, 0 for
+// none.  Lanes 0 .. 7 ask row qlo, lanes 8 .. 11 the rows above it.  Lanes whose neighbour took none of the tile's splits take one of
+// twelve spread places, but C_all of row qlo reads like split qlo, the first of the tile, and is left so: lanes
+// that agree gather fewer lines, and with places of their own no batch was faster (8 x 192 stages, 4096 slots 4433 us,
+// 4427 with places; 3 x 254, 1500 slots 2075, 2070; 1 x 192, 4096 slots 1134, 1134; 1 x 254, 1500 slots 1646, 1653).
+constexpr int asked_split(int x, int number, int qlo, int nq) {
+    const int k = number - 1 - qlo;
+    return k < 0 || k >= nq ? x * nq / 12 : k;
 }
 
 // Whether the rows that the block product of one diagonal stores, five bytes a cell of tiles x 64 rows of `pitch` columns for B

@@ -11,6 +11,7 @@ SHIM = """
 #include "ckpt_rules.h"
 extern "C" int ask() { return ckpt_rules::kAsk; }
 extern "C" int spread_split(int x, int slice, int KS, int nq) { return ckpt_rules::spread_split(x, slice, KS, nq); }
+extern "C" int asked_split(int x, int number, int qlo, int nq) { return ckpt_rules::asked_split(x, number, qlo, nq); }
 extern "C" int rows_pass(int tiles, int pitch, int B) { return ckpt_rules::rows_pass(tiles, pitch, B); }
 """
 
@@ -41,6 +42,25 @@ def test_slices_fetch_the_bounds_of_different_splits(rules, KS):
             assert len({k for g in sharing for k in g}) == min(nq, lanes), (KS, nq)
         if asking:
             assert len(set(got[0])) == 4
+
+
+def test_asked_neighbours_give_a_split_of_the_tile(rules):
+    """Whatever byte stands in the table, the place lies in the tile.  Lanes 0 .. 7 ask cells (qlo, j) and lanes 8 .. 11 cells
+    (i, j0 - 1) above them; split q has the number q + 1, C_all of row i the number i + 1, an infeasible cell 0.  A split of the
+    tile is taken, C_all of row qlo is split qlo, and in all other cases a lane has its own place of twelve."""
+    for I, nq in [(0, 41), (3, 41), (0, 49), (7, 57), (20, 81), (0, 241)]:
+        qlo = 8 * (I + 1)
+        qhi = qlo + nq - 1  # = j0
+        place = [x * nq // 12 for x in range(12)]
+        assert len(set(place)) == 12 and place[0] == 0 and place[-1] < nq
+        for x in range(12):
+            assert all(0 <= rules.asked_split(x, n, qlo, nq) < nq for n in range(256))
+            assert rules.asked_split(x, 0, qlo, nq) == place[x]
+            for i in [qlo] if x < 8 else range(8 * I, qlo):
+                assert rules.asked_split(x, i + 1, qlo, nq) == (0 if i == qlo else place[x]), (I, nq, x, i, "C_all")
+                for q in range(i + 1, qhi + x + 1 if x < 8 else qhi):
+                    want = q - qlo if qlo <= q <= qhi else place[x]
+                    assert rules.asked_split(x, q + 1, qlo, nq) == want, (I, nq, x, i, q)
 
 
 @pytest.mark.parametrize("tiles,pitch,B,passing", [
