@@ -374,7 +374,9 @@ __device__ __forceinline__ void wave_settle() {
 // Wide accesses of a wave: eight rows of the table (the cells (i, jb) .. (i, jb + 7) of a row of a tile lie in consecutive
 // ones), 64 columns each, as two instructions of 16 bytes a lane instead of eight of 4.  Lane l holds columns
 // 4 (l & 15) .. + 3 of rows l >> 4 and 4 + (l >> 4); a turn through LDS brings values to lane = column, or from there.
-// The work-groups of a compute unit share one path to memory that takes an instruction every 16 to 20 clocks.
+// Fewer instructions, each whole lines: the compute unit's address path is busy 25 clocks a buffer instruction in the block product,
+// 35 % of its time in 8 x 192 stages and 52 % in 64 x 96 (TA_TA_BUSY in profiles/): a share of the bound, not the bound.  Wide rows
+// gained 0.4 to 1.1 % in large batches and nothing in small ones.
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -409,8 +411,8 @@ __device__ __forceinline__ void store_samples(const Ctx& c, int b, int i, int J,
 // the chunks there keep 50 to 150 splits, others 4 to 16: in a launch of few work-groups they decide when it ends,
 // so they start early, behind the ones below them that have nothing to do.  Launches of many work-groups (one slice)
 // fill their tail with the cheap chunks at the low end: from the largest budget down.  Rising and falling: 3 x 254 stages,
-// 1500 slots 2263 us and 2363, 20 x 80, 600 slots 434 and 450, 16 x 48, 1024 slots 218 and 224; with rising for one
-// slice as well 64 x 96 stages 3277 us and 3212, 128 x 96, 1024 slots 3500 and 3430, 8 x 192, 4096 slots 3727 and 3739.
+// 1500 slots 2154 us and 2258, 20 x 80, 600 slots 425 and 429, 16 x 48, 1024 slots 211 and 216; with rising for one
+// slice as well 64 x 96 stages, 2048 slots 3109 us and 3100, 8 x 192, 4096 slots 3681 and 3727.
 struct Work { int chunk, tile, chain; };
 __device__ __forceinline__ Work work_of_block(bool rising) {
     const uint32_t nt = gridDim.y * gridDim.z;
@@ -505,8 +507,8 @@ __device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, co
 // the mark "not finished", arg[] <- its number; the row kernels finish them.  Row 7 has no split
 // in its own row block, so its partial minimum stays in registers and the wave finishes the row
 // itself.
-// What bounds it: the gathers of the samples and the chunks with the longest lists, 19 % of the vector issue
-// slots busy; 2.3 ms a solve for L = 192, M = 4096, B = 8 at 4.3 TB/s asked for (2.5 and 4.6 with upper bounds from all splits), where evaluating every
+// What bounds it: the gathers of the samples and the chunks with the longest lists, 23 % of the vector issue
+// slots busy; 2.2 ms a solve for L = 192, M = 4096, B = 8 at 4.5 TB/s asked for (2.5 and 4.6 with upper bounds from all splits), where evaluating every
 // feasible split took 5.7 ms and 29 GB (5.5 % of the splits are left instead of 67 %).  kG = 16: bounds
 // over 64 columns leave 11.7 %, over 32 7.5 %.  Half a tile a wave keeps it at 128 registers, four waves a SIMD.
 // The epilogue reads nothing behind its stores (a load behind a store waits until it is through, and the
@@ -519,8 +521,9 @@ __device__ __forceinline__ void finish_row(const Ctx& c, int b, size_t chain, co
 // through LDS at the end.
 // Halves of a tile in one work-group.  The longest lists decide when a small launch ends, and evaluating them is float64
 // issue: four slices of both halves would be two waves on every SIMD of one compute unit while others idle, so with four slices
-// a half is a work-group of its own (1 x 254 stages, 1500 slots 1741 us with both, 1604 so; 1 x 128, 2048 slots 612 and 578;
-// 1 x 192, 4096 slots 1151 and 1119).  Two slices fill the SIMDs once and keep both halves (3 x 254 2209 us so, 2296 apart).
+// a half is a work-group of its own (1 x 254 stages, 1500 slots 1780 us with both, 1639 so; 1 x 128, 2048 slots 632 and 594;
+// 1 x 192, 4096 slots 1192 and 1135; 3 x 254, 1500 slots 2205 and 2154).  Two slices fill the SIMDs once and keep both halves
+// (3 x 254, 1500 slots 2154 us so, 2219 apart; but 8 x 128, 1024 slots 771 and 763, 16 x 48, 1024 slots 211 and 209).
 constexpr int halves_of(int KS) { return KS >= 4 ? 1 : 2; }
 
 template <int CH, int KS, bool CNT>
@@ -627,7 +630,7 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
         // Any splits give an upper bound; the best ones are mostly those that finished neighbours took at the end of
         // the sub-chunk: the first row of the next tile down (8 cells), the last column of the tile to the left (4), and four
         // (the other slices: sixteen) spread over the range.  One pass instead of one for every 16 splits, and as many
-        // splits are dropped: a pass is a gather of about 30 lines and costs the compute unit's one path to memory 200 clocks a wave.
+        // splits are dropped: a pass is six loads, four of a word and two of 16 bytes, that gather about 30 lines.
         // With kAsk splits and fewer all are spread, which does without the trip to the neighbours' numbers (ckpt_rules.h).
         // 8 x 192 stages, 4096 slots: 4.00 -> 3.89 ms a solve; 3 x 254, 1500 slots: 2.39 -> 2.33.
         Bound nx;
@@ -2242,7 +2245,8 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             // passes of 16: 8 x 192 stages gain 2 % up to 7000 chunks (D = 11), while with 5000 chunks at D = 4
             // (40 x 60 stages) or 2000 at D = 3 (30 x 32) a list for one slice is 3.5 % faster a solve; at D = 4, with
             // two passes, 4 slices cost 16 x 48 stages 3 % against 2.  4 slices up to 600, 800 and 1100 chunks: 3 x 254 stages
-            // 2211, 2180 and 2163 us, 1 x 192 1124, 1105 and 1118, 20 x 80 427, 432 and 439, 8 x 128 792, 793 and 805.
+            // 2186, 2154 and 2138 us, 1 x 192 1162, 1135 and 1133, 20 x 80 419, 425 and 432, 8 x 128 774, 771 and 781,
+            // 8 x 96, 2048 slots 654, 654 and 660.
             const long long chunks = (long long)(nblk - D) * (pitch / 64) * B;
             const int ks = want_ks ? want_ks : (chunks <= 800 && D >= 5 ? 4 : (chunks <= 600 * D ? 2 : 1));
             const int ch = ks == 1 ? kCH : 1, halves = halves_of(ks), gx = (pitch / 64 + ch - 1) / ch * (2 / halves);
