@@ -169,8 +169,8 @@ def roofline_of(r):
     if dom == "gemm_kernel":
         dom_evals, ops_per_eval = g_evals, 2
         alu_unit = "Tlane-op/s (float64 add + min per candidate, nominal candidate count)"
-    else:
-        dom_evals, ops_per_eval = r["evals"] - g_evals, 4
+    else:  # small batches: one kernel does both, and there is no block product of its own
+        dom_evals, ops_per_eval = r["evals"] - (g_evals if kinds["gemm_kernel"]["launches_per_step"] else 0), 4
         alu_unit = "Tlane-op/s (32-bit add, compare, two selects per candidate, nominal candidate count)"
     step_s = r["ms"] * 1e-3
     floor_bytes = FLOOR_BYTES_PER_CELL * r["cells"]

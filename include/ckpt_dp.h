@@ -151,7 +151,8 @@ int ckpt_solve_batched(const ckpt_chains_t* chains, int L, int M, int B, void* s
  *   side_streams  caller-owned hipStream_t for groups 2, 3, 4, or all NULL: the library's
  *                 helper streams.  The fork and join events are the library's in both cases.
  *   list_split    0: automatic.  1, 2 or 4: waves that share one chunk's list of splits in
- *                 every launch of the block-product kernel.
+ *                 every launch of the block-product kernel (small batches too are then filled by
+ *                 two launches a block diagonal instead of one for all).
  *   row_launches  0: the rows of all tiles of a block diagonal are finished by one launch whose
  *                 work-groups wait for each other's rows.  1: one launch per row of the tiles.
  *   stagger       1: half of the groups start their first block product when the first group has
@@ -212,6 +213,7 @@ int ckpt_solve_batched_noalloc(const ckpt_chains_t* chains, int L, int M, int B,
  *                            of table loads of kind k (256 per wave and load), entry 2k + 1 =
  *                            bytes stored (320 per wave and cell: cost and candidate number).
  *                            Work that the feasibility tests skip is not counted.
+ * CKPT_K_ROW also counts the kernel that takes small batches in one launch, block products and rows.
  * Creates and destroys events and a small device buffer (allocates); not for latency-critical
  * callers.  Returns as ckpt_solve_batched.
  */

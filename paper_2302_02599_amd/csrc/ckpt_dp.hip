@@ -73,7 +73,8 @@ inline bool hip_ok(hipError_t e) {
 //   need  [B][L][L] int32  feasibility frontier: smallest m at which cell (i, j) can be finite
 //   prog  [B][tiles][chunks + 1] int32  rows of tile (I, J) finished by tile_rows_kernel for the chunk
 //                          of 64 columns; tiles = nblk (nblk + 1) / 2, chunks = pitch / 64; last word: bands of
-//                          the tile that work-groups have taken
+//                          the tile that work-groups have taken.  flow_kernel: 1 where the tile is finished; last
+//                          words: of the first tile, tickets of the chain; of the last one, the chain's largest shift
 //   fault [1]      int32   set when a bounded wait inside tile_rows_kernel expired
 //   samp  [B][4 nblk (nblk + 1)][pitch / kG][8] int32  every kG-th column of the finished cells, eight cells of a
 //                          row side by side (see gemm_kernel); left out where they are not used or do not fit
@@ -197,18 +198,30 @@ __host__ __device__ inline int tri_row(int L, int i, int j) {  // 0-based i <= j
 
 constexpr uint32_t kNoRead = 0xfffffff0u;  // buffer offset beyond any table: the load returns 0, no access
 
-// Input checks, prefix sums, shifts and both threshold tables (last display of the Theorem).  A
+// Input checks, prefix sums, shifts and both threshold tables (last display of the Theorem), and for flow_kernel the marks
+// of the first diagonal's tiles (further work-groups).  A
 // work-group per chain and kPreRows rows of the tables, thread = column t: the maximum over the stages
 // between s and t grows by one stage from row to row, bottom-up, and the rows are written in whole
 // lines.  The work-group of the first rows also does what there is once per chain.  What bounds it: one round
 // trip to memory and a serial pass over the stages below the first row, in LDS.  One work-group per chain with
 // a thread per row took 52 us for 192 stages (8 chains), 12.6 us for 50 (10 chains).
-constexpr int kPreThreads = 256, kPreRows = 16;
+constexpr int kPreThreads = 256, kPreRows = 16, kMarkCols = 512;
+constexpr uint32_t kMark = 0x80000000u;  // a cell that waits for its row
 static_assert(CKPT_MAX_L < kPreThreads, "a thread per stage");
 
-__global__ void __launch_bounds__(kPreThreads) precompute_kernel(ckpt_chains_t ch, int L, int pitch, Workspace ws) {
-    const int b = blockIdx.x, part = blockIdx.y;
+__global__ void __launch_bounds__(kPreThreads) precompute_kernel(ckpt_chains_t ch, int L, int pitch, Workspace ws, int32_t* cost) {
+    const int b = blockIdx.x, part = blockIdx.y, parts = (L + kPreRows - 1) / kPreRows;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool flow = int(gridDim.y) > parts;  // for flow_kernel
+    if (part >= parts) {  // marks kMarkCols columns of rows 1 .. 7 of a tile of the first diagonal
+        const int segs = (pitch + kMarkCols - 1) / kMarkCols, I = (part - parts) / segs, m = (part - parts) % segs * kMarkCols + 4 * (tid & 127);
+        int4* at = reinterpret_cast<int4*>(cost + size_t(b) * (size_t(L) * (L + 1) / 2) * pitch + m);
+        if (m < pitch)
+            for (int r = 1 + (tid >> 7); r < kT && I * kT + r < L; r += 2)
+                for (int cc = r; cc < kT && I * kT + cc < L; ++cc)
+                    at[size_t(tri_row(L, I * kT + r, I * kT + cc)) * (pitch / 4)] = make_int4(int(kMark), int(kMark), int(kMark), int(kMark));
+        return;
+    }
     const int32_t* uf = ch.uf + size_t(b) * L;
     const int32_t* ub = ch.ub + size_t(b) * L;
     const int32_t* wa = ch.wa + size_t(b) * (L + 1);
@@ -219,17 +232,18 @@ __global__ void __launch_bounds__(kPreThreads) precompute_kernel(ckpt_chains_t c
     __shared__ int32_t s_wa[kPreThreads], s_wd[kPreThreads], s_wab[kPreThreads], s_of[kPreThreads], s_ob[kPreThreads];
     __shared__ int32_t s_pair[kPreThreads];  // [j] = omega_a^{j-1} + omega_a^j + o_f^j
     __shared__ uint32_t s_total[kPreThreads / 64];
-    __shared__ int s_flags;
+    __shared__ int s_flags, s_reach;
     const bool stage = tid < L;
     const int a_in = tid <= L ? wa[tid] : 0, d_in = tid <= L ? wd[tid] : 0, ab_in = stage ? wab[tid] : 0;
     const int of_in = stage && of ? of[tid] : 0, ob_in = stage && ob ? ob[tid] : 0;
     // Sizes are clamped into [0, 2^28] so that thresholds of a bad chain cannot overflow.
     auto sz = [](int v) { return min(max(v, 0), 1 << 28); };
     s_wa[tid] = sz(a_in), s_wd[tid] = sz(d_in), s_wab[tid] = sz(ab_in), s_of[tid] = sz(of_in), s_ob[tid] = sz(ob_in);
-    if (tid == 0) s_flags = 0;
+    if (tid == 0) s_flags = s_reach = 0;
     {   // progress and ticket words of this chain's tiles, and (first block) the fault word
         const size_t n = tiles_of(L) * prog_words(pitch);
-        for (size_t k = size_t(part) * kPreThreads + tid; k < n; k += size_t(gridDim.y) * kPreThreads) ws.prog[size_t(b) * n + k] = 0;
+        for (size_t k = size_t(part) * kPreThreads + tid; k < n; k += size_t(parts) * kPreThreads)
+            if (!flow || blocks_of(L) == 1 || k != n - 1) ws.prog[size_t(b) * n + k] = 0;
         if (b == 0 && part == 0 && tid == 0) ws.fault[0] = 0;
     }
     __syncthreads();
@@ -266,9 +280,19 @@ __global__ void __launch_bounds__(kPreThreads) precompute_kernel(ckpt_chains_t c
         if (tid == 0) P[0] = 0;
         if (stage) P[tid + 1] = int32_t(min(sum, kInf - 1));
         if (flags) atomicOr(&s_flags, flags);
+        if (flow) {
+            int reach = stage ? min(max(max(a_in, ab_in), 0), pitch) : 0;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) reach = max(reach, __shfl_xor(reach, o));
+            if (lane == 0) atomicMax(&s_reach, reach);
+        }
     }
     __syncthreads();
-    if (part == 0 && tid == 0) ws.flags[b] = s_flags;
+    if (part == 0 && tid == 0) {
+        ws.flags[b] = s_flags;
+        const size_t n = tiles_of(L) * prog_words(pitch);
+        if (flow && blocks_of(L) > 1) ws.prog[size_t(b) * n + n - 1] = s_reach;
+    }
 
     const int t = tid + 1;
     if (t > L) return;
@@ -1546,6 +1570,546 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
         TileRows<DC, RF, CNT, false>::run(x, s_row);
 }
 
+// ---------------------------------------------------------------------------
+// Every tile of a solve in ONE launch (flow_kernel), for batches that leave the chip half empty.
+//
+// There a solve is a chain of dependent steps, and what it takes is the length of the chain: launches and the gaps between
+// them, round trips to memory, and the instructions of a lone wave, 4.4 clocks a vector instruction and 8 a scalar one (measured; with
+// four waves a SIMD the vector ones take 4.4 in all).  So a work-group owns one tile and 64 columns, and four lanes share a column.
+//   - Splits between the blocks: the four waves fetch the 16 operand rows of a split together, 16 bytes a lane and two batches of
+//     four splits ahead, and pass them through LDS; each evaluates 4 x 4 cells, lane = column, as float64 keys (see
+//     gemm_kernel).  All feasible splits are evaluated: about 500 clocks each.  The partial minima stay in LDS.
+//   - Rows, bottom-up: a wave holds 16 columns, lane k of the four of a column cells k and k + 4 of the row.  A finished cell
+//     reaches the other lanes of its column as the operand of an addition (quad broadcast).  A row is about 190 instructions, 1250 clocks,
+//     where tile_rows_kernel takes 900, 5500 to 6500 clocks.
+// No launch boundary separates the diagonals.
+//   - A chain's work-groups take its tiles by ticket, in the order of D, band, I, so whatever one of them waits for belongs
+//     to a work-group that already runs.  Every wait is bounded, see tile_rows_kernel.
+//   - Rows of the same tile at columns below the band: every cell is marked by bit 31 until its row is finished, and a lane that
+//     finds the mark reads again.  These reads are requested a row ahead, and mostly find the band below finished.
+//     A tile's cells are marked by the work-group of the tile to its left, those of the first diagonal by precompute_kernel.
+//   - Other tiles: a flag per tile and 64 columns, set behind its last store.  A tile waits for the tiles to its left and
+//     below it, there at all chunks that the chain's largest shift can reach; those waited for theirs, so everything it
+//     reads is finished.  The splits whose operands lie two diagonals down and more do not wait for the last one.
+// Everything read is read with device scope: lines may lie in this die's L2 with the marks in them.
+// Results bit for bit those of the other kernels.  us a solve, two launches a diagonal and this: 1 x 24 stages, 512 slots 71 and 40;
+// 5 x 53, 777 slots 233 and 112; 16 x 48, 1024 slots 211 and 158; 10 x 50, 500 slots 219 and 102 (the rule: ckpt_rules::flow_pays).
+// What bounds it: of 26000 clocks a diagonal (5 x 53 stages) rows take 10500, the 16 splits of the last neighbours 7800,
+// their operands and those of the rows 3700, the stores and the flag 2000.
+//
+// Inside, a candidate of row i stands plus P[i]: a right operand carries the prefix sum of its split, and a split costs one addition.
+// ---------------------------------------------------------------------------
+template <class F, int... K>
+__device__ __forceinline__ void for_each_of(std::integer_sequence<int, K...>, F&& f) {
+    (f(std::integral_constant<int, K>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F&& f) {
+    for_each_of(std::make_integer_sequence<int, N>{}, f);
+}
+
+// The value of lane K of every four lanes.
+template <int K>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v) {
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), K * 0x55, 0xf, 0xf, true));
+}
+
+__device__ __forceinline__ u32x4 tld4_dev(rsrc_t tab, uint32_t voff) {
+    return __builtin_amdgcn_raw_buffer_load_b128(tab, int(voff), 0, 16);
+}
+
+constexpr uint32_t kHuge = 0xbfffffffu;  // never smaller than a candidate that counts; no overflow on top of a cost
+constexpr int kFar = 0x7f000000;         // a byte offset beyond every row
+constexpr int kFlow = 256;               // threads of a work-group: four waves, 64 columns of a tile
+constexpr int kBatch = 4;                // splits whose operands pass through LDS together
+constexpr int kLeft = kT * (kT + 1) / 2;
+
+struct FlowRow {  // of row i = i0 + r; offsets and shifts in bytes
+    int32_t sh, wab, Pu, fb;      // shift of split i + 1, of C_all; P[i + 1]; u_f + u_b
+    int32_t P, under, own, need;  // P[i]; offsets of cells (i + 1, j0) and (i, j0); the row's frontier
+};
+
+struct FlowLds {
+    union {
+        uint32_t buf[2][kBatch][2 * kT][64];  // operands of splits: left (i0 + r, q - 1), then right (q, j0 + cc) at its shift
+        uint32_t stage[2][64][64];            // [1]: left operands of the row block, right operands of the column block
+        struct {
+            uint32_t part[kT * kT][64];       // partial minima plus P[i] and their numbers
+            uint8_t pnum[kT * kT][64];
+        } p;
+    } u;
+    uint32_t row[2][kT][72];
+    __align__(16) uint8_t num[2][kT][64];
+    int4 item[64];                            // staged rows: byte offset, shift, rotation of the columns in LDS
+    int2 split[2][kFlow];                     // lists of splits: byte offset and shift of cell (i0, q - 1), of cell (q, j0)
+    double key[kFlow];                        // P[q] + (q + 1) / 256 + kKeyBase
+    FlowRow rows[kT];
+    int4 gate[kT][4];                         // of cells k and k + 4: m_all, m_null
+    int32_t Pj[kT];
+    int32_t ticket, fault, reach, n_edge, n_inner;
+};
+constexpr int kEdge = 16;                     // the edge list: entries 0 .. 15, the inner list behind it
+
+struct Flow {
+    const Ctx& c;
+    FlowLds& s;
+    rsrc_t tab, atab;
+    int32_t* prog;
+    int b, I, J, D, L, pitch, i0, j0, cend, m0, lane, wq;
+    uint32_t rowpitch;
+    size_t bl;
+};
+
+// Until the chunks chunk, chunk - 1, .. chunk - reach of both tiles are finished (first wave only).
+__device__ __forceinline__ bool wait_tiles(const Flow& x, int tile_a, int tile_b, int chunk, int reach) {
+    const int k = x.lane & 31, words = prog_words(x.pitch);
+    const int32_t* flags = x.prog + size_t(x.lane < 32 ? tile_a : tile_b) * words + chunk;
+    if (x.c.spin_limit < 0) return false;
+    for (int base = 0; base <= min(reach, chunk); base += 32) {
+        const int back = base + k;
+        const bool look = back <= reach && back <= chunk;
+        for (int spin = 0;; ++spin) {
+            const bool ok = !look || __hip_atomic_load(flags - back, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+            if (__all(ok)) break;
+            if (spin >= x.c.spin_limit ||
+                ((spin & 63) == 63 && __hip_atomic_load(x.c.ws.fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0))
+                return false;
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+    return true;
+}
+
+// Marks this work-group's columns of rows 1 .. 7 of tile (I, J): what the waits inside that tile look for.
+__device__ __forceinline__ void mark_tile(const Flow& x, int J) {
+    const int cend = min(kT, x.L - J * kT);
+    for (int s = x.wq; s < 14; s += 4) {  // four cells an instruction
+        const int e = s * 4 + (x.lane >> 4), r = 1 + (e >> 3), cc = e & 7;
+        const uint32_t at = (uint32_t(tri_row(x.L, x.i0 + r, J * kT + cc)) * uint32_t(x.pitch) + uint32_t(x.m0 + 4 * (x.lane & 15))) * 4u;
+        tst4<16>(x.tab, int(cc < cend ? at : kNoRead), u32x4{kMark, kMark, kMark, kMark});
+    }
+}
+
+// The rows of the tile, bottom-up.  DIAG: a tile of the first diagonal.
+template <bool DIAG>
+__device__ __forceinline__ void flow_rows(Flow& x, const uint32_t (&leftL)[kT], const uint32_t (&leftH)[kT],
+                                          const uint32_t (&colL)[kT], const uint32_t (&colH)[kT], uint32_t alL, uint32_t alH) {
+    constexpr int T = kT, RF = T - 1;
+    const Ctx& c = x.c;
+    FlowLds& s = x.s;
+    const int lane = x.lane, k4 = lane & 3, cb = x.wq * 16 + (lane >> 2), cend = x.cend, L = x.L;
+    const uint32_t rp = x.rowpitch;
+    const int m = x.m0 + cb, cb4 = 4 * cb, below4 = 4 * x.m0;
+    const int mine = (cb + 16 * k4) & 63;
+    // this lane's cells from (row, j0); a cell that does not exist reads nothing
+    const uint32_t ownL = uint32_t(k4) * rp, ownH = uint32_t(k4 + 4) * rp;
+    const int mL4 = k4 < cend ? 4 * m : kFar, mH4 = k4 + 4 < cend ? 4 * m : kFar;
+    // stores: two cells of 64 columns a wave, two columns a lane
+    const int scell = 2 * x.wq + (lane >> 5), scol = 2 * (lane & 31);
+    const uint32_t sown = uint32_t(scell) * rp + uint32_t(x.m0 + scol) * 4u;
+    const bool sgo = scell < cend;
+
+    uint32_t below[T + 1][2];
+#pragma unroll
+    for (int u = 0; u <= T; ++u) below[u][0] = below[u][1] = kHuge;
+    uint32_t pf[4] = {0, 0, 0, 0}, po[4] = {kNoRead, kNoRead, kNoRead, kNoRead};  // operands from lower bands, requested a row ahead, and where
+    auto fetch = [&]() {
+        pf[0] = tld_dev(x.tab, po[0], 0), pf[1] = tld_dev(x.tab, po[1], 0);
+        pf[2] = tld_dev(x.tab, po[2], 0), pf[3] = tld_dev(x.tab, po[3], 0);
+    };
+    FlowRow now = s.rows[RF];
+    unrolled<RF + 1>([&](auto step) {
+        constexpr int R = RF - decltype(step)::value, U = R + 1, CF = DIAG ? R : 0;
+        const FlowRow w = now;
+        if constexpr (R > 0) now = s.rows[R - 1];
+        if (DIAG && x.i0 + R >= L) return;  // ragged last block: uniform over the work-group
+        uint32_t bL = 0xffffffffu, bH = 0xffffffffu, nL = 0, nH = 0;
+        if constexpr (!DIAG) {
+            bL = s.u.p.part[R * T + k4][mine], bH = s.u.p.part[R * T + k4 + 4][mine];
+            nL = s.u.p.pnum[R * T + k4][mine], nH = s.u.p.pnum[R * T + k4 + 4][mine];
+        }
+        const int4 gate = s.gate[R][k4];
+        if constexpr (R < RF) {
+            const int t = max(cb4 - w.sh, 0), t2 = max(cb4 - w.wab, 0);
+            const char* row = reinterpret_cast<const char*>(&s.row[U & 1][k4][0]);
+            constexpr int hi = 4 * 72 * 4;
+            uint32_t rL = *reinterpret_cast<const uint32_t*>(row + t), rH = *reinterpret_cast<const uint32_t*>(row + t + hi);
+            alL = *reinterpret_cast<const uint32_t*>(row + t2), alH = *reinterpret_cast<const uint32_t*>(row + t2 + hi);
+            bool again = int(pf[0] | pf[1] | pf[2] | pf[3]) < 0;
+            if (c.spin_limit < 0) again = (po[0] & po[1] & po[2] & po[3]) != kNoRead;  // forced: every read from another band gives up
+            if (__any(again)) {  // some lane met a cell that its owner has not finished yet
+                for (int spin = 0; __any(again); ++spin) {
+                    if (spin >= c.spin_limit ||
+                        ((spin & 63) == 63 && __hip_atomic_load(c.ws.fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+                        if (lane == 0) __hip_atomic_store(c.ws.fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        break;
+                    }
+                    if (again) {
+                        fetch();
+                        again = int(pf[0] | pf[1] | pf[2] | pf[3]) < 0;
+                    }
+                }
+            }
+            const bool out = cb4 < w.sh, out2 = cb4 < w.wab;
+            rL = (out ? pf[0] : rL) + uint32_t(w.Pu), rH = (out ? pf[1] : rH) + uint32_t(w.Pu);
+            alL = out2 ? pf[2] : alL, alH = out2 ? pf[3] : alH;
+            if constexpr (DIAG) {
+                rL = k4 >= U && x.i0 + U < L ? rL : kHuge;
+                rH = k4 + 4 >= U && x.i0 + U < L ? rH : kHuge;
+            }
+            below[U][0] = rL, below[U][1] = rH;
+        }
+        if constexpr (R > 0) {  // the next row's operands from the bands below: mostly finished there already
+            auto far = [&](int m4, uint32_t own, int shift, bool exists) {  // columns below the band, not below zero
+                const uint32_t e = uint32_t(m4 - shift);
+                return exists && e < uint32_t(below4) ? own + uint32_t(now.under) + e : kNoRead;
+            };
+            const bool isL = !DIAG || k4 >= R, isH = !DIAG || k4 + 4 >= R;
+            po[0] = far(mL4, ownL, now.sh, isL), po[1] = far(mH4, ownH, now.sh, isH);
+            po[2] = far(mL4, ownL, now.wab, isL), po[3] = far(mH4, ownH, now.wab, isH);
+            fetch();
+        }
+        // splits of the row block, in falling order with <=: the smallest number among equal costs stays
+        if constexpr (!DIAG)
+            unrolled<T - 1>([&](auto up) {
+                constexpr int v = T - 2 - decltype(up)::value;  // left operand (i, i0 + v), split i0 + v + 1
+                if constexpr (v >= R) {
+                    const uint32_t l = v < 4 ? quad_lane<v & 3>(leftL[R]) : quad_lane<v & 3>(leftH[R]);
+                    const uint32_t a = l + below[v + 1][0], d = l + below[v + 1][1];
+                    const uint32_t q = uint32_t(x.i0 + v + 2);
+                    nL = a <= bL ? q : nL, bL = min(a, bL);
+                    nH = d <= bH ? q : nH, bH = min(d, bH);
+                }
+            });
+        // gates: a closed one is larger than any candidate
+        const uint32_t ckL = uint32_t((m - gate.y) >> 31), ckH = uint32_t((m - gate.w) >> 31);
+        uint32_t aL = alL, aH = alH;
+        if constexpr (DIAG) {  // a chain of one stage
+            if (k4 == R) aL = 0;
+            if (k4 + 4 == R) aH = 0;
+        }
+        aL = (uint32_t(w.fb) + aL) | uint32_t((m - gate.x) >> 31);
+        aH = (uint32_t(w.fb) + aH) | uint32_t((m - gate.z) >> 31);
+        const uint32_t p = uint32_t(w.P);
+        unrolled<T - 1>([&](auto c2c) {  // splits of the column block: left operand = the cell just finished
+            constexpr int c2 = decltype(c2c)::value;
+            if constexpr (c2 >= CF) {
+                const uint32_t v = c2 < 4 ? min(min(aL, max(bL - p, ckL)), kInf) : min(min(aH, max(bH - p, ckH)), kInf);
+                const uint32_t l = quad_lane<c2 & 3>(v);
+                const uint32_t q = uint32_t(x.j0 + c2 + 2);
+                if constexpr (c2 < 3) {
+                    const uint32_t a = l + (DIAG ? below[c2 + 1][0] : colL[c2]);
+                    nL = a < bL ? q : nL, bL = min(a, bL);
+                }
+                const uint32_t d = l + (DIAG ? below[c2 + 1][1] : colH[c2]);
+                nH = d < bH ? q : nH, bH = min(d, bH);
+            }
+        });
+        const uint32_t cL = max(bL - p, ckL), cH = max(bH - p, ckH);
+        const uint32_t vL = min(min(aL, cL), kInf), vH = min(min(aH, cH), kInf);
+        nL = aL <= cL ? uint32_t(x.i0 + R + 1) : nL, nH = aH <= cH ? uint32_t(x.i0 + R + 1) : nH;
+        nL = vL < kInf ? nL : 0u, nH = vH < kInf ? nH : 0u;
+        s.row[R & 1][k4][cb] = vL, s.row[R & 1][k4 + 4][cb] = vH;
+        s.num[R & 1][k4][cb] = uint8_t(nL), s.num[R & 1][k4 + 4][cb] = uint8_t(nH);
+        __syncthreads();
+        {   // without a branch: the next row's wait for its operands can then tell these stores from them
+            const u32x2 v = *reinterpret_cast<const u32x2*>(&s.row[R & 1][scell][scol]);
+            const uint16_t n = *reinterpret_cast<const uint16_t*>(&s.num[R & 1][scell][scol]);
+            const uint32_t at = sown + uint32_t(w.own);
+            const bool go = sgo && (!DIAG || scell >= CF);
+            __builtin_amdgcn_raw_buffer_store_b64(v, x.tab, int(go ? at : kNoRead), 0, 16);
+            __builtin_amdgcn_raw_buffer_store_b16(n, x.atab, int(go ? at >> 2 : kNoRead), 0, 0);
+        }
+    });
+}
+
+// Puts the splits q of 64 lanes that can be feasible in these columns into a list in LDS (one wave; the order does not matter).
+__device__ __forceinline__ void list_splits(const Flow& x, int q, bool valid, int first, int32_t* count) {
+    const Ctx& c = x.c;
+    FlowLds& s = x.s;
+    const int L = x.L;
+    const int32_t* need = c.ws.need + x.bl * L;
+    const int sh = c.ws.wsh[x.bl + q], P = c.ws.P[size_t(x.b) * (L + 1) + q];
+    int tl = 1 << 30, tr = 1 << 30;
+#pragma unroll
+    for (int r = 0; r < kT; ++r) {
+        tl = min(tl, need[(x.i0 + r) * L + q - 1]);
+        tr = min(tr, need[q * L + min(x.j0 + r, L - 1)]);
+    }
+    const bool on = valid && x.m0 + 63 >= max(tl, tr + sh);
+    const unsigned long long mask = __ballot(on);
+    int at = 0;
+    if (x.lane == 0) at = atomicAdd(count, __popcll(mask));
+    at = first + __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((1ull << x.lane) - 1ull));
+    if (on) {
+        s.split[0][at] = make_int2(int(uint32_t(row_base(L, x.i0) + q - 1) * x.rowpitch), 0);
+        s.split[1][at] = make_int2(int(uint32_t(row_base(L, q) + x.j0) * x.rowpitch), 4 * sh);
+        s.key[at] = double(P) + double(q + 1) * (1.0 / 256.0) + kKeyBase;
+    }
+}
+
+// Evaluates a list for the 4 x 4 cells of every wave.  The four waves fetch the 16 operand rows of a split, 16 bytes a
+// lane, two batches ahead, and pass them through LDS.  `between` runs behind the first requests.
+template <class F>
+__device__ __forceinline__ void flow_splits(Flow& x, int first, int n, double (&key)[4][4], int& half, bool low, F&& between) {
+    FlowLds& s = x.s;
+    const int L = x.L, lane = x.lane, wq = x.wq, h = 4 * (wq & 1), lr = lane >> 4, lc = 4 * (lane & 15);
+    // what this wave fetches: waves 0, 1 the left rows, waves 2, 3 the right ones
+    const bool right = wq >= 2;
+    const uint32_t step = uint32_t(right ? h + lr : row_base(L, x.i0 + h + lr) - row_base(L, x.i0)) * x.rowpitch;
+    const int col4 = right && h + lr >= x.cend ? -kFar : 4 * (x.m0 + lc);
+    u32x4 st[2][kBatch];
+    const int2* list = &s.split[right ? 1 : 0][first];
+    auto request = [&](u32x4 (&w)[kBatch], int k) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            const int2 e = list[k + u];
+            const int col = col4 - e.y;
+            const uint32_t at = step + uint32_t(e.x) + uint32_t(max(col, 0));
+            w[u] = tld4_dev(x.tab, at | (col > -16 ? 0u : kNoRead));
+        }
+    };
+    auto deposit = [&](const u32x4 (&w)[kBatch], int k) {
+        u32x4* to = reinterpret_cast<u32x4*>(&s.u.buf[half][0][wq * 4 + lr][lc]);
+        constexpr int next = 2 * kT * 64 / 4;
+        if (low && right) {  // uniform: a shift may end inside a lane's four columns
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                const int d = list[k + u].y - col4;
+                const u32x4 a = w[u];
+                to[u * next] = u32x4{d == 4 || d == 8 || d == 12 ? 0 : a.x, d == 4 ? a.x : d == 8 || d == 12 ? 0 : a.y,
+                                     d == 4 ? a.y : d == 8 ? a.x : d == 12 ? 0 : a.z, d == 4 ? a.z : d == 8 ? a.y : d == 12 ? a.x : a.w};
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) to[u * next] = w[u];
+        }
+    };
+    const int rq = (wq >> 1) * 4, cq = (wq & 1) * 4;
+    auto evaluate = [&](int k) {
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+            if (k + u >= n) break;
+            const double add = s.key[first + k + u];
+            double l[4], r[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                l[v] = double(s.u.buf[half][u][rq + v][lane]), r[v] = double(s.u.buf[half][u][kT + cq + v][lane]) + add;
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int d = 0; d < 4; ++d) key[a][d] = fmin(key[a][d], l[a] + r[d]);
+        }
+    };
+    if (n) request(st[0], 0), request(st[1], kBatch);
+    between();
+    for (int k = 0; k < n; k += 2 * kBatch) {
+        deposit(st[0], k);
+        __syncthreads();
+        if (k + 2 * kBatch < n) request(st[0], k + 2 * kBatch);
+        evaluate(k);
+        half ^= 1;
+        if (k + kBatch >= n) break;
+        deposit(st[1], k + kBatch);
+        __syncthreads();
+        if (k + 3 * kBatch < n) request(st[1], k + 3 * kBatch);
+        evaluate(k + kBatch);
+        half ^= 1;
+    }
+}
+
+// 130 registers; 46 KB of LDS, three work-groups a compute unit.  The frontier (ws.need) must not change while the kernel runs: what a
+// work-group does by it is decided by several waves.
+__global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
+    constexpr int T = kT;
+    __shared__ FlowLds s;
+    const int L = c.L, pitch = c.pitch, nblk = blocks_of(L), chunks = pitch / 64, lane = threadIdx.x & 63;
+    const int b = int(blockIdx.x) % B;
+    const int words = prog_words(pitch);
+    int32_t* prog = c.ws.prog + size_t(b) * tiles_of(L) * words;
+    if (threadIdx.x == 0) {
+        s.ticket = atomicAdd(prog + chunks, 1);  // the chain's counter stands with its first tile
+        s.fault = __hip_atomic_load(c.ws.fault, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s.reach = prog[(tiles_of(L) - 1) * words + chunks];
+        s.n_edge = s.n_inner = 0;
+    }
+    s.split[0][threadIdx.x] = s.split[1][threadIdx.x] = make_int2(0, kFar);  // reads nothing
+    __syncthreads();
+    // tiles in the order of D, then of the bands, then of I
+    int ticket = __builtin_amdgcn_readfirstlane(s.ticket);
+    const int D = __popcll(__ballot(lane < nblk && ticket >= chunks * (lane * nblk - lane * (lane - 1) / 2))) - 1;
+    ticket -= chunks * (D * nblk - D * (D - 1) / 2);
+    if (ticket >= chunks * (nblk - D)) return;  // cannot happen: one ticket per work-group
+    const int band = ticket / (nblk - D), I = ticket - band * (nblk - D), J = I + D;
+    const size_t chain = size_t(b) * c.rows * pitch;
+    const size_t bl = size_t(b) * L;
+    Flow x{c, s, table_rsrc(c.cost + chain, uint32_t(c.rows) * uint32_t(pitch) * 4u),
+           __builtin_amdgcn_make_buffer_rsrc(c.arg + chain, 0, int(uint32_t(c.rows) * uint32_t(pitch)), 0x00020000), prog,
+           b, I, J, D, L, pitch, I * T, J * T, min(T, L - J * T), band * 64, lane,
+           __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), uint32_t(pitch) * 4u, bl};
+    if (s.fault != 0) return;  // an earlier work-group gave up: drain
+    const uint32_t rp = x.rowpitch;
+    const int wq = x.wq, i0 = x.i0, j0 = x.j0, cend = x.cend, m0 = x.m0;
+    {   // parameters of the tile
+        const int t = threadIdx.x;
+        const int32_t* P = c.ws.P + size_t(b) * (L + 1);
+        if (t < 64) {
+            const int r = t >> 3, cc = t & 7;
+            const size_t at = (bl + min(i0 + r, L - 1)) * L + min(j0 + cc, L - 1);
+            reinterpret_cast<int2*>(&s.gate[r][cc & 3])[cc >> 2] = make_int2(c.ws.mall[at], c.ws.mnull[at]);
+            int need = cc >= (D == 0 ? r : 0) && cc < cend && i0 + r < L ? c.ws.need[at] : 1 << 30;
+#pragma unroll
+            for (int o = 4; o > 0; o >>= 1) need = min(need, __shfl_xor(need, o));
+            if (cc == 0) s.rows[r].need = need;
+        } else if (t < 128) {
+            const int e = t - 64;
+            if (D == 0) {
+            } else if (e < kLeft) {  // left operand (i0 + r, i0 + v)
+                const int r = (e >= 8) + (e >= 15) + (e >= 21) + (e >= 26) + (e >= 30) + (e >= 33) + (e >= 35), v = e - (r * T - r * (r - 1) / 2) + r;
+                s.item[e] = make_int4(int(uint32_t(tri_row(L, i0 + r, i0 + v)) * rp), 0, 16 * v & 63, 0);
+            } else {  // right operand (q, j0 + cc) of split q = j0 + c2 + 1
+                const int p = e - kLeft, c2 = (p >= 7) + (p >= 13) + (p >= 18) + (p >= 22) + (p >= 25) + (p >= 27);
+                const int cc = p - c2 * (2 * T - 1 - c2) / 2 + c2 + 1, q = min(j0 + c2 + 1, L - 1);
+                s.item[e] = make_int4(int(cc < cend ? uint32_t(row_base(L, q) + j0 + cc) * rp : kNoRead), c.ws.wsh[bl + q], 16 * cc & 63, 0);
+            }
+        } else if (t < 128 + T) {
+            const int r = t - 128, i = min(i0 + r, L - 1), u = min(i0 + r + 1, L - 1);
+            FlowRow& w = s.rows[r];
+            w.sh = 4 * c.ws.wsh[bl + u], w.wab = 4 * c.ws.wabs[bl + i];
+            w.Pu = P[u], w.fb = c.ws.fb[bl + i], w.P = P[i];
+            w.under = int(uint32_t(row_base(L, u) + j0) * rp), w.own = int(uint32_t(row_base(L, i) + j0) * rp);
+        } else if (t >= 192 && t < 192 + T) {
+            s.Pj[t - 192] = P[min(j0 + t - 192 + 1, L - 1)];
+        }
+    }
+    if (J + 1 < nblk) mark_tile(x, J + 1);
+    __syncthreads();
+    int tile_need = 1 << 30;
+#pragma unroll
+    for (int r = 0; r < T; ++r) tile_need = min(tile_need, s.rows[r].need);
+    const bool empty = m0 + 63 < tile_need;  // below the frontier of every cell
+    auto ready = [&](int back) {  // the neighbours back diagonals down
+        if (wq == 0 && !wait_tiles(x, tile_index(nblk, I, J - back), tile_index(nblk, I + back, J), band, (s.reach + 63) >> 6)) {
+            if (lane == 0) {
+                __hip_atomic_store(c.ws.fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s.fault = 1;
+            }
+        }
+        __syncthreads();
+        return s.fault == 0;
+    };
+    uint32_t leftL[T], leftH[T], colL[T], colH[T], alL = 0, alH = 0;
+#pragma unroll
+    for (int r = 0; r < T; ++r) leftL[r] = leftH[r] = colL[r] = colH[r] = 0;
+    int evaluated = 0;
+    if (empty) {
+        // the neighbours first: one of them marks these cells, and whoever sees this tile finished relies on both
+        if (D > 0 && !ready(1)) return;
+        for (int k = wq; k < 2 * T; k += 4) {
+            const int e = k * 4 + (lane >> 4), r = e >> 3, cc = e & 7;
+            const bool is = i0 + r < L && cc < cend && (D != 0 || cc >= r);
+            const uint32_t at = uint32_t(tri_row(L, i0 + r, j0 + cc)) * uint32_t(pitch) + uint32_t(m0 + 4 * (lane & 15));
+            tst4<16>(x.tab, int(is ? at * 4u : kNoRead), u32x4{kInf, kInf, kInf, kInf});
+            __builtin_amdgcn_raw_buffer_store_b32(0, x.atab, int(is ? at : kNoRead), 0, 0);
+        }
+    } else if (D > 0) {
+        double key[4][4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int cc = 0; cc < 4; ++cc) key[r][cc] = kKeyBase + 4294967295.0;
+        int half = 0;
+        const bool low = s.reach > m0;
+        // the splits whose operands the neighbours finish, and those whose operands are older; the first wave looks at the neighbours meanwhile
+        const int lo = i0 + 2 * T, ni = D > 2 ? 8 * (D - 3) + 1 : 0;
+        if (wq == 1) {
+            const int ne = D == 1 ? 1 : D == 2 ? 9 : 16, k = min(lane, ne - 1);
+            list_splits(x, D > 2 && k >= 8 ? j0 - T + k - 7 : i0 + T + k, lane < ne, 0, &s.n_edge);
+        } else if (wq > 1) {
+            for (int k = 64 * (wq - 2); k < ni; k += 128) list_splits(x, lo + min(k + lane, ni - 1), k + lane < ni, kEdge, &s.n_inner);
+        }
+        if (D > 2) {
+            if (!ready(2)) return;
+            const int n = __builtin_amdgcn_readfirstlane(s.n_inner);
+            flow_splits(x, kEdge, n, key, half, low, [] {});
+            evaluated = n;
+        }
+        if (!ready(1)) return;
+        // staged rows, 16 bytes a lane; row 7's operands of C_all
+        const int k4 = lane & 3, cb = wq * 16 + (lane >> 2), m = m0 + cb, mine = (cb + 16 * k4) & 63, lr = lane >> 4, lc = 4 * (lane & 15);
+        u32x4 st[4];
+        {
+            const FlowRow w = s.rows[T - 1];
+            const uint32_t o = uint32_t(k4) * rp + uint32_t(4 * m) - uint32_t(w.wab) + uint32_t(w.under);
+            alL = tld_dev(x.tab, 4 * m >= w.wab && k4 < cend ? o : kNoRead, 0);
+            alH = tld_dev(x.tab, 4 * m >= w.wab && k4 + 4 < cend ? o + 4 * rp : kNoRead, 0);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int4 it = s.item[(4 * wq + k) * 4 + lr];
+            const int col = m0 + lc - it.y;
+            st[k] = tld4_dev(x.tab, uint32_t(it.x) != kNoRead && col > -4 ? uint32_t(it.x) + 4u * uint32_t(max(col, 0)) : kNoRead);
+        }
+        half = 0;
+        const int n = __builtin_amdgcn_readfirstlane(s.n_edge);
+        evaluated += n;
+        flow_splits(x, 0, n, key, half, low, [&] {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int4 it = s.item[(4 * wq + k) * 4 + lr];
+                if (low) {  // a shift may end inside a lane's four columns
+                    const u32x4 v = st[k];
+                    const int d = it.y - m0 - lc;
+                    if (d == 1) st[k] = u32x4{0, v.x, v.y, v.z};
+                    if (d == 2) st[k] = u32x4{0, 0, v.x, v.y};
+                    if (d == 3) st[k] = u32x4{0, 0, 0, v.x};
+                }
+                *reinterpret_cast<u32x4*>(&s.u.stage[1][(4 * wq + k) * 4 + lr][(lc + it.z) & 63]) = st[k];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < T; ++r) {
+                const int at = r * T - r * (r - 1) / 2 - r;  // + column
+                if (r < 4) leftL[r] = s.u.stage[1][at + max(k4, r)][r == 0 ? mine : (cb + 16 * max(k4, r)) & 63];
+                leftH[r] = s.u.stage[1][at + max(k4 + 4, r)][r <= 4 ? mine : (cb + 16 * max(k4 + 4, r)) & 63];
+            }
+#pragma unroll
+            for (int c2 = 0; c2 < T - 1; ++c2) {
+                const int at = kLeft + c2 * (2 * T - 1 - c2) / 2 - c2 - 1;
+                if (c2 < 3) {
+                    const int cc = max(k4, c2 + 1);
+                    const uint32_t v = s.u.stage[1][at + cc][(cb + 16 * cc) & 63];
+                    colL[c2] = k4 > c2 ? v + uint32_t(s.Pj[c2]) : kHuge;
+                }
+                const int cc = max(k4 + 4, c2 + 1);
+                const uint32_t v = s.u.stage[1][at + cc][(cb + 16 * cc) & 63];
+                colH[c2] = k4 + 4 > c2 ? v + uint32_t(s.Pj[c2]) : kHuge;
+            }
+            __syncthreads();  // the staged rows have been read
+        });
+        __syncthreads();
+        const int rq = (wq >> 1) * 4, cq = (wq & 1) * 4;
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const unsigned long long bits = __builtin_bit_cast(unsigned long long, key[a][d]);
+                const int at = (lane + 16 * (cq + d)) & 63;
+                s.u.p.part[(rq + a) * T + cq + d][at] = uint32_t(bits >> 8);
+                s.u.p.pnum[(rq + a) * T + cq + d][at] = uint8_t(bits);
+            }
+        __syncthreads();
+        flow_rows<false>(x, leftL, leftH, colL, colH, alL, alH);
+    } else {
+        flow_rows<true>(x, leftL, leftH, colL, colH, 0, 0);
+    }
+    if (c.work && wq == 0) count_work<true>(c.work, 2, unsigned(empty ? 0 : 16 * evaluated + (D > 0 ? 64 : 0)), unsigned(T * cend));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_s_waitcnt(0);  // the stores are through
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(prog + size_t(tile_index(nblk, I, J)) * words + band, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 using RowFn = void (*)(Ctx, int);
 template <int T, int DC, int... Rs>
 constexpr std::array<RowFn, sizeof...(Rs)> row_table(std::integer_sequence<int, Rs...>) {
@@ -2152,6 +2716,8 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     groups = std::min(groups, B);
     if (nblk < 3) groups = 1;  // no diagonal to split
     const bool would_split = groups > 1;
+    // Small batches: every tile in one launch.  A schedule that the caller asks for is made of separate launches.
+    const bool flow = groups == 1 && fused_rows && !want_ks && ckpt_rules::flow_pays(nblk, pitch / 64, B);
     if (prof) groups = 1;  // the event trail times one stream
     Device* dev = nullptr;
     if (groups > 1) {
@@ -2200,7 +2766,8 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
                hip_ok(hipStreamWaitEvent(st, side->join[k], 0));
     };
     auto enqueue = [&]() -> int {
-        hipLaunchKernelGGL(precompute_kernel, dim3(B, (L + kPreRows - 1) / kPreRows), dim3(kPreThreads), 0, st, *chains, L, pitch, ws);
+        const int pre_parts = (L + kPreRows - 1) / kPreRows, mark_parts = flow ? nblk * ((pitch + kMarkCols - 1) / kMarkCols) : 0;
+        hipLaunchKernelGGL(precompute_kernel, dim3(B, pre_parts + mark_parts), dim3(kPreThreads), 0, st, *chains, L, pitch, ws, cost);
         CKPT_AFTER_LAUNCH(CKPT_K_PRECOMPUTE);
         if (side) {
             if (!hip_ok(hipEventRecord(side->fork, st)) || !hip_ok(hipStreamWaitEvent(gs[1], side->fork, 0)))
@@ -2212,6 +2779,12 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
             CKPT_AFTER_LAUNCH(CKPT_K_FRONTIER);
         }
 
+        if (flow) {
+            const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work, false};
+            hipLaunchKernelGGL(flow_kernel, dim3(unsigned(tiles_of(L) * (pitch / 64) * B)), dim3(kFlow), 0, st, ctx, B);
+            CKPT_AFTER_LAUNCH(CKPT_K_ROW);
+            return CKPT_OK;
+        }
         const int nbands = bands_of(pitch);
         for (int D = 0; D < 2 && D < nblk; ++D) {
             const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work, false};

@@ -49,4 +49,22 @@ constexpr int asked_split(int x, int number, int qlo, int nq) {
 //   117 MB: 4 x 192, 4096 slots 2229, 2218;  84 MB: 40 x 60, 1024 slots 515, 509;  54 MB: 8 x 96, 2048 slots 675, 668
 constexpr bool rows_pass(int tiles, int pitch, int B) { return 320LL * tiles * pitch * B >= 128LL * 1000 * 1000; }
 
+// Whether all tiles of a solve are one launch whose work-groups wait for each other's data (flow_kernel), or two launches a
+// diagonal.  One launch has no gaps between diagonals and a quarter of the instructions a row step, but a work-group
+// of four waves for every 64 columns of a tile, and it evaluates every feasible split: it pays while the chip is not full.
+// `wide` counts the work-groups of the first diagonal; `wide * nblk` grows with the splits that bounds would have dropped, which
+// they do better in tables of 1100 columns and more.  us a solve, two launches a diagonal and one:
+//   one block: 14 x 7 stages, 780 slots (182 by that measure) 20 and 16;  67 x 8, 184 slots (201) 15 and 14;  100 x 6, 810 slots (1300) 20 and 24
+//   two: 67 x 9, 524 slots (1206) 45 and 38;  126 x 16, 315 slots (1260) 44 and 44;  65 x 15, 829 slots (1690) 52 and 59
+//   three: 37 x 20, 1074 slots (1887) 93 and 76;  19 x 24, 2245 slots (2052) 97 and 100;  77 x 24, 791 slots (3003) 98 and 106
+//   more: 5 x 53, 777 slots (455) 233 and 112;  6 x 53, 1295 slots (882) 246 and 134;  33 x 63, 410 slots (1848) 369 and 210;  38 x 49, 794 slots
+//   (3458) 330 and 295;  112 x 29, 470 slots (3584) 147 and 155;  185 x 26, 390 slots (5180) 180 and 216
+//   wide tables, wide * nblk: 4 x 129, 1389 slots (25 k) 740 and 544;  1 x 192, 4096 slots (37 k) 1072 and 1128;  2 x 165, 3436 slots (48 k) 1160 and 1256
+//   narrow ones: 15 x 121, 665 slots (42 k) 888 and 778;  25 x 162, 317 slots (55 k) 1611 and 1290;  30 x 122, 463 slots (61 k) 1203 and 1208
+constexpr bool flow_pays(int nblk, int chunks, long long B) {
+    const long long wide = B * chunks * nblk;
+    if (nblk < 4) return wide <= (nblk == 1 ? 224 : nblk == 2 ? 1200 : 2000);
+    return wide <= 3500 && wide * nblk <= (chunks >= 18 ? 33000 : 60000);
+}
+
 }  // namespace ckpt_rules
