@@ -1578,13 +1578,15 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
 // four waves a SIMD the vector ones take 4.4 in all).  So a work-group owns one tile and 64 columns, and four lanes share a column.
 //   - Splits between the blocks: the four waves fetch the 16 operand rows of a split together, 16 bytes a lane and two batches of
 //     four splits ahead, and pass them through LDS; each evaluates 4 x 4 cells, lane = column, as float64 keys (see
-//     gemm_kernel).  All feasible splits are evaluated: about 500 clocks each.  The partial minima stay in LDS.
+//     gemm_kernel), about 500 clocks a split.  The partial minima stay in LDS.  BOUNDS: splits are dropped as in gemm_kernel, each
+//     wave for four rows; the upper bounds of the splits whose operands the neighbours finish come from the minima found
+//     so far.  Else all feasible ones are evaluated.
 //   - Rows, bottom-up: a wave holds 16 columns, lane k of the four of a column cells k and k + 4 of the row.  A finished cell
 //     reaches the other lanes of its column as the operand of an addition (quad broadcast).  A row is about 190 instructions, 1250 clocks,
 //     where tile_rows_kernel takes 900, 5500 to 6500 clocks.
 // No launch boundary separates the diagonals.
-//   - A chain's work-groups take its tiles by ticket, in the order of D, band, I, so whatever one of them waits for belongs
-//     to a work-group that already runs.  Every wait is bounded, see tile_rows_kernel.
+//   - A chain's work-groups take its tiles by ticket, in an order in which a tile stands behind all that it waits for (see
+//     flow_place), so that belongs to work-groups that already run.  Every wait is bounded, see tile_rows_kernel.
 //   - Rows of the same tile at columns below the band: every cell is marked by bit 31 until its row is finished, and a lane that
 //     finds the mark reads again.  These reads are requested a row ahead, and mostly find the band below finished.
 //     A tile's cells are marked by the work-group of the tile to its left, those of the first diagonal by precompute_kernel.
@@ -1593,9 +1595,11 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
 //     reads is finished.  The splits whose operands lie two diagonals down and more do not wait for the last one.
 // Everything read is read with device scope: lines may lie in this die's L2 with the marks in them.
 // Results bit for bit those of the other kernels.  us a solve, two launches a diagonal and this: 1 x 24 stages, 512 slots 71 and 40;
-// 5 x 53, 777 slots 233 and 112; 16 x 48, 1024 slots 211 and 158; 10 x 50, 500 slots 219 and 102 (the rule: ckpt_rules::flow_pays).
+// 5 x 53, 777 slots 233 and 113; 16 x 48, 1024 slots 211 and 141; 10 x 50, 500 slots 219 and 103; 1 x 192, 4096 slots 1141 and 666; 3 x 254,
+// 1500 slots 2156 and 1438 (the rule: ckpt_rules::flow_pays).
 // What bounds it: of 26000 clocks a diagonal (5 x 53 stages) rows take 10500, the 16 splits of the last neighbours 7800,
-// their operands and those of the rows 3700, the stores and the flag 2000.
+// their operands and those of the rows 3700, the stores and the flag 2000.  Long chains are bound by vector issue and by the slots for
+// work-groups (1 x 192 stages: a work-group takes 60000 clocks, 12000 of them rows, most of the rest round trips): four a compute unit.
 //
 // Inside, a candidate of row i stands plus P[i]: a right operand carries the prefix sum of its split, and a split costs one addition.
 // ---------------------------------------------------------------------------
@@ -1629,10 +1633,12 @@ struct FlowRow {  // of row i = i0 + r; offsets and shifts in bytes
     int32_t P, under, own, need;  // P[i]; offsets of cells (i + 1, j0) and (i, j0); the row's frontier
 };
 
+template <bool BOUNDS>
 struct FlowLds {
+    static constexpr int NBUF = BOUNDS ? 1 : 2;
     union {
-        uint32_t buf[2][kBatch][2 * kT][64];  // operands of splits: left (i0 + r, q - 1), then right (q, j0 + cc) at its shift
-        uint32_t stage[2][64][64];            // [1]: left operands of the row block, right operands of the column block
+        uint32_t buf[NBUF][kBatch][2 * kT][64];  // operands of splits: left (i0 + r, q - 1), then right (q, j0 + cc) at its shift
+        uint32_t stage[NBUF][64][64];            // the last: left operands of the row block, right operands of the column block
         struct {
             uint32_t part[kT * kT][64];       // partial minima plus P[i] and their numbers
             uint8_t pnum[kT * kT][64];
@@ -1648,11 +1654,20 @@ struct FlowLds {
     int32_t Pj[kT];
     int32_t ticket, fault, reach, n_edge, n_inner;
 };
+struct FlowBounds {                           // bounds of the splits, see gemm_kernel
+    int2 qp[kFlow];                           // of the lists: q, P[q]
+    uint32_t ub[2][4][4 * kT];                // upper bound of every cell in every sub-chunk, rows 0 .. 3 and 4 .. 7
+    uint8_t keep[2][kFlow];                   // which half of the rows needs an entry
+    uint16_t index[kFlow];                    // the entries that are left, bits 8 and 9: for which half
+    int32_t left;
+};
 constexpr int kEdge = 16;                     // the edge list: entries 0 .. 15, the inner list behind it
 
+template <bool BOUNDS>
 struct Flow {
     const Ctx& c;
-    FlowLds& s;
+    FlowLds<BOUNDS>& s;
+    FlowBounds* bounds;
     rsrc_t tab, atab;
     int32_t* prog;
     int b, I, J, D, L, pitch, i0, j0, cend, m0, lane, wq;
@@ -1660,8 +1675,41 @@ struct Flow {
     size_t bl;
 };
 
+// The tile and band of a ticket.  Tiles are taken in the order of kSkew D + band, then of D, then of I: a band behind the one
+// below it, a diagonal kSkew bands behind the last.  In the order of D alone neighbouring bands of a tile start together and
+// wait for each other through all rows, 31000 clocks a tile instead of 12000, each holding its place on the chip; in the order of the
+// bands alone diagonals do.  us a solve with 1, 3, 5, 8, 12, 24 and by D alone: 1 x 192 stages, 4096 slots 938, 747, 727, 738, 755, 805, 905;
+// 3 x 254, 1500 slots 1562, 1583, 1620, 1662, 1703, 1818, 1818; 5 x 53, 777 slots 129, 118, 115, 113, 114, 114, 114.
+constexpr int kSkew = 6;
+struct FlowPlace { int D, band, I; };
+__device__ __forceinline__ FlowPlace flow_place(int ticket, int nblk, int chunks, int lane) {
+    // places before key k: of diagonals D < full all bands, of those up to `part` the bands below k - kSkew D
+    auto before = [&](int k) {
+        const int full = min(nblk, max(0, k - chunks + kSkew) / kSkew), part = min(nblk, (k + kSkew - 1) / kSkew);
+        auto s1 = [](int n) { return n * (n - 1) / 2; };                // sums of D and D^2 below n
+        auto s2 = [](int n) { return (n - 1) * n * (2 * n - 1) / 6; };
+        return chunks * (full * nblk - s1(full)) + (part - full) * nblk * k - (k + kSkew * nblk) * (s1(part) - s1(full)) + kSkew * (s2(part) - s2(full));
+    };
+    int key = 0;
+    for (int step = 64 * 64; step >= 1; step /= 64) key += step * (__popcll(__ballot(before(key + step * lane) <= ticket)) - 1);
+    const int D0 = max(0, key - chunks + kSkew) / kSkew;  // first diagonal with this key
+    ticket -= before(key);
+    // of diagonal D0 + lane
+    const int D = D0 + lane, here = D < nblk && D * kSkew <= key ? nblk - D : 0;
+    int sum = here;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+        const int v = __shfl_up(sum, o);
+        if (lane >= o) sum += v;
+    }
+    const int n = __popcll(__ballot(lane < 32 && sum <= ticket));
+    const int I = ticket - (n ? __builtin_amdgcn_readlane(sum, n - 1) : 0);
+    return {n < 32 ? D0 + n : nblk, key - kSkew * (D0 + n), I};
+}
+
 // Until the chunks chunk, chunk - 1, .. chunk - reach of both tiles are finished (first wave only).
-__device__ __forceinline__ bool wait_tiles(const Flow& x, int tile_a, int tile_b, int chunk, int reach) {
+template <bool BOUNDS>
+__device__ __forceinline__ bool wait_tiles(const Flow<BOUNDS>& x, int tile_a, int tile_b, int chunk, int reach) {
     const int k = x.lane & 31, words = prog_words(x.pitch);
     const int32_t* flags = x.prog + size_t(x.lane < 32 ? tile_a : tile_b) * words + chunk;
     if (x.c.spin_limit < 0) return false;
@@ -1681,7 +1729,8 @@ __device__ __forceinline__ bool wait_tiles(const Flow& x, int tile_a, int tile_b
 }
 
 // Marks this work-group's columns of rows 1 .. 7 of tile (I, J): what the waits inside that tile look for.
-__device__ __forceinline__ void mark_tile(const Flow& x, int J) {
+template <bool BOUNDS>
+__device__ __forceinline__ void mark_tile(const Flow<BOUNDS>& x, int J) {
     const int cend = min(kT, x.L - J * kT);
     for (int s = x.wq; s < 14; s += 4) {  // four cells an instruction
         const int e = s * 4 + (x.lane >> 4), r = 1 + (e >> 3), cc = e & 7;
@@ -1691,12 +1740,12 @@ __device__ __forceinline__ void mark_tile(const Flow& x, int J) {
 }
 
 // The rows of the tile, bottom-up.  DIAG: a tile of the first diagonal.
-template <bool DIAG>
-__device__ __forceinline__ void flow_rows(Flow& x, const uint32_t (&leftL)[kT], const uint32_t (&leftH)[kT],
+template <bool DIAG, bool BOUNDS>
+__device__ __forceinline__ void flow_rows(Flow<BOUNDS>& x, const uint32_t (&leftL)[kT], const uint32_t (&leftH)[kT],
                                           const uint32_t (&colL)[kT], const uint32_t (&colH)[kT], uint32_t alL, uint32_t alH) {
     constexpr int T = kT, RF = T - 1;
     const Ctx& c = x.c;
-    FlowLds& s = x.s;
+    auto& s = x.s;
     const int lane = x.lane, k4 = lane & 3, cb = x.wq * 16 + (lane >> 2), cend = x.cend, L = x.L;
     const uint32_t rp = x.rowpitch;
     const int m = x.m0 + cb, cb4 = 4 * cb, below4 = 4 * x.m0;
@@ -1708,6 +1757,10 @@ __device__ __forceinline__ void flow_rows(Flow& x, const uint32_t (&leftL)[kT], 
     const int scell = 2 * x.wq + (lane >> 5), scol = 2 * (lane & 31);
     const uint32_t sown = uint32_t(scell) * rp + uint32_t(x.m0 + scol) * 4u;
     const bool sgo = scell < cend;
+    // samples: the last column of a wave is the last of a sub-chunk
+    const uint32_t line = uint32_t(x.pitch / kG) * uint32_t(4 * T);
+    const rsrc_t smp = table_rsrc(c.ws.samp + (BOUNDS ? size_t(x.b) * samp_ints(L, x.pitch) : 0), BOUNDS ? uint32_t(samp_rows(L)) * line : 0);
+    const uint32_t sat = (lane >> 2) == 15 ? uint32_t(4 * x.J * (x.J + 1) + x.i0) * line + uint32_t(m / kG) * uint32_t(4 * T) + 4u * uint32_t(k4) : kNoRead;
 
     uint32_t below[T + 1][2];
 #pragma unroll
@@ -1811,6 +1864,10 @@ __device__ __forceinline__ void flow_rows(Flow& x, const uint32_t (&leftL)[kT], 
         nL = vL < kInf ? nL : 0u, nH = vH < kInf ? nH : 0u;
         s.row[R & 1][k4][cb] = vL, s.row[R & 1][k4 + 4][cb] = vH;
         s.num[R & 1][k4][cb] = uint8_t(nL), s.num[R & 1][k4 + 4][cb] = uint8_t(nH);
+        if constexpr (BOUNDS) {
+            __builtin_amdgcn_raw_buffer_store_b32(int(vL), smp, int(sat), int(R * line), 16);
+            __builtin_amdgcn_raw_buffer_store_b32(int(vH), smp, int(sat), int(R * line + 16), 16);
+        }
         __syncthreads();
         {   // without a branch: the next row's wait for its operands can then tell these stores from them
             const u32x2 v = *reinterpret_cast<const u32x2*>(&s.row[R & 1][scell][scol]);
@@ -1824,9 +1881,9 @@ __device__ __forceinline__ void flow_rows(Flow& x, const uint32_t (&leftL)[kT], 
 }
 
 // Puts the splits q of 64 lanes that can be feasible in these columns into a list in LDS (one wave; the order does not matter).
-__device__ __forceinline__ void list_splits(const Flow& x, int q, bool valid, int first, int32_t* count) {
+__device__ __forceinline__ void list_splits(const Flow<false>& x, int q, bool valid, int first, int32_t* count) {
     const Ctx& c = x.c;
-    FlowLds& s = x.s;
+    auto& s = x.s;
     const int L = x.L;
     const int32_t* need = c.ws.need + x.bl * L;
     const int sh = c.ws.wsh[x.bl + q], P = c.ws.P[size_t(x.b) * (L + 1) + q];
@@ -1848,22 +1905,130 @@ __device__ __forceinline__ void list_splits(const Flow& x, int q, bool valid, in
     }
 }
 
+// Bounds of sixteen splits at the four sub-chunks of the band, for four rows: lane = (sub-chunk, split).
+struct FlowBound { uint32_t l[kT / 2], r[kT]; };
+__device__ __forceinline__ void fetch_bound(const Flow<true>& x, rsrc_t smp, FlowBound& v, int q, int half, int kl, int kr) {
+    const uint32_t line = uint32_t(x.pitch / kG) * uint32_t(4 * kT);
+    const int jq = (q - 1) >> 3;
+    const uint32_t lo = kl >= 0 ? uint32_t(4 * jq * (jq + 1) + x.i0 + 4 * half) * line + uint32_t(kl) * uint32_t(4 * kT) + uint32_t((q - 1) & 7) * 4u : kNoRead;
+    const uint32_t ro = kr >= 0 ? uint32_t(4 * x.J * (x.J + 1) + q) * line + uint32_t(kr) * uint32_t(4 * kT) : kNoRead;
+#pragma unroll
+    for (int r = 0; r < kT / 2; ++r) v.l[r] = tld_dev(smp, lo, uint32_t(r) * line);
+    const u32x4 a = __builtin_amdgcn_raw_buffer_load_b128(smp, int(ro), 0, 16), d = __builtin_amdgcn_raw_buffer_load_b128(smp, int(ro), 16, 16);
+#pragma unroll
+    for (int cc = 0; cc < 4; ++cc) v.r[cc] = a[cc], v.r[cc + 4] = d[cc];
+}
+__device__ __forceinline__ void settle_bound(const Flow<true>& x, FlowBound& v, uint32_t Pq, int kl, int kr) {
+#pragma unroll
+    for (int r = 0; r < kT / 2; ++r) v.l[r] = kl < 0 ? kInf : v.l[r];
+#pragma unroll
+    for (int cc = 0; cc < kT; ++cc) v.r[cc] = (kr < 0 || cc >= x.cend ? kInf : v.r[cc]) + Pq;
+}
+
+// Upper bounds of the cells from 32 splits spread over a list of n (first .. first + n - 1), 16 a wave.
+__device__ __forceinline__ void upper_bounds(Flow<true>& x, rsrc_t smp, int first, int n) {
+    constexpr int R = kT / 2, T = kT;
+    const int half = x.wq & 1, slice = x.wq >> 1, sub = x.lane >> 4, v = x.lane & 15, kk = x.m0 / kG + sub;
+    const int e = first + (2 * (16 * slice + v) + 1) * n / 64;
+    const int2 qp = x.bounds->qp[e];
+    const int sh = x.s.split[1][e].y >> 2, kr = ((kk * kG + 1 - sh) >> 4) - 1;
+    FlowBound w;
+    fetch_bound(x, smp, w, qp.x, half, kk - 1, kr);
+    settle_bound(x, w, uint32_t(qp.y), kk - 1, kr);
+    // minimum over the 16 lanes of a sub-chunk, as in gemm_kernel
+    uint32_t h[R * T / 2];
+#pragma unroll
+    for (int t = 0; t < R * T / 2; ++t) {
+        const uint32_t e0 = w.l[(2 * t) >> 3] + w.r[(2 * t) & 7], e1 = w.l[(2 * t + 1) >> 3] + w.r[(2 * t + 1) & 7];
+        const uint32_t mine = (v & 1) ? e1 : e0, other = (v & 1) ? e0 : e1;
+        h[t] = min(mine, uint32_t(__builtin_amdgcn_update_dpp(0, int(other), 0xB1, 0xf, 0xf, true)));
+    }
+#pragma unroll
+    for (int t = 0; t < R * T / 4; ++t) {
+        const uint32_t mine = (v & 2) ? h[2 * t + 1] : h[2 * t], other = (v & 2) ? h[2 * t] : h[2 * t + 1];
+        uint32_t f = min(mine, uint32_t(__builtin_amdgcn_update_dpp(0, int(other), 0x4E, 0xf, 0xf, true)));
+        f = min(f, uint32_t(__builtin_amdgcn_update_dpp(0, int(f), 0x124, 0xf, 0xf, true)));
+        f = min(f, uint32_t(__builtin_amdgcn_update_dpp(0, int(f), 0x128, 0xf, 0xf, true)));
+        if (v < 4) atomicMin(&x.bounds->ub[half][sub][4 * t + (v & 3)], f);
+    }
+}
+
+// Splits 16 p + slice .. of a list that can attain a minimum of four rows: their lower bound is at most the upper bound of some cell in
+// some sub-chunk.  Every entry's answer is written, by the wave of its half.
+// `between` runs behind the first request and ends in a barrier.
+template <int SLICES, class F>
+__device__ __forceinline__ void lower_bounds(Flow<true>& x, rsrc_t smp, int first, int n, F&& between) {
+    constexpr int T = kT, R = T / 2;
+    const int half = x.wq & 1, slice = x.wq >> 1, sub = x.lane >> 4, v = x.lane & 15, kk = x.m0 / kG + sub;
+    FlowBound next;
+    int2 qp;
+    int kr = 0;
+    auto request = [&](int k) {
+        const int e = first + min(k + v, n - 1);
+        qp = x.bounds->qp[e];
+        kr = (kk * kG + kG - 1 - (x.s.split[1][e].y >> 2)) >> 4;
+        fetch_bound(x, smp, next, qp.x, half, kk, kr);
+    };
+    if (slice < SLICES) request(16 * slice);
+    between();
+    if (slice >= SLICES) return;
+    uint32_t ub[R][T];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int cc = 0; cc < T; ++cc) ub[r][cc] = x.bounds->ub[half][sub][r * T + cc];
+    for (int k = 16 * slice; k < n; k += 16 * SLICES) {
+        FlowBound w = next;
+        const uint32_t Pq = uint32_t(qp.y);
+        const int kc = kr;
+        if (k + 16 * SLICES < n) request(k + 16 * SLICES);
+        settle_bound(x, w, Pq, kk, kc);
+        // a left operand not above ub - right for some column; nothing above zero is lost where the difference would be negative
+        bool on = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            uint32_t most = 0;
+#pragma unroll
+            for (int cc = 0; cc < T; ++cc) most = max(most, __builtin_elementwise_sub_sat(ub[r][cc], w.r[cc]));
+            on = on || w.l[r] <= most;
+        }
+        unsigned long long mask = __ballot(on);
+        mask |= mask >> 32;
+        mask |= mask >> 16;
+        if (x.lane < 16 && k + v < n) x.bounds->keep[half][first + k + v] = uint8_t(uint32_t(mask) >> v & 1u);
+    }
+}
+
+// The entries of a list that some half of the rows needs, into bounds->index.  Every wave, behind a barrier; ends in one.
+__device__ __forceinline__ int left_over(Flow<true>& x, int first, int n, bool all) {
+    const int t = threadIdx.x;
+    const uint32_t f = t >= n ? 0u : all ? 3u : uint32_t(x.bounds->keep[0][first + t]) | uint32_t(x.bounds->keep[1][first + t]) << 1;
+    const unsigned long long mask = __ballot(f != 0);
+    int at = 0;
+    if (x.lane == 0 && mask) at = atomicAdd(&x.bounds->left, __popcll(mask));
+    at = __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((1ull << x.lane) - 1ull));
+    if (f) x.bounds->index[at] = uint16_t(first + t + (f << 8));
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(x.bounds->left);
+}
+
 // Evaluates a list for the 4 x 4 cells of every wave.  The four waves fetch the 16 operand rows of a split, 16 bytes a
 // lane, two batches ahead, and pass them through LDS.  `between` runs behind the first requests.
-template <class F>
-__device__ __forceinline__ void flow_splits(Flow& x, int first, int n, double (&key)[4][4], int& half, bool low, F&& between) {
-    FlowLds& s = x.s;
+template <bool BOUNDS, class F>
+__device__ __forceinline__ void flow_splits(Flow<BOUNDS>& x, int first, int n, double (&key)[4][4], int& half, bool low, F&& between) {
+    auto& s = x.s;
     const int L = x.L, lane = x.lane, wq = x.wq, h = 4 * (wq & 1), lr = lane >> 4, lc = 4 * (lane & 15);
     // what this wave fetches: waves 0, 1 the left rows, waves 2, 3 the right ones
     const bool right = wq >= 2;
     const uint32_t step = uint32_t(right ? h + lr : row_base(L, x.i0 + h + lr) - row_base(L, x.i0)) * x.rowpitch;
     const int col4 = right && h + lr >= x.cend ? -kFar : 4 * (x.m0 + lc);
     u32x4 st[2][kBatch];
-    const int2* list = &s.split[right ? 1 : 0][first];
+    const int2* list = &s.split[right ? 1 : 0][BOUNDS ? 0 : first];
+    auto entry = [&](int k) { return BOUNDS ? int(x.bounds->index[k] & 255u) : k; };
     auto request = [&](u32x4 (&w)[kBatch], int k) {
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const int2 e = list[k + u];
+            const int2 e = list[entry(k + u)];
             const int col = col4 - e.y;
             const uint32_t at = step + uint32_t(e.x) + uint32_t(max(col, 0));
             w[u] = tld4_dev(x.tab, at | (col > -16 ? 0u : kNoRead));
@@ -1875,10 +2040,11 @@ __device__ __forceinline__ void flow_splits(Flow& x, int first, int n, double (&
         if (low && right) {  // uniform: a shift may end inside a lane's four columns
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) {
-                const int d = list[k + u].y - col4;
+                const int d = list[entry(k + u)].y - col4;
                 const u32x4 a = w[u];
-                to[u * next] = u32x4{d == 4 || d == 8 || d == 12 ? 0 : a.x, d == 4 ? a.x : d == 8 || d == 12 ? 0 : a.y,
-                                     d == 4 ? a.y : d == 8 ? a.x : d == 12 ? 0 : a.z, d == 4 ? a.z : d == 8 ? a.y : d == 12 ? a.x : a.w};
+                // columns below zero are infeasible: minima of the first columns of sub-chunks bound others
+                to[u * next] = u32x4{d > 0 ? kInf : a.x, d > 4 ? kInf : d == 4 ? a.x : a.y,
+                                     d > 8 ? kInf : d == 8 ? a.x : d == 4 ? a.y : a.z, d > 12 ? kInf : d == 12 ? a.x : d == 8 ? a.y : d == 4 ? a.z : a.w};
             }
         } else {
 #pragma unroll
@@ -1890,7 +2056,8 @@ __device__ __forceinline__ void flow_splits(Flow& x, int first, int n, double (&
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
             if (k + u >= n) break;
-            const double add = s.key[first + k + u];
+            if (BOUNDS && !(__builtin_amdgcn_readfirstlane(int(x.bounds->index[k + u])) >> 8 & (rq ? 2 : 1))) continue;
+            const double add = s.key[BOUNDS ? entry(k + u) : first + k + u];
             double l[4], r[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v)
@@ -1903,26 +2070,33 @@ __device__ __forceinline__ void flow_splits(Flow& x, int first, int n, double (&
     };
     if (n) request(st[0], 0), request(st[1], kBatch);
     between();
+    auto turn = [&] {  // one buffer: until it has been read; two: the other one has
+        if constexpr (BOUNDS) __syncthreads();
+        else half ^= 1;
+    };
     for (int k = 0; k < n; k += 2 * kBatch) {
         deposit(st[0], k);
         __syncthreads();
         if (k + 2 * kBatch < n) request(st[0], k + 2 * kBatch);
         evaluate(k);
-        half ^= 1;
+        turn();
         if (k + kBatch >= n) break;
         deposit(st[1], k + kBatch);
         __syncthreads();
         if (k + 3 * kBatch < n) request(st[1], k + 3 * kBatch);
         evaluate(k + kBatch);
-        half ^= 1;
+        turn();
     }
 }
 
-// 130 registers; 46 KB of LDS, three work-groups a compute unit.  The frontier (ws.need) must not change while the kernel runs: what a
+// Without bounds 131 registers and 46 KB of LDS, three work-groups a compute unit; with them 128 and 38 KB, four (one buffer for operands instead of two;
+// with three 1 x 192 stages, 4096 slots took 727 us instead of 666).  The frontier (ws.need) must not change while the kernel runs: what a
 // work-group does by it is decided by several waves.
-__global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
-    constexpr int T = kT;
-    __shared__ FlowLds s;
+template <bool BOUNDS>
+__global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int B) {
+    constexpr int T = kT, NBUF = FlowLds<BOUNDS>::NBUF;
+    __shared__ FlowLds<BOUNDS> s;
+    __shared__ std::conditional_t<BOUNDS, FlowBounds, int> sb;
     const int L = c.L, pitch = c.pitch, nblk = blocks_of(L), chunks = pitch / 64, lane = threadIdx.x & 63;
     const int b = int(blockIdx.x) % B;
     const int words = prog_words(pitch);
@@ -1933,17 +2107,16 @@ __global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
         s.reach = prog[(tiles_of(L) - 1) * words + chunks];
         s.n_edge = s.n_inner = 0;
     }
-    s.split[0][threadIdx.x] = s.split[1][threadIdx.x] = make_int2(0, kFar);  // reads nothing
+    if constexpr (!BOUNDS) s.split[0][threadIdx.x] = s.split[1][threadIdx.x] = make_int2(0, kFar);  // reads nothing
     __syncthreads();
-    // tiles in the order of D, then of the bands, then of I
-    int ticket = __builtin_amdgcn_readfirstlane(s.ticket);
-    const int D = __popcll(__ballot(lane < nblk && ticket >= chunks * (lane * nblk - lane * (lane - 1) / 2))) - 1;
-    ticket -= chunks * (D * nblk - D * (D - 1) / 2);
-    if (ticket >= chunks * (nblk - D)) return;  // cannot happen: one ticket per work-group
-    const int band = ticket / (nblk - D), I = ticket - band * (nblk - D), J = I + D;
+    const FlowPlace at = flow_place(__builtin_amdgcn_readfirstlane(s.ticket), nblk, chunks, lane);
+    if (at.D >= nblk) return;  // cannot happen: one ticket per work-group
+    const int D = at.D, band = at.band, I = at.I, J = I + D;
     const size_t chain = size_t(b) * c.rows * pitch;
     const size_t bl = size_t(b) * L;
-    Flow x{c, s, table_rsrc(c.cost + chain, uint32_t(c.rows) * uint32_t(pitch) * 4u),
+    FlowBounds* bounds = nullptr;
+    if constexpr (BOUNDS) bounds = &sb;
+    Flow<BOUNDS> x{c, s, bounds, table_rsrc(c.cost + chain, uint32_t(c.rows) * uint32_t(pitch) * 4u),
            __builtin_amdgcn_make_buffer_rsrc(c.arg + chain, 0, int(uint32_t(c.rows) * uint32_t(pitch)), 0x00020000), prog,
            b, I, J, D, L, pitch, I * T, J * T, min(T, L - J * T), band * 64, lane,
            __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)), uint32_t(pitch) * 4u, bl};
@@ -1982,6 +2155,21 @@ __global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
             s.Pj[t - 192] = P[min(j0 + t - 192 + 1, L - 1)];
         }
     }
+    // the splits whose operands the neighbours finish, and those whose operands are older
+    const int ne = D == 0 ? 0 : D == 1 ? 1 : D == 2 ? 9 : 16, ni = D > 2 ? 8 * (D - 3) + 1 : 0, inner = i0 + 2 * T;
+    if constexpr (BOUNDS) {  // an entry a thread
+        const int k = threadIdx.x;
+        if (k < kEdge ? k < ne : k - kEdge < ni) {
+            const int q = k >= kEdge ? inner + k - kEdge : D > 2 && k >= 8 ? j0 - T + k - 7 : i0 + T + k;
+            const int sh = c.ws.wsh[bl + q], Pq = c.ws.P[size_t(b) * (L + 1) + q];
+            s.split[0][k] = make_int2(int(uint32_t(row_base(L, i0) + q - 1) * rp), 0);
+            s.split[1][k] = make_int2(int(uint32_t(row_base(L, q) + j0) * rp), 4 * sh);
+            s.key[k] = double(Pq) + double(q + 1) * (1.0 / 256.0) + kKeyBase;
+            sb.qp[k] = make_int2(q, Pq);
+        } else {
+            s.split[0][k] = s.split[1][k] = make_int2(0, kFar);  // reads nothing
+        }
+    }
     if (J + 1 < nblk) mark_tile(x, J + 1);
     __syncthreads();
     int tile_need = 1 << 30;
@@ -2012,6 +2200,13 @@ __global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
             tst4<16>(x.tab, int(is ? at * 4u : kNoRead), u32x4{kInf, kInf, kInf, kInf});
             __builtin_amdgcn_raw_buffer_store_b32(0, x.atab, int(is ? at : kNoRead), 0, 0);
         }
+        if (BOUNDS) {
+            const int r = int(threadIdx.x) >> 5, kk = (threadIdx.x >> 3) & 3;
+            const uint32_t line = uint32_t(pitch / kG) * uint32_t(4 * T);
+            const rsrc_t smp = table_rsrc(c.ws.samp + size_t(b) * samp_ints(L, pitch), uint32_t(samp_rows(L)) * line);
+            const uint32_t at = uint32_t(4 * J * (J + 1) + i0 + r) * line + (uint32_t(m0 / kG + kk) * T + (threadIdx.x & 7)) * 4u;
+            __builtin_amdgcn_raw_buffer_store_b32(int(kInf), smp, int(i0 + r < L ? at : kNoRead), 0, 16);
+        }
     } else if (D > 0) {
         double key[4][4];
 #pragma unroll
@@ -2020,19 +2215,49 @@ __global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
             for (int cc = 0; cc < 4; ++cc) key[r][cc] = kKeyBase + 4294967295.0;
         int half = 0;
         const bool low = s.reach > m0;
-        // the splits whose operands the neighbours finish, and those whose operands are older; the first wave looks at the neighbours meanwhile
-        const int lo = i0 + 2 * T, ni = D > 2 ? 8 * (D - 3) + 1 : 0;
-        if (wq == 1) {
-            const int ne = D == 1 ? 1 : D == 2 ? 9 : 16, k = min(lane, ne - 1);
-            list_splits(x, D > 2 && k >= 8 ? j0 - T + k - 7 : i0 + T + k, lane < ne, 0, &s.n_edge);
-        } else if (wq > 1) {
-            for (int k = 64 * (wq - 2); k < ni; k += 128) list_splits(x, lo + min(k + lane, ni - 1), k + lane < ni, kEdge, &s.n_inner);
+        if constexpr (!BOUNDS) {  // the first wave looks at the neighbours meanwhile
+            if (wq == 1) {
+                const int k = min(lane, ne - 1);
+                list_splits(x, D > 2 && k >= 8 ? j0 - T + k - 7 : i0 + T + k, lane < ne, 0, &s.n_edge);
+            } else if (wq > 1) {
+                for (int k = 64 * (wq - 2); k < ni; k += 128) list_splits(x, inner + min(k + lane, ni - 1), k + lane < ni, kEdge, &s.n_inner);
+            }
+        }
+        const rsrc_t smp = table_rsrc(c.ws.samp + (BOUNDS ? size_t(b) * samp_ints(L, pitch) : 0), BOUNDS ? uint32_t(samp_rows(L)) * uint32_t(pitch / kG) * uint32_t(4 * T) : 0);
+        if constexpr (BOUNDS) {
+            const int t = threadIdx.x;
+            (&sb.ub[0][0][0])[t] = kInf - 1 + uint32_t(s.rows[(t >> 7) * 4 + ((t & 31) >> 3)].P);
+            sb.index[t] = kFlow - 1;  // an entry that reads nothing
+            if (t == 0) sb.left = 0;
         }
         if (D > 2) {
             if (!ready(2)) return;
-            const int n = __builtin_amdgcn_readfirstlane(s.n_inner);
-            flow_splits(x, kEdge, n, key, half, low, [] {});
+            int n = BOUNDS ? ni : __builtin_amdgcn_readfirstlane(s.n_inner);
+            if constexpr (BOUNDS) {
+                if (n > 16) {
+                    lower_bounds<2>(x, smp, kEdge, n, [&] {
+                        upper_bounds(x, smp, kEdge, n);
+                        __syncthreads();
+                    });
+                    __syncthreads();
+                }
+                n = left_over(x, kEdge, n, n <= 16);
+            }
+            flow_splits<BOUNDS>(x, kEdge, n, key, half, low, [] {});
             evaluated = n;
+            if constexpr (BOUNDS) {
+                // what is evaluated bounds the cells from above: a minimum at the first column of a sub-chunk
+                if ((lane & 15) == 0) {
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+#pragma unroll
+                        for (int d = 0; d < 4; ++d)
+                            atomicMin(&sb.ub[wq >> 1][lane >> 4][a * T + (wq & 1) * 4 + d], uint32_t(__builtin_bit_cast(unsigned long long, key[a][d]) >> 8));
+                }
+                __syncthreads();  // the list has been read
+                sb.index[threadIdx.x] = kFlow - 1;
+                if (threadIdx.x == 0) sb.left = 0;
+            }
         }
         if (!ready(1)) return;
         // staged rows, 16 bytes a lane; row 7's operands of C_all
@@ -2051,9 +2276,16 @@ __global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
             st[k] = tld4_dev(x.tab, uint32_t(it.x) != kNoRead && col > -4 ? uint32_t(it.x) + 4u * uint32_t(max(col, 0)) : kNoRead);
         }
         half = 0;
-        const int n = __builtin_amdgcn_readfirstlane(s.n_edge);
+        int n = BOUNDS ? ne : __builtin_amdgcn_readfirstlane(s.n_edge);
+        if constexpr (BOUNDS) {
+            if (D > 2) {
+                lower_bounds<1>(x, smp, 0, n, [] {});
+                __syncthreads();
+            }
+            n = left_over(x, 0, n, D <= 2);
+        }
         evaluated += n;
-        flow_splits(x, 0, n, key, half, low, [&] {
+        flow_splits<BOUNDS>(x, 0, n, key, half, low, [&] {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int4 it = s.item[(4 * wq + k) * 4 + lr];
@@ -2064,25 +2296,25 @@ __global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
                     if (d == 2) st[k] = u32x4{0, 0, v.x, v.y};
                     if (d == 3) st[k] = u32x4{0, 0, 0, v.x};
                 }
-                *reinterpret_cast<u32x4*>(&s.u.stage[1][(4 * wq + k) * 4 + lr][(lc + it.z) & 63]) = st[k];
+                *reinterpret_cast<u32x4*>(&s.u.stage[NBUF - 1][(4 * wq + k) * 4 + lr][(lc + it.z) & 63]) = st[k];
             }
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < T; ++r) {
                 const int at = r * T - r * (r - 1) / 2 - r;  // + column
-                if (r < 4) leftL[r] = s.u.stage[1][at + max(k4, r)][r == 0 ? mine : (cb + 16 * max(k4, r)) & 63];
-                leftH[r] = s.u.stage[1][at + max(k4 + 4, r)][r <= 4 ? mine : (cb + 16 * max(k4 + 4, r)) & 63];
+                if (r < 4) leftL[r] = s.u.stage[NBUF - 1][at + max(k4, r)][r == 0 ? mine : (cb + 16 * max(k4, r)) & 63];
+                leftH[r] = s.u.stage[NBUF - 1][at + max(k4 + 4, r)][r <= 4 ? mine : (cb + 16 * max(k4 + 4, r)) & 63];
             }
 #pragma unroll
             for (int c2 = 0; c2 < T - 1; ++c2) {
                 const int at = kLeft + c2 * (2 * T - 1 - c2) / 2 - c2 - 1;
                 if (c2 < 3) {
                     const int cc = max(k4, c2 + 1);
-                    const uint32_t v = s.u.stage[1][at + cc][(cb + 16 * cc) & 63];
+                    const uint32_t v = s.u.stage[NBUF - 1][at + cc][(cb + 16 * cc) & 63];
                     colL[c2] = k4 > c2 ? v + uint32_t(s.Pj[c2]) : kHuge;
                 }
                 const int cc = max(k4 + 4, c2 + 1);
-                const uint32_t v = s.u.stage[1][at + cc][(cb + 16 * cc) & 63];
+                const uint32_t v = s.u.stage[NBUF - 1][at + cc][(cb + 16 * cc) & 63];
                 colH[c2] = k4 + 4 > c2 ? v + uint32_t(s.Pj[c2]) : kHuge;
             }
             __syncthreads();  // the staged rows have been read
@@ -2099,9 +2331,9 @@ __global__ void __launch_bounds__(kFlow, 3) flow_kernel(Ctx c, int B) {
                 s.u.p.pnum[(rq + a) * T + cq + d][at] = uint8_t(bits);
             }
         __syncthreads();
-        flow_rows<false>(x, leftL, leftH, colL, colH, alL, alH);
+        flow_rows<false, BOUNDS>(x, leftL, leftH, colL, colH, alL, alH);
     } else {
-        flow_rows<true>(x, leftL, leftH, colL, colH, 0, 0);
+        flow_rows<true, BOUNDS>(x, leftL, leftH, colL, colH, 0, 0);
     }
     if (c.work && wq == 0) count_work<true>(c.work, 2, unsigned(empty ? 0 : 16 * evaluated + (D > 0 ? 64 : 0)), unsigned(T * cend));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -2717,7 +2949,8 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     if (nblk < 3) groups = 1;  // no diagonal to split
     const bool would_split = groups > 1;
     // Small batches: every tile in one launch.  A schedule that the caller asks for is made of separate launches.
-    const bool flow = groups == 1 && fused_rows && !want_ks && ckpt_rules::flow_pays(nblk, pitch / 64, B);
+    const bool flow = groups == 1 && fused_rows && !want_ks && ckpt_rules::flow_pays(nblk, pitch / 64, B, ws.samp);
+    const bool flow_bounds = ckpt_rules::flow_bounds(nblk, pitch / 64, B, ws.samp);
     if (prof) groups = 1;  // the event trail times one stream
     Device* dev = nullptr;
     if (groups > 1) {
@@ -2781,7 +3014,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
 
         if (flow) {
             const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work, false};
-            hipLaunchKernelGGL(flow_kernel, dim3(unsigned(tiles_of(L) * (pitch / 64) * B)), dim3(kFlow), 0, st, ctx, B);
+            hipLaunchKernelGGL(flow_bounds ? flow_kernel<true> : flow_kernel<false>, dim3(unsigned(tiles_of(L) * (pitch / 64) * B)), dim3(kFlow), 0, st, ctx, B);
             CKPT_AFTER_LAUNCH(CKPT_K_ROW);
             return CKPT_OK;
         }

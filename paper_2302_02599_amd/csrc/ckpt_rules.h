@@ -57,14 +57,27 @@ constexpr bool rows_pass(int tiles, int pitch, int B) { return 320LL * tiles * p
 //   one block: 14 x 7 stages, 780 slots (182 by that measure) 20 and 16;  67 x 8, 184 slots (201) 15 and 14;  100 x 6, 810 slots (1300) 20 and 24
 //   two: 67 x 9, 524 slots (1206) 45 and 38;  126 x 16, 315 slots (1260) 44 and 44;  65 x 15, 829 slots (1690) 52 and 59
 //   three: 37 x 20, 1074 slots (1887) 93 and 76;  19 x 24, 2245 slots (2052) 97 and 100;  77 x 24, 791 slots (3003) 98 and 106
-//   more: 5 x 53, 777 slots (455) 233 and 112;  6 x 53, 1295 slots (882) 246 and 134;  33 x 63, 410 slots (1848) 369 and 210;  38 x 49, 794 slots
+//   more, without samples: 5 x 53, 777 slots (455) 233 and 112;  6 x 53, 1295 slots (882) 246 and 134;  33 x 63, 410 slots (1848) 369 and 210;  38 x 49, 794 slots
 //   (3458) 330 and 295;  112 x 29, 470 slots (3584) 147 and 155;  185 x 26, 390 slots (5180) 180 and 216
 //   wide tables, wide * nblk: 4 x 129, 1389 slots (25 k) 740 and 544;  1 x 192, 4096 slots (37 k) 1072 and 1128;  2 x 165, 3436 slots (48 k) 1160 and 1256
 //   narrow ones: 15 x 121, 665 slots (42 k) 888 and 778;  25 x 162, 317 slots (55 k) 1611 and 1290;  30 x 122, 463 slots (61 k) 1203 and 1208
-constexpr bool flow_pays(int nblk, int chunks, long long B) {
+// With samples of the finished cells (see uses_bounds) splits are dropped by bounds in that launch too, and it pays for wider batches of
+// four blocks and more, longer chains more than short ones (their lists are longer):
+//   20 x 39, 2671 slots, five blocks (4200) 276 and 270;  41 x 82, 677 slots (4961) 794 and 746;  43 x 35, 1500 slots (5160) 265 and 274;
+//   59 x 56, 884 slots (5782) 484 and 516;  56 x 57, 774 slots, eight blocks (5824) 565 and 560;  116 x 106, 196 slots (6496) 1689 and 1611;
+//   24 x 138, 993 slots (6912) 2071 and 2065;  wider batches are split over streams: 8 x 192, 4096 slots (12480) 3609 and 5001
+constexpr bool flow_pays(int nblk, int chunks, long long B, bool samples) {
     const long long wide = B * chunks * nblk;
+    if (samples && nblk >= 4) return wide <= (nblk < 8 ? 4500 : 7000);
     if (nblk < 4) return wide <= (nblk == 1 ? 224 : nblk == 2 ? 1200 : 2000);
     return wide <= 3500 && wide * nblk <= (chunks >= 18 ? 33000 : 60000);
+}
+
+// Whether it drops splits by bounds: where there are enough of them.  us a solve without and with: 4 x 50 stages, 2004 slots (wide 896) 143 and
+// 150;  2 x 61, 3002 slots (752) 163 and 168;  8 x 58, 1659 slots (1664) 208 and 194;  36 x 56, 643 slots (2772) 267 and 236;  1 x 139, 1609
+// slots (468) 357 and 324;  4 x 112, 1967 slots (1736) 475 and 371; narrow tables lose a little, 7 x 236, 263 slots 1104 and 1155.
+constexpr bool flow_bounds(int nblk, int chunks, long long B, bool samples) {
+    return samples && (nblk >= 8 || (nblk >= 4 && B * chunks * nblk >= 1600));
 }
 
 }  // namespace ckpt_rules

@@ -25,6 +25,9 @@ def amd():
     (41, 3000, 2, 2900),                           # shifts over more than 32 chunks, tiles below their frontier
     (90, 70, 2, 6),                                # a list of splits longer than a wave
     (254, 65, 1, 3),                               # the longest chain
+    (64, 1100, 8, 90), (65, 1919, 5, 700),         # splits dropped by bounds; sizes of a third of the budget
+    (88, 300, 39, 0), (200, 1300, 1, 60),          # no shift at all; lists of more splits than two waves have lanes
+    (37, 1500, 29, 100),                           # five blocks, the shortest chains with bounds
 ])
 def test_every_tile_in_one_launch(amd, oracle_mod, L, M, B, size_hi):
     import torch
@@ -40,7 +43,8 @@ def test_every_tile_in_one_launch(amd, oracle_mod, L, M, B, size_hi):
 
 
 @pytest.mark.parametrize("L,M,B", [(8, 500, 28), (8, 500, 29), (16, 500, 75), (16, 500, 76), (20, 600, 66), (20, 600, 67),
-                                   (32, 500, 109), (32, 500, 110), (120, 1200, 7), (120, 1200, 8)])
+                                   (32, 500, 109), (32, 500, 110), (32, 2000, 27), (32, 2000, 28),
+                                   (56, 700, 58), (56, 700, 59), (96, 800, 44), (96, 800, 45)])
 def test_both_sides_of_the_rule(amd, L, M, B):
     import torch
     batch = random_chain_batch(L, M, B, 2300 + L + B, size_hi=M // 20, time_hi=900)
