@@ -1690,21 +1690,14 @@ __device__ __forceinline__ FlowPlace flow_place(int ticket, int nblk, int chunks
         auto s2 = [](int n) { return (n - 1) * n * (2 * n - 1) / 6; };
         return chunks * (full * nblk - s1(full)) + (part - full) * nblk * k - (k + kSkew * nblk) * (s1(part) - s1(full)) + kSkew * (s2(part) - s2(full));
     };
-    int key = 0;
-    for (int step = 64 * 64; step >= 1; step /= 64) key += step * (__popcll(__ballot(before(key + step * lane) <= ticket)) - 1);
+    // keys lie far below 64 * 64 (flow_pays): the last one with no more than `ticket` places before it
+    int key = 64 * (__popcll(__ballot(before(64 * lane) <= ticket)) - 1);
+    key += __popcll(__ballot(before(key + lane) <= ticket)) - 1;
     const int D0 = max(0, key - chunks + kSkew) / kSkew;  // first diagonal with this key
     ticket -= before(key);
-    // of diagonal D0 + lane
-    const int D = D0 + lane, here = D < nblk && D * kSkew <= key ? nblk - D : 0;
-    int sum = here;
-#pragma unroll
-    for (int o = 1; o < 32; o <<= 1) {
-        const int v = __shfl_up(sum, o);
-        if (lane >= o) sum += v;
-    }
-    const int n = __popcll(__ballot(lane < 32 && sum <= ticket));
-    const int I = ticket - (n ? __builtin_amdgcn_readlane(sum, n - 1) : 0);
-    return {n < 32 ? D0 + n : nblk, key - kSkew * (D0 + n), I};
+    const int upto = lane * (nblk - D0) - lane * (lane - 1) / 2;  // places of `lane` diagonals from there
+    const int n = __popcll(__ballot(D0 + lane <= nblk && upto <= ticket)) - 1;
+    return {D0 + n, key - kSkew * (D0 + n), ticket - (n * (nblk - D0) - n * (n - 1) / 2)};
 }
 
 // Until the chunks chunk, chunk - 1, .. chunk - reach of both tiles are finished (first wave only).
@@ -2110,7 +2103,7 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
     if constexpr (!BOUNDS) s.split[0][threadIdx.x] = s.split[1][threadIdx.x] = make_int2(0, kFar);  // reads nothing
     __syncthreads();
     const FlowPlace at = flow_place(__builtin_amdgcn_readfirstlane(s.ticket), nblk, chunks, lane);
-    if (at.D >= nblk) return;  // cannot happen: one ticket per work-group
+    if (at.D >= nblk || at.band < 0) return;  // cannot happen: one ticket per work-group
     const int D = at.D, band = at.band, I = at.I, J = I + D;
     const size_t chain = size_t(b) * c.rows * pitch;
     const size_t bl = size_t(b) * L;
