@@ -2413,13 +2413,23 @@ __global__ void __launch_bounds__(64) store_budgets_kernel(SweepBudgets budget, 
 // round trips, so the tree is taken breadth first, all pending cells at once (wave 0), and runs of C_all
 // are followed ahead of their numbers: the lanes of a cell read (s + u, t, m - sum of abar^s .. abar^{s+u-1})
 // together, and the first number that is not C_all ends the run.  Few pending cells get many lanes each.
-// Then the sizes of the subtrees are summed bottom-up, the positions of their operations top-down,
-// and all waves write the list.  8 chains of 192 stages, 4096 slots: 50 us a call, 290 us for one thread per
-// chain with its stack in memory (a cell every microsecond); 10 chains of 50 stages: 16 and 89 us.
+// A wave by itself issues an instruction every 4 (vector) or 8 (scalar) clocks and waits 130 for each
+// access to LDS, so a round is kept short: a node is one 16-byte word, what a stage adds to an address and
+// to m is a second one, the ends of all runs come from one addition to the mask of the lanes that go on,
+// and the read is not behind a branch.
+// Positions need no pass over the tree: the operations before a cell are those that its ancestors put
+// before their children and all that start right of it, and its own subtree is what starts in its stages,
+// less the ancestors that start where it does.  So sums by stage place every node, and all waves write the list.
+// 8 chains of 192 stages, 4096 slots (29 to 38 rounds): 26 us a call; 50 with 300 instructions a round and
+// the sizes of subtrees summed round by round (10 us of it), 290 for one thread per chain with its stack
+// in memory (a cell every microsecond); 10 chains of 50 stages (7 to 12 rounds): 12, 20 and 89 us.  Reading both children
+// of every split a cell could have ahead of its number saves a quarter of the rounds (runs and
+// right children alternate, and a run's length is not known), and three reads a stage cost more: 52 us.
 // Cells below a run cover disjoint stages, so a walk has at most L leaves, L - 1 splits and L - 1 cells
 // that only continue a run.
 constexpr int kWalkNodes = 3 * CKPT_MAX_L;
 constexpr int kWalkThreads = 256;
+static_assert(CKPT_MAX_L < kWalkThreads, "tables by stage; s_total is indexed by a stage and the one after it");
 
 __global__ void __launch_bounds__(kWalkThreads) schedule_kernel(const uint8_t* __restrict__ arg,
                                                                  const int32_t* __restrict__ wa,
@@ -2428,155 +2438,158 @@ __global__ void __launch_bounds__(kWalkThreads) schedule_kernel(const uint8_t* _
                                                                  ckpt_op_t* __restrict__ ops, int cap,
                                                                  int32_t* __restrict__ n_ops) {
     enum { kLeaf = 0, kSplit = 1, kMore = 2, kBad = 3 };  // how a node ends after its run of C_all
-    struct Node {
-        int m;        // before expansion: slots of the cell, held in 32 bits (outside 0 .. M there is no
-                      // cell: the node is bad); afterwards: first position of its operations
-        int size;     // operations of the subtree
-        short child;  // first child (the second of a split follows it)
-        uint8_t s, t, run, end, k;
+    // A node, as one 16-byte word:
+    //   x  slots of the cell, held in 32 bits (outside 0 .. M there is no cell: the node is bad)
+    //   y  s | t << 8 | operations of its ancestors that come before their children's << 16 (at most L(L+1)/2 + L)
+    //   z  operations of its ancestors that start at the same stage
+    //   w  run | end << 8 | k << 16
+    __shared__ int4 s_node[kWalkNodes + 64];  // a round's lanes look at 64 of them: those beyond the last one have s > t
+    struct alignas(16) Stage {
+        long long sum;  // of abar before the stage
+        int row;        // offset of its cells' row in the table, less that of t = 0
+        int wab;
     };
-    __shared__ Node s_node[kWalkNodes];
-    __shared__ short s_round[kWalkNodes + 1];  // first node of every round of the walk
-    __shared__ long long s_sum[CKPT_MAX_L + 1];  // s_sum[i] = sum of abar^1 .. abar^i
-    __shared__ int32_t s_wa[CKPT_MAX_L + 1], s_wab[CKPT_MAX_L];
+    __shared__ Stage s_stage[kWalkThreads];
+    __shared__ int32_t s_wa[CKPT_MAX_L + 1];
+    __shared__ int s_total[kWalkThreads + 1];  // operations of the nodes that start at a stage, then before it
+    __shared__ long long s_part[kWalkThreads / 64];
+    __shared__ int s_wave[kWalkThreads / 64];
     __shared__ int s_count, s_first_bad;
-    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint8_t* tab = arg + size_t(b) * rows * pitch;
     // Sizes of a chain that ckpt_check_inputs would flag are taken as they come: a negative one raises m.
     auto left = [](long long m, int size) { return __builtin_elementwise_sub_sat(int(m), size); };  // m in 0 .. M
+    const int wab = tid > 0 && tid <= L ? wabar[size_t(b) * L + tid - 1] : 0;
+    for (int k = tid; k <= L; k += kWalkThreads) s_wa[k] = wa[size_t(b) * (L + 1) + k];
     const int m0 = m_budget[b];
     if (m0 < 0) {  // uniform
         if (tid == 0) n_ops[b] = CKPT_E_ARG;
         return;
     }
-    for (int k = tid; k <= L; k += kWalkThreads) s_wa[k] = wa[size_t(b) * (L + 1) + k];
-    for (int k = tid; k < L; k += kWalkThreads) s_wab[k] = wabar[size_t(b) * L + k];
+    for (int i = tid; i < kWalkNodes + 64; i += kWalkThreads)
+        s_node[i] = i == 0 ? make_int4(min(m0, M), 1 | L << 8, 0, 0) : make_int4(0, 1, 0, 0);
+    s_total[tid] = 0;
     if (tid == 0) s_first_bad = INT32_MAX;
+    long long sum = wab;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const long long w = __shfl_up(sum, o);
+        if (lane >= o) sum += w;
+    }
+    if (lane == 63) s_part[wave] = sum;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) sum += s_part[w];
+    s_stage[tid] = Stage{sum - wab, int(unsigned((tid - 1) * L - (tid - 1) * (tid - 2) / 2 - tid) * unsigned(pitch)), wab};
     __syncthreads();
 
     if (tid < 64) {
-        long long carry = 0;
-        for (int base = 0; base < L; base += 64) {
-            long long v = base + lane < L ? s_wab[base + lane] : 0;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const long long w = __shfl_up(v, o);
-                if (lane >= o) v += w;
-            }
-            if (base + lane < L) s_sum[base + lane + 1] = carry + v;
-            carry += __shfl(v, 63);
-        }
-        if (lane == 0) {
-            s_sum[0] = 0;
-            s_node[0].s = 1, s_node[0].t = uint8_t(L), s_node[0].m = min(m0, M);
-        }
-        int head = 0, tail = 1, rounds = 0;
+        int head = 0, tail = 1;
         while (head < tail) {  // head grows in every round, tail is bounded: see kWalkNodes
             wave_settle();
             const int n = min(tail - head, 64);
             const int log_groups = n > 1 ? 32 - __builtin_clz(n - 1) : 0;
             const int width = 64 >> log_groups, group = lane >> (6 - log_groups), u = lane & (width - 1);
-            if (lane == 0) s_round[rounds] = short(head);
-            ++rounds;
-            bool here = group < n, read = false;
-            int s = 1, t = 1, k = 0;
-            long long m = 0;
-            if (here) {
-                const Node& nd = s_node[head + group];
-                s = nd.s + u, t = nd.t;
-                here = s <= t;
-                if (here) {
-                    m = nd.m - (s_sum[s - 1] - s_sum[s - 1 - u]);
-                    // inside the table, and ahead of its turn a lane reads no further than this cell could
-                    read = m >= 0 && m <= min(nd.m, M);
-                    if (read) k = tab[size_t(tri_row(L, s - 1, t - 1)) * pitch + m];
-                }
-            }
-            const bool goes_on = read && k == s && s < t;  // C_all
-            const unsigned long long stop = __ballot(!goes_on);
-            const unsigned long long mine = (width == 64 ? ~0ull : ((1ull << width) - 1)) << (group * width);
-            const unsigned long long in_group = stop & mine;
-            // the lane that ends the run: the first that does not go on, or the last one as a C_all cell
-            const int last = in_group ? __builtin_ctzll(in_group) : group * width + width - 1;
-            const bool ends = here && lane == last;
-            int end = kLeaf;
-            if (goes_on || (!read && m > 0 && m <= M)) end = kMore;
-            else if (!read || k < s || k > t) end = kBad;
-            else if (k > s) end = kSplit;
-            const unsigned long long splits = __ballot(ends && end == kSplit), more = __ballot(ends && end == kMore);
-            if (ends) {
-                Node& nd = s_node[head + group];
-                const unsigned long long below = (1ull << lane) - 1;
-                const int at = tail + 2 * __popcll(splits & below) + __popcll(more & below);
-                nd.run = uint8_t(u + (goes_on ? 1 : 0));
-                nd.end = uint8_t(end);
-                nd.k = uint8_t(end == kBad && head + group == 0 && u == 0 && k == 0 ? 1 : k);
-                nd.child = short(at);
-                if (end == kSplit) {  // (k, t, m - a^{k-1}) is walked first, then (s, k - 1, m)
-                    s_node[at].s = uint8_t(k), s_node[at].t = uint8_t(t), s_node[at].m = left(m, s_wa[k - 1]);
-                    s_node[at + 1].s = uint8_t(s), s_node[at + 1].t = uint8_t(k - 1), s_node[at + 1].m = int(m);
-                } else if (end == kMore) {
-                    s_node[at].s = uint8_t(goes_on ? s + 1 : s), s_node[at].t = uint8_t(t);
-                    s_node[at].m = goes_on ? left(m, s_wab[s - 1]) : int(m);
+            const int4 nd = s_node[head + group];
+            const int s0 = nd.y & 255, t = nd.y >> 8 & 255, s = s0 + u;
+            const bool here = s <= t;
+            const Stage at_s = s_stage[min(s, t)];
+            const long long m = nd.x - (at_s.sum - s_stage[s0].sum);
+            // inside the table, and ahead of its turn a lane reads no further than this cell could
+            const bool read = here & (m >= 0) & (m <= min(nd.x, M));
+            const int in_table = tab[read ? unsigned(at_s.row + t * pitch + int(m)) : 0u], k = read ? in_table : 0;
+            const bool goes_on = k == s && s < t;  // C_all
+            const unsigned long long on = __ballot(goes_on);
+            // The lane that ends the run: the first that does not go on, or the last one as a C_all cell.  A bit
+            // added where each group begins carries to it.
+            const unsigned long long first = __ballot(here && u == 0);
+            const unsigned long long carry = on & ~(first << (width - 1)), ends = (carry + first) & ~carry;
+            const unsigned long long splits = ends & __ballot(k > s) & __ballot(k <= t);
+            // a size below zero raised m: not read ahead of its turn
+            const unsigned long long more = ends & (on | __ballot(here && m > nd.x && m <= M));
+            const unsigned long long bit = 1ull << lane;
+            if (ends & bit) {
+                const bool split = splits & bit, next = more & bit;
+                const int run = u + (goes_on ? 1 : 0);
+                const int end = next ? kMore : split ? kSplit : k == s ? kLeaf : kBad;
+                s_node[head + group].w = run | end << 8 | k << 16;
+                if (split || next) {
+                    const int at = tail + 2 * __popcll(splits & (bit - 1)) + __popcll(more & (bit - 1));
+                    const int own = split ? k - s0 : run;  // before the children
+                    const int a = s_wa[split ? k - 1 : 0], slots = left(m, split ? a : goes_on ? at_s.wab : 0);
+                    // (k, t, m - a^{k-1}) is walked first, then (s, k - 1, m)
+                    s_node[at] = make_int4(slots, (split ? k : s0 + run) | ((nd.y & ~255) + (own << 16)), 0, 0);
+                    if (split)
+                        s_node[at + 1] = make_int4(int(m), s | (k - 1) << 8 | ((nd.y & ~0xffff) + (own << 16)),
+                                                   u == 0 ? nd.z + own : 0, 0);
                 }
             }
             tail += 2 * __popcll(splits) + __popcll(more);
             head += n;
         }
-        if (lane == 0) s_round[rounds] = short(head), s_count = head;
-        wave_settle();
-        // operations before the children: the run's F_all, then F_all B of a leaf or F_ck F_null .. of a split
-        auto before = [&](const Node& nd) {
-            return nd.run + (nd.end == kLeaf ? 2 : nd.end == kSplit ? nd.k - nd.s - nd.run : 0);
-        };
-        for (int r = rounds - 1; r >= 0; --r) {
-            const int i = s_round[r] + lane;
-            if (i < s_round[r + 1]) {
-                Node& nd = s_node[i];
-                int size = before(nd) + nd.run;
-                if (nd.end == kSplit) size += s_node[nd.child].size + s_node[nd.child + 1].size;
-                if (nd.end == kMore) size += s_node[nd.child].size;
-                nd.size = size;
-            }
-            wave_settle();
-        }
-        if (lane == 0) s_node[0].m = 0;
-        for (int r = 0; r < rounds; ++r) {
-            wave_settle();
-            const int i = s_round[r] + lane;
-            if (i < s_round[r + 1]) {
-                const Node& nd = s_node[i];
-                const int pos = nd.m + before(nd);
-                if (nd.end == kSplit) s_node[nd.child].m = pos, s_node[nd.child + 1].m = pos + s_node[nd.child].size;
-                if (nd.end == kMore) s_node[nd.child].m = pos;
-                if (nd.end == kBad) atomicMin(&s_first_bad, pos);
-            }
-        }
+        if (lane == 0) s_count = head;
     }
     __syncthreads();
-    const int n = s_node[0].size, bad = s_first_bad;
+    const int count = s_count;
+    struct Node {
+        int s, t, before, same, run, end, k;
+    };
+    auto node = [&](int i) {
+        const int4 nd = s_node[i];
+        return Node{nd.y & 255, nd.y >> 8 & 255, int(unsigned(nd.y) >> 16), nd.z, nd.w & 255, nd.w >> 8 & 255, nd.w >> 16};
+    };
+    // operations before the children: the run's F_all, then F_all B of a leaf or F_ck F_null .. of a split
+    auto before = [](const Node& nd) { return nd.end == kSplit ? nd.k - nd.s : nd.run + (nd.end == kLeaf ? 2 : 0); };
+    for (int i = tid; i < count; i += kWalkThreads) {
+        const Node nd = node(i);
+        atomicAdd(&s_total[nd.s], before(nd) + nd.run);
+    }
+    __syncthreads();
+    int upto = s_total[tid];
+    const int here = upto;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int w = __shfl_up(upto, o);
+        if (lane >= o) upto += w;
+    }
+    if (lane == 63) s_wave[wave] = upto;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) upto += s_wave[w];
+    s_total[tid] = upto - here;
+    if (tid == kWalkThreads - 1) s_total[kWalkThreads] = upto;
+    __syncthreads();
+    const int n = s_total[kWalkThreads];
+    auto position = [&](const Node& nd) { return nd.before + n - s_total[nd.t + 1]; };
+    for (int i = tid; i < count; i += kWalkThreads) {
+        const Node nd = node(i);
+        if (nd.end == kBad) atomicMin(&s_first_bad, position(nd) + before(nd));
+    }
+    __syncthreads();
+    const int bad = s_first_bad;
     const int limit = min(cap, bad);  // the list ends where the walk in order would have ended
     ckpt_op_t* out = ops + size_t(b) * cap;
     auto emit = [&](int at, int kind, int stage) {
         if (at < limit) out[at].kind = uint8_t(kind), out[at].stage = uint8_t(stage);
     };
-    for (int i = tid >> 3; i < s_count; i += kWalkThreads / 8) {  // eight lanes a node
-        const Node& nd = s_node[i];
-        const int s = nd.s + nd.run, x = tid & 7;
+    for (int i = tid >> 3; i < count; i += kWalkThreads / 8) {  // eight lanes a node
+        const Node nd = node(i);
+        const int s = nd.s + nd.run, x = tid & 7, first = position(nd);
+        const int last = first + s_total[nd.t + 1] - s_total[nd.s] - nd.same - 1;
         for (int u = x; u < nd.run; u += 8) {
-            emit(nd.m + u, CKPT_OP_F_ALL, nd.s + u);
-            emit(nd.m + nd.size - 1 - u, CKPT_OP_B, nd.s + u);
+            emit(first + u, CKPT_OP_F_ALL, nd.s + u);
+            emit(last - u, CKPT_OP_B, nd.s + u);
         }
-        if (nd.end == kLeaf && x < 2) emit(nd.m + nd.run + x, x ? CKPT_OP_B : CKPT_OP_F_ALL, s);
+        if (nd.end == kLeaf && x < 2) emit(first + nd.run + x, x ? CKPT_OP_B : CKPT_OP_F_ALL, s);
         if (nd.end == kSplit)
-            for (int j = s + x; j < nd.k; j += 8) emit(nd.m + nd.run + j - s, j == s ? CKPT_OP_F_CK : CKPT_OP_F_NULL, j);
+            for (int j = s + x; j < nd.k; j += 8) emit(first + nd.run + j - s, j == s ? CKPT_OP_F_CK : CKPT_OP_F_NULL, j);
     }
     if (tid == 0) {
         int rc = n;
-        if (bad <= cap)
-            rc = s_node[0].end == kBad && s_node[0].run == 0 && s_node[0].k == 1 ? CKPT_E_INFEASIBLE : CKPT_E_CORRUPT;
-        else if (n > cap || bad != INT32_MAX)
+        if (bad <= cap) {
+            const Node nd = node(0);  // its first number is read in every case: 0 is the table's mark of an infeasible cell
+            rc = nd.end == kBad && nd.run == 0 && nd.k == 0 ? CKPT_E_INFEASIBLE : CKPT_E_CORRUPT;
+        } else if (n > cap || bad != INT32_MAX) {
             rc = CKPT_E_SMALLBUF;
+        }
         n_ops[b] = rc;
     }
 }
