@@ -2594,52 +2594,49 @@ __global__ void __launch_bounds__(kWalkThreads) schedule_kernel(const uint8_t* _
     }
 }
 
-// Checkpoint block index of every stage (Section "Code generation"): one wave per chain reads the
-// first forward sweep of its operation list.  In a list produced by the walk above, operation k
+// Checkpoint block index of every stage (Section "Code generation"): one work-group per chain reads the
+// first forward sweep of its operation list, a thread per stage.  In a list produced by the walk above, operation k
 // (k < L) is the first forward of stage k + 1 and operation L is B^L; F_ck opens a block, F_null
 // continues it, F_all lies in none.  The block number of a stage is the count of F_ck up to it,
-// minus one: an inclusive prefix sum over the lanes, carried across passes of 64 stages.
-__global__ void __launch_bounds__(64) block_index_kernel(const ckpt_op_t* __restrict__ ops, int cap,
+// minus one: bits of a ballot.  Bounded by the launch and one read, which does not wait for the length
+// of the list: 8 chains of 192 stages 3.1 us, 3.8 for one wave in passes of 64 stages.
+constexpr int kBlockThreads = 256;
+static_assert(CKPT_MAX_L < kBlockThreads, "a thread per stage and one for B^L");
+
+__global__ void __launch_bounds__(kBlockThreads) block_index_kernel(const ckpt_op_t* __restrict__ ops, int cap,
                                                           const int32_t* __restrict__ n_ops, int L,
                                                           int32_t* __restrict__ block_of_stage,
                                                           int32_t* __restrict__ n_blocks) {
-    const int b = blockIdx.x, lane = threadIdx.x;
+    constexpr int kWaves = kBlockThreads / 64;
+    __shared__ unsigned long long s_opens[kWaves], s_inside[kWaves];
+    const int b = blockIdx.x, k = threadIdx.x, lane = k & 63, wave = k >> 6;
+    ckpt_op_t op{CKPT_OP_F_ALL, uint8_t(k + 1)};
+    if (k <= L && k < cap) op = ops[size_t(b) * cap + k];
     const int n = n_ops[b];
     int32_t* out = block_of_stage + size_t(b) * L;
     if (n < 0 || n > cap || n < L + 1) {  // uniform: a failed walk keeps its code, a short list is corrupt
-        for (int k = lane; k < L; k += 64) out[k] = -1;
-        if (lane == 0) n_blocks[b] = n < 0 ? n : (n > cap ? CKPT_E_ARG : CKPT_E_CORRUPT);
+        if (k < L) out[k] = -1;
+        if (k == 0) n_blocks[b] = n < 0 ? n : (n > cap ? CKPT_E_ARG : CKPT_E_CORRUPT);
         return;
     }
-    const ckpt_op_t* list = ops + size_t(b) * cap;
-    int carry = 0;       // F_ck seen in earlier passes
-    int prev_in = 0;     // was the last stage of the previous pass inside a block
-    bool bad = false;
-    for (int base = 0; base < L; base += 64) {  // L is uniform: every lane takes every pass
-        const int k = base + lane;
-        const bool valid = k < L;
-        const int kind = valid ? list[k].kind : CKPT_OP_F_ALL;
-        const int stage = valid ? list[k].stage : k + 1;
-        const bool opens = valid && kind == CKPT_OP_F_CK;
-        const bool inside = valid && (kind == CKPT_OP_F_CK || kind == CKPT_OP_F_NULL);
-        int before = __shfl_up(int(inside), 1);
-        if (lane == 0) before = prev_in;
-        if (valid && (stage != k + 1 || kind > CKPT_OP_F_NULL || (kind == CKPT_OP_F_NULL && !before))) bad = true;
-        int scan = int(opens);
+    const bool valid = k < L;
+    const unsigned long long opens = __ballot(valid && op.kind == CKPT_OP_F_CK);
+    const unsigned long long inside = __ballot(valid && (op.kind == CKPT_OP_F_CK || op.kind == CKPT_OP_F_NULL));
+    if (lane == 0) s_opens[wave] = opens, s_inside[wave] = inside;
+    __syncthreads();
+    int before = 0, blocks = 0;  // blocks opened in earlier waves, and in all
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int v = __shfl_up(scan, o);
-            if (lane >= o) scan += v;
-        }
-        if (valid) out[k] = inside ? carry + scan - 1 : -1;
-        carry += __shfl(scan, 63);
-        prev_in = __shfl(int(inside), 63);
+    for (int w = 0; w < kWaves; ++w) {
+        const int count = __popcll(s_opens[w]);
+        if (w < wave) before += count;
+        blocks += count;
     }
-    if (lane == 0 && (list[L].kind != CKPT_OP_B || list[L].stage != L)) bad = true;
-    bad = __any(bad);
-    if (bad)
-        for (int k = lane; k < L; k += 64) out[k] = -1;
-    if (lane == 0) n_blocks[b] = bad ? CKPT_E_CORRUPT : carry;
+    const bool after_one = lane ? inside >> (lane - 1) & 1 : wave && s_inside[wave - 1] >> 63;
+    bool bad = valid && (op.stage != k + 1 || op.kind > CKPT_OP_F_NULL || (op.kind == CKPT_OP_F_NULL && !after_one));
+    if (k == L && (op.kind != CKPT_OP_B || op.stage != L)) bad = true;
+    bad = __syncthreads_or(bad);
+    if (valid) out[k] = !bad && inside >> lane & 1 ? before + __popcll(opens & (~0ull >> (63 - lane))) - 1 : -1;
+    if (k == 0) n_blocks[b] = bad ? CKPT_E_CORRUPT : blocks;
 }
 
 // Self-check of operation lists: one work-group per chain executes its list under the memory model
@@ -2648,27 +2645,58 @@ __global__ void __launch_bounds__(64) block_index_kernel(const ckpt_op_t* __rest
 // as none of them finds an operand missing -- and then the list is corrupt whatever follows.  So a thread
 // takes a stage and steps through its own operations (found by a bit mask per stage), all stages
 // at once; the thread of an operation's input stage also notes by how much the operation changes the
-// resident sum.  Then a thread takes an operation: prefix sums give the memory before each one.
-// What bounds it: a few dependent LDS reads per operation of the busiest stage.  About 8 us, where one lane
-// stepping through the whole list took 210 us for the lists of 8 chains of 192 stages.
+// resident sum.  Then a thread takes four operations: prefix sums give the memory before each one.
+// What bounds it: the operations of the busiest stage, some 60 instructions each by a lone wave a SIMD.  So a
+// thread goes from one of its operations to the next whatever the other lanes do, kinds are two bits that come with a
+// word of its mask, empty words are not looked at, and the list is asked for before its length is known.
+// 8 chains of 192 stages: 8 us; 16 with the words of the masks taken by all lanes together, 210 for one
+// lane stepping through the whole list.
 constexpr int kSimThreads = 256;  // at least CKPT_MAX_L + 1 stages and the empty mask after them
-constexpr int kSimChunk = 4 * kSimThreads;  // operations staged per pass
+constexpr int kSimPer = 4;        // operations of a thread in a pass, one after another in the list
+constexpr int kSimChunk = kSimPer * kSimThreads;  // operations staged per pass
 static_assert(CKPT_MAX_L + 2 <= kSimThreads, "a thread per stage");
+static_assert(kSimChunk == 32 * 32, "a word of s_any has a bit for every word of a mask");
 
 __global__ void __launch_bounds__(kSimThreads) simulate_kernel(ckpt_chains_t ch, int L, const ckpt_op_t* __restrict__ ops,
                                                                 int cap, const int32_t* __restrict__ n_ops,
                                                                 long long* __restrict__ time_out,
                                                                 long long* __restrict__ peak_out,
                                                                 int32_t* __restrict__ status) {
-    constexpr int kPer = kSimChunk / kSimThreads, kWaves = kSimThreads / 64;
-    __shared__ int32_t s_uf[CKPT_MAX_L], s_ub[CKPT_MAX_L], s_wab[CKPT_MAX_L], s_of[CKPT_MAX_L], s_ob[CKPT_MAX_L];
-    __shared__ int32_t s_wa[CKPT_MAX_L + 1], s_wd[CKPT_MAX_L + 1];
-    __shared__ uint32_t s_mask[kSimChunk / 32][kSimThreads];  // [word][stage]: which operations of the pass are the stage's
-    __shared__ uint8_t s_kind[kSimChunk], s_stage[kSimChunk];
-    __shared__ long long s_delta[kSimChunk];
+    constexpr int kWords = kSimChunk / 32, kWaves = kSimThreads / 64;
+    __shared__ int2 s_forward[CKPT_MAX_L], s_backward[CKPT_MAX_L];  // time and overhead of stage x + 1
+    __shared__ int32_t s_made[2][CKPT_MAX_L];                       // a and abar of stage x + 1
+    __shared__ uint32_t s_mask[kWords][kSimThreads];  // [word][stage]: which operations of the pass are the stage's
+    __shared__ uint32_t s_any[kSimThreads];           // [stage]: which words of its mask are not empty
+    __shared__ uint32_t s_kind[kWords][2];            // the two bits of an operation's kind
+    __shared__ __align__(16) long long s_delta[kSimChunk];
     __shared__ long long s_total[kWaves], s_peak[kWaves], s_time[kWaves];
-    __shared__ int s_bad;
     const int b = blockIdx.x, x = threadIdx.x, lane = x & 63, wave = x >> 6;
+    const ckpt_op_t* list = ops + size_t(b) * cap;
+    ckpt_op_t op[kSimPer];
+    auto fetch = [&](int base, int end) {
+#pragma unroll
+        for (int u = 0; u < kSimPer; ++u) {
+            op[u] = ckpt_op_t{};
+            if (base + kSimPer * x + u < end) op[u] = list[base + kSimPer * x + u];
+        }
+    };
+    fetch(0, cap);
+    const int32_t* wd = ch.wdelta ? ch.wdelta : ch.wa;
+    // of stage x: a, delta; of stage x + 1: a, abar, delta
+    long long a = 0, d = 0, a1 = 0, ab1 = 0, d1 = 0;
+    const long long d_last = wd[size_t(b) * (L + 1) + L];
+    if (x <= L) {
+        a = x ? ch.wa[size_t(b) * (L + 1) + x] : 0;  // the chain input a^0 is not counted
+        d = wd[size_t(b) * (L + 1) + x];
+    }
+    if (x < L) {
+        a1 = ch.wa[size_t(b) * (L + 1) + x + 1];
+        d1 = wd[size_t(b) * (L + 1) + x + 1];
+        ab1 = ch.wabar[size_t(b) * L + x];
+        s_forward[x] = make_int2(ch.uf[size_t(b) * L + x], ch.of ? ch.of[size_t(b) * L + x] : 0);
+        s_backward[x] = make_int2(ch.ub[size_t(b) * L + x], ch.ob ? ch.ob[size_t(b) * L + x] : 0);
+        s_made[0][x] = int32_t(a1), s_made[1][x] = int32_t(ab1);
+    }
     const int n = n_ops[b];
     if (n < 0 || n > cap) {  // uniform over the work-group
         if (x == 0) {
@@ -2677,70 +2705,72 @@ __global__ void __launch_bounds__(kSimThreads) simulate_kernel(ckpt_chains_t ch,
         }
         return;
     }
-    const int32_t* wd = ch.wdelta ? ch.wdelta : ch.wa;
-    if (x == 0) s_bad = 0;
-    if (x < L) {
-        s_uf[x] = ch.uf[size_t(b) * L + x];
-        s_ub[x] = ch.ub[size_t(b) * L + x];
-        s_wab[x] = ch.wabar[size_t(b) * L + x];
-        s_of[x] = ch.of ? ch.of[size_t(b) * L + x] : 0;
-        s_ob[x] = ch.ob ? ch.ob[size_t(b) * L + x] : 0;
-    }
-    if (x <= L) {
-        s_wa[x] = x ? ch.wa[size_t(b) * (L + 1) + x] : 0;  // the chain input a^0 is not counted
-        s_wd[x] = wd[size_t(b) * (L + 1) + x];
-    }
-    const ckpt_op_t* list = ops + size_t(b) * cap;
     int state = x == 0 ? 1 : x == L ? 4 : 0;  // a^0 and delta^L are there from the start
     bool bad = false;
-    long long time = 0, peak = 0, carry = 0;
+    long long time = 0, peak = 0, carry = d_last;
     for (int base = 0; base < n; base += kSimChunk) {  // n is uniform over the work-group
         const int count = min(kSimChunk, n - base), words = (count + 31) / 32;
         for (int w = 0; w < words; ++w) s_mask[w][x] = 0;
+        s_any[x] = 0;
+        if (x < 2 * kWords) s_kind[x >> 1][x & 1] = 0;
         __syncthreads();
-        for (int k = x; k < count; k += kSimThreads) {
-            const int kind = list[base + k].kind, j = list[base + k].stage;
-            s_kind[k] = uint8_t(kind), s_stage[k] = uint8_t(j);
-            if (j < 1 || j > L || kind > CKPT_OP_B) bad = true;
-            else atomicOr(&s_mask[k >> 5][j], 1u << (k & 31));
+        int kind[kSimPer], stage[kSimPer];
+        uint32_t bits[2] = {0, 0};
+#pragma unroll
+        for (int u = 0; u < kSimPer; ++u) {
+            const int k = kSimPer * x + u;
+            kind[u] = op[u].kind, stage[u] = op[u].stage;
+            if (k >= count) continue;
+            if (stage[u] < 1 || stage[u] > L || kind[u] > CKPT_OP_B) {
+                bad = true;
+            } else {
+                atomicOr(&s_mask[k >> 5][stage[u]], 1u << (k & 31));
+                atomicOr(&s_any[stage[u]], 1u << (k >> 5));
+                bits[0] |= uint32_t(kind[u] & 1) << (k & 31), bits[1] |= uint32_t(kind[u] >> 1) << (k & 31);
+            }
         }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) atomicOr(&s_kind[kSimPer * x >> 5][h], bits[h]);
+        const int next_base = base + kSimChunk;
+        if (next_base < n) fetch(next_base, n);  // uniform
         __syncthreads();
-        if (base == 0) carry = s_wd[L];
         if (x <= L) {
-            for (int w = 0; w < words; ++w) {
-                const uint32_t next = s_mask[w][x + 1];  // operations that read a^x: those of stage x + 1
-                for (uint32_t todo = s_mask[w][x] | next; todo; todo &= todo - 1) {
-                    const int bit = __builtin_ctz(todo), k = 32 * w + bit;
-                    const int kind = s_kind[k];
-                    if (next >> bit & 1u) {  // j = x + 1
-                        if (kind == CKPT_OP_B) {  // its output is not counted while it runs
-                            bad = bad || !(state & 3);
-                            s_delta[k] = ((state & 4) ? 0ll : (long long)s_wd[x]) - ((state & 1) ? (long long)s_wa[x] : 0ll) -
-                                         s_wd[x + 1] - s_wab[x];
-                            state = (state & 2) | 4;
-                        } else {  // a forward operation adds its output; F_null drops its input
-                            const bool drops = kind == CKPT_OP_F_NULL;
-                            bad = bad || !(state & 3) || (drops && !(state & 1));
-                            s_delta[k] = (long long)(kind == CKPT_OP_F_ALL ? s_wab[x] : s_wa[x + 1]) - (drops ? (long long)s_wa[x] : 0ll);
-                            if (drops) state &= ~1;
-                        }
-                    } else if (kind == CKPT_OP_B) {  // needs delta^x and abar^x
-                        bad = bad || (state & 6) != 6;
-                        state &= 1;
-                    } else {
-                        const int made = kind == CKPT_OP_F_ALL ? 2 : 1;
-                        bad = bad || (state & made);
-                        state |= made;
-                    }
+            uint32_t any = s_any[x] | s_any[x + 1], todo = 0, next = 0, kind0 = 0, kind1 = 0;
+            int w = 0;
+            while (any | todo) {
+                if (!todo) {
+                    w = __builtin_ctz(any);
+                    any &= any - 1;
+                    next = s_mask[w][x + 1];  // operations that read a^x: those of stage x + 1
+                    todo = s_mask[w][x] | next;
+                    kind0 = s_kind[w][0], kind1 = s_kind[w][1];
+                }
+                const int bit = __builtin_ctz(todo);
+                todo &= todo - 1;
+                const int what = int(kind0 >> bit & 1u) | int(kind1 >> bit & 1u) << 1;
+                if (next >> bit & 1u) {  // of stage x + 1
+                    const bool back = what == CKPT_OP_B, drops = what == CKPT_OP_F_NULL;
+                    bad = bad || !(state & 3) || (drops && !(state & 1));
+                    // B: its output is not counted while it runs; a forward operation adds its output, F_null drops its input
+                    const long long gone = (back ? state & 1 : drops) ? a : 0;
+                    const long long made = back ? ((state & 4) ? 0 : d) - d1 - ab1 : what == CKPT_OP_F_ALL ? ab1 : a1;
+                    s_delta[32 * w + bit] = made - gone;
+                    state = back ? (state & 2) | 4 : drops ? state & ~1 : state;
+                } else if (what == CKPT_OP_B) {  // needs delta^x and abar^x
+                    bad = bad || (state & 6) != 6;
+                    state &= 1;
+                } else {
+                    const int made = what == CKPT_OP_F_ALL ? 2 : 1;
+                    bad = bad || (state & made);
+                    state |= made;
                 }
             }
         }
         __syncthreads();
-        long long delta[kPer], before = 0;  // this thread's operations follow each other
+        long long delta[kSimPer], before = 0;
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int k = kPer * x + u;
-            delta[u] = k < count ? s_delta[k] : 0;
+        for (int u = 0; u < kSimPer; ++u) {
+            delta[u] = kSimPer * x + u < count ? s_delta[kSimPer * x + u] : 0;
             before += delta[u];
         }
         const long long own = before;
@@ -2758,20 +2788,16 @@ __global__ void __launch_bounds__(kSimThreads) simulate_kernel(ckpt_chains_t ch,
             carry += s_total[w];
         }
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int k = kPer * x + u;
-            if (k >= count) break;
-            const int kind = s_kind[k], j = min(max(int(s_stage[k]), 1), L);
-            if (kind == CKPT_OP_B) {
-                peak = max(peak, before + s_ob[j - 1]);
-                time += s_ub[j - 1];
-            } else {  // a forward operation needs room for its output and o_f
-                peak = max(peak, before + (kind == CKPT_OP_F_ALL ? s_wab[j - 1] : s_wa[j]) + s_of[j - 1]);
-                time += s_uf[j - 1];
-            }
+        for (int u = 0; u < kSimPer; ++u) {
+            const int j = min(max(stage[u], 1), L) - 1;
+            const bool back = kind[u] == CKPT_OP_B, valid = kSimPer * x + u < count;
+            const int2 cost = back ? s_backward[j] : s_forward[j];
+            const int made = s_made[kind[u] == CKPT_OP_F_ALL][j];
+            // a forward operation needs room for its output and o_f
+            const long long need = before + (back ? 0 : made) + cost.y;
+            if (valid) peak = max(peak, need), time += cost.x;
             before += delta[u];
         }
-        __syncthreads();  // the next pass overwrites the list
     }
     if (x == 0 && !(state & 4)) bad = true;  // the list must end with delta^0
 #pragma unroll
@@ -2780,14 +2806,12 @@ __global__ void __launch_bounds__(kSimThreads) simulate_kernel(ckpt_chains_t ch,
         peak = max(peak, __shfl_xor(peak, o));
     }
     if (lane == 0) s_time[wave] = time, s_peak[wave] = peak;
-    if (n == 0) __syncthreads();  // s_bad is set
-    if (bad) s_bad = 1;
-    __syncthreads();
+    bad = __syncthreads_or(bad);
     if (x == 0) {
         for (int w = 1; w < kWaves; ++w) time += s_time[w], peak = max(peak, s_peak[w]);
-        status[b] = s_bad ? CKPT_E_CORRUPT : CKPT_OK;
-        time_out[b] = s_bad ? -1 : time;
-        peak_out[b] = s_bad ? -1 : peak;
+        status[b] = bad ? CKPT_E_CORRUPT : CKPT_OK;
+        time_out[b] = bad ? -1 : time;
+        peak_out[b] = bad ? -1 : peak;
     }
 }
 
@@ -3317,7 +3341,7 @@ int ckpt_block_indices_batched(const ckpt_op_t* ops, int ops_cap, const int32_t*
                                int32_t* block_of_stage, int32_t* n_blocks) {
     if (!ops || !n_ops || !block_of_stage || !n_blocks || ops_cap < 0 || L < 1 || B < 1) return CKPT_E_ARG;
     if (L > CKPT_MAX_L) return CKPT_E_LIMIT;
-    hipLaunchKernelGGL(block_index_kernel, dim3(B), dim3(64), 0, static_cast<hipStream_t>(stream), ops, ops_cap, n_ops,
+    hipLaunchKernelGGL(block_index_kernel, dim3(B), dim3(kBlockThreads), 0, static_cast<hipStream_t>(stream), ops, ops_cap, n_ops,
                        L, block_of_stage, n_blocks);
     return hip_ok(hipGetLastError()) ? CKPT_OK : CKPT_E_HIP;
 }
