@@ -198,119 +198,130 @@ __host__ __device__ inline int tri_row(int L, int i, int j) {  // 0-based i <= j
 
 constexpr uint32_t kNoRead = 0xfffffff0u;  // buffer offset beyond any table: the load returns 0, no access
 
+// Inclusive scan over the 64 lanes of a wave; 0 is the identity of op.
+template <class Op>
+__device__ __forceinline__ int wave_scan(int v, Op op) {
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false));  // one, two, four, eight lanes before, in a row of 16
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false));
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false));
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false));
+    v = op(v, __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false));     // the end of rows 0 and 2 to rows 1 and 3
+    return op(v, __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false));  // the end of row 1 to rows 2 and 3
+}
+
 // Input checks, prefix sums, shifts and both threshold tables (last display of the Theorem), and for flow_kernel the marks
-// of the first diagonal's tiles (further work-groups).  A
-// work-group per chain and kPreRows rows of the tables, thread = column t: the maximum over the stages
-// between s and t grows by one stage from row to row, bottom-up, and the rows are written in whole
-// lines.  The work-group of the first rows also does what there is once per chain.  What bounds it: one round
-// trip to memory and a serial pass over the stages below the first row, in LDS.  One work-group per chain with
-// a thread per row took 52 us for 192 stages (8 chains), 12.6 us for 50 (10 chains).
-constexpr int kPreThreads = 256, kPreRows = 16, kMarkCols = 512;
+// of the first diagonal's tiles.  A chain has `parts` work-groups with `rows` rows of the tables each, one for what there
+// is once per chain, and those that mark.  Rows have a thread per column t: the maximum over the stages
+// between s and t is a scan for the lowest row and grows by one stage from row to row, and the rows are written in whole
+// lines.  What bounds it: a launch, one round trip to memory and some hundred instructions of a lone wave; with
+// thousands of chains the start of work-groups, so these have the waves that the stages fill (marks need all four).
+// 8 chains of 192 stages: 6.6 us, 18.0 with sixteen rows and a loop over the stages above them, by work-groups of which
+// one had the chain's part too; 10 chains of 50: 4.2 and 8.6, 1 of 8: 2.7 and 4.0, 20000 of 8: 23 and 40.
+constexpr int kPreThreads = 256, kMarkCols = 512;
 constexpr uint32_t kMark = 0x80000000u;  // a cell that waits for its row
 static_assert(CKPT_MAX_L < kPreThreads, "a thread per stage");
 
-__global__ void __launch_bounds__(kPreThreads) precompute_kernel(ckpt_chains_t ch, int L, int pitch, Workspace ws, int32_t* cost) {
-    const int b = blockIdx.x, part = blockIdx.y, parts = (L + kPreRows - 1) / kPreRows;
+__global__ void __launch_bounds__(kPreThreads) precompute_kernel(ckpt_chains_t ch, int L, int pitch, Workspace ws, int rows,
+                                                                  int parts, int32_t* cost) {
+    const int b = blockIdx.x, part = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const bool flow = int(gridDim.y) > parts;  // for flow_kernel
-    if (part >= parts) {  // marks kMarkCols columns of rows 1 .. 7 of a tile of the first diagonal
-        const int segs = (pitch + kMarkCols - 1) / kMarkCols, I = (part - parts) / segs, m = (part - parts) % segs * kMarkCols + 4 * (tid & 127);
+    const bool flow = int(gridDim.y) > parts + 1;  // for flow_kernel
+    if (part > parts) {  // marks kMarkCols columns of rows 1 .. 7 of a tile of the first diagonal
+        const int segs = (pitch + kMarkCols - 1) / kMarkCols, seg = part - parts - 1;
+        const int I = seg / segs, m = seg % segs * kMarkCols + 4 * (tid & 127);
         int4* at = reinterpret_cast<int4*>(cost + size_t(b) * (size_t(L) * (L + 1) / 2) * pitch + m);
-        if (m < pitch)
+        if (m < pitch)  // kPreThreads threads: two rows at a time
             for (int r = 1 + (tid >> 7); r < kT && I * kT + r < L; r += 2)
                 for (int cc = r; cc < kT && I * kT + cc < L; ++cc)
                     at[size_t(tri_row(L, I * kT + r, I * kT + cc)) * (pitch / 4)] = make_int4(int(kMark), int(kMark), int(kMark), int(kMark));
         return;
     }
-    const int32_t* uf = ch.uf + size_t(b) * L;
-    const int32_t* ub = ch.ub + size_t(b) * L;
     const int32_t* wa = ch.wa + size_t(b) * (L + 1);
-    const int32_t* wab = ch.wabar + size_t(b) * L;
     const int32_t* wd = ch.wdelta ? ch.wdelta + size_t(b) * (L + 1) : wa;
-    const int32_t* of = ch.of ? ch.of + size_t(b) * L : nullptr;
-    const int32_t* ob = ch.ob ? ch.ob + size_t(b) * L : nullptr;
-    __shared__ int32_t s_wa[kPreThreads], s_wd[kPreThreads], s_wab[kPreThreads], s_of[kPreThreads], s_ob[kPreThreads];
-    __shared__ int32_t s_pair[kPreThreads];  // [j] = omega_a^{j-1} + omega_a^j + o_f^j
-    __shared__ uint32_t s_total[kPreThreads / 64];
-    __shared__ int s_flags, s_reach;
-    const bool stage = tid < L;
-    const int a_in = tid <= L ? wa[tid] : 0, d_in = tid <= L ? wd[tid] : 0, ab_in = stage ? wab[tid] : 0;
-    const int of_in = stage && of ? of[tid] : 0, ob_in = stage && ob ? ob[tid] : 0;
-    // Sizes are clamped into [0, 2^28] so that thresholds of a bad chain cannot overflow.
-    auto sz = [](int v) { return min(max(v, 0), 1 << 28); };
-    s_wa[tid] = sz(a_in), s_wd[tid] = sz(d_in), s_wab[tid] = sz(ab_in), s_of[tid] = sz(of_in), s_ob[tid] = sz(ob_in);
-    if (tid == 0) s_flags = s_reach = 0;
-    {   // progress and ticket words of this chain's tiles, and (first block) the fault word
-        const size_t n = tiles_of(L) * prog_words(pitch);
-        for (size_t k = size_t(part) * kPreThreads + tid; k < n; k += size_t(parts) * kPreThreads)
-            if (!flow || blocks_of(L) == 1 || k != n - 1) ws.prog[size_t(b) * n + k] = 0;
-        if (b == 0 && part == 0 && tid == 0) ws.fault[0] = 0;
-    }
-    __syncthreads();
-    if (tid >= 1 && tid <= L) s_pair[tid] = s_wa[tid - 1] + s_wa[tid] + s_of[tid - 1];
+    const int t = tid + 1;
+    const bool stage = t <= L;
+    // a and delta of tensors t - 1 and t, the rest of stage t
+    const int a_in = stage ? wa[t - 1] : 0, a_out = stage ? wa[t] : 0, d_out = stage ? wd[t] : 0;
+    const int ab_in = stage ? ch.wabar[size_t(b) * L + t - 1] : 0;
+    const int of_in = stage && ch.of ? ch.of[size_t(b) * L + t - 1] : 0, ob_in = stage && ch.ob ? ch.ob[size_t(b) * L + t - 1] : 0;
+    const size_t words = tiles_of(L) * prog_words(pitch);  // progress and ticket words of a chain's tiles
+    int32_t* prog = ws.prog + size_t(b) * words;
+    const bool has_reach = flow && blocks_of(L) > 1;  // in the last of them
+    __shared__ int s_part[kPreThreads / 64];
 
-    if (part == 0) {  // uniform over the work-group
-        const int f = stage ? uf[tid] : 0, bw = stage ? ub[tid] : 0;
+    if (part == parts) {  // once per chain
+        __shared__ int s_flags[kPreThreads / 64], s_reach[kPreThreads / 64];
+        const int f = stage ? ch.uf[size_t(b) * L + t - 1] : 0, bw = stage ? ch.ub[size_t(b) * L + t - 1] : 0;
+        const int d_first = wd[0];
+        if (b == 0 && tid == 0) ws.fault[0] = 0;
         int flags = 0;
         if (f < 0 || bw < 0) flags |= 1;
         if (f >= (1 << 30) || bw >= (1 << 30)) flags |= 2;
-        for (int v : {a_in, d_in, ab_in, of_in, ob_in}) {  // a^0 and delta^0 among them
+        for (int v : {a_in, a_out, d_out, d_first, ab_in, of_in, ob_in}) {  // a^0 and delta^0 among them
             if (v < 0) flags |= 1;
             if (v > (1 << 28)) flags |= 4;
         }
-        if (stage && ab_in < wa[tid + 1]) flags |= 8;  // abar^k must contain a^k: outside the Theorem's model
+        if (ab_in < a_out) flags |= 8;  // abar^k must contain a^k: outside the Theorem's model
         const int fc = min(max(f, 0), (1 << 30) - 1), bc = min(max(bw, 0), 1 << 30);
         if (stage) {
-            ws.fb[size_t(b) * L + tid] = int32_t(min(kInf, uint32_t(fc) + uint32_t(bc)));
-            ws.wsh[size_t(b) * L + tid] = min(max(a_in, 0), pitch);
-            ws.wabs[size_t(b) * L + tid] = min(max(ab_in, 0), pitch);
+            ws.fb[size_t(b) * L + t - 1] = int32_t(min(kInf, uint32_t(fc) + uint32_t(bc)));
+            ws.wsh[size_t(b) * L + t - 1] = min(max(a_in, 0), pitch);
+            ws.wabs[size_t(b) * L + t - 1] = min(max(ab_in, 0), pitch);
         }
         // prefix sums of the forward times, held at 2^30 (then the chain is flagged) and stored as 2^30 - 1
-        uint32_t sum = uint32_t(fc);
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const uint32_t v = __shfl_up(sum, o);
-            if (lane >= o) sum = min(sum + v, kInf);
-        }
-        if (lane == 63) s_total[wave] = sum;
+        auto held = [](int x, int y) { return int(min(uint32_t(x) + uint32_t(y), kInf)); };
+        int sum = wave_scan(fc, held);
+        // the largest shift; a^L is none
+        const int reach = wave_scan(min(max(max(a_in, ab_in), 0), pitch), [](int x, int y) { return max(x, y); });
+        flags = wave_scan(flags, [](int x, int y) { return x | y; });
+        if (lane == 63) s_part[wave] = sum, s_flags[wave] = flags, s_reach[wave] = reach;
         __syncthreads();
-        for (int w = 0; w < wave; ++w) sum = min(sum + s_total[w], kInf);
-        if (sum >= kInf) flags |= 2;
+        for (int w = 0; w < wave; ++w) sum = held(sum, s_part[w]);
         int32_t* P = ws.P + size_t(b) * (L + 1);
         if (tid == 0) P[0] = 0;
-        if (stage) P[tid + 1] = int32_t(min(sum, kInf - 1));
-        if (flags) atomicOr(&s_flags, flags);
-        if (flow) {
-            int reach = stage ? min(max(max(a_in, ab_in), 0), pitch) : 0;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) reach = max(reach, __shfl_xor(reach, o));
-            if (lane == 0) atomicMax(&s_reach, reach);
+        if (stage) P[t] = min(sum, int(kInf) - 1);
+        if (tid == int(blockDim.x) - 1) {  // the last thread's sum is the chain's
+            int all = sum >= int(kInf) ? 2 : 0, most = 0;
+            for (int w = 0; w <= wave; ++w) all |= s_flags[w], most = max(most, s_reach[w]);
+            ws.flags[b] = all;
+            if (has_reach) prog[words - 1] = most;
         }
-    }
-    __syncthreads();
-    if (part == 0 && tid == 0) {
-        ws.flags[b] = s_flags;
-        const size_t n = tiles_of(L) * prog_words(pitch);
-        if (flow && blocks_of(L) > 1) ws.prog[size_t(b) * n + n - 1] = s_reach;
+        return;
     }
 
-    const int t = tid + 1;
-    if (t > L) return;
-    const int s_lo = part * kPreRows + 1, s_hi = min(s_lo + kPreRows - 1, L);
-    int between = 0;  // largest pair of the stages s + 1 .. t - 1
-    for (int j = s_hi + 1; j < t; ++j) between = max(between, s_pair[j]);
-    for (int s = s_hi; s >= s_lo; --s) {
-        if (t < s) continue;
-        const int keep = max(s_wd[t] + s_wab[s - 1] + s_of[s - 1], s_wd[s] + s_wab[s - 1] + s_ob[s - 1]);
-        const int ck = s_wd[t] + max(s_wa[s] + s_of[s - 1], between);
-        const size_t at = (size_t(b) * L + s - 1) * L + t - 1;
-        ws.mall[at] = keep;
-        ws.mnull[at] = ck;
-        // A first, weak feasibility frontier: a finite cell passes at least one of its two gates.
-        // The frontier kernel overwrites it with the exact one while the fill already runs;
-        // whichever value a reader sees is a valid lower bound.
-        ws.need[at] = min(keep, ck);
-        if (s < t) between = max(between, s_pair[s]);
+    for (size_t k = size_t(part) * blockDim.x + tid; k < words - (has_reach ? 1 : 0); k += size_t(parts) * blockDim.x) prog[k] = 0;
+    // Sizes are clamped into [0, 2^28] so that thresholds of a bad chain cannot overflow.
+    auto sz = [](int v) { return min(max(v, 0), 1 << 28); };
+    const int a0 = sz(a_in), a1 = sz(a_out), d1 = sz(d_out), ab1 = sz(ab_in), f1 = sz(of_in), b1 = sz(ob_in);
+    __shared__ int4 s_row[kPreThreads];  // what stage s brings to the thresholds of row s; w: what it needs where it lies between
+    s_row[tid] = make_int4(ab1 + f1, d1 + ab1 + b1, a1 + f1, a0 + a1 + f1);
+    const int s_lo = part * rows + 1, s_hi = min(s_lo + rows - 1, L);
+    const int upto = wave_scan(stage && t > s_hi ? a0 + a1 + f1 : 0, [](int x, int y) { return max(x, y); });
+    if (lane == 63) s_part[wave] = upto;
+    int between = __shfl_up(upto, 1);  // largest of the stages s_hi + 1 .. t - 1
+    if (lane == 0) between = 0;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) between = max(between, s_part[w]);
+    for (int top = s_hi; top >= s_lo; top -= 4) {
+        int4 row[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) row[u] = s_row[max(top - u, 1) - 1];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int s = top - u;
+            if (s < s_lo) break;  // uniform
+            if (s <= t && stage) {
+                const int keep = max(d1 + row[u].x, row[u].y), ck = d1 + max(row[u].z, between);
+                const size_t at = (size_t(b) * L + s - 1) * L + t - 1;
+                ws.mall[at] = keep;
+                ws.mnull[at] = ck;
+                // A first, weak feasibility frontier: a finite cell passes at least one of its two gates.
+                // The frontier kernel overwrites it with the exact one while the fill already runs;
+                // whichever value a reader sees is a valid lower bound.
+                ws.need[at] = min(keep, ck);
+                if (s < t) between = max(between, row[u].w);
+            }
+        }
     }
 }
 
@@ -3029,8 +3040,10 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
                hip_ok(hipStreamWaitEvent(st, side->join[k], 0));
     };
     auto enqueue = [&]() -> int {
-        const int pre_parts = (L + kPreRows - 1) / kPreRows, mark_parts = flow ? nblk * ((pitch + kMarkCols - 1) / kMarkCols) : 0;
-        hipLaunchKernelGGL(precompute_kernel, dim3(B, pre_parts + mark_parts), dim3(kPreThreads), 0, st, *chains, L, pitch, ws, cost);
+        const int pre_rows = ckpt_rules::precompute_rows(L, B), pre_parts = (L + pre_rows - 1) / pre_rows;
+        const int mark_parts = flow ? nblk * ((pitch + kMarkCols - 1) / kMarkCols) : 0;
+        hipLaunchKernelGGL(precompute_kernel, dim3(B, pre_parts + 1 + mark_parts), dim3(flow ? kPreThreads : (L + 63) / 64 * 64), 0, st,
+                           *chains, L, pitch, ws, pre_rows, pre_parts, cost);
         CKPT_AFTER_LAUNCH(CKPT_K_PRECOMPUTE);
         if (side) {
             if (!hip_ok(hipEventRecord(side->fork, st)) || !hip_ok(hipStreamWaitEvent(gs[1], side->fork, 0)))

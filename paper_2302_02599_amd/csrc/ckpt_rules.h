@@ -80,4 +80,11 @@ constexpr bool flow_bounds(int nblk, int chunks, long long B, bool samples) {
     return samples && (nblk >= 8 || (nblk >= 4 && B * chunks * nblk >= 1600));
 }
 
+// Rows of the threshold tables that a work-group of precompute_kernel writes.  Few, where work-groups are too few to fill the
+// chip and each is a serial chain of rows; more, where what a work-group costs to start and its reads of the chain count.
+// us with 4, 8, 16 and 32 rows, by the number of work-groups with 4:
+//   1 x 24 stages (6) 3.2, 3.2, 3.4, 4.1;  10 x 50 (130) 4.2, 4.4, 5.2, 6.7;  3 x 254 (192) 4.2, 4.5, 5.1, 6.7;  8 x 192 (384) 6.6, 7.6, 7.3, 9.4
+//   64 x 96 (1536) 9.6, 8.5, 7.8, 9.0;  256 x 24 (1536) 8.1, 6.6, 6.3, 6.6;  700 x 64 (11200) 11.8, 10.2, 9.0, 10.0;  20000 x 8 (40000) 29, 23, 23, 23
+constexpr int precompute_rows(int L, long long B) { return B * ((L + 3) / 4) <= 1024 ? 4 : 16; }
+
 }  // namespace ckpt_rules
