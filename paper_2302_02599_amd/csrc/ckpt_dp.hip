@@ -1605,11 +1605,11 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
 //     below it, there at all chunks that the chain's largest shift can reach; those waited for theirs, so everything it
 //     reads is finished.  The splits whose operands lie two diagonals down and more do not wait for the last one.
 // Everything read is read with device scope: lines may lie in this die's L2 with the marks in them.
-// Results bit for bit those of the other kernels.  us a solve, two launches a diagonal and this: 1 x 24 stages, 512 slots 71 and 40;
-// 5 x 53, 777 slots 233 and 113; 16 x 48, 1024 slots 211 and 141; 10 x 50, 500 slots 219 and 103; 1 x 192, 4096 slots 1141 and 666; 3 x 254,
-// 1500 slots 2156 and 1438 (the rule: ckpt_rules::flow_pays).
-// What bounds it: of 26000 clocks a diagonal (5 x 53 stages) rows take 10500, the 16 splits of the last neighbours 7800,
-// their operands and those of the rows 3700, the stores and the flag 2000.  Long chains are bound by vector issue and by the slots for
+// Results bit for bit those of the other kernels.  us a solve, two launches a diagonal and this: 1 x 24 stages, 512 slots 67 and 37;
+// 5 x 53, 777 slots 229 and 105; 16 x 48, 1024 slots 211 and 134; 10 x 50, 500 slots 214 and 94; 1 x 192, 4096 slots 1177 and 649; 3 x 254,
+// 1500 slots 2273 and 1407 (the rule: ckpt_rules::flow_pays).
+// What bounds it: of 26000 clocks a diagonal (5 x 53 stages) rows take 12000, the 16 splits of the last neighbours 8000 (500 each whether or
+// not their operands are read from LDS ahead), their first operands 2300, the stores and the flag 2000.  Long chains are bound by vector issue and by the slots for
 // work-groups (1 x 192 stages: a work-group takes 60000 clocks, 12000 of them rows, most of the rest round trips): four a compute unit.
 //
 // Inside, a candidate of row i stands plus P[i]: a right operand carries the prefix sum of its split, and a split costs one addition.
@@ -2263,33 +2263,20 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
                 if (threadIdx.x == 0) sb.left = 0;
             }
         }
-        if (!ready(1)) return;
-        // staged rows, 16 bytes a lane; row 7's operands of C_all
-        const int k4 = lane & 3, cb = wq * 16 + (lane >> 2), m = m0 + cb, mine = (cb + 16 * k4) & 63, lr = lane >> 4, lc = 4 * (lane & 15);
+        // The operands of the rows from the tiles (I, I) and (J, J).  Whatever is finished two diagonals down has waited for these, so
+        // they can be here before the last neighbours have finished: us a solve so and behind those, 5 x 53 stages, 777 slots
+        // 105 and 109;  10 x 50, 500 slots 94 and 99;  2 x 61, 3002 slots 168 and 173.  With bounds there are no registers to hold them meanwhile.
+        const int k4 = lane & 3, cb = wq * 16 + (lane >> 2), mine = (cb + 16 * k4) & 63, lr = lane >> 4, lc = 4 * (lane & 15);
         u32x4 st[4];
-        {
-            const FlowRow w = s.rows[T - 1];
-            const uint32_t o = uint32_t(k4) * rp + uint32_t(4 * m) - uint32_t(w.wab) + uint32_t(w.under);
-            alL = tld_dev(x.tab, 4 * m >= w.wab && k4 < cend ? o : kNoRead, 0);
-            alH = tld_dev(x.tab, 4 * m >= w.wab && k4 + 4 < cend ? o + 4 * rp : kNoRead, 0);
-        }
+        auto request_rows = [&] {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int4 it = s.item[(4 * wq + k) * 4 + lr];
-            const int col = m0 + lc - it.y;
-            st[k] = tld4_dev(x.tab, uint32_t(it.x) != kNoRead && col > -4 ? uint32_t(it.x) + 4u * uint32_t(max(col, 0)) : kNoRead);
-        }
-        half = 0;
-        int n = BOUNDS ? ne : __builtin_amdgcn_readfirstlane(s.n_edge);
-        if constexpr (BOUNDS) {
-            if (D > 2) {
-                lower_bounds<1>(x, smp, 0, n, [] {});
-                __syncthreads();
+            for (int k = 0; k < 4; ++k) {
+                const int4 it = s.item[(4 * wq + k) * 4 + lr];
+                const int col = m0 + lc - it.y;
+                st[k] = tld4_dev(x.tab, uint32_t(it.x) != kNoRead && col > -4 ? uint32_t(it.x) + 4u * uint32_t(max(col, 0)) : kNoRead);
             }
-            n = left_over(x, 0, n, D <= 2);
-        }
-        evaluated += n;
-        flow_splits<BOUNDS>(x, 0, n, key, half, low, [&] {
+        };
+        auto settle_rows = [&] {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int4 it = s.item[(4 * wq + k) * 4 + lr];
@@ -2322,6 +2309,38 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
                 colH[c2] = k4 + 4 > c2 ? v + uint32_t(s.Pj[c2]) : kHuge;
             }
             __syncthreads();  // the staged rows have been read
+        };
+        const bool early = !BOUNDS && D > 1;
+        if (early) {
+            if (D == 2) {
+                if (!ready(2)) return;
+            } else {
+                __syncthreads();  // the last splits have been read
+            }
+            request_rows();
+            settle_rows();
+        }
+        if (!ready(1)) return;
+        if (!early) request_rows();
+        {   // row 7's operands of C_all
+            const int m = m0 + cb;
+            const FlowRow w = s.rows[T - 1];
+            const uint32_t o = uint32_t(k4) * rp + uint32_t(4 * m) - uint32_t(w.wab) + uint32_t(w.under);
+            alL = tld_dev(x.tab, 4 * m >= w.wab && k4 < cend ? o : kNoRead, 0);
+            alH = tld_dev(x.tab, 4 * m >= w.wab && k4 + 4 < cend ? o + 4 * rp : kNoRead, 0);
+        }
+        half = 0;
+        int n = BOUNDS ? ne : __builtin_amdgcn_readfirstlane(s.n_edge);
+        if constexpr (BOUNDS) {
+            if (D > 2) {
+                lower_bounds<1>(x, smp, 0, n, [] {});
+                __syncthreads();
+            }
+            n = left_over(x, 0, n, D <= 2);
+        }
+        evaluated += n;
+        flow_splits<BOUNDS>(x, 0, n, key, half, low, [&] {
+            if (!early) settle_rows();
         });
         __syncthreads();
         const int rq = (wq >> 1) * 4, cq = (wq & 1) * 4;
