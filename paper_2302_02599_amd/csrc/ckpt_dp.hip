@@ -2365,6 +2365,118 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
     if (threadIdx.x == 0) __hip_atomic_store(prog + size_t(tile_index(nblk, I, J)) * words + band, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// ---------------------------------------------------------------------------
+// Short chains (chain_kernel): one launch, a work-group per chain, thread = column.  The cells of the whole table but its first
+// row (nobody reads that) stand in LDS, so nothing waits for memory but the first reads of the chain, and the thresholds are
+// computed by the first wave: no table of them, no marks, no tickets.  Rows bottom-up with a barrier each; left operands are
+// the thread's own cells of the row, right operands and those of C_all come from LDS at a shifted column.  A column
+// below zero reads column 0: its gate is closed.  The barriers wait for LDS and not for the stores.  Rows, cells and splits are
+// unrolled (with a loop over the rows, which needs a test a split, 1 x 8 stages, 64 slots take 11.1 us instead of 7.2), and what
+// belongs to a split is held by every thread (in scalar registers it spilled: 200 x 13, 500 slots 32 us instead of 24).
+// What bounds it: up to eight stages the launch and the first reads; longer chains vector issue, 6 instructions a split and
+// 20 a cell, by the few waves that a chain's columns fill.  1 x 8 stages, 64 slots 10.0 -> 7.2 us a solve, 200 x 13, 500 slots 49 -> 24
+// (the rule: ckpt_rules::chain_pays).
+// ---------------------------------------------------------------------------
+template <int N>
+__global__ void __launch_bounds__(1024) chain_kernel(ckpt_chains_t ch, int L, int pitch, Workspace ws, int32_t* __restrict__ cost,
+                                                      uint8_t* __restrict__ arg, unsigned long long* work) {
+    extern __shared__ uint32_t s_cell[];  // rows 1 .. L - 1
+    __shared__ int s_a[N + 1], s_d[N + 1], s_ab[N], s_of[N], s_ob[N];
+    __shared__ int s_P[N + 1], s_sh[N], s_wabs[N], s_fb[N];
+    __shared__ int2 s_gate[N][N];  // m_all, m_null
+    const int b = blockIdx.x, tid = threadIdx.x;
+    if (tid < 64) {
+        const bool tensor = tid <= L, stage = tid < L;
+        const size_t at = size_t(b) * L + tid;
+        const int a_in = tensor ? ch.wa[at + b] : 0, d_in = tensor ? (ch.wdelta ? ch.wdelta : ch.wa)[at + b] : 0;
+        const int ab_in = stage ? ch.wabar[at] : 0, f = stage ? ch.uf[at] : 0, bw = stage ? ch.ub[at] : 0;
+        const int of_in = stage && ch.of ? ch.of[at] : 0, ob_in = stage && ch.ob ? ch.ob[at] : 0;
+        const int a_next = __shfl_down(a_in, 1);
+        auto sz = [](int v) { return min(max(v, 0), 1 << 28); };  // as in precompute_kernel
+        const int fc = min(max(f, 0), (1 << 30) - 1), bc = min(max(bw, 0), 1 << 30);
+        if (tensor) s_a[tid] = sz(a_in), s_d[tid] = sz(d_in);
+        if (stage) {
+            s_ab[tid] = sz(ab_in), s_of[tid] = sz(of_in), s_ob[tid] = sz(ob_in);
+            s_sh[tid] = min(max(a_in, 0), pitch), s_wabs[tid] = min(max(ab_in, 0), pitch);
+            s_fb[tid] = int(min(kInf, uint32_t(fc) + uint32_t(bc)));
+        }
+        const int sum = wave_scan(fc, [](int x, int y) { return int(min(uint32_t(x) + uint32_t(y), kInf)); });
+        if (tid == 0) s_P[0] = 0;
+        if (stage) s_P[tid + 1] = min(sum, int(kInf) - 1);
+        int flags = 0;
+        if (f < 0 || bw < 0) flags |= 1;
+        if (f >= (1 << 30) || bw >= (1 << 30) || sum >= int(kInf)) flags |= 2;
+        for (int v : {a_in, d_in, ab_in, of_in, ob_in}) {
+            if (v < 0) flags |= 1;
+            if (v > (1 << 28)) flags |= 4;
+        }
+        if (stage && ab_in < a_next) flags |= 8;
+        flags = wave_scan(flags, [](int x, int y) { return x | y; });
+        if (tid == 63) {
+            ws.flags[b] = flags;
+            if (b == 0) ws.fault[0] = 0;
+        }
+        wave_settle();
+        for (int e = tid; e < N * N; e += 64) {
+            const int r = e / N, t = e % N + 1;  // stages r + 1 to t, counted from one
+            if (r >= t || t > L) continue;
+            int most = s_a[r + 1] + s_of[r];
+            for (int j = r + 2; j < t; ++j) most = max(most, s_a[j - 1] + s_a[j] + s_of[j - 1]);
+            s_gate[r][t - 1] = make_int2(max(s_d[t] + s_of[r], s_d[r + 1] + s_ob[r]) + s_ab[r], s_d[t] + most);
+        }
+    }
+    __syncthreads();
+    const uint32_t row4 = uint32_t(pitch) * 4u;
+    const char* cells = reinterpret_cast<const char*>(s_cell);
+    auto first = [&](int q) { return uint32_t(tri_row(L, q, 0) - L) * row4; };  // cell (q, j) is j rows further
+    const int m = tid, m4 = 4 * tid;
+    uint32_t from[N], P[N];  // of split q
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+        const int u = min(q, L - 1);
+        from[q] = first(q) + uint32_t(max(m4 - 4 * s_sh[u], 0)), P[q] = uint32_t(s_P[u]);
+    }
+    int32_t* ctab = cost + size_t(b) * (size_t(L) * (L + 1) / 2) * pitch;
+    uint8_t* atab = arg + size_t(b) * (size_t(L) * (L + 1) / 2) * pitch;
+    unrolled<N>([&](auto step) {
+        constexpr int i = N - 1 - decltype(step)::value;
+        if (i >= L) return;  // uniform
+        {
+            uint32_t val[N];
+            const uint32_t under = first(i + 1) + uint32_t(max(m4 - 4 * s_wabs[i], 0)), fb = uint32_t(s_fb[i]);
+#pragma unroll
+            for (int j = i; j < N; ++j) {
+                if (j >= L) break;  // uniform
+                const int2 gate = s_gate[i][j];
+                uint32_t best = kInf, pick = 0;
+#pragma unroll
+                for (int q = i + 1; q <= j; ++q) {
+                    const uint32_t v = val[q - 1] + (P[q] - P[i]) + *reinterpret_cast<const uint32_t*>(cells + from[q] + j * row4);
+                    pick = q == i + 1 || v < best ? uint32_t(q + 1) : pick;
+                    best = q == i + 1 ? v : min(v, best);
+                }
+                uint32_t all = fb;
+                if (j > i) all += *reinterpret_cast<const uint32_t*>(cells + under + j * row4);
+                const uint32_t ck = m >= gate.y ? best : kInf;
+                all = m >= gate.x ? all : kInf;
+                pick = all <= ck ? uint32_t(i + 1) : pick;
+                val[j] = min(min(all, ck), kInf);
+                pick = val[j] < kInf ? pick : 0u;
+                const size_t at = size_t(tri_row(L, i, j)) * pitch + m;
+                if (i > 0) s_cell[at - size_t(L) * pitch] = val[j];
+                ctab[at] = int32_t(val[j]);
+                atab[at] = uint8_t(pick);
+            }
+            if (work) count_work<true>(work, 2, 0, unsigned(L - i));
+        }
+        if (i > 0) {  // for LDS: the stores to memory are nobody's business
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+        }
+    });
+}
+
 using RowFn = void (*)(Ctx, int);
 template <int T, int DC, int... Rs>
 constexpr std::array<RowFn, sizeof...(Rs)> row_table(std::integer_sequence<int, Rs...>) {
@@ -2940,15 +3052,17 @@ bool helpers_ready(Device& d) {
     return d.helpers_ok;
 }
 
-// The frontier kernel keeps its triangle in LDS; above the default per-block limit it has to be
+// The frontier kernel keeps its triangle in LDS, chain_kernel its table; above the default per-block limit they have to be
 // allowed the size.  Set once (to the largest size any L can need); allocates nothing.
-bool allow_frontier_lds() {
+bool allow_lds() {
     static std::once_flag once;
     static bool ok = false;
     std::call_once(once, [] {
         ok = hip_ok(hipFuncSetAttribute(reinterpret_cast<const void*>(frontier_kernel),
                                         hipFuncAttributeMaxDynamicSharedMemorySize,
                                         int(ckpt_table_rows(CKPT_MAX_L) * sizeof(int32_t))));
+        for (const void* f : {reinterpret_cast<const void*>(chain_kernel<8>), reinterpret_cast<const void*>(chain_kernel<ckpt_rules::kChainStages>)})
+            ok = ok && hip_ok(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(ckpt_rules::kChainLds)));
     });
     return ok;
 }
@@ -2987,7 +3101,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     const Workspace ws = carve(workspace, L, pitch, B, workspace_bytes >= ckpt_workspace_bytes(L, M, B));
 
     const size_t frontier_lds = ckpt_table_rows(L) * sizeof(int32_t);
-    if (frontier_lds > 48 * 1024 && !allow_frontier_lds()) return CKPT_E_HIP;
+    if (frontier_lds > 48 * 1024 && !allow_lds()) return CKPT_E_HIP;
     constexpr int T = kT;
     const int nblk = (L + T - 1) / T;
     const int gx_row = (pitch + kRowWG - 1) / kRowWG;
@@ -3010,6 +3124,10 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     const bool would_split = groups > 1;
     // Small batches: every tile in one launch.  A schedule that the caller asks for is made of separate launches.
     const bool flow = groups == 1 && fused_rows && !want_ks && ckpt_rules::flow_pays(nblk, pitch / 64, B, ws.samp);
+    const size_t chain_lds = ckpt_rules::chain_lds(L, pitch);
+    const bool chain = fused_rows && !want_groups && !want_ks && frontier_mode == 0 && !(opts && opts->spin_limit) &&
+                       ckpt_rules::chain_pays(L, pitch);
+    if (chain && chain_lds > 48 * 1024 && !allow_lds()) return CKPT_E_HIP;
     const bool flow_bounds = ckpt_rules::flow_bounds(nblk, pitch / 64, B, ws.samp);
     if (prof) groups = 1;  // the event trail times one stream
     Device* dev = nullptr;
@@ -3059,6 +3177,12 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
                hip_ok(hipStreamWaitEvent(st, side->join[k], 0));
     };
     auto enqueue = [&]() -> int {
+        if (chain) {
+            hipLaunchKernelGGL(L <= 8 ? chain_kernel<8> : chain_kernel<ckpt_rules::kChainStages>, dim3(B), dim3(pitch), chain_lds, st, *chains, L,
+                               pitch, ws, cost, arg, work);
+            CKPT_AFTER_LAUNCH(CKPT_K_ROW);
+            return CKPT_OK;
+        }
         const int pre_rows = ckpt_rules::precompute_rows(L, B), pre_parts = (L + pre_rows - 1) / pre_rows;
         const int mark_parts = flow ? nblk * ((pitch + kMarkCols - 1) / kMarkCols) : 0;
         hipLaunchKernelGGL(precompute_kernel, dim3(B, pre_parts + 1 + mark_parts), dim3(flow ? kPreThreads : (L + 63) / 64 * 64), 0, st,
@@ -3191,7 +3315,7 @@ int ckpt_init(int device) {
     if (device >= 64) return CKPT_E_LIMIT;
     if (device != prev && !hip_ok(hipSetDevice(device))) return CKPT_E_HIP;
     Device& d = g_devices[device];
-    const bool ok = ensure_helpers(d) && ensure_scratch(d) != nullptr && allow_frontier_lds();
+    const bool ok = ensure_helpers(d) && ensure_scratch(d) != nullptr && allow_lds();
     if (device != prev && !hip_ok(hipSetDevice(prev))) return CKPT_E_HIP;
     return ok ? CKPT_OK : CKPT_E_HIP;
 }

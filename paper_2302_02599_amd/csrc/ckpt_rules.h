@@ -87,4 +87,16 @@ constexpr bool flow_bounds(int nblk, int chunks, long long B, bool samples) {
 //   64 x 96 (1536) 9.6, 8.5, 7.8, 9.0;  256 x 24 (1536) 8.1, 6.6, 6.3, 6.6;  700 x 64 (11200) 11.8, 10.2, 9.0, 10.0;  20000 x 8 (40000) 29, 23, 23, 23
 constexpr int precompute_rows(int L, long long B) { return B * ((L + 3) / 4) <= 1024 ? 4 : 16; }
 
+// Whether a solve is one launch with a work-group per chain (chain_kernel): up to so many stages, a thread for every column, and all
+// rows but the first have to fit into LDS.  A column's instructions grow with the cube of the stages and are one thread's: longer
+// chains are better cut into tiles.  us a solve by the kernels of longer chains and by this one:
+//   1 x 8 stages, 64 slots 10.0 and 7.2;  67 x 8, 184 slots 12.5 and 7.9;  60 x 8, 1000 slots 21 and 12;  3000 x 8, 300 slots 58 and 37
+//   1 x 10, 300 slots 21.8 and 12.4;  10 x 9, 900 slots 29 and 15;  3000 x 12, 200 slots 147 and 102;  1 x 13, 500 slots 25.4 and 20.7;
+//   200 x 13, 500 slots 49 and 24;  1000 x 13, 60 slots 58 and 21
+//   600 x 14, 400 slots 82.5 and 82.4;  1 x 16, 64 slots 19 and 29;  300 x 16, 300 slots 54 and 65;  2000 x 16, 60 slots 85 and 65
+constexpr int kChainStages = 13;
+constexpr long long kChainLds = 156 * 1024;
+constexpr long long chain_lds(int L, int pitch) { return 4LL * (L * (L - 1) / 2) * pitch; }
+constexpr bool chain_pays(int L, int pitch) { return L <= kChainStages && pitch <= 1024 && chain_lds(L, pitch) <= kChainLds; }
+
 }  // namespace ckpt_rules

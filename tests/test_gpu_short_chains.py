@@ -1,0 +1,48 @@
+"""Chains of up to thirteen stages, a work-group each with the table in LDS, against the oracle and against the kernels of
+longer chains (every schedule asked for with list_split is made of those)."""
+import pytest
+
+from gpu_util import assert_tables_equal
+from workloads import random_chain_batch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def amd():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2302_02599_amd as amd
+    amd.load_library()
+    return amd
+
+
+@pytest.mark.parametrize("L,M,B,size_hi", [
+    (1, 0, 1, 1), (1, 1023, 2, 9), (2, 63, 3, 5), (3, 64, 2, 100), (5, 300, 4, 0), (7, 130, 2, 40),  # no shift at all; shifts beyond the budget
+    (8, 1023, 3, 300), (8, 1024, 2, 300),  # the widest table with a thread a column, and the next one
+    (9, 64, 2, 13), (10, 700, 3, 90), (12, 447, 5, 2), (13, 511, 300, 30),  # more work-groups than compute units
+    (13, 512, 2, 30), (14, 300, 2, 30),  # beyond LDS; longer
+])
+def test_short_chains(amd, oracle_mod, L, M, B, size_hi):
+    import torch
+    batch = random_chain_batch(L, M, B, 4100 + L, size_hi=size_hi, time_hi=900, overheads=True, own_wdelta=True, zero_sizes=size_hi == 0)
+    print(f"case {batch.name}", flush=True)
+    sol = amd.solve(batch)
+    assert_tables_equal(oracle_mod, batch, sol, nthreads=4)
+    apart = amd.solve(batch, list_split=1)
+    assert torch.equal(sol.cost[..., :M + 1], apart.cost[..., :M + 1]) and torch.equal(sol.arg[..., :M + 1], apart.arg[..., :M + 1])
+
+
+@pytest.mark.parametrize("L", [1, 8, 13])
+def test_times_up_to_the_largest_and_flags(amd, L):
+    import torch
+    batch = random_chain_batch(L, 90, 4, 4200 + L, size_hi=9, time_hi=900)
+    batch.wabar[:] = batch.wa[:, 1:] + 1
+    batch.uf[1], batch.ub[1] = (1 << 30) // (L + 1), (1 << 30) - 1   # sums that reach 2^30
+    batch.uf[2, L - 1] = -5
+    batch.wa[3, L] = (1 << 28) + 1
+    batch.wabar[3, L - 1] = (1 << 28) + 1
+    sol, apart = amd.solve(batch, check=False), amd.solve(batch, check=False, list_split=1)
+    flags = [amd.ckpt_check_inputs(s.workspace, s.L, s.M, s.B).tolist() for s in (sol, apart)]
+    assert flags[0] == flags[1] and flags[0][0] == 0 and flags[0][2] & 1 and flags[0][3] & 4
+    assert torch.equal(sol.cost[:2, :, :91], apart.cost[:2, :, :91]) and torch.equal(sol.arg[:2, :, :91], apart.arg[:2, :, :91])
