@@ -53,7 +53,8 @@ constexpr bool rows_pass(int tiles, int pitch, int B) { return 320LL * tiles * p
 // diagonal.  One launch has no gaps between diagonals and a quarter of the instructions a row step, but a work-group
 // of four waves for every 64 columns of a tile, and it evaluates every feasible split: it pays while the chip is not full.
 // `wide` counts the work-groups of the first diagonal; `wide * nblk` grows with the splits that bounds would have dropped, which
-// they do better in tables of 1100 columns and more.  us a solve, two launches a diagonal and one:
+// they do better in tables of 1100 columns and more.  (Chains that chain_pays takes come here only where the caller asks for one
+// group.)  us a solve, two launches a diagonal and one:
 //   one block: 14 x 7 stages, 780 slots (182 by that measure) 20 and 16;  67 x 8, 184 slots (201) 15 and 14;  100 x 6, 810 slots (1300) 20 and 24
 //   two: 67 x 9, 524 slots (1206) 45 and 38;  126 x 16, 315 slots (1260) 44 and 44;  65 x 15, 829 slots (1690) 52 and 59
 //   three: 37 x 20, 1074 slots (1887) 93 and 76;  19 x 24, 2245 slots (2052) 97 and 100;  77 x 24, 791 slots (3003) 98 and 106
