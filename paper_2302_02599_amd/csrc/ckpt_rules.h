@@ -74,11 +74,14 @@ constexpr bool flow_pays(int nblk, int chunks, long long B, bool samples) {
     return wide <= 3500 && wide * nblk <= (chunks >= 18 ? 33000 : 60000);
 }
 
-// Whether it drops splits by bounds: where there are enough of them.  us a solve without and with: 4 x 50 stages, 2004 slots (wide 896) 143 and
-// 150;  2 x 61, 3002 slots (752) 163 and 168;  8 x 58, 1659 slots (1664) 208 and 194;  36 x 56, 643 slots (2772) 267 and 236;  1 x 139, 1609
-// slots (468) 357 and 324;  4 x 112, 1967 slots (1736) 475 and 371; narrow tables lose a little, 7 x 236, 263 slots 1104 and 1155.
+// Whether it drops splits by bounds: where there are enough of them.  us a solve without and with, four to seven blocks by the same measure:
+//   4 x 50 stages, 2004 slots (896) 134 and 144;  6 x 48, 2048 slots (1188) 132 and 139;  12 x 48, 1024 slots (1224) 120 and 117;
+//   10 x 33, 1700 slots (1350) 110 and 111;  5 x 45, 3000 slots (1410) 153 and 158;  14 x 42, 1024 slots (1428) 128 and 121;  14 x 50, 900 slots
+//   (1470) 155 and 141;  16 x 48, 1024 slots (1632) 143 and 134;  9 x 33, 2500 slots (1800) 136 and 134;  36 x 56, 643 slots (2772) 263 and 225
+// Eight blocks and more, before what belongs to the rows was read early without bounds (4 % of some): 8 x 58, 1659 slots (1664) 208 and 194;
+// 1 x 139, 1609 slots (468) 357 and 324;  4 x 112, 1967 slots (1736) 475 and 371; narrow tables lose a little, 7 x 236, 263 slots 1104 and 1155.
 constexpr bool flow_bounds(int nblk, int chunks, long long B, bool samples) {
-    return samples && (nblk >= 8 || (nblk >= 4 && B * chunks * nblk >= 1600));
+    return samples && (nblk >= 8 || (nblk >= 4 && B * chunks * nblk >= 1420));
 }
 
 // Rows of the threshold tables that a work-group of precompute_kernel writes.  Few, where work-groups are too few to fill the
