@@ -213,7 +213,8 @@ int ckpt_solve_batched_noalloc(const ckpt_chains_t* chains, int L, int M, int B,
  *                            of table loads of kind k (256 per wave and load), entry 2k + 1 =
  *                            bytes stored (320 per wave and cell: cost and candidate number).
  *                            Work that the feasibility tests skip is not counted.
- * CKPT_K_ROW also counts the kernel that takes small batches in one launch, block products and rows.
+ * CKPT_K_ROW also counts the kernels that take small batches in one launch, block products and rows, and chains of a few
+ * stages with their precomputation (then there is no CKPT_K_PRECOMPUTE).
  * Creates and destroys events and a small device buffer (allocates); not for latency-critical
  * callers.  Returns as ckpt_solve_batched.
  */

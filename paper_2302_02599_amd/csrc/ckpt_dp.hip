@@ -55,6 +55,8 @@ inline bool hip_ok(hipError_t e) {
 // A row is finished by its near-i splits, the partial minimum of gemm_kernel, its near-j splits, then C_all and the
 // two gates.  Launch order per D: gemm (D >= 2), which also finishes row T-1, then tile_rows_kernel, one launch for
 // rows T-2 .. 0 (T-1 .. 0 for D < 2) of every tile.  row_kernel, one launch per row, is the alternative schedule.
+// Batches that leave the chip half empty take all tiles in one launch (flow_kernel), short chains are one launch altogether
+// (chain_kernel); ckpt_rules.h says which.
 //
 // Reads at m - shift are not bounds-checked against m < shift: a lane whose m is below
 // a shift of one of its splits is below m_null (m_all for C_all) of that cell, because
@@ -75,10 +77,10 @@ inline bool hip_ok(hipError_t e) {
 //                          of 64 columns; tiles = nblk (nblk + 1) / 2, chunks = pitch / 64; last word: bands of
 //                          the tile that work-groups have taken.  flow_kernel: 1 where the tile is finished; last
 //                          words: of the first tile, tickets of the chain; of the last one, the chain's largest shift
-//   fault [1]      int32   set when a bounded wait inside tile_rows_kernel expired
+//   fault [1]      int32   set when a bounded wait inside tile_rows_kernel or flow_kernel expired
 //   samp  [B][4 nblk (nblk + 1)][pitch / kG][8] int32  every kG-th column of the finished cells, eight cells of a
 //                          row side by side (see gemm_kernel); left out where they are not used or do not fit
-// prog and fault are cleared by precompute_kernel at the start of every solve.
+// prog and fault are cleared by precompute_kernel at the start of every solve.  chain_kernel uses flags and fault only.
 struct Workspace {
     int32_t* P;
     int32_t* fb;
