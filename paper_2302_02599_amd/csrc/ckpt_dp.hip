@@ -95,7 +95,7 @@ struct Workspace {
     int32_t* samp;  // null: no samples are kept
 };
 
-constexpr int kG = 16;  // columns between samples
+using ckpt_rules::kG;  // columns between samples
 constexpr double kKeyBase = 0x1p44;
 
 constexpr int kBand = kRowWG;  // columns of m per work-group of the row kernels
@@ -661,8 +661,8 @@ __global__ void __launch_bounds__(64 * halves_of(KS) * CH * KS, 4) gemm_kernel(C
         uint32_t ub[R][T];
         const int stride = 16 * KS;
         auto split_of = [&](int k0) { return min(k0 + x, nq - 1); };
-        auto below = [&](int sh) { return ((kk * kG + 1 - sh) >> 4) - 1; };
-        auto above = [&](int sh) { return (kk * kG + kG - 1 - sh) >> 4; };
+        auto below = [&](int sh) { return ckpt_rules::right_below(kk, sh); };
+        auto above = [&](int sh) { return ckpt_rules::right_above(kk, sh); };
         const int kend = passes * 16;
         // Any splits give an upper bound; the best ones are mostly those that finished neighbours took at the end of
         // the sub-chunk: the first row of the next tile down (8 cells), the last column of the tile to the left (4), and four
@@ -1604,7 +1604,8 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
 //     finds the mark reads again.  These reads are requested a row ahead, and mostly find the band below finished.
 //     A tile's cells are marked by the work-group of the tile to its left, those of the first diagonal by precompute_kernel.
 //   - Other tiles: a flag per tile and 64 columns, set behind its last store.  A tile waits for the tiles to its left and
-//     below it, there at all chunks that the chain's largest shift can reach; those waited for theirs, so everything it
+//     below it, there at all chunks that the chain's largest shift can reach (upper bounds read samples up to 15 columns further
+//     down: ckpt_rules::sample_chunks); those waited for theirs, so everything it
 //     reads is finished.  The splits whose operands lie two diagonals down and more do not wait for the last one.
 // Everything read is read with device scope: lines may lie in this die's L2 with the marks in them.
 // Results bit for bit those of the other kernels.  us a solve, two launches a diagonal and this: 1 x 24 stages, 512 slots 67 and 37;
@@ -1937,10 +1938,10 @@ __device__ __forceinline__ void upper_bounds(Flow<true>& x, rsrc_t smp, int firs
     const int half = x.wq & 1, slice = x.wq >> 1, sub = x.lane >> 4, v = x.lane & 15, kk = x.m0 / kG + sub;
     const int e = first + (2 * (16 * slice + v) + 1) * n / 64;
     const int2 qp = x.bounds->qp[e];
-    const int sh = x.s.split[1][e].y >> 2, kr = ((kk * kG + 1 - sh) >> 4) - 1;
+    const int kl = ckpt_rules::left_below(kk), kr = ckpt_rules::right_below(kk, x.s.split[1][e].y >> 2);
     FlowBound w;
-    fetch_bound(x, smp, w, qp.x, half, kk - 1, kr);
-    settle_bound(x, w, uint32_t(qp.y), kk - 1, kr);
+    fetch_bound(x, smp, w, qp.x, half, kl, kr);
+    settle_bound(x, w, uint32_t(qp.y), kl, kr);
     // minimum over the 16 lanes of a sub-chunk, as in gemm_kernel
     uint32_t h[R * T / 2];
 #pragma unroll
@@ -1972,8 +1973,8 @@ __device__ __forceinline__ void lower_bounds(Flow<true>& x, rsrc_t smp, int firs
     auto request = [&](int k) {
         const int e = first + min(k + v, n - 1);
         qp = x.bounds->qp[e];
-        kr = (kk * kG + kG - 1 - (x.s.split[1][e].y >> 2)) >> 4;
-        fetch_bound(x, smp, next, qp.x, half, kk, kr);
+        kr = ckpt_rules::right_above(kk, x.s.split[1][e].y >> 2);
+        fetch_bound(x, smp, next, qp.x, half, ckpt_rules::left_above(kk), kr);
     };
     if (slice < SLICES) request(16 * slice);
     between();
@@ -1988,7 +1989,7 @@ __device__ __forceinline__ void lower_bounds(Flow<true>& x, rsrc_t smp, int firs
         const uint32_t Pq = uint32_t(qp.y);
         const int kc = kr;
         if (k + 16 * SLICES < n) request(k + 16 * SLICES);
-        settle_bound(x, w, Pq, kk, kc);
+        settle_bound(x, w, Pq, ckpt_rules::left_above(kk), kc);
         // a left operand not above ub - right for some column; nothing above zero is lost where the difference would be negative
         bool on = false;
 #pragma unroll
@@ -2182,8 +2183,8 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
 #pragma unroll
     for (int r = 0; r < T; ++r) tile_need = min(tile_need, s.rows[r].need);
     const bool empty = m0 + 63 < tile_need;  // below the frontier of every cell
-    auto ready = [&](int back) {  // the neighbours back diagonals down
-        if (wq == 0 && !wait_tiles(x, tile_index(nblk, I, J - back), tile_index(nblk, I + back, J), band, (s.reach + 63) >> 6)) {
+    auto ready = [&](int back, int below) {  // the neighbours back diagonals down, this band and `below` chunks under it
+        if (wq == 0 && !wait_tiles(x, tile_index(nblk, I, J - back), tile_index(nblk, I + back, J), band, below)) {
             if (lane == 0) {
                 __hip_atomic_store(c.ws.fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 s.fault = 1;
@@ -2192,13 +2193,14 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
         __syncthreads();
         return s.fault == 0;
     };
+    const int operands = ckpt_rules::operand_chunks(s.reach), samples = ckpt_rules::sample_chunks(s.reach);
     uint32_t leftL[T], leftH[T], colL[T], colH[T], alL = 0, alH = 0;
 #pragma unroll
     for (int r = 0; r < T; ++r) leftL[r] = leftH[r] = colL[r] = colH[r] = 0;
     int evaluated = 0;
     if (empty) {
         // the neighbours first: one of them marks these cells, and whoever sees this tile finished relies on both
-        if (D > 0 && !ready(1)) return;
+        if (D > 0 && !ready(1, operands)) return;
         for (int k = wq; k < 2 * T; k += 4) {
             const int e = k * 4 + (lane >> 4), r = e >> 3, cc = e & 7;
             const bool is = i0 + r < L && cc < cend && (D != 0 || cc >= r);
@@ -2237,7 +2239,7 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
             if (t == 0) sb.left = 0;
         }
         if (D > 2) {
-            if (!ready(2)) return;
+            if (!ready(2, BOUNDS ? samples : operands)) return;
             int n = BOUNDS ? ni : __builtin_amdgcn_readfirstlane(s.n_inner);
             if constexpr (BOUNDS) {
                 if (n > 16) {
@@ -2315,14 +2317,14 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
         const bool early = !BOUNDS && D > 1;
         if (early) {
             if (D == 2) {
-                if (!ready(2)) return;
+                if (!ready(2, operands)) return;
             } else {
                 __syncthreads();  // the last splits have been read
             }
             request_rows();
             settle_rows();
         }
-        if (!ready(1)) return;
+        if (!ready(1, operands)) return;
         if (!early) request_rows();
         {   // row 7's operands of C_all
             const int m = m0 + cb;

@@ -84,6 +84,22 @@ constexpr bool flow_bounds(int nblk, int chunks, long long B, bool samples) {
     return samples && (nblk >= 8 || (nblk >= 4 && B * chunks * nblk >= 1420));
 }
 
+// Samples of the finished cells: of every kG columns the last one, sample k is column kG k + kG - 1.  Sub-chunk kk holds columns
+// kG kk .. kG kk + kG - 1.  Costs do not rise with m, so the operands of a split of shift `shift` are, in all columns of the
+// sub-chunk, at most (first column, upper bounds) what the samples of *_below say and at least (last column) what those of *_above say.
+// Below zero: no sample, the operand is infeasible.
+constexpr int kG = 16;
+constexpr int left_below(int kk) { return kk - 1; }
+constexpr int right_below(int kk, int shift) { return ((kk * kG + 1 - shift) >> 4) - 1; }
+constexpr int left_above(int kk) { return kk; }
+constexpr int right_above(int kk, int shift) { return (kk * kG + kG - 1 - shift) >> 4; }
+
+// Chunks of 64 columns below its own that a work-group of flow_kernel waits for at other tiles, by the chain's largest shift:
+// those of the operands, column m0 - reach at the lowest, and where it reads samples for upper bounds too, column
+// m0 - reach - 15 at the lowest (m0 - 1 without shifts).
+constexpr int operand_chunks(int reach) { return (reach + 63) >> 6; }
+constexpr int sample_chunks(int reach) { return (reach + kG - 1 + 63) >> 6; }
+
 // Rows of the threshold tables that a work-group of precompute_kernel writes.  Few, where work-groups are too few to fill the
 // chip and each is a serial chain of rows; more, where what a work-group costs to start and its reads of the chain count.
 // us with 4, 8, 16 and 32 rows, by the number of work-groups with 4:

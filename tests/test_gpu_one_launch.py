@@ -1,8 +1,10 @@
 """The kernel that fills small batches in one launch, against the oracle and against the kernels that take two launches a
 block diagonal (every schedule asked for with list_split is made of those)."""
+import numpy as np
 import pytest
 
 from gpu_util import assert_tables_equal
+from paper_2302_02599_amd.binding import Solution
 from workloads import random_chain_batch
 
 pytestmark = pytest.mark.gpu
@@ -50,3 +52,30 @@ def test_both_sides_of_the_rule(amd, L, M, B):
     batch = random_chain_batch(L, M, B, 2300 + L + B, size_hi=M // 20, time_hi=900)
     sol, apart = amd.solve(batch), amd.solve(batch, list_split=2)
     assert torch.equal(sol.cost[..., :M + 1], apart.cost[..., :M + 1]) and torch.equal(sol.arg[..., :M + 1], apart.arg[..., :M + 1])
+
+
+@pytest.mark.parametrize("largest", [0, 50, 63, 64, 128])
+def test_samples_below_the_lowest_operand(amd, oracle_mod, largest):
+    """Splits dropped by bounds where a sample lies in the chunk below that of the lowest operand: no shift at all, but
+    overheads, so that cells become feasible in different columns; and largest shifts at the edge of a chunk.  Into tables and a workspace
+    that hold a solve of much smaller costs: whatever is read too early is too low."""
+    import torch
+    L, M, B = 66, 1100, 5  # nine blocks, 18 chunks
+    batch = random_chain_batch(L, M, B, 2500 + largest, size_hi=60 if largest else 500, time_hi=100000, overheads=True, own_wdelta=True)
+    batch.wa[:] = np.random.default_rng(2600 + largest).choice([0, 1, largest // 2, largest], size=batch.wa.shape)
+    batch.wa[:, 1:-1:5] = largest
+    batch.wabar[:] = batch.wa[:, 1:]
+    dev = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in batch.dense()]
+    cost = torch.empty((B, amd.ckpt_table_rows(L), amd.ckpt_row_pitch(M)), dtype=torch.int32, device="cuda")
+    arg = torch.empty(cost.shape, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(amd.ckpt_workspace_bytes(L, M, B), dtype=torch.uint8, device="cuda")
+
+    def fill(uf, ub):
+        amd.ckpt_solve_batched(uf, ub, *dev[2:4], L, M, B, cost, arg, ws, wdelta=dev[4], of=dev[5], ob=dev[6])
+        assert amd.ckpt_check_inputs(ws, L, M, B).tolist() == [0] * B
+
+    print(f"case {batch.name}", flush=True)
+    for _ in range(3):
+        fill(torch.ones_like(dev[0]), torch.ones_like(dev[1]))
+        fill(*dev[:2])
+        assert_tables_equal(oracle_mod, batch, Solution(L, M, B, cost, arg, ws), nthreads=4)

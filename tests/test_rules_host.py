@@ -12,6 +12,12 @@ SHIM = """
 extern "C" int ask() { return ckpt_rules::kAsk; }
 extern "C" int spread_split(int x, int slice, int KS, int nq) { return ckpt_rules::spread_split(x, slice, KS, nq); }
 extern "C" int asked_split(int x, int number, int qlo, int nq) { return ckpt_rules::asked_split(x, number, qlo, nq); }
+extern "C" int operand_chunks(int reach) { return ckpt_rules::operand_chunks(reach); }
+extern "C" int sample_chunks(int reach) { return ckpt_rules::sample_chunks(reach); }
+extern "C" int left_below(int kk) { return ckpt_rules::left_below(kk); }
+extern "C" int left_above(int kk) { return ckpt_rules::left_above(kk); }
+extern "C" int right_below(int kk, int shift) { return ckpt_rules::right_below(kk, shift); }
+extern "C" int right_above(int kk, int shift) { return ckpt_rules::right_above(kk, shift); }
 extern "C" int rows_pass(int tiles, int pitch, int B) { return ckpt_rules::rows_pass(tiles, pitch, B); }
 """
 
@@ -70,3 +76,24 @@ def test_rows_pass_through_the_caches_by_their_size(rules, tiles, pitch, B, pass
     """128 MB of rows in one diagonal: 64 x 96 stages, 8 x 192 and the smallest batch that is split unasked are above it,
     batches of the sizes that only a caller splits below."""
     assert rules.rows_pass(tiles, pitch, B) == passing
+
+
+def test_whatever_a_work_group_reads_of_other_tiles_has_been_waited_for(rules):
+    """Every shift up to the chain's largest one, every sub-chunk of a band: the lowest column of an operand and of a sample lie in
+    chunks that are waited for, no chunk is waited for in vain, nothing is read above the band, and a sample stands on
+    the right side of the columns that it bounds."""
+    band = 12
+    m0, first, last = 64 * band, 4 * band, 4 * band + 3
+    column = lambda k: 16 * k + 15
+    for reach in range(500):
+        operands, samples = 64 * (band - rules.operand_chunks(reach)), 64 * (band - rules.sample_chunks(reach))
+        assert operands <= m0 - reach and (reach == 0 or operands > m0 - reach - 64)
+        lowest = m0
+        for shift in {0, reach, *range(max(0, reach - 80), reach)}:
+            for kk in range(first, last + 1):
+                assert column(rules.left_below(kk)) == 16 * kk - 1 and column(rules.left_above(kk)) == 16 * kk + 15
+                below, above = column(rules.right_below(kk, shift)), column(rules.right_above(kk, shift))
+                assert below <= 16 * kk - shift < below + 17 and above - 16 < 16 * kk + 15 - shift <= above, (kk, shift)
+                assert operands <= above <= m0 + 63, (reach, shift, kk)
+                lowest = min(lowest, below, column(rules.left_below(kk)))
+        assert samples <= lowest < samples + 64, (reach, lowest)
