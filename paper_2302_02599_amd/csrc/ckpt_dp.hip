@@ -1637,7 +1637,7 @@ __device__ __forceinline__ u32x4 tld4_dev(rsrc_t tab, uint32_t voff) {
 }
 
 constexpr uint32_t kHuge = 0xbfffffffu;  // never smaller than a candidate that counts; no overflow on top of a cost
-constexpr int kFar = 0x7f000000;         // a byte offset beyond every row
+using ckpt_rules::kFar;                  // a byte offset beyond every row
 constexpr int kFlow = 256;               // threads of a work-group: four waves, 64 columns of a tile
 constexpr int kBatch = 4;                // splits whose operands pass through LDS together
 constexpr int kLeft = kT * (kT + 1) / 2;

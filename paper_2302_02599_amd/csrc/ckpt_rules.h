@@ -74,6 +74,11 @@ constexpr bool flow_pays(int nblk, int chunks, long long B, bool samples) {
     return wide <= 3500 && wide * nblk <= (chunks >= 18 ? 33000 : 60000);
 }
 
+// Byte offset in flow_kernel that lies beyond every row: the column of a cell that does not exist, negative where it is the left side of
+// a difference, and the shift of an entry that reads nothing.  A column less a shift has to stay a 32-bit number with both,
+// and beyond every row with one of them; flow_pays takes no table of more than 1125 chunks.
+constexpr int kFar = 0x3f000000;
+
 // Whether it drops splits by bounds: where there are enough of them.  us a solve without and with, four to seven blocks by the same measure:
 //   4 x 50 stages, 2004 slots (896) 134 and 144;  6 x 48, 2048 slots (1188) 132 and 139;  12 x 48, 1024 slots (1224) 120 and 117;
 //   10 x 33, 1700 slots (1350) 110 and 111;  5 x 45, 3000 slots (1410) 153 and 158;  14 x 42, 1024 slots (1428) 128 and 121;  14 x 50, 900 slots

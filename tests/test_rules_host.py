@@ -18,6 +18,8 @@ extern "C" int left_below(int kk) { return ckpt_rules::left_below(kk); }
 extern "C" int left_above(int kk) { return ckpt_rules::left_above(kk); }
 extern "C" int right_below(int kk, int shift) { return ckpt_rules::right_below(kk, shift); }
 extern "C" int right_above(int kk, int shift) { return ckpt_rules::right_above(kk, shift); }
+extern "C" int far_offset() { return ckpt_rules::kFar; }
+extern "C" int flow_pays(int nblk, int chunks, long long B, int samples) { return ckpt_rules::flow_pays(nblk, chunks, B, samples); }
 extern "C" int rows_pass(int tiles, int pitch, int B) { return ckpt_rules::rows_pass(tiles, pitch, B); }
 """
 
@@ -97,3 +99,18 @@ def test_whatever_a_work_group_reads_of_other_tiles_has_been_waited_for(rules):
                 assert operands <= above <= m0 + 63, (reach, shift, kk)
                 lowest = min(lowest, below, column(rules.left_below(kk)))
         assert samples <= lowest < samples + 64, (reach, lowest)
+
+
+def test_differences_with_the_far_offset_are_32_bit_numbers_beyond_every_row(rules):
+    """In the widest table that the one launch takes: a missing column less any shift, any column less the shift that reads
+    nothing, and the one less the other."""
+    widest = max(chunks for nblk in range(1, 33) for samples in (0, 1) for chunks in range(1, 4096)
+                 if rules.flow_pays(nblk, chunks, ctypes.c_longlong(1), samples))
+    assert widest == 1125
+    far, row = rules.far_offset(), 4 * 64 * widest  # bytes of a row; columns and shifts lie in 0 .. row
+    for column in (-far, 0, row - 4):
+        for shift in (0, row, far):
+            assert -2**31 <= column - shift < 2**31 and -2**31 <= shift - column < 2**31, (column, shift)
+            if column < 0 or shift == far:
+                assert column - shift <= -row - 16, (column, shift)
+    assert far - row >= row  # cells that do not exist, from the bands below
