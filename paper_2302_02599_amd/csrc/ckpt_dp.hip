@@ -2430,15 +2430,18 @@ __global__ void __launch_bounds__(1024) chain_kernel(ckpt_chains_t ch, int L, in
         }
     }
     __syncthreads();
-    const uint32_t row4 = uint32_t(pitch) * 4u;
+    const int row4 = pitch * 4;
     const char* cells = reinterpret_cast<const char*>(s_cell);
-    auto first = [&](int q) { return uint32_t(tri_row(L, q, 0) - L) * row4; };  // cell (q, j) is j rows further
     const int m = tid, m4 = 4 * tid;
-    uint32_t from[N], P[N];  // of split q
+    // The column of cell (q, q) that a shift of `shift` slots leads to; cell (q, j) is j - q rows further.
+    auto column = [&](int q, int shift) { return cells + ckpt_rules::chain_row(L, min(q, L)) * row4 + max(m4 - 4 * shift, 0); };
+    auto cell = [&](const char* at, int down) { return *reinterpret_cast<const uint32_t*>(at + down * row4); };
+    const char* from[N];  // of split q
+    uint32_t P[N];
 #pragma unroll
     for (int q = 0; q < N; ++q) {
         const int u = min(q, L - 1);
-        from[q] = first(q) + uint32_t(max(m4 - 4 * s_sh[u], 0)), P[q] = uint32_t(s_P[u]);
+        from[q] = column(max(q, 1), s_sh[u]), P[q] = uint32_t(s_P[u]);
     }
     int32_t* ctab = cost + size_t(b) * (size_t(L) * (L + 1) / 2) * pitch;
     uint8_t* atab = arg + size_t(b) * (size_t(L) * (L + 1) / 2) * pitch;
@@ -2447,7 +2450,8 @@ __global__ void __launch_bounds__(1024) chain_kernel(ckpt_chains_t ch, int L, in
         if (i >= L) return;  // uniform
         {
             uint32_t val[N];
-            const uint32_t under = first(i + 1) + uint32_t(max(m4 - 4 * s_wabs[i], 0)), fb = uint32_t(s_fb[i]);
+            const char* under = column(i + 1, s_wabs[i]);
+            const uint32_t fb = uint32_t(s_fb[i]);
 #pragma unroll
             for (int j = i; j < N; ++j) {
                 if (j >= L) break;  // uniform
@@ -2455,12 +2459,12 @@ __global__ void __launch_bounds__(1024) chain_kernel(ckpt_chains_t ch, int L, in
                 uint32_t best = kInf, pick = 0;
 #pragma unroll
                 for (int q = i + 1; q <= j; ++q) {
-                    const uint32_t v = val[q - 1] + (P[q] - P[i]) + *reinterpret_cast<const uint32_t*>(cells + from[q] + j * row4);
+                    const uint32_t v = val[q - 1] + (P[q] - P[i]) + cell(from[q], j - q);
                     pick = q == i + 1 || v < best ? uint32_t(q + 1) : pick;
                     best = q == i + 1 ? v : min(v, best);
                 }
                 uint32_t all = fb;
-                if (j > i) all += *reinterpret_cast<const uint32_t*>(cells + under + j * row4);
+                if (j > i) all += cell(under, j - i - 1);
                 const uint32_t ck = m >= gate.y ? best : kInf;
                 all = m >= gate.x ? all : kInf;
                 pick = all <= ck ? uint32_t(i + 1) : pick;

@@ -122,6 +122,8 @@ constexpr int precompute_rows(int L, long long B) { return B * ((L + 3) / 4) <= 
 constexpr int kChainStages = 13;
 constexpr long long kChainLds = 156 * 1024;
 constexpr long long chain_lds(int L, int pitch) { return 4LL * (L * (L - 1) / 2) * pitch; }
+// Row of cell (q, q) in LDS, cell (q, j) stands j - q rows further; the first row of the table (q = 0) is not kept.
+constexpr int chain_row(int L, int q) { return (q - 1) * L - q * (q - 1) / 2; }
 constexpr bool chain_pays(int L, int pitch) { return L <= kChainStages && pitch <= 1024 && chain_lds(L, pitch) <= kChainLds; }
 
 }  // namespace ckpt_rules

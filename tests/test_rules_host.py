@@ -20,6 +20,9 @@ extern "C" int right_below(int kk, int shift) { return ckpt_rules::right_below(k
 extern "C" int right_above(int kk, int shift) { return ckpt_rules::right_above(kk, shift); }
 extern "C" int far_offset() { return ckpt_rules::kFar; }
 extern "C" int flow_pays(int nblk, int chunks, long long B, int samples) { return ckpt_rules::flow_pays(nblk, chunks, B, samples); }
+extern "C" int chain_stages() { return ckpt_rules::kChainStages; }
+extern "C" int chain_row(int L, int q) { return ckpt_rules::chain_row(L, q); }
+extern "C" long long chain_lds(int L, int pitch) { return ckpt_rules::chain_lds(L, pitch); }
 extern "C" int rows_pass(int tiles, int pitch, int B) { return ckpt_rules::rows_pass(tiles, pitch, B); }
 """
 
@@ -114,3 +117,13 @@ def test_differences_with_the_far_offset_are_32_bit_numbers_beyond_every_row(rul
             if column < 0 or shift == far:
                 assert column - shift <= -row - 16, (column, shift)
     assert far - row >= row  # cells that do not exist, from the bands below
+
+
+def test_rows_of_a_short_chain_in_lds(rules):
+    """Cells (q, j), 1 <= q <= j < L, one row each in the order of the table and no other; where a row begins is never
+    below the first one nor beyond the end, also for the row below the last (read by nobody)."""
+    rules.chain_lds.restype = ctypes.c_longlong
+    for L in range(1, rules.chain_stages() + 1):
+        rows = rules.chain_lds(L, 64) // (4 * 64)
+        assert [rules.chain_row(L, q) + j - q for q in range(1, L) for j in range(q, L)] == list(range(rows)), L
+        assert all(0 <= rules.chain_row(L, q) <= rows for q in range(1, L + 1)), L
