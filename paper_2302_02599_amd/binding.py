@@ -124,15 +124,27 @@ def ckpt_workspace_bytes(L: int, M: int, B: int) -> int:
     return load_library().ckpt_workspace_bytes(L, M, B)
 
 
-@functools.lru_cache(maxsize=64, typed=True)
-def _sizes(L, M, B):
-    """Elements of a table and bytes of workspace."""
+@functools.lru_cache(maxsize=64)
+def _sizes_of_ints(L, M, B):
     return ckpt_table_elems(L, M, B), ckpt_workspace_bytes(L, M, B)
 
 
-@functools.lru_cache(maxsize=64, typed=True)
-def _walk_bytes(L, B):
+@functools.lru_cache(maxsize=64)
+def _walk_bytes_of_ints(L, B):
     return ckpt_schedule_workspace_bytes(L, B)
+
+
+# Only ints are looked up.  Whatever else counts as one is asked for its value in every call: a tensor of one element is hashed
+# by its identity and may hold another number by now, an array is not hashed at all.
+def _sizes(L, M, B):
+    """Elements of a table and bytes of workspace."""
+    if type(L) is type(M) is type(B) is int:
+        return _sizes_of_ints(L, M, B)
+    return _sizes_of_ints.__wrapped__(L, M, B)
+
+
+def _walk_bytes(L, B):
+    return _walk_bytes_of_ints(L, B) if type(L) is type(B) is int else _walk_bytes_of_ints.__wrapped__(L, B)
 
 
 # The entry points are called between kernels of a few microseconds, so what they do in Python counts: each
@@ -169,8 +181,9 @@ def _marshal(uf, ub, wa, wabar, L, M, B, cost, arg, workspace, wdelta, of, ob, s
     per_stage, per_tensor = (B, L), (B, L + 1)
     ch = _Chains(_dev_ptr(torch, uf, "uf", per_stage), _dev_ptr(torch, ub, "ub", per_stage),
                  _dev_ptr(torch, wa, "wa", per_tensor), _dev_ptr(torch, wabar, "wabar", per_stage),
-                 _dev_ptr(torch, wdelta, "wdelta", per_tensor), _dev_ptr(torch, of, "of", per_stage),
-                 _dev_ptr(torch, ob, "ob", per_stage))
+                 None if wdelta is None else _dev_ptr(torch, wdelta, "wdelta", per_tensor),
+                 None if of is None else _dev_ptr(torch, of, "of", per_stage),
+                 None if ob is None else _dev_ptr(torch, ob, "ob", per_stage))
     n, ws = _sizes(L, M, B)
     if n and (cost.numel() < n or arg.numel() < n or cost.dtype != torch.int32 or arg.dtype != torch.uint8):
         raise ValueError("cost/arg tables too small or of the wrong dtype")
