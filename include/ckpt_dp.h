@@ -214,7 +214,9 @@ int ckpt_solve_batched_noalloc(const ckpt_chains_t* chains, int L, int M, int B,
  *                            bytes stored (320 per wave and cell: cost and candidate number).
  *                            Work that the feasibility tests skip is not counted.
  * CKPT_K_ROW also counts the kernels that take small batches in one launch, block products and rows, and chains of a few
- * stages with their precomputation (then there is no CKPT_K_PRECOMPUTE).
+ * stages with their precomputation (then there is no CKPT_K_PRECOMPUTE); ckpt_kernel_name_of says which it is.  Of the bytes
+ * that the former of them loads the operands are counted, but not the reads between bands of a tile nor the
+ * samples of the bounds, and of what it stores the cells; the latter loads no table.
  * Creates and destroys events and a small device buffer (allocates); not for latency-critical
  * callers.  Returns as ckpt_solve_batched.
  */
@@ -223,6 +225,8 @@ int ckpt_solve_profiled(const ckpt_chains_t* chains, int L, int M, int B, void* 
                         uint8_t* arg, void* workspace, float* kind_ms, int* kind_launches, double* kind_bytes);
 /* Name of a kernel kind as it appears in a rocprofv3 kernel trace; NULL if out of range. */
 const char* ckpt_kernel_name(int kind);
+/* The same for the kernel that ckpt_solve_profiled launches as that kind for B chains of L stages in M slots. */
+const char* ckpt_kernel_name_of(int kind, int L, int M, int B);
 
 /*
  * After ckpt_solve_batched on the same stream (workspace = the one it was given; NULL = the

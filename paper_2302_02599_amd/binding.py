@@ -78,6 +78,7 @@ def load_library():
     lib.ckpt_solve_profiled.restype = i
     lib.ckpt_solve_profiled.argtypes = [ctypes.POINTER(_Chains), i, i, i, vp, vp, vp, vp, vp, vp, vp]
     lib.ckpt_kernel_name.restype, lib.ckpt_kernel_name.argtypes = ctypes.c_char_p, [i]
+    lib.ckpt_kernel_name_of.restype, lib.ckpt_kernel_name_of.argtypes = ctypes.c_char_p, [i, i, i, i]
     lib.ckpt_check_inputs.restype = i
     lib.ckpt_check_inputs.argtypes = [vp, i, i, i, vp, vp]
     lib.ckpt_schedule.restype = i
@@ -208,10 +209,10 @@ def ckpt_solve_profiled(uf, ub, wa, wabar, L, M, B, cost, arg, workspace, *, wde
                                  workspace.data_ptr(), ms, cnt, nbytes if count_bytes else None)
     if rc != 0:
         raise CkptError(rc, "ckpt_solve_profiled")
+    names = [lib.ckpt_kernel_name_of(k, L, M, B).decode() for k in range(n)]
     if count_bytes:
-        return {lib.ckpt_kernel_name(k).decode(): (float(ms[k]), int(cnt[k]), nbytes[2 * k], nbytes[2 * k + 1])
-                for k in range(n)}
-    return {lib.ckpt_kernel_name(k).decode(): (float(ms[k]), int(cnt[k])) for k in range(n)}
+        return {name: (float(ms[k]), int(cnt[k]), nbytes[2 * k], nbytes[2 * k + 1]) for k, name in enumerate(names)}
+    return {name: (float(ms[k]), int(cnt[k])) for k, name in enumerate(names)}
 
 
 def ckpt_solve_batched(uf, ub, wa, wabar, L, M, B, cost, arg, workspace, *, wdelta=None, of=None, ob=None,

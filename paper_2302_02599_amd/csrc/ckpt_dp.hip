@@ -151,6 +151,8 @@ inline size_t limit_ints(int L, int pitch, int B) {
 constexpr size_t kScratchSlack = 4096;
 static_assert(CKPT_MAX_L <= 256 && kScratchSlack >= 22 * 30 * sizeof(int32_t), "see limit_ints");
 
+inline bool samples_of(int L, int pitch, int B) { return uses_bounds(L, pitch, B) && samp_ints(L, pitch); }
+
 inline Workspace carve(void* base, int L, int pitch, int B, bool samples) {
     int32_t* p = static_cast<int32_t*>(base);
     Workspace w;
@@ -164,7 +166,7 @@ inline Workspace carve(void* base, int L, int pitch, int B, bool samples) {
     w.need = p;   p += align64(size_t(B) * L * L);
     w.prog = p;   p += align64(size_t(B) * tiles_of(L) * prog_words(pitch));
     w.fault = p;  p += 64;
-    w.samp = samples && uses_bounds(L, pitch, B) && samp_ints(L, pitch) ? p : nullptr;
+    w.samp = samples && samples_of(L, pitch, B) ? p : nullptr;
     return w;
 }
 
@@ -183,10 +185,11 @@ struct Ctx {
 };
 constexpr int kWorkSets = 256;
 
-// One lane per wave adds the wave's byte counts (per lane 4 bytes a load, 5 a stored cell).
+// One lane per wave adds the wave's byte counts (per lane 4 bytes a load, 5 a stored cell).  gemm_kernel and tile_rows_kernel count
+// in instantiations of their own, at no cost otherwise; flow_kernel (a work-group once) and chain_kernel (a row) ask at run time.
 template <bool CNT>
 __device__ __forceinline__ void count_work(unsigned long long* work, int slot, unsigned loads, unsigned cells) {
-    if constexpr (!CNT) return;  // the counting variants are separate instantiations: no cost otherwise
+    if constexpr (!CNT) return;
     if (work && (threadIdx.x & 63) == 0) {
         const unsigned set = (blockIdx.x * 7u + blockIdx.y * 13u + blockIdx.z * 29u + (threadIdx.x >> 6)) % kWorkSets;
         atomicAdd(work + set * 4 + slot, 256ull * loads);
@@ -2362,7 +2365,9 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
     } else {
         flow_rows<true, BOUNDS>(x, leftL, leftH, colL, colH, 0, 0);
     }
-    if (c.work && wq == 0) count_work<true>(c.work, 2, unsigned(empty ? 0 : 16 * evaluated + (D > 0 ? 64 : 0)), unsigned(T * cend));
+    // operands of the evaluated splits; 64 rows for the splits of the row and column blocks, eight for C_all of row 7
+    if (c.work && wq == 0)
+        count_work<true>(c.work, 2, unsigned(empty || D == 0 ? 0 : 16 * evaluated + 72), unsigned(D == 0 ? cend * (cend + 1) / 2 : T * cend));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __builtin_amdgcn_s_waitcnt(0);  // the stores are through
     __syncthreads();
@@ -3078,6 +3083,37 @@ bool allow_lds() {
     return ok;
 }
 
+// Which kernels fill the table, and on how many streams.
+//
+// Several streams.  Chains are independent, so from D = 2 on the batch is split in up to four
+// groups that run the same launch sequence on as many streams: the many short row launches
+// of one group overlap with work of the others instead of leaving the machine idle between
+// dependent launches.  The frontier kernel (a few busy CUs for a long time) runs on the first
+// side stream beside everything else: the fill prunes with whatever frontier is in memory,
+// the weak one of the precompute kernel or the exact one.  The side streams are forked from
+// and joined back into the caller's stream with events.  Small problems are bound by launch
+// latency, where more streams only add launches.
+// Automatic choice: split when the batch is large enough to be bound by the GPU and not by
+// launch latency (where more streams only add launches).  The caller can force either way.
+struct Route {
+    int groups;         // of chains, a stream each
+    bool chain, flow;   // one launch: chain_kernel, or (behind precompute_kernel) flow_kernel
+    bool flow_bounds;
+};
+Route route_of(int L, int pitch, int B, bool samples, const ckpt_solve_opts_t* opts) {
+    const int nblk = blocks_of(L), want_groups = opts ? opts->groups : 0;
+    const bool large = B >= 2 && size_t(B) * nblk * pitch >= (size_t(1) << 19);
+    Route r{};
+    r.groups = std::min(want_groups ? want_groups : (large ? kSideStreams + 1 : 1), B);
+    if (nblk < 3) r.groups = 1;  // no diagonal to split
+    // Small batches: every tile in one launch.  A schedule that the caller asks for is made of separate launches.
+    const bool apart = opts && (opts->row_launches || opts->list_split);
+    r.flow = r.groups == 1 && !apart && ckpt_rules::flow_pays(nblk, pitch / 64, B, samples);
+    r.chain = !apart && !want_groups && !(opts && (opts->frontier || opts->spin_limit)) && ckpt_rules::chain_pays(L, pitch);
+    r.flow_bounds = ckpt_rules::flow_bounds(nblk, pitch / 64, B, samples);
+    return r;
+}
+
 int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, int32_t* cost, uint8_t* arg,
                void* workspace, size_t workspace_bytes, Profile* prof, const ckpt_solve_opts_t* opts,
                bool may_create_helpers) {
@@ -3117,29 +3153,12 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
     const int nblk = (L + T - 1) / T;
     const int gx_row = (pitch + kRowWG - 1) / kRowWG;
 
-    // Several streams.  Chains are independent, so from D = 2 on the batch is split in up to four
-    // groups that run the same launch sequence on as many streams: the many short row launches
-    // of one group overlap with work of the others instead of leaving the machine idle between
-    // dependent launches.  The frontier kernel (a few busy CUs for a long time) runs on the first
-    // side stream beside everything else: the fill prunes with whatever frontier is in memory,
-    // the weak one of the precompute kernel or the exact one.  The side streams are forked from
-    // and joined back into the caller's stream with events.  Small problems are bound by launch
-    // latency, where more streams only add launches.
-    // Automatic choice: split when the batch is large enough to be bound by the GPU and not by
-    // launch latency (where more streams only add launches).  The caller can force either way.
-    const bool large = B >= 2 && size_t(B) * nblk * pitch >= (size_t(1) << 19);
-
-    int groups = want_groups ? want_groups : (large ? kSideStreams + 1 : 1);
-    groups = std::min(groups, B);
-    if (nblk < 3) groups = 1;  // no diagonal to split
+    const Route route = route_of(L, pitch, B, ws.samp, opts);
+    const bool chain = route.chain, flow = route.flow;
+    int groups = route.groups;
     const bool would_split = groups > 1;
-    // Small batches: every tile in one launch.  A schedule that the caller asks for is made of separate launches.
-    const bool flow = groups == 1 && fused_rows && !want_ks && ckpt_rules::flow_pays(nblk, pitch / 64, B, ws.samp);
     const size_t chain_lds = ckpt_rules::chain_lds(L, pitch);
-    const bool chain = fused_rows && !want_groups && !want_ks && frontier_mode == 0 && !(opts && opts->spin_limit) &&
-                       ckpt_rules::chain_pays(L, pitch);
     if (chain && chain_lds > 48 * 1024 && !allow_lds()) return CKPT_E_HIP;
-    const bool flow_bounds = ckpt_rules::flow_bounds(nblk, pitch / 64, B, ws.samp);
     if (prof) groups = 1;  // the event trail times one stream
     Device* dev = nullptr;
     if (groups > 1) {
@@ -3211,7 +3230,7 @@ int solve_impl(const ckpt_chains_t* chains, int L, int M, int B, void* stream, i
 
         if (flow) {
             const Ctx ctx{L, M, pitch, rows, 0, spin_limit, ws, cost, arg, work, false};
-            hipLaunchKernelGGL(flow_bounds ? flow_kernel<true> : flow_kernel<false>, dim3(unsigned(tiles_of(L) * (pitch / 64) * B)), dim3(kFlow), 0, st, ctx, B);
+            hipLaunchKernelGGL(route.flow_bounds ? flow_kernel<true> : flow_kernel<false>, dim3(unsigned(tiles_of(L) * (pitch / 64) * B)), dim3(kFlow), 0, st, ctx, B);
             CKPT_AFTER_LAUNCH(CKPT_K_ROW);
             return CKPT_OK;
         }
@@ -3404,6 +3423,16 @@ const char* ckpt_kernel_name(int kind) {
         case CKPT_K_ROW: return "tile_rows_kernel";
         default: return nullptr;
     }
+}
+
+const char* ckpt_kernel_name_of(int kind, int L, int M, int B) {
+    if (kind == CKPT_K_ROW && check_dims(L, M, B) == CKPT_OK) {
+        const int pitch = int(ckpt_row_pitch(M));
+        const Route route = route_of(L, pitch, B, samples_of(L, pitch, B), nullptr);
+        if (route.chain) return "chain_kernel";
+        if (route.flow) return "flow_kernel";
+    }
+    return ckpt_kernel_name(kind);
 }
 
 int ckpt_check_inputs(const void* workspace, int L, int M, int B, void* stream, int32_t* flags_host) {
