@@ -265,6 +265,34 @@ def test_a_wait_that_expires_is_reported_and_every_kernel_still_ends(amd):
     assert (arg.view(B, -1, pitch)[:, :, :M + 1] == ref.arg[:, :, :M + 1]).all()
 
 
+@pytest.mark.parametrize("L,M,B,size_hi,opts", [
+    (40, 3000, 3, 300, dict(list_split=1)),  # two launches a diagonal: progress words and marks of tile_rows_kernel
+    (40, 3000, 3, 300, dict(groups=3)),      # the same on three streams
+    (40, 3000, 3, 300, {}),                  # one launch, every feasible split
+    (66, 1100, 5, 90, {}), (66, 1100, 5, 0, {}),  # one launch, splits dropped by bounds; no shift, so that only tiles wait
+    (14, 300, 2, 40, {}),                    # two blocks: nothing waits two diagonals down
+])
+def test_a_wait_that_expires_in_each_kernel_that_waits(amd, L, M, B, size_hi, opts):
+    """The same failure path in every kernel that has one: forced from the host, reported, drained, and gone with the next solve
+    into the same buffers."""
+    import torch
+    batch = random_chain_batch(L, M, B, 62 + L, size_hi=size_hi, time_hi=2000, overheads=True, zero_sizes=size_hi == 0)
+    print(f"case {batch.name} {opts}", flush=True)
+    amd.ckpt_init()
+    ref = amd.solve(batch, row_launches=1)
+    dev = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in batch.dense()]
+    cost, arg, ws = torch.empty_like(ref.cost), torch.empty_like(ref.arg), torch.empty_like(ref.workspace)
+    args, extra = (*dev[:4], L, M, B, cost, arg, ws), dict(wdelta=dev[4], of=dev[5], ob=dev[6])
+    for _ in range(2):
+        amd.ckpt_solve_batched_opts(*args, spin_limit=-1, **opts, **extra)
+        rc = amd.load_library().ckpt_check_inputs(ws.data_ptr(), L, M, B, None, np.zeros(B, np.int32).ctypes.data)
+        torch.cuda.synchronize()
+        assert rc == -9, rc
+        amd.ckpt_solve_batched_opts(*args, **opts, **extra)
+        assert amd.ckpt_check_inputs(ws, L, M, B).tolist() == [0] * B
+        assert torch.equal(cost[..., :M + 1], ref.cost[..., :M + 1]) and torch.equal(arg[..., :M + 1], ref.arg[..., :M + 1])
+
+
 def test_solve_with_other_streams_busy(amd, oracle_mod):
     """A split solve issued while streams of the process that the library does not know are busy
     with copies and kernels of their own."""

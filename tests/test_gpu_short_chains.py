@@ -38,7 +38,7 @@ def test_times_up_to_the_largest_and_flags(amd, L):
     import torch
     batch = random_chain_batch(L, 90, 4, 4200 + L, size_hi=9, time_hi=900)
     batch.wabar[:] = batch.wa[:, 1:] + 1
-    batch.uf[1], batch.ub[1] = (1 << 30) // (L + 1), (1 << 30) - 1   # sums that reach 2^30
+    batch.uf[1], batch.ub[1] = (1 << 30) // (L + 1), (1 << 30) - 1   # sums close below 2^30
     batch.uf[2, L - 1] = -5
     batch.wa[3, L] = (1 << 28) + 1
     batch.wabar[3, L - 1] = (1 << 28) + 1
@@ -46,3 +46,18 @@ def test_times_up_to_the_largest_and_flags(amd, L):
     flags = [amd.ckpt_check_inputs(s.workspace, s.L, s.M, s.B).tolist() for s in (sol, apart)]
     assert flags[0] == flags[1] and flags[0][0] == 0 and flags[0][2] & 1 and flags[0][3] & 4
     assert torch.equal(sol.cost[:2, :, :91], apart.cost[:2, :, :91]) and torch.equal(sol.arg[:2, :, :91], apart.arg[:2, :, :91])
+
+
+@pytest.mark.parametrize("L", [2, 7, 8, 9, 13])
+def test_forward_times_that_add_up_to_the_sentinel(amd, oracle_mod, L):
+    """2^30 is flagged, one less is not and its table is the oracle's."""
+    import torch
+    batch = random_chain_batch(L, 90, 3, 4300 + L, size_hi=9, time_hi=900)
+    for b, total in ((0, (1 << 30) - 1), (1, 1 << 30)):
+        batch.uf[b] = total // L
+        batch.uf[b, L // 2] += total - L * (total // L)
+        assert int(batch.uf[b].sum(dtype="int64")) == total
+    sol, apart = amd.solve(batch, check=False), amd.solve(batch, check=False, list_split=1)
+    for s in (sol, apart):
+        assert amd.ckpt_check_inputs(s.workspace, s.L, s.M, s.B).tolist() == [0, 2, 0]
+        assert_tables_equal(oracle_mod, batch, s, chains=[0, 2])
