@@ -1615,8 +1615,10 @@ __global__ void __launch_bounds__(kRowWG, 3) tile_rows_kernel(Ctx c, int D) {
 // 5 x 53, 777 slots 229 and 105; 16 x 48, 1024 slots 211 and 134; 10 x 50, 500 slots 214 and 94; 1 x 192, 4096 slots 1177 and 649; 3 x 254,
 // 1500 slots 2273 and 1407 (the rule: ckpt_rules::flow_pays).
 // What bounds it: of 26000 clocks a diagonal (5 x 53 stages) rows take 12000, the 16 splits of the last neighbours 8000 (500 each whether or
-// not their operands are read from LDS ahead), their first operands 2300, the stores and the flag 2000.  Long chains are bound by vector issue and by the slots for
-// work-groups (1 x 192 stages: a work-group takes 60000 clocks, 12000 of them rows, most of the rest round trips): four a compute unit.
+// not their operands are read from LDS ahead), their first operands 2300, the stores and the flag 2000.  By the counters (profiles/) a wave waits, for
+// memory, LDS or the others, 67 % of that time, and vector issue fills 26 % of the chip.  Long chains fill the places for work-groups, four a
+// compute unit, and then both count: 1 x 192 stages, a work-group takes 63000 clocks, of which a wave waits 54 %, in a queue to issue 19 %, and vector issue
+// fills 55 % of the chip (3 x 254 stages 74000, 52, 22 and 60; 16 x 48 41000, 47, 21 and 56).
 //
 // Inside, a candidate of row i stands plus P[i]: a right operand carries the prefix sum of its split, and a split costs one addition.
 // ---------------------------------------------------------------------------
@@ -2382,8 +2384,9 @@ __global__ void __launch_bounds__(kFlow, BOUNDS ? 4 : 3) flow_kernel(Ctx c, int 
 // below zero reads column 0: its gate is closed.  The barriers wait for LDS and not for the stores.  Rows, cells and splits are
 // unrolled (with a loop over the rows, which needs a test a split, 1 x 8 stages, 64 slots take 11.1 us instead of 7.2), and what
 // belongs to a split is held by every thread (in scalar registers it spilled: 200 x 13, 500 slots 32 us instead of 24).
-// What bounds it: up to eight stages the launch and the first reads; longer chains vector issue, 6 instructions a split and
-// 20 a cell, by the few waves that a chain's columns fill.  1 x 8 stages, 64 slots 10.0 -> 7.2 us a solve, 200 x 13, 500 slots 49 -> 24
+// What bounds it: up to eight stages the launch and the first reads; longer chains the few waves that a chain's columns fill, with
+// 6 vector instructions a split and 20 a cell.  200 x 13 stages, 500 slots: a wave issues 3500 of them in 48700 clocks, two waves a SIMD, and
+// waits for LDS, the barriers and its stores 48 % of the time.  1 x 8 stages, 64 slots 10.0 -> 7.2 us a solve, 200 x 13, 500 slots 49 -> 23
 // (the rule: ckpt_rules::chain_pays).
 // ---------------------------------------------------------------------------
 template <int N>

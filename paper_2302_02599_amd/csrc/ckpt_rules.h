@@ -114,13 +114,17 @@ constexpr int precompute_rows(int L, long long B) { return B * ((L + 3) / 4) <= 
 
 // Whether a solve is one launch with a work-group per chain (chain_kernel): up to so many stages, a thread for every column, and all
 // rows but the first have to fit into LDS.  A column's instructions grow with the cube of the stages and are one thread's: longer
-// chains are better cut into tiles.  us a solve by the kernels of longer chains and by this one:
+// chains are better cut into tiles, unless they are many.  us a solve by the kernels of longer chains and by this one:
 //   1 x 8 stages, 64 slots 10.0 and 7.2;  67 x 8, 184 slots 12.5 and 7.9;  60 x 8, 1000 slots 21 and 12;  3000 x 8, 300 slots 58 and 37
 //   1 x 10, 300 slots 21.8 and 12.4;  10 x 9, 900 slots 29 and 15;  3000 x 12, 200 slots 147 and 102;  1 x 13, 500 slots 25.4 and 20.7;
-//   200 x 13, 500 slots 49 and 24;  1000 x 13, 60 slots 58 and 21
-//   600 x 14, 400 slots 82.5 and 82.4;  1 x 16, 64 slots 19 and 29;  300 x 16, 300 slots 54 and 65;  2000 x 16, 60 slots 85 and 65
+//   200 x 13, 500 slots 49 and 23;  1000 x 13, 60 slots 58 and 21
+// From 14 stages on a few chains lose.  Many gain, in narrow tables (which this line leaves out: it goes by stages and columns only):
+//   1 x 14, 60 slots 18.8 and 20.5;  40 x 14, 120 slots 20.9 and 22.5;  100 x 14, 300 slots 32.7 and 25.9;  600 x 14, 188 slots 44.3 and 45.2;
+//   600 x 14, 380 slots 80.3 and 72.4;  2000 x 14, 60 slots 86.7 and 46.7
+//   1 x 15, 188 slots 20.3 and 25.2;  300 x 15, 188 slots 37.5 and 52.3;  2000 x 15, 188 slots 104 and 200;  2000 x 15, 60 slots 87.4 and 54.5
+//   1 x 16, 60 slots 18.8 and 27.1;  300 x 16, 300 slots 53.9 and 64.6;  600 x 16, 60 slots 37.1 and 31.5;  2000 x 16, 60 slots 85.4 and 63.9
 constexpr int kChainStages = 13;
-constexpr long long kChainLds = 156 * 1024;
+constexpr long long kChainLds = 156 * 1024;  // of a compute unit's 160 KB; the static arrays take 2
 constexpr long long chain_lds(int L, int pitch) { return 4LL * (L * (L - 1) / 2) * pitch; }
 // Row of cell (q, q) in LDS, cell (q, j) stands j - q rows further; the first row of the table (q = 0) is not kept.
 constexpr int chain_row(int L, int q) { return (q - 1) * L - q * (q - 1) / 2; }
