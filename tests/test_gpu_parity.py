@@ -285,7 +285,8 @@ def test_a_wait_that_expires_in_each_kernel_that_waits(amd, L, M, B, size_hi, op
     args, extra = (*dev[:4], L, M, B, cost, arg, ws), dict(wdelta=dev[4], of=dev[5], ob=dev[6])
     for _ in range(2):
         amd.ckpt_solve_batched_opts(*args, spin_limit=-1, **opts, **extra)
-        rc = amd.load_library().ckpt_check_inputs(ws.data_ptr(), L, M, B, None, np.zeros(B, np.int32).ctypes.data)
+        flags = np.zeros(B, np.int32)
+        rc = amd.load_library().ckpt_check_inputs(ws.data_ptr(), L, M, B, None, flags.ctypes.data)
         torch.cuda.synchronize()
         assert rc == -9, rc
         amd.ckpt_solve_batched_opts(*args, **opts, **extra)
