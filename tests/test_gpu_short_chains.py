@@ -61,3 +61,37 @@ def test_forward_times_that_add_up_to_the_sentinel(amd, oracle_mod, L):
     for s in (sol, apart):
         assert amd.ckpt_check_inputs(s.workspace, s.L, s.M, s.B).tolist() == [0, 2, 0]
         assert_tables_equal(oracle_mod, batch, s, chains=[0, 2])
+
+
+def test_first_solve_of_a_process_inside_a_capture():
+    """A table of more LDS than a kernel has by default, captured without ckpt_init by a process that has solved nothing:
+    what the kernel has to be allowed is no work for a stream.  Every replay gives the tables of the eager solve."""
+    import os
+    import subprocess
+    import sys
+    code = r'''
+import numpy as np, torch, sys
+sys.path.insert(0, %r)
+import paper_2302_02599_amd as amd
+from workloads import random_chain_batch
+batch = random_chain_batch(13, 500, 20, 4400, size_hi=60, time_hi=900)
+L, M, B = batch.L, batch.M, batch.B
+ins = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in (batch.uf, batch.ub, batch.wa, batch.wabar)]
+cost = torch.empty((B, amd.ckpt_table_rows(L), amd.ckpt_row_pitch(M)), dtype=torch.int32, device="cuda")
+arg = torch.empty(cost.shape, dtype=torch.uint8, device="cuda")
+ws = torch.empty(amd.ckpt_workspace_bytes(L, M, B), dtype=torch.uint8, device="cuda")
+side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+torch.cuda.synchronize()
+with torch.cuda.graph(graph, stream=side):
+    amd.ckpt_solve_batched(*ins, L, M, B, cost, arg, ws)
+same = []
+for _ in range(3):
+    cost.fill_(-1), arg.fill_(99)
+    graph.replay()
+    torch.cuda.synchronize()
+    ref = amd.solve(batch, list_split=1)
+    same.append(torch.equal(cost[..., :M + 1], ref.cost[..., :M + 1]) and torch.equal(arg[..., :M + 1], ref.arg[..., :M + 1]))
+print("RESULT", amd.load_library().ckpt_kernel_name_of(3, L, M, B), same)
+''' % os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    out = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert "RESULT b'chain_kernel' [True, True, True]" in out.stdout, out.stdout[-2000:] + out.stderr[-2000:]
